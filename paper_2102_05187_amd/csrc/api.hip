@@ -6,6 +6,7 @@
 #include <new>
 
 #include "kernels.hpp"
+#include "pieces.hpp"
 #include "stream_kernels.hpp"
 #include "tensor.hpp"
 
@@ -106,6 +107,7 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st) {
         rs = read_i32((const int32_t *)mx->ptr, 1, &h, st);
         if (rs != COMET_OK) return rs;
         sc.empty_segments = h;
+        HIP_TRY(comet::piece_plan_build(t.pos_i(leaf), sc.nseg, sc.nnz, sc.pieces, st));
         if (t.levels[0] == COMET_CU) {
             HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
             HIP_TRY(comet::max_coordinate_gap(t.crd_i(0), t.crd_len[0], t.dims[0], (int32_t *)mx->ptr, st));
@@ -411,7 +413,7 @@ static size_t scratch_need(const comet_tensor *t, int64_t R) {
     size_t need = 0;
     if (t->sched.nchunks > 0) need = comet::stream_scratch_bytes(t->sched.nchunks, 1);
     if (t->sched.ntiles > 0 && comet::stream_supports_rank(R)) {
-        size_t b = comet::stream_scratch_bytes(t->sched.ntiles, R);
+        size_t b = comet::segreduce_scratch_bytes(t->sched, R);
         if (t->sched.heavy.nunits > 0) b += comet::heavy_partial_bytes(t->sched.heavy, R > 64 ? 64 : R);
         if (t->sched.fibers.nheavy > 0) b += comet::fiber_partial_bytes(t->sched.fibers, R >= 32 ? 32 : 16);
         if (b > need) need = b;
@@ -723,7 +725,7 @@ static comet_status matrix_product(const comet_tensor *A, const double *Dn, int6
     if (R < 1 || R > 1024) return COMET_ERR_UNSUPPORTED;
     const int64_t nseg = A->pos_len[1] - 1, nnz = A->nvals;
     const bool tiled = nnz > 0 && use_tiled(A, R, Dn, out, A->dims[1], A->sched.max_seg_len);
-    const size_t carry = tiled ? comet::stream_scratch_bytes(R == 1 ? A->sched.nchunks : A->sched.ntiles, R) : 0;
+    const size_t carry = tiled ? comet::segreduce_scratch_bytes(A->sched, R) : 0;
     // The heavy-row sweep pays when the dense operand is much larger than the L2 caches (else its rows are
     // cache hits anyway) and the long rows hold a good share of the nonzeros (decided when the plan was built).
     const bool heavy = tiled && !ext_scratch && A->variant != 3 && A->sched.heavy.nunits > 0 &&
@@ -761,7 +763,7 @@ static comet_status matrix_product(const comet_tensor *A, const double *Dn, int6
             // (whose rows carry their result rows, DCSR's included)
             const comet_tensor *Lh = A->light.get();
             if (Lh && Lh->sched.ntiles > 0) {
-                comet_status rs = ensure_scratch(Lh, comet::stream_scratch_bytes(Lh->sched.ntiles, R));
+                comet_status rs = ensure_scratch(Lh, comet::segreduce_scratch_bytes(Lh->sched, R));
                 if (rs != COMET_OK) return rs;
                 HIP_TRY(comet::stream_segreduce(Lh->sched, Lh->pos_i(1), Lh->crd_i(1), Lh->vals_d(), Lh->crd_i(0), Dn,
                                                 A->dims[1], R, out, Lh->scratch->ptr, false, st, ep));
@@ -922,7 +924,7 @@ static comet_status leaf_contract(const comet_tensor *X, int mode, const double 
                 const bool sweep = kind == 2 && C->variant != 3 && Lh && comet::fiber_supports(C->sched.fibers, R) &&
                                    Lh->sched.ntiles > 0 && aligned16(Lh->crd_i(1)) && aligned16(Lh->vals_d());
                 if (sweep) {
-                    rs = ensure_scratch(Lh, comet::stream_scratch_bytes(Lh->sched.ntiles, R));
+                    rs = ensure_scratch(Lh, comet::segreduce_scratch_bytes(Lh->sched, R));
                     if (rs != COMET_OK) return rs;
                     rs = ensure_scratch(C, comet::fiber_partial_bytes(C->sched.fibers, R));
                     if (rs != COMET_OK) return rs;
@@ -931,7 +933,7 @@ static comet_status leaf_contract(const comet_tensor *X, int mode, const double 
                     HIP_TRY(comet::fiber_ttm(C->sched.fibers, C->crd_i(2), C->vals_d(), Dn, C->dims[2], R, yv,
                                              C->scratch->ptr, st));
                 } else {
-                    rs = ensure_scratch(C, comet::stream_scratch_bytes(R == 1 ? C->sched.nchunks : C->sched.ntiles, R));
+                    rs = ensure_scratch(C, comet::segreduce_scratch_bytes(C->sched, R));
                     if (rs != COMET_OK) return rs;
                     HIP_TRY(comet::stream_segreduce(C->sched, C->pos_i(2), C->crd_i(2), C->vals_d(), nullptr, Dn, C->dims[2], R,
                                                     yv, C->scratch->ptr, C->variant == 3, st));

@@ -179,7 +179,7 @@ hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t 
     if (sc.ntiles <= 0) return hipSuccess;
     if (!stream_mttkrp_supports_rank(R) || !sc.slice_begin) return hipErrorNotSupported;
     const int r = (int)R;
-    hipError_t e = COMET_DISPATCH_RANK(launch_mttkrp, R, sc, pos2, crd1, pos3, crd2, crd3, vals, B, C, r, M, scratch, st, ep);
+    hipError_t e = COMET_DISPATCH_GROUPS(launch_mttkrp, R, sc, pos2, crd1, pos3, crd2, crd3, vals, B, C, r, M, scratch, st, ep);
     if (e != hipSuccess) return e;
     return run_fixup(scratch, sc.ntiles, r, nullptr, M, sc.max_parent_len > 0 ? sc.max_parent_len / kTile + 2 : 0, st, ep);
 }

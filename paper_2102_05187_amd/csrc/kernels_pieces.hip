@@ -1,0 +1,284 @@
+// Rank-R kernel (SpMM, TTM): lane groups of 4, 8 or 16 walk the pieces of a level (pieces.hpp).
+//
+// What bounds it.  Every vector memory instruction keeps the texture-address unit of a compute unit busy for 16 clocks and
+// more, however few of its lanes are active, and the vector L1 behind it returns data in order, so that the times for
+// gathering operand rows, reading nonzeros and writing results add up rather than overlap (measured: rows of 128 bytes
+// from L2 132 us for 35 M, streaming 480 MB 82 us, storing 832 MB 157 us; all three at once 394 us).  The kernel therefore
+// spends as few instructions as it can: rows 16 bytes per lane, nonzeros 16 bytes per lane into LDS, from where a lane
+// group reads one with a broadcast, and result rows stored for all groups of a wavefront at once, which pieces of equal
+// length make possible.  A walk that asks at every nonzero whether a segment ends (kernels_rankR.hip) stores few rows at a time.
+// Measured before and after, that walk and this: SpMM on 11.3 M nonzeros within 2000 columns of the diagonal, rank 20,
+// 313 and 157 us; TTM on 8 M nonzeros in 1.6 M fibers, rank 32, 181 and 127 us; 200 000 nonzeros, rank 16, 29 and 14 us.
+#include "pieces.hpp"
+#include "stream_common.hpp"
+
+namespace comet {
+
+namespace {
+
+struct Item { unsigned off, pad; double val; };                   // a nonzero: where its operand row starts, and its value
+
+// Bytes of LDS: the tile's nonzeros (up to 7 more for the 16-byte boundaries around them), its pieces, its partial sums.
+__host__ __device__ inline int lds_pieces_at(int units) { return (tile_items(units) + 7) * (int)sizeof(Item); }
+__host__ __device__ inline int lds_parts_at(int units) { return lds_pieces_at(units) + ((tile_pieces(units) + 3) & ~3) * 4; }
+
+// stream: the nonzeros are read around the caches, and neighbouring tiles go to different XCDs (see kLargeNnz)
+template <int L, int E, int NL, bool FULL, bool BIG, bool ROWMAP>
+__global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, const uint32_t *__restrict__ pieces,
+                                                const uint32_t *__restrict__ joins, int units, int stream,
+                                                const int32_t *__restrict__ crd, const double *__restrict__ vals,
+                                                const int32_t *__restrict__ rowmap, const double *__restrict__ Dn,
+                                                double *__restrict__ out, int64_t nnz, int R, double *__restrict__ head,
+                                                double *__restrict__ tail, Epilogue ep) {
+    constexpr int V = E * NL, KP = 64 / L, kRow = L * V;          // pieces side by side in a wavefront
+    constexpr int G = V <= 2 ? 4 : (V <= 4 ? 2 : 1);              // gathers of a piece in flight, next to as many being used
+    constexpr int KB = G;                                         // pieces of a group at a time, when they are short
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    Item *item = reinterpret_cast<Item *>(lds);
+    uint32_t *piece = reinterpret_cast<uint32_t *>(lds + lds_pieces_at(units));
+    double *part = reinterpret_cast<double *>(lds + lds_parts_at(units));
+    // Workgroups go to the eight XCDs in turn.  Each XCD gets a contiguous eighth of the tiles, so that operand rows which
+    // neighbouring segments share are shared in its L2 (banded matrix above: 177 -> 167 us).
+    const int n8 = stream ? 0 : (int)gridDim.x / 8;
+    const int t = (int)blockIdx.x < 8 * n8 ? ((int)blockIdx.x & 7) * n8 + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+    const int4 t0 = tiles[t], t1 = tiles[t + 1];
+    const int np = t1.z - t0.z, nj = t1.w - t0.w;
+    const unsigned unit = (unsigned)R * (BIG ? 1u : 8u);          // row offsets: bytes, or doubles for operands of 4 GiB and more
+    // nonzeros of the tile from the 16-byte boundary in front of them
+    const int p0 = t0.x & ~3, lead = t0.x - p0, n_items = t1.x - p0;
+    for (int i = (int)threadIdx.x * 4; i < n_items; i += 1024) {
+        int c[4];
+        double a[4];
+        if ((int64_t)p0 + i + 4 <= nnz) {
+            typedef int v4i __attribute__((ext_vector_type(4)));
+            typedef double v2d __attribute__((ext_vector_type(2)));
+            const v4i *pc = reinterpret_cast<const v4i *>(crd + p0 + i);
+            const v2d *pv = reinterpret_cast<const v2d *>(vals + p0 + i);
+            v4i cv;
+            v2d x, y;
+            if (stream) { cv = __builtin_nontemporal_load(pc); x = __builtin_nontemporal_load(pv); y = __builtin_nontemporal_load(pv + 1); }
+            else { cv = pc[0]; x = pv[0]; y = pv[1]; }
+            c[0] = cv.x; c[1] = cv.y; c[2] = cv.z; c[3] = cv.w;
+            a[0] = x.x; a[1] = x.y; a[2] = y.x; a[3] = y.y;
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { const bool in = i + u < n_items; c[u] = in ? crd[p0 + i + u] : 0; a[u] = in ? vals[p0 + i + u] : 0.0; }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) item[i + u] = Item{(unsigned)c[u] * unit, 0u, a[u]};
+    }
+    for (int i = threadIdx.x; i < np; i += 256) piece[i] = pieces[t0.z + i];
+    __syncthreads();
+
+    const int k = threadIdx.x % L, gw = (threadIdx.x & 63) / L, wave = threadIdx.x >> 6;
+    const RowOf<L, E, NL, FULL> rw(R, k);
+    const char *base = reinterpret_cast<const char *>(Dn);
+    const Item *items = item + lead;
+    auto result_row = [&](uint32_t pd) {
+        const int s = t0.y + (piece_is_part(pd) ? 0 : piece_num(pd));
+        return ROWMAP ? rowmap[s] : s;
+    };
+    auto finish = [&](uint32_t pd, int r, const double *acc) {
+        if (piece_is_part(pd)) rw.put(part + piece_num(pd) * kRow, acc);
+        else rw.store_result(out + (int64_t)r * R, acc, ep);
+    };
+    // Longest pieces first: batches of one piece per group until the longest piece of a batch is short.
+    int b = wave * KP;
+    for (; b < np; b += 4 * KP) {
+        const int longest = piece_len(piece[b]);
+        if (longest <= 2 * G) break;
+        const bool mine = b + gw < np;
+        const uint32_t pd = piece[mine ? b + gw : b];
+        const int len = mine ? piece_len(pd) : 0;
+        const int shortest = b + KP <= np ? piece_len(piece[b + KP - 1]) : 0;
+        const int r = result_row(pd);
+        const Item *it = items + piece_start(pd);
+        const int last = len > 0 ? len - 1 : 0;
+        double acc[V], row[2][G][V], val[2][G];
+#pragma unroll
+        for (int q = 0; q < V; ++q) acc[q] = 0.0;
+        auto issue = [&](int j, double (*d)[V], double *v) {
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const Item x = it[j + u < last ? j + u : last];
+                v[u] = x.val;
+                rw.template load<BIG>(base, x.off, d[u]);
+            }
+        };
+        auto consume = [&](int j, const double (*d)[V], const double *v) {
+            if (j + G <= shortest) {
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+#pragma unroll
+                    for (int q = 0; q < V; ++q) acc[q] = fma(v[u], d[u][q], acc[q]);
+            } else {
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+                    if (j + u < len) {
+#pragma unroll
+                        for (int q = 0; q < V; ++q) acc[q] = fma(v[u], d[u][q], acc[q]);
+                    }
+            }
+        };
+        issue(0, row[0], val[0]);
+        for (int j = 0; j < longest; j += 2 * G) {
+            issue(j + G, row[1], val[1]);
+            consume(j, row[0], val[0]);
+            issue(j + 2 * G, row[0], val[0]);
+            consume(j + G, row[1], val[1]);
+        }
+        if (mine) finish(pd, r, acc);
+    }
+    // Short pieces: KB of them per group at the same time.
+    for (; b < np; b += 4 * KP * KB) {
+        const int longest = piece_len(piece[b]);
+        uint32_t pd[KB];
+        int len[KB], r[KB];
+        double acc[KB][V];
+#pragma unroll
+        for (int m = 0; m < KB; ++m) {
+            const int i = b + 4 * KP * m + gw;
+            pd[m] = i < np ? piece[i] : 0u;
+            len[m] = i < np ? piece_len(pd[m]) : -1;
+            r[m] = result_row(pd[m]);
+#pragma unroll
+            for (int q = 0; q < V; ++q) acc[m][q] = 0.0;
+        }
+        double row[2][KB][V], val[2][KB];
+        auto issue = [&](int j, double (*d)[V], double *v) {
+#pragma unroll
+            for (int m = 0; m < KB; ++m) {
+                const Item x = items[j < len[m] ? piece_start(pd[m]) + j : 0];
+                v[m] = x.val;
+                rw.template load<BIG>(base, x.off, d[m]);
+            }
+        };
+        auto consume = [&](int j, const double (*d)[V], const double *v) {
+#pragma unroll
+            for (int m = 0; m < KB; ++m)
+                if (j < len[m]) {
+#pragma unroll
+                    for (int q = 0; q < V; ++q) acc[m][q] = fma(v[m], d[m][q], acc[m][q]);
+                }
+        };
+        if (longest > 0) issue(0, row[0], val[0]);
+        for (int j = 0; j < longest; j += 2) {
+            if (j + 1 < longest) issue(j + 1, row[1], val[1]);
+            consume(j, row[0], val[0]);
+            if (j + 1 >= longest) break;
+            if (j + 2 < longest) issue(j + 2, row[0], val[0]);
+            consume(j + 1, row[1], val[1]);
+        }
+#pragma unroll
+        for (int m = 0; m < KB; ++m)
+            if (len[m] >= 0) finish(pd[m], r[m], acc[m]);
+    }
+    if (nj == 0) return;
+    __syncthreads();
+    for (int i = threadIdx.x / L; i < nj; i += 256 / L) {
+        const uint32_t jn = joins[t0.w + i];
+        const double *ps = part + join_slot(jn) * kRow;
+        double sum[V], v[V];
+#pragma unroll
+        for (int q = 0; q < V; ++q) sum[q] = 0.0;
+        const int n = join_count(jn);
+        for (int m = 0; m < n; ++m) {
+            rw.get(ps + m * kRow, v);
+#pragma unroll
+            for (int q = 0; q < V; ++q) sum[q] += v[q];
+        }
+        const int to = join_to(jn);
+        if (to == kJoinRow) {
+            const int s = t0.y + join_seg(jn);
+            rw.store_result(out + (int64_t)(ROWMAP ? rowmap[s] : s) * R, sum, ep);
+        } else {
+            rw.store((to == kJoinHead ? head : tail) + (int64_t)t * R, sum);
+        }
+    }
+}
+
+// Segments cut by tile boundaries: what the first tile holds of one behind its boundary, then what the following tiles
+// hold in front of theirs.  A thread per (segment, column); the last workgroups of the grid take the segments over many
+// tiles, one each, with the tiles dealt over 256 / R threads per column.
+__global__ void __launch_bounds__(256) k_piece_cut_sums(const int4 *__restrict__ cuts, int ncut, int nlong, int64_t ntiles,
+                                                        const double *__restrict__ head, const double *__restrict__ tail, int R,
+                                                        const int32_t *__restrict__ rowmap, double *__restrict__ out, Epilogue ep) {
+    __shared__ double sums[256];
+    const int narrow = (int)gridDim.x - nlong;
+    if ((int)blockIdx.x < narrow) {
+        const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+        if (g >= (int64_t)ncut * R) return;
+        const int i = (int)(g / R), r = (int)(g - (int64_t)i * R);
+        const int4 c = cuts[i];
+        double s = tail[(int64_t)c.y * R + r];
+        for (int t = c.y + 1; t <= c.z; ++t) s += head[(int64_t)t * R + r];
+        double *o = out + (int64_t)(rowmap ? rowmap[c.x] : c.x) * R + r;
+        *o = ep_apply(ep, s, o);
+        return;
+    }
+    const int4 c = cuts[ntiles - 1 - ((int)blockIdx.x - narrow)];
+    // thread (lane, r): tiles lane, lane + nl, ...; R <= 128, so at least two lanes of tiles
+    const int nl = 256 / R, lane = threadIdx.x / R, r = threadIdx.x - lane * R;
+    double s = 0.0;
+    if (lane < nl) {
+        if (lane == 0) s = tail[(int64_t)c.y * R + r];
+        for (int64_t t = c.y + 1 + lane; t <= c.z; t += nl) s += head[t * R + r];
+        sums[threadIdx.x] = s;
+    }
+    __syncthreads();
+    if (lane != 0) return;
+    for (int m = 1; m < nl; ++m) s += sums[m * R + r];
+    double *o = out + (int64_t)(rowmap ? rowmap[c.x] : c.x) * R + r;
+    *o = ep_apply(ep, s, o);
+}
+
+struct PieceArgs {
+    const PiecePlan &plan;
+    const int32_t *crd;
+    const double *vals;
+    const int32_t *rowmap;
+    const double *Dn;
+    double *out;
+    int64_t nnz;
+    int R;
+    double *head, *tail;
+    hipStream_t st;
+    Epilogue ep;
+};
+
+template <int L, int E, int NL, bool FULL, bool BIG>
+hipError_t launch_pieces(const PieceArgs &a) {
+    const int lds = lds_parts_at(a.plan.units) + tile_parts(a.plan.units) * L * E * NL * 8;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)a.plan.ntiles), dim3(256), (unsigned)lds, a.st, (const int4 *)a.plan.tiles->ptr,
+                           (const uint32_t *)a.plan.pieces->ptr, (const uint32_t *)a.plan.joins->ptr, a.plan.units, a.plan.units == kUnitsLarge,
+                           a.crd, a.vals, a.rowmap, a.Dn, a.out, a.nnz, a.R, a.head, a.tail, a.ep);
+    };
+    if (lds > 64 * 1024) {
+        static const hipError_t allowed[2] = {
+            hipFuncSetAttribute((const void *)k_pieces<L, E, NL, FULL, BIG, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
+            hipFuncSetAttribute((const void *)k_pieces<L, E, NL, FULL, BIG, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)};
+        if (allowed[a.rowmap ? 1 : 0] != hipSuccess) return allowed[a.rowmap ? 1 : 0];
+    }
+    if (a.rowmap) go(k_pieces<L, E, NL, FULL, BIG, true>); else go(k_pieces<L, E, NL, FULL, BIG, false>);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+size_t piece_scratch_bytes(const PiecePlan &plan, int64_t R) { return (size_t)plan.ntiles * (size_t)R * 2 * sizeof(double); }
+
+hipError_t piece_rows(const PiecePlan &plan, const int32_t *crd, const double *vals, int64_t nnz, const int32_t *rowmap, const double *Dn,
+                      int64_t dense_rows, int R, double *out, void *scratch, hipStream_t st, Epilogue ep) {
+    double *head = (double *)scratch, *tail = head + plan.ntiles * R;
+    const PieceArgs a{plan, crd, vals, rowmap, Dn, out, nnz, R, head, tail, st, ep};
+    const bool big = dense_rows * R * 8 >= (int64_t(1) << 32);    // row offsets in bytes no longer fit 32 bits
+    const hipError_t e = COMET_DISPATCH_RANK(launch_pieces, R, big, a);
+    if (e != hipSuccess || plan.ncut + plan.ncut_long == 0) return e;
+    const int64_t narrow = (plan.ncut * R + 255) / 256;
+    hipLaunchKernelGGL(k_piece_cut_sums, dim3((unsigned)(narrow + plan.ncut_long)), dim3(256), 0, st, (const int4 *)plan.cuts->ptr,
+                       (int)plan.ncut, (int)plan.ncut_long, plan.ntiles, (const double *)head, (const double *)tail, R, rowmap, out, ep);
+    return hipGetLastError();
+}
+
+}  // namespace comet

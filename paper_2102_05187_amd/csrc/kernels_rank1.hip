@@ -2,6 +2,7 @@
 // carry fix-up kernels shared by all of them, and the host entry points of the family.
 #include <atomic>
 
+#include "pieces.hpp"
 #include "stream_common.hpp"
 
 namespace comet {
@@ -569,6 +570,12 @@ size_t stream_scratch_bytes(int64_t ntiles, int64_t R) {
     return total + 256;
 }
 
+size_t segreduce_scratch_bytes(const Schedule &sc, int64_t R) {
+    if (R == 1) return stream_scratch_bytes(sc.nchunks, 1);
+    const size_t a = stream_scratch_bytes(sc.ntiles, R), b = piece_scratch_bytes(sc.pieces, R);
+    return a > b ? a : b;
+}
+
 hipError_t stream_segreduce(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals,
                             const int32_t *rowmap, const double *Dn, int64_t dense_rows, int64_t R, double *out,
                             void *scratch, bool plain, hipStream_t st, Epilogue ep) {
@@ -609,6 +616,12 @@ hipError_t stream_segreduce(const Schedule &sc, const int32_t *pos, const int32_
                                rowmap, Dn, out, sc.nnz, sc.ntiles, scratch, ep);
         e = hipGetLastError();
     } else {
+        // Which walk: the pieces, except for narrow rows of full width over many nonzeros, where memory bounds both and
+        // the walk over whole tiles of nonzeros keeps more of the list in flight (TTM at rank 16, 36 M nonzeros in 6.5 M
+        // fibers: 485 us against 535; level at 12 M nonzeros, behind by 1.3 to 2 at 5 M and below).
+        const bool long_list = sc.nnz >= kLargeNnz && (R == 8 || R == 16);
+        if (!long_list)
+            return piece_rows(sc.pieces, crd, vals, sc.nnz, rowmap, Dn, dense_rows, (int)R, out, scratch, st, ep);
         e = stream_segreduce_rankR(sc, pos, crd, vals, rowmap, Dn, (int)R, out, scratch, st, ep);
     }
     if (e != hipSuccess) return e;

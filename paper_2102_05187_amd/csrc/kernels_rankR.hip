@@ -1,4 +1,5 @@
-// Rank-R kernel of the nonzero-tiled family (SpMM, TTM): lane groups walk runs of consecutive nonzeros.
+// Rank-R kernel of the nonzero-tiled family (SpMM, TTM): lane groups walk runs of consecutive nonzeros.  Serves ranks 8 and
+// 16 over long lists; see stream_segreduce for where the line to the piece kernel lies.
 #include "stream_common.hpp"
 
 namespace comet {
@@ -128,7 +129,9 @@ hipError_t launch_rankR(const Schedule &sc, const int32_t *pos, const int32_t *c
 hipError_t stream_segreduce_rankR(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals,
                                   const int32_t *rowmap, const double *Dn, int R, double *out, void *scratch,
                                   hipStream_t st, Epilogue ep) {
-    return COMET_DISPATCH_RANK(launch_rankR, R, sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
+    if (R == 8) return launch_rankR<4, 2, true>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
+    if (R == 16) return launch_rankR<8, 2, true>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
+    return hipErrorNotSupported;
 }
 
 }  // namespace comet

@@ -1,0 +1,172 @@
+// Builds the piece plan of a compressed level (see pieces.hpp); runs once per tensor.
+#include "pieces.hpp"
+
+#include "kernels.hpp"
+
+namespace comet {
+
+namespace {
+
+// Boundary of tile t: the segment s it lies in (or starts at) and the first nonzero of the tile.  In the order "a
+// segment's nonzeros, then the segment itself" the boundary is unit t * units: the smallest s whose end lies beyond it.
+__global__ void __launch_bounds__(256) k_piece_tiles(const int32_t *__restrict__ pos, int64_t nseg, int64_t nnz, int units,
+                                                     int64_t ntiles, int4 *__restrict__ tiles) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t > ntiles) return;
+    int64_t s = nseg, p = nnz;
+    const int64_t d = t * units;
+    if (d < nnz + nseg) {
+        int64_t lo = 0, hi = nseg - 1;                       // smallest s with pos[s + 1] + s + 1 > d
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if ((int64_t)pos[mid + 1] + mid + 1 > d) hi = mid; else lo = mid + 1;
+        }
+        s = lo;
+        const int64_t b = pos[s], e = pos[s + 1];
+        p = d - s;
+        if (p > e) p = e;
+        if (e - b <= kSnap) p = b;                           // the whole short segment goes to this tile
+        if (p == e && e > b) { p = e; s += 1; }              // all of it belongs to the tile before
+    }
+    tiles[t] = make_int4((int)p, (int)s, 0, 0);
+}
+
+// The pieces and joins of tile t; FILL = false only counts them.
+template <bool FILL>
+__global__ void __launch_bounds__(256) k_piece_fill(const int32_t *__restrict__ pos, int64_t nseg, int64_t ntiles, int4 *__restrict__ tiles,
+                                                    uint64_t *__restrict__ counts, uint32_t *__restrict__ pieces,
+                                                    uint32_t *__restrict__ joins) {
+    __shared__ int bin[64], npart, njoin;
+    const int64_t t = blockIdx.x;
+    const int4 a = tiles[t], b = tiles[t + 1];
+    const int p0 = a.x, p1 = b.x, s0 = a.y;
+    // segments of the tile: [s0, s1), the last of them possibly continued
+    const int s1 = b.y + (b.y < nseg && pos[b.y] < p1 ? 1 : 0);
+    if (threadIdx.x < 64) bin[threadIdx.x] = 0;
+    if (threadIdx.x == 0) { npart = 0; njoin = 0; }
+    __syncthreads();
+    auto each = [&](auto &&whole, auto &&cut) {
+        for (int s = s0 + (int)threadIdx.x; s < s1; s += 256) {
+            const int sb = pos[s], se = pos[s + 1];
+            const int lo = sb > p0 ? sb : p0, hi = se < p1 ? se : p1, n = hi - lo;
+            const bool begins = sb >= p0, ends = se <= p1;
+            if (begins && ends && n <= kWhole) whole(s, lo, n);
+            else cut(s, lo, n, ends ? (begins ? kJoinRow : kJoinHead) : (begins ? kJoinTail : kJoinHead));
+        }
+    };
+    each([&](int, int, int n) { atomicAdd(&bin[n], 1); },
+         [&](int, int, int n, int) {
+             const int np = (n + kPiece - 1) / kPiece;
+             for (int q = 0; q < np; ++q) atomicAdd(&bin[(int)((int64_t)n * (q + 1) / np) - (int)((int64_t)n * q / np)], 1);
+             atomicAdd(&njoin, 1);
+         });
+    __syncthreads();
+    if (!FILL) {
+        if (threadIdx.x == 0) {
+            int total = 0;
+            for (int i = 0; i < 64; ++i) total += bin[i];
+            counts[t] = (uint64_t)(uint32_t)total | ((uint64_t)(uint32_t)njoin << 32);
+        }
+        return;
+    }
+    if (threadIdx.x == 0) {
+        int at = 0;
+        for (int i = 63; i >= 0; --i) { const int n = bin[i]; bin[i] = at; at += n; }      // longest first
+        tiles[t].z = (int)(uint32_t)counts[t];
+        tiles[t].w = (int)(uint32_t)(counts[t] >> 32);
+        njoin = 0;
+    }
+    __syncthreads();
+    uint32_t *pc = pieces + (uint32_t)counts[t], *jn = joins + (uint32_t)(counts[t] >> 32);
+    each([&](int s, int lo, int n) { pc[atomicAdd(&bin[n], 1)] = piece_pack(lo - p0, n, s - s0, 0); },
+         [&](int s, int lo, int n, int to) {
+             const int np = (n + kPiece - 1) / kPiece;
+             const int slot = atomicAdd(&npart, np);
+             for (int q = 0; q < np; ++q) {
+                 const int x = (int)((int64_t)n * q / np), y = (int)((int64_t)n * (q + 1) / np);
+                 pc[atomicAdd(&bin[y - x], 1)] = piece_pack(lo - p0 + x, y - x, slot + q, 1);
+             }
+             jn[atomicAdd(&njoin, 1)] = join_pack(slot, np, s - s0, to);
+         });
+}
+
+__global__ void k_piece_end(int4 *__restrict__ tiles, int64_t ntiles, int npieces, int njoins) {
+    tiles[ntiles].z = npieces;
+    tiles[ntiles].w = njoins;
+}
+
+constexpr int kLongCut = 16;           // tiles from which on a cut segment is summed by a whole workgroup
+
+// Segments that begin in a tile and go on behind it.
+__global__ void __launch_bounds__(256) k_piece_cuts(const int32_t *__restrict__ pos, int64_t nseg, const int4 *__restrict__ tiles,
+                                                    int64_t ntiles, int4 *__restrict__ cuts, int *__restrict__ counters) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t + 1 >= ntiles) return;
+    const int p0 = tiles[t].x, p1 = tiles[t + 1].x, s = tiles[t + 1].y;
+    if (s >= nseg || pos[s] >= p1 || pos[s] < p0) return;
+    const int e = pos[s + 1];
+    int64_t lo = t + 1, hi = ntiles - 1;                     // last tile that starts before the segment's end
+    while (lo < hi) {
+        const int64_t mid = (lo + hi + 1) >> 1;
+        if (tiles[mid].x < e) lo = mid; else hi = mid - 1;
+    }
+    const int4 c = make_int4(s, (int)t, (int)lo, 0);
+    if (lo - t < kLongCut) cuts[atomicAdd(&counters[0], 1)] = c;
+    else cuts[ntiles - 1 - atomicAdd(&counters[1], 1)] = c;
+}
+
+unsigned grid_for(int64_t n) { return (unsigned)((n + 255) / 256); }
+
+}  // namespace
+
+hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, int64_t nnz, PiecePlan &plan, hipStream_t st) {
+    plan = PiecePlan();
+    if (nseg < 1 || nnz < 1) return hipSuccess;
+    const int units = nnz >= kLargeNnz ? kUnitsLarge : kUnitsSmall;
+    const int64_t ntiles = (nnz + nseg + units - 1) / units;
+    auto fail = [&](hipError_t e) { plan = PiecePlan(); return e; };
+    plan.tiles = dev_alloc(sizeof(int4) * (ntiles + 1));
+    plan.cuts = dev_alloc(sizeof(int4) * ntiles);
+    DevRef counts = dev_alloc(sizeof(uint64_t) * (ntiles + 1)), before = dev_alloc(sizeof(uint64_t) * (ntiles + 1));
+    DevRef counters = dev_alloc(2 * sizeof(int));
+    if (!plan.tiles || !plan.cuts || !counts || !before || !counters) return fail(hipErrorOutOfMemory);
+    int4 *tiles = (int4 *)plan.tiles->ptr;
+    uint64_t *cn = (uint64_t *)counts->ptr, *bf = (uint64_t *)before->ptr;
+    hipLaunchKernelGGL(k_piece_tiles, dim3(grid_for(ntiles + 1)), dim3(256), 0, st, pos, nseg, nnz, units, ntiles, tiles);
+    hipError_t e = hipMemsetAsync(cn + ntiles, 0, sizeof(uint64_t), st);
+    if (e == hipSuccess) e = hipMemsetAsync(counters->ptr, 0, 2 * sizeof(int), st);
+    if (e != hipSuccess) return fail(e);
+    hipLaunchKernelGGL((k_piece_fill<false>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, tiles, cn, (uint32_t *)nullptr,
+                       (uint32_t *)nullptr);
+    hipLaunchKernelGGL(k_piece_cuts, dim3(grid_for(ntiles)), dim3(256), 0, st, pos, nseg, (const int4 *)tiles, ntiles,
+                       (int4 *)plan.cuts->ptr, (int *)counters->ptr);
+    size_t tb = 0;
+    e = reorder_scan_flags(nullptr, &tb, cn, bf, ntiles + 1, st);
+    if (e != hipSuccess) return fail(e);
+    DevRef temp = dev_alloc(tb ? tb : 16);
+    if (!temp) return fail(hipErrorOutOfMemory);
+    e = reorder_scan_flags(temp->ptr, &tb, cn, bf, ntiles + 1, st);
+    uint64_t total = 0;
+    int nc[2] = {0, 0};
+    if (e == hipSuccess) e = hipMemcpyAsync(&total, bf + ntiles, sizeof total, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(nc, counters->ptr, sizeof nc, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return fail(e);
+    plan.nseg = nseg;
+    plan.units = units;
+    plan.ntiles = ntiles;
+    plan.npieces = (int64_t)(uint32_t)total;
+    plan.njoins = (int64_t)(uint32_t)(total >> 32);
+    plan.ncut = nc[0];
+    plan.ncut_long = nc[1];
+    plan.pieces = dev_alloc(sizeof(uint32_t) * plan.npieces);
+    plan.joins = dev_alloc(sizeof(uint32_t) * plan.njoins);
+    if (!plan.pieces || !plan.joins) return fail(hipErrorOutOfMemory);
+    hipLaunchKernelGGL((k_piece_fill<true>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, tiles, bf,
+                       (uint32_t *)plan.pieces->ptr, (uint32_t *)plan.joins->ptr);
+    hipLaunchKernelGGL(k_piece_end, dim3(1), dim3(1), 0, st, tiles, ntiles, (int)plan.npieces, (int)plan.njoins);
+    e = hipStreamSynchronize(st);                            // the temporaries go out of scope
+    return e == hipSuccess ? hipGetLastError() : fail(e);
+}
+
+}  // namespace comet

@@ -1,0 +1,58 @@
+// Piece plan of a compressed level: how the rank-R kernel takes its segments (built once per tensor, pieces.hip).
+//
+// The level is cut into tiles of `units` units -- a nonzero is a unit and a segment is one, so that a tile is the same
+// work whether it holds one long segment or hundreds of single nonzeros.  Inside a tile the segments become pieces of
+// at most kWhole nonzeros, sorted by length: the lane groups of a wavefront then walk pieces of (almost) equal length
+// side by side, and no nonzero asks whether a segment ends behind it.  A piece that is a whole segment writes its result
+// row; the sums of the pieces of a longer or cut segment meet in LDS (a join).  Segments cut by a tile boundary are
+// finished by a small kernel that works off a list.  The nonzeros themselves stay where the caller has them.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <cstdint>
+
+#include "tensor.hpp"
+
+namespace comet {
+
+// Units per tile.  Small tiles leave room for more workgroups per compute unit (LDS), which hides the latencies at the start of
+// a tile; that wins while the nonzeros (12 bytes each) fit the 256 MB memory-side cache beside other things.  Beyond,
+// memory bounds the kernel and larger tiles (and loads that do not displace the operand from that cache) are better:
+// TTM at rank 32, 8 M nonzeros 127 us with 768, 148 with 1536; 50 M nonzeros at rank 16 473 and 449 us.
+constexpr int kUnitsSmall = 768, kUnitsLarge = 1536;
+constexpr int64_t kLargeNnz = int64_t(10) << 20;
+constexpr int kWhole = 48;             // longest segment that is taken as one piece
+constexpr int kPiece = 32;             // longest piece of any other segment
+constexpr int kSnap = 32;              // a tile boundary inside a segment of at most this many nonzeros moves to its start
+
+// Most nonzeros, pieces and pieces that are not whole segments in a tile.
+__host__ __device__ constexpr int tile_items(int units) { return units + kSnap + 1; }
+__host__ __device__ constexpr int tile_pieces(int units) { return units + kSnap + 1; }
+__host__ __device__ constexpr int tile_parts(int units) { return 2 * tile_items(units) / (kWhole + 1) + 6; }
+
+// piece: start in the tile (11 bits), length (6), number (11), flag (1).  The number is the segment's number in the tile
+// for a whole segment, else the piece's slot among the partial sums (and the flag is set).
+static_assert(tile_items(kUnitsLarge) < 2048 && kWhole < 64, "fields of a piece");
+__host__ __device__ inline unsigned piece_pack(int start, int len, int num, int part) {
+    return (unsigned)start | ((unsigned)len << 11) | ((unsigned)num << 17) | ((unsigned)part << 28);
+}
+__device__ __forceinline__ int piece_start(unsigned p) { return (int)(p & 2047u); }
+__device__ __forceinline__ int piece_len(unsigned p) { return (int)((p >> 11) & 63u); }
+__device__ __forceinline__ int piece_num(unsigned p) { return (int)((p >> 17) & 2047u); }
+__device__ __forceinline__ bool piece_is_part(unsigned p) { return (p >> 28) & 1u; }
+
+// join: first slot (7 bits), slots (7), segment's number in the tile (11), where the sum goes (2)
+static_assert(tile_parts(kUnitsLarge) < 128, "fields of a join");
+enum JoinTo { kJoinRow = 0, kJoinHead = 1, kJoinTail = 2 };
+__host__ __device__ inline unsigned join_pack(int slot, int n, int seg, int to) {
+    return (unsigned)slot | ((unsigned)n << 7) | ((unsigned)seg << 14) | ((unsigned)to << 25);
+}
+__device__ __forceinline__ int join_slot(unsigned j) { return (int)(j & 127u); }
+__device__ __forceinline__ int join_count(unsigned j) { return (int)((j >> 7) & 127u); }
+__device__ __forceinline__ int join_seg(unsigned j) { return (int)((j >> 14) & 2047u); }
+__device__ __forceinline__ int join_to(unsigned j) { return (int)(j >> 25); }
+
+// Builds the plan for a level of nseg segments over nnz nonzeros.  Synchronises with st.
+hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, int64_t nnz, PiecePlan &plan, hipStream_t st);
+
+}  // namespace comet

@@ -41,6 +41,10 @@ hipError_t stream_segreduce_rankR(const Schedule &sc, const int32_t *pos, const 
                                   const int32_t *rowmap, const double *Dn, int R, double *out, void *scratch,
                                   hipStream_t st, Epilogue ep = Epilogue());
 
+// The same over the piece plan (defined in kernels_pieces.hip).
+hipError_t piece_rows(const PiecePlan &plan, const int32_t *crd, const double *vals, int64_t nnz, const int32_t *rowmap, const double *Dn,
+                      int64_t dense_rows, int R, double *out, void *scratch, hipStream_t st, Epilogue ep = Epilogue());
+
 namespace {
 
 // Carry-buffer layout inside the per-tensor scratch.  Level 0 holds one summary per tile: first[R],
@@ -278,13 +282,129 @@ __device__ __forceinline__ void finish_tile_walkers(const double *wopen, const i
     }
 }
 
+// A dense row of R values spread over the L lanes of a group: NL pieces of E values per lane, piece q of lane k at
+// columns E*(L*q + k) ...  A load instruction costs the texture-address unit 16 clocks however wide it is, so rows are
+// read 16 bytes per lane (E = 2) whenever R is even.  FULL: R = L*E*NL.  Otherwise lanes whose columns lie beyond R
+// read the row's last columns again (the same cache lines, no mask in the way of the load) and store nothing.
+// With E = 2 only the last piece can be ragged.
+template <int L, int E, int NL, bool FULL>
+struct RowOf {
+    static constexpr int V = E * NL;
+    static constexpr int kOwn = FULL ? 1 : (E == 2 ? (NL > 1 ? 2 : 1) : NL);   // different byte offsets kept per lane
+    unsigned at[kOwn];       // E = 2 and FULL: all pieces but the last, the last; E = 1: one per piece
+    int R, k;
+    __device__ __forceinline__ RowOf(int R_, int k_) : R(R_), k(k_) {
+        if constexpr (FULL) {
+            at[0] = 8u * E * (unsigned)k;
+        } else if constexpr (E == 2) {
+            if constexpr (NL > 1) at[0] = 16u * (unsigned)k;
+            const int c = col(NL - 1);
+            at[kOwn - 1] = 8u * (unsigned)(c < R ? c : R - E);
+        } else {
+#pragma unroll
+            for (int q = 0; q < NL; ++q) at[q] = 8u * (unsigned)(col(q) < R ? col(q) : R - 1);
+        }
+    }
+    __device__ __forceinline__ int col(int q) const { return E * (L * q + k); }
+    __device__ __forceinline__ bool has(int q) const { return FULL || col(q) < R; }
+    // the row that starts `o` bytes (BIG: doubles) into base
+    template <bool BIG>
+    __device__ __forceinline__ void load(const char *base, unsigned o, double *d) const {
+        if constexpr (BIG) {
+            const char *p = base + (size_t)o * 8;
+#pragma unroll
+            for (int q = 0; q < NL; ++q) read(p + byte(q), d + E * q);
+        } else if constexpr (FULL) {
+#pragma unroll
+            for (int q = 0; q < NL; ++q) read(base + (o + at[0]) + (size_t)(8 * L * E * q), d + E * q);
+        } else if constexpr (E == 2) {
+#pragma unroll
+            for (int q = 0; q + 1 < NL; ++q) read(base + (o + at[0]) + (size_t)(16 * L * q), d + E * q);
+            read(base + (o + at[kOwn - 1]), d + E * (NL - 1));
+        } else {
+#pragma unroll
+            for (int q = 0; q < NL; ++q) read(base + (o + at[q]), d + q);
+        }
+    }
+    __device__ __forceinline__ void load_at(const double *p, double *d) const {
+#pragma unroll
+        for (int q = 0; q < NL; ++q) read(reinterpret_cast<const char *>(p) + byte(q), d + E * q);
+    }
+    __device__ __forceinline__ void store(double *p, const double *v) const {
+#pragma unroll
+        for (int q = 0; q < NL; ++q)
+            if (has(q)) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) p[col(q) + e] = v[E * q + e];
+            }
+    }
+    // a finished result row, which is not read again: epilogue applied, non-temporal
+    __device__ __forceinline__ void store_result(double *p, const double *v, const Epilogue &ep) const {
+        double o[V];
+#pragma unroll
+        for (int q = 0; q < V; ++q) o[q] = v[q];
+        if (ep.on) {
+            if (ep.beta != 0.0) {
+                double old[V];
+                load_at(p, old);
+#pragma unroll
+                for (int q = 0; q < V; ++q) o[q] = fma(ep.alpha, v[q], ep.beta * old[q]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < V; ++q) o[q] = ep.alpha * v[q];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < NL; ++q)
+            if (has(q)) {
+                if constexpr (E == 2) {
+                    typedef double v2d __attribute__((ext_vector_type(2)));
+                    v2d x; x.x = o[2 * q]; x.y = o[2 * q + 1];
+                    __builtin_nontemporal_store(x, reinterpret_cast<v2d *>(p + col(q)));
+                } else {
+                    __builtin_nontemporal_store(o[q], p + col(q));
+                }
+            }
+    }
+    // rows in LDS take the lanes' pieces one after the other: L*V doubles, no holes
+    __device__ __forceinline__ void put(double *lds, const double *v) const {
+#pragma unroll
+        for (int q = 0; q < NL; ++q) {
+            if constexpr (E == 2) *reinterpret_cast<double2 *>(lds + col(q)) = make_double2(v[2 * q], v[2 * q + 1]);
+            else lds[col(q)] = v[q];
+        }
+    }
+    __device__ __forceinline__ void get(const double *lds, double *v) const {
+#pragma unroll
+        for (int q = 0; q < NL; ++q) {
+            if constexpr (E == 2) { const double2 x = *reinterpret_cast<const double2 *>(lds + col(q)); v[2 * q] = x.x; v[2 * q + 1] = x.y; }
+            else v[q] = lds[col(q)];
+        }
+    }
+
+private:
+    __device__ __forceinline__ unsigned byte(int q) const {
+        if constexpr (FULL) return at[0] + 8u * L * E * q;
+        else if constexpr (E == 2) return q < NL - 1 ? at[0] + 16u * L * q : at[kOwn - 1];
+        else return at[q];
+    }
+    static __device__ __forceinline__ void read(const char *p, double *d) {
+        if constexpr (E == 2) {
+            const double2 x = *reinterpret_cast<const double2 *>(p);
+            d[0] = x.x; d[1] = x.y;
+        } else {
+            d[0] = *reinterpret_cast<const double *>(p);
+        }
+    }
+};
+
 }  // namespace
 
 // Lane-group width of the rank-R kernels: 8 lanes, quads for ranks up to 8.
 inline int lanes_per_item(int64_t R) { return R <= 8 ? 4 : 8; }
 
 // Calls F<L, V, WIDE>(args...) for the specialisation that covers rank R.
-#define COMET_DISPATCH_RANK(F, R, ...)                                                     \
+#define COMET_DISPATCH_GROUPS(F, R, ...)                                                     \
     [&]() -> hipError_t {                                                                  \
         const int r_ = (int)(R);                                                           \
         if (lanes_per_item(r_) == 4) {                                                     \
@@ -303,5 +423,39 @@ inline int lanes_per_item(int64_t R) { return R <= 8 ? 4 : 8; }
         if (r_ <= 64)  return F<8, 8, false>(__VA_ARGS__);                                 \
         return F<8, 16, false>(__VA_ARGS__);                                               \
     }()
+
+// Calls F<L, E, NL, FULL, BIG>(args...) for the row layout that covers rank R (see RowOf).  big: operand rows need 64-bit
+// offsets; rare enough for the general layout to serve them.
+#define COMET_DISPATCH_RANK(F, R, big, ...)                                                \
+    [&]() -> hipError_t {                                                                  \
+        const int r_ = (int)(R);                                                           \
+        if (big || (r_ & 1)) {                                                             \
+            if (big) {                                                                     \
+                if (r_ <= 16) return F<16, 1, 1, false, true>(__VA_ARGS__);                \
+                if (r_ <= 32) return F<16, 1, 2, false, true>(__VA_ARGS__);                \
+                if (r_ <= 64) return F<16, 1, 4, false, true>(__VA_ARGS__);                \
+                return F<16, 1, 8, false, true>(__VA_ARGS__);                              \
+            }                                                                              \
+            if (r_ <= 4)  return F<4, 1, 1, false, false>(__VA_ARGS__);                    \
+            if (r_ <= 8)  return F<8, 1, 1, false, false>(__VA_ARGS__);                    \
+            if (r_ <= 16) return F<16, 1, 1, false, false>(__VA_ARGS__);                   \
+            if (r_ <= 32) return F<16, 1, 2, false, false>(__VA_ARGS__);                   \
+            if (r_ <= 64) return F<16, 1, 4, false, false>(__VA_ARGS__);                   \
+            return F<16, 1, 8, false, false>(__VA_ARGS__);                                 \
+        }                                                                                  \
+        if (r_ == 8)   return F<4, 2, 1, true, false>(__VA_ARGS__);                        \
+        if (r_ == 16)  return F<8, 2, 1, true, false>(__VA_ARGS__);                        \
+        if (r_ == 32)  return F<16, 2, 1, true, false>(__VA_ARGS__);                       \
+        if (r_ == 64)  return F<16, 2, 2, true, false>(__VA_ARGS__);                       \
+        if (r_ == 96)  return F<16, 2, 3, true, false>(__VA_ARGS__);                       \
+        if (r_ == 128) return F<16, 2, 4, true, false>(__VA_ARGS__);                       \
+        if (r_ < 8)    return F<4, 2, 1, false, false>(__VA_ARGS__);                       \
+        if (r_ < 16)   return F<8, 2, 1, false, false>(__VA_ARGS__);                       \
+        if (r_ < 32)   return F<16, 2, 1, false, false>(__VA_ARGS__);                      \
+        if (r_ < 64)   return F<16, 2, 2, false, false>(__VA_ARGS__);                      \
+        if (r_ < 96)   return F<16, 2, 3, false, false>(__VA_ARGS__);                      \
+        return F<16, 2, 4, false, false>(__VA_ARGS__);                                     \
+    }()
+
 
 }  // namespace comet

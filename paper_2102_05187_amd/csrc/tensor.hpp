@@ -93,6 +93,17 @@ struct FiberPlan {
     LightCopy light;      // all other fibers (row = fiber)
 };
 
+// Plan of the rank-R kernel (pieces.hpp).
+struct PiecePlan {
+    int64_t nseg = 0, ntiles = 0, npieces = 0, njoins = 0;
+    int     units = 0;                 // units per tile
+    int64_t ncut = 0, ncut_long = 0;   // segments cut by tile boundaries: over few tiles, over many
+    DevRef  tiles;        // int4 [ntiles + 1]: first nonzero, segment, piece and join of a tile
+    DevRef  pieces;       // uint32 [npieces], longest first inside a tile
+    DevRef  joins;        // uint32 [njoins]
+    DevRef  cuts;         // int4 [ntiles]: {segment, first tile, last tile}; the short ones in front, the long ones from the end
+};
+
 // Per-tensor schedule for the nonzero-tiled kernels, built once at creation.
 //   The leaf level's nonzeros are cut into tiles of kTile consecutive positions; seg_begin[t] is
 //   the segment (row / fiber) that contains the first nonzero of tile t (seg_begin[0] = 0 and
@@ -112,6 +123,7 @@ struct Schedule {
     int64_t max_seg_len = 0;      // longest leaf segment, in nonzeros (0 = unknown)
     int64_t max_parent_len = 0;   // CSF3: most nonzeros under one slice (0 = unknown)
     int64_t max_root_gap = -1;    // compressed root level: longest run of absent root coordinates (-1 = unknown)
+    PiecePlan pieces;
     HeavyPlan heavy;              // matrices only; nunits = 0 when the sweep does not apply
     FiberPlan fibers;             // CSF3 only; nheavy = 0 when the sweep does not apply
 };

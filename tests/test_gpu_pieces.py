@@ -1,0 +1,62 @@
+"""The rank-R kernel over pieces: segment lengths around its limits (pieces of 32, whole segments of 48, tiles of 768 and
+1536 units), segments over many tiles, empty ones, every row layout, with and without accumulation."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from synth import formats as fmt
+from synth import generate as gen
+from util import assert_values_close, np_
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 0, 31, 32, 33, 47, 48, 49, 2, 63, 64, 65, 0, 0, 95, 96, 97, 3, 767, 768, 769, 1, 1535, 1536, 1537, 700, 40, 5000, 7, 20000, 0]
+
+
+@pytest.fixture(scope="module")
+def comet():
+    from paper_2102_05187_amd import build
+    build.build_if_missing()
+    import paper_2102_05187_amd as c
+    return c
+
+
+def _edges():
+    lens = torch.tensor(EDGES * 2 + [1] * 1500 + [0] * 900 + [2, 48, 49] * 300 + [0, 30000], dtype=torch.int64)
+    return (lens.numel(), 40000), gen.matrix_from_row_lengths(lens.numel(), 40000, lens, 5)
+
+
+@pytest.mark.parametrize("R", [2, 3, 4, 7, 8, 9, 10, 16, 20, 31, 32, 33, 34, 48, 63, 64, 66, 96, 100, 127, 128])
+@pytest.mark.parametrize("layout", ["csr", "dcsr"])
+def test_edges_of_pieces(comet, layout, R):
+    (I, J), (rows, cols, vals) = _edges()
+    pack = fmt.pack_csr if layout == "csr" else fmt.pack_dcsr
+    A = comet.from_levels(pack(I, J, rows, cols, vals).to("cuda")).set_variant(2)
+    B = gen.dense_operand(3, 0, (J, R))
+    print("pieces %s R=%d nnz=%d" % (layout, R, vals.numel()), flush=True)
+    C = torch.full((I, R), float("nan"), dtype=torch.float64, device="cuda")
+    comet.comet_spmm(A, B.to("cuda"), C)
+    ref, absum = oracle.spmm(np_(rows), np_(cols), np_(vals), (I, J), np_(B))
+    assert_values_close(np_(C), ref, absum, "pieces %s R=%d" % (layout, R))
+    again = comet.comet_spmm(A, B.to("cuda"))
+    assert torch.equal(C, again), "two runs differ"
+    old = gen.dense_operand(4, 0, (I, R))
+    D = old.to("cuda")
+    comet.comet_spmm_axpby(A, 0.75, B.to("cuda"), -0.5, D)
+    assert_values_close(np_(D), 0.75 * ref - 0.5 * np_(old), 0.75 * absum + 0.5 * np.abs(np_(old)), "pieces axpby R=%d" % R)
+
+
+@pytest.mark.parametrize("R", [20, 33])
+def test_many_nonzeros_take_large_tiles(comet, R):
+    n = 650_000
+    lens = gen.zipf_row_lengths(n, 1.75, 4000, 3)
+    lens[::7] = 0
+    rows, cols, vals = gen.matrix_from_row_lengths(n, n, lens, 6, "cuda")
+    assert vals.numel() > 10 << 20
+    A = comet.from_levels(fmt.pack_csr(n, n, rows, cols, vals))
+    B = gen.dense_operand(3, 0, (n, R))
+    print("large tiles R=%d nnz=%d" % (R, vals.numel()), flush=True)
+    C = comet.comet_spmm(A, B.to("cuda"))
+    ref, absum = oracle.spmm(np_(rows.cpu()), np_(cols.cpu()), np_(vals.cpu()), (n, n), np_(B))
+    assert_values_close(np_(C), ref, absum, "large tiles R=%d" % R)
