@@ -78,7 +78,8 @@ __global__ void __launch_bounds__(256) k_piece_fill(const int32_t *__restrict__ 
     }
     __syncthreads();
     uint32_t *pc = pieces + (uint32_t)counts[t], *jn = joins + (uint32_t)(counts[t] >> 32);
-    each([&](int s, int lo, int n) { pc[atomicAdd(&bin[n], 1)] = piece_pack(lo - p0, n, s - s0, 0); },
+    // an empty segment starts nowhere: behind the tile's last nonzero there is none that its lanes could read beside longer pieces
+    each([&](int s, int lo, int n) { pc[atomicAdd(&bin[n], 1)] = piece_pack(n ? lo - p0 : 0, n, s - s0, 0); },
          [&](int s, int lo, int n, int to) {
              const int np = (n + kPiece - 1) / kPiece;
              const int slot = atomicAdd(&npart, np);

@@ -23,7 +23,9 @@ def comet():
 
 
 def _edges():
-    lens = torch.tensor(EDGES * 2 + [1] * 1500 + [0] * 900 + [2, 48, 49] * 300 + [0, 30000], dtype=torch.int64)
+    # behind them tiles that end with empty rows next to a few long ones
+    lens = torch.tensor(EDGES * 2 + [1] * 1500 + [0] * 900 + [2, 48, 49] * 300 + [0, 30000] + ([20, 24, 28] + [0] * 900) * 4,
+                        dtype=torch.int64)
     return (lens.numel(), 40000), gen.matrix_from_row_lengths(lens.numel(), 40000, lens, 5)
 
 
