@@ -25,10 +25,12 @@ constexpr int kWhole = 48;             // longest segment that is taken as one p
 constexpr int kPiece = 32;             // longest piece of any other segment
 constexpr int kSnap = 32;              // a tile boundary inside a segment of at most this many nonzeros moves to its start
 
-// Most nonzeros, pieces and pieces that are not whole segments in a tile.
+// Most nonzeros, pieces and pieces that are not whole segments in a tile.  The last: n > kWhole nonzeros become at most
+// 3 n / 65 pieces (65 make 3), a cut segment at either end of the tile at most one more than that.
 __host__ __device__ constexpr int tile_items(int units) { return units + kSnap + 1; }
 __host__ __device__ constexpr int tile_pieces(int units) { return units + kSnap + 1; }
-__host__ __device__ constexpr int tile_parts(int units) { return 2 * tile_items(units) / (kWhole + 1) + 6; }
+__host__ __device__ constexpr int tile_parts(int units) { return 3 * tile_items(units) / 65 + 3; }
+static_assert(kWhole == 48 && kPiece == 32, "tile_parts");
 
 // piece: start in the tile (11 bits), length (6), number (11), flag (1).  The number is the segment's number in the tile
 // for a whole segment, else the piece's slot among the partial sums (and the flag is set).

@@ -62,3 +62,18 @@ def test_many_nonzeros_take_large_tiles(comet, R):
     C = comet.comet_spmm(A, B.to("cuda"))
     ref, absum = oracle.spmm(np_(rows.cpu()), np_(cols.cpu()), np_(vals.cpu()), (n, n), np_(B))
     assert_values_close(np_(C), ref, absum, "large tiles R=%d" % R)
+
+
+@pytest.mark.parametrize("R", [20, 128])
+def test_most_partial_sums_in_a_tile(comet, R):
+    # rows of 65 are three pieces each: 23 whole ones and a cut one at both ends give a large tile 71 partial sums
+    n = 165_000
+    lens = torch.full((n,), 65, dtype=torch.int64)
+    rows, cols, vals = gen.matrix_from_row_lengths(n, 50_000, lens, 7, "cuda")
+    assert vals.numel() > 10 << 20
+    A = comet.from_levels(fmt.pack_csr(n, 50_000, rows, cols, vals))
+    B = gen.dense_operand(3, 0, (50_000, R))
+    print("partial sums R=%d nnz=%d" % (R, vals.numel()), flush=True)
+    C = comet.comet_spmm(A, B.to("cuda"))
+    ref, absum = oracle.spmm(np_(rows.cpu()), np_(cols.cpu()), np_(vals.cpu()), (n, 50_000), np_(B))
+    assert_values_close(np_(C), ref, absum, "partial sums R=%d" % R)
