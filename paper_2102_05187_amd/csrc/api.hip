@@ -102,6 +102,12 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st) {
         if (!sc.chunk_seg_begin) return COMET_ERR_ALLOC;
         HIP_TRY(comet::build_seg_begin(t.pos_i(leaf), sc.nseg, sc.nnz, comet::kChunk, sc.nchunks,
                                        (int32_t *)sc.chunk_seg_begin->ptr, st));
+        if (t.fmt == Format::CSF3 && sc.nnz < comet::kChunkWalkNnz) {
+            sc.chunk_slice_begin = comet::dev_alloc(sizeof(int32_t) * (sc.nchunks + 1));
+            if (!sc.chunk_slice_begin) return COMET_ERR_ALLOC;
+            HIP_TRY(comet::build_parent_begin(t.pos_i(1), t.pos_len[1] - 1, (const int32_t *)sc.chunk_seg_begin->ptr,
+                                              sc.nchunks, (int32_t *)sc.chunk_slice_begin->ptr, st));
+        }
         HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
         HIP_TRY(comet::count_empty_segments(t.pos_i(leaf), sc.nseg, (int32_t *)mx->ptr, st));
         rs = read_i32((const int32_t *)mx->ptr, 1, &h, st);
@@ -417,6 +423,10 @@ static size_t scratch_need(const comet_tensor *t, int64_t R) {
         if (t->sched.heavy.nunits > 0) b += comet::heavy_partial_bytes(t->sched.heavy, R > 64 ? 64 : R);
         if (t->sched.fibers.nheavy > 0) b += comet::fiber_partial_bytes(t->sched.fibers, R >= 32 ? 32 : 16);
         if (b > need) need = b;
+        if (t->fmt == Format::CSF3) {
+            b = comet::mttkrp_scratch_bytes(t->sched, R);
+            if (b > need) need = b;
+        }
     }
     return need;
 }
@@ -1005,7 +1015,7 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
     }
     if (X->nvals == 0) return COMET_OK;
     if (tiled) {
-        comet_status rs = ensure_scratch(X, comet::stream_scratch_bytes(X->sched.ntiles, R));
+        comet_status rs = ensure_scratch(X, comet::mttkrp_scratch_bytes(X->sched, R));
         if (rs != COMET_OK) return rs;
         HIP_TRY(comet::stream_mttkrp(X->sched, X->pos_i(1), X->crd_i(0), nslice, X->pos_i(2), X->crd_i(1),
                                      X->crd_i(2), X->vals_d(), B, C, R, M, X->scratch->ptr, st, ep));

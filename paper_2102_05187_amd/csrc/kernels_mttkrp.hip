@@ -13,7 +13,8 @@ namespace {
 // row crd1[slice] of M.  Two LDS maps, both keyed by tile item: ts = the fiber's coordinate crd2[fiber]
 // (its row of B) at a fiber's last nonzero, tm = output row at a slice's last nonzero (-1 elsewhere).  Both
 // are looked up while the maps are built, with coalesced loads, so that the walk has no dependent index load.
-template <int L, int V, bool WIDE>
+// TILE: kTile, or kChunk for lists below kChunkWalkNnz.
+template <int L, int V, bool WIDE, int TILE>
 __global__ void __launch_bounds__(256) k_stream_mttkrp(const int32_t *__restrict__ pos2, const int32_t *__restrict__ crd1,
                                                        const int32_t *__restrict__ pos3, const int32_t *__restrict__ crd2,
                                                        const int32_t *__restrict__ crd3, const double *__restrict__ vals,
@@ -22,22 +23,22 @@ __global__ void __launch_bounds__(256) k_stream_mttkrp(const int32_t *__restrict
                                                        const double *__restrict__ Bm, const double *__restrict__ Cm,
                                                        double *__restrict__ M, int64_t nnz, int64_t nfib, int64_t ntiles,
                                                        int R, void *scratch, Epilogue ep) {
-    constexpr int NW = 256 / L, WI = kTile / NW, SB = 4 * L;
-    constexpr int kMapInts = 2 * kTile;
+    constexpr int NW = 256 / L, WI = TILE / NW, SB = 4 * L;
+    constexpr int kMapInts = 2 * TILE;
     constexpr int kOpenInts = 256 * V * 2;
     constexpr int kLdsInts = kMapInts > kOpenInts ? kMapInts : kOpenInts;
     __shared__ __attribute__((aligned(16))) int32_t lds[kLdsInts];
     __shared__ int wht[NW], wfirst_j[NW];
-    int32_t *ts = lds, *tm = lds + kTile;
+    int32_t *ts = lds, *tm = lds + TILE;
     double *wopen = reinterpret_cast<double *>(lds);              // reused once the maps are dead
     const int64_t t = blockIdx.x;
-    const int64_t tb = t * (int64_t)kTile, te = tb + kTile;
+    const int64_t tb = t * (int64_t)TILE, te = tb + TILE;
     const int g = threadIdx.x / L, j = threadIdx.x % L;
     const int64_t gb = tb + (int64_t)g * WI;
     LaneItems cur;
     lane_load_items(cur, crd3, vals, gb + 4 * j, nnz);            // in flight while the maps are built
 
-    for (int i = threadIdx.x * 4; i < 2 * kTile; i += blockDim.x * 4)
+    for (int i = threadIdx.x * 4; i < 2 * TILE; i += blockDim.x * 4)
         *reinterpret_cast<int4 *>(lds + i) = make_int4(-1, -1, -1, -1);
     __syncthreads();
     for (int32_t f = seg_begin[t] + threadIdx.x; f < seg_begin[t + 1]; f += blockDim.x) {
@@ -163,13 +164,21 @@ template <int L, int V, bool WIDE>
 hipError_t launch_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, const int32_t *pos3,
                          const int32_t *crd2, const int32_t *crd3, const double *vals, const double *B, const double *C,
                          int R, double *M, void *scratch, hipStream_t st, Epilogue ep) {
-    hipLaunchKernelGGL((k_stream_mttkrp<L, V, WIDE>), dim3((unsigned)sc.ntiles), dim3(256), 0, st, pos2, crd1, pos3, crd2,
-                       crd3, vals, (const int32_t *)sc.seg_begin->ptr, (const int32_t *)sc.slice_begin->ptr, B, C, M,
-                       sc.nnz, sc.nseg, sc.ntiles, R, scratch, ep);
+    auto go = [&](auto kernel, int64_t ntiles, const DevRef &fibers, const DevRef &slices) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)ntiles), dim3(256), 0, st, pos2, crd1, pos3, crd2, crd3, vals,
+                           (const int32_t *)fibers->ptr, (const int32_t *)slices->ptr, B, C, M, sc.nnz, sc.nseg, ntiles, R,
+                           scratch, ep);
+    };
+    if (sc.chunk_slice_begin) go(k_stream_mttkrp<L, V, WIDE, kChunk>, sc.nchunks, sc.chunk_seg_begin, sc.chunk_slice_begin);
+    else go(k_stream_mttkrp<L, V, WIDE, kTile>, sc.ntiles, sc.seg_begin, sc.slice_begin);
     return hipGetLastError();
 }
 
 }  // namespace
+
+size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R) {
+    return stream_scratch_bytes(sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, R);
+}
 
 hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, int64_t nslice,
                          const int32_t *pos3, const int32_t *crd2, const int32_t *crd3, const double *vals,
@@ -181,7 +190,9 @@ hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t 
     const int r = (int)R;
     hipError_t e = COMET_DISPATCH_GROUPS(launch_mttkrp, R, sc, pos2, crd1, pos3, crd2, crd3, vals, B, C, r, M, scratch, st, ep);
     if (e != hipSuccess) return e;
-    return run_fixup(scratch, sc.ntiles, r, nullptr, M, sc.max_parent_len > 0 ? sc.max_parent_len / kTile + 2 : 0, st, ep);
+    const int tile = sc.chunk_slice_begin ? kChunk : kTile;
+    return run_fixup(scratch, sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, r, nullptr, M,
+                     sc.max_parent_len > 0 ? sc.max_parent_len / tile + 2 : 0, st, ep);
 }
 
 }  // namespace comet

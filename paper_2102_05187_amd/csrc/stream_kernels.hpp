@@ -22,6 +22,7 @@ bool   stream_supports_coo();
 size_t stream_scratch_bytes(int64_t ntiles, int64_t R);
 size_t piece_scratch_bytes(const PiecePlan &plan, int64_t R);
 size_t segreduce_scratch_bytes(const Schedule &sc, int64_t R);     // what stream_segreduce needs
+size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R);        // what stream_mttkrp needs
 
 // out[row(s), :] = sum_{p in segment s} vals[p] * Dn[crd[p], :],  row(s) = rowmap ? rowmap[s] : s.
 // Every segment of the level is written (empty ones with zeros).  dense_rows = number of rows of Dn.

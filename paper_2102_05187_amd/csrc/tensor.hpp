@@ -44,6 +44,11 @@ enum class Format { CSR, DCSR, COO2, COO3, CSF3, CSF3_DENSE_LEAF, COO3_DENSE_LEA
 constexpr int kTile = 4096;
 // Items per chunk of the wavefront-per-chunk kernel (one wavefront's share of a tile).
 constexpr int kChunk = 1024;
+// Nonzeros below which MTTKRP walks chunks instead of tiles: a walker's items are a serial chain of gathers, four times
+// shorter then, and a short list fills the chip only with chunks.  Tiles and chunks, power-law tensors: 100 000 nonzeros, rank
+// 10, 54 and 28 us, rank 64, 91 and 49; 1 M, rank 16, 73 and 55; 2.5 M, ranks 16 / 32 / 64, 87 / 133 / 234 and 77 / 123 / 210.
+// From 5 M (119 / 196 / 341 and 122 / 212 / 336) the partial sums and the fuller chip go against chunks; 40 M, rank 32: 988 and 1186.
+constexpr int64_t kChunkWalkNnz = int64_t(3) << 20;
 
 // The segments (rows / fibers) of a compressed level that a sweep does NOT take, copied out as a [CU,CU] matrix
 // of their own: row r of the copy holds the nonzeros of one such segment and stands for result row rows[r].
@@ -118,6 +123,7 @@ struct Schedule {
     int64_t nruns = 0;     // COO3: number of distinct (i,j) pairs
     DevRef  chunk_seg_begin;   // int32 [nchunks + 1]: seg_begin at kChunk granularity
     DevRef  chunk_run_base;    // int32 [nchunks + 1]: run_base at kChunk granularity (COO3 only)
+    DevRef  chunk_slice_begin; // int32 [nchunks + 1]: slice_begin at kChunk granularity (CSF3 below kChunkWalkNnz only)
     int64_t nchunks = 0;
     int64_t empty_segments = -1;  // leaf segments without a nonzero (-1 = unknown)
     int64_t max_seg_len = 0;      // longest leaf segment, in nonzeros (0 = unknown)
