@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
     };
     auto finish = [&](uint32_t pd, int r, const double *acc) {
         if (piece_is_part(pd)) rw.put(part + piece_num(pd) * kRow, acc);
-        else rw.store_result(out + (int64_t)r * R, acc, ep);
+        else rw.store_result(out + (int64_t)r * R, acc, ep, piece_len(pd) == 0);
     };
     // Longest pieces first: batches of one piece per group until the longest piece of a batch is short.
     int b = wave * KP;

@@ -338,8 +338,9 @@ struct RowOf {
                 for (int e = 0; e < E; ++e) p[col(q) + e] = v[E * q + e];
             }
     }
-    // a finished result row, which is not read again: epilogue applied, non-temporal
-    __device__ __forceinline__ void store_result(double *p, const double *v, const Epilogue &ep) const {
+    // a finished result row, which is not read again: epilogue applied, non-temporal.  empty: no nonzero contributed to it, so
+    // that alpha has no part in it (alpha * 0 is not 0 for an infinite or NaN alpha), see ep_empty
+    __device__ __forceinline__ void store_result(double *p, const double *v, const Epilogue &ep, bool empty = false) const {
         double o[V];
 #pragma unroll
         for (int q = 0; q < V; ++q) o[q] = v[q];
@@ -348,10 +349,10 @@ struct RowOf {
                 double old[V];
                 load_at(p, old);
 #pragma unroll
-                for (int q = 0; q < V; ++q) o[q] = fma(ep.alpha, v[q], ep.beta * old[q]);
+                for (int q = 0; q < V; ++q) o[q] = empty ? ep.beta * old[q] : fma(ep.alpha, v[q], ep.beta * old[q]);
             } else {
 #pragma unroll
-                for (int q = 0; q < V; ++q) o[q] = ep.alpha * v[q];
+                for (int q = 0; q < V; ++q) o[q] = empty ? 0.0 : ep.alpha * v[q];
             }
         }
 #pragma unroll

@@ -86,6 +86,26 @@ def test_spmm_axpby_with_heavy_rows(comet, layout, R, alpha, beta):
     assert_values_close(np_(C), ref, absum, "spmm_axpby heavy R=%d" % R)
 
 
+@pytest.mark.parametrize("alpha", [float("inf"), float("nan")])
+@pytest.mark.parametrize("beta", [0.0, -1.5])
+@pytest.mark.parametrize("variant", [2, 3])
+@pytest.mark.parametrize("R", [1, 3, 16, 20, 128])
+@pytest.mark.parametrize("layout", ["csr", "dcsr"])
+def test_a_non_finite_alpha_leaves_rows_without_nonzeros_alone(comet, layout, R, variant, beta, alpha):
+    """Rows that receive no contribution become beta times their old value, whatever alpha is."""
+    lens = torch.tensor([40, 0, 3, 0, 0, 5000] + [0] * 900 + [1, 60], dtype=torch.int64)
+    rows, cols, vals = gen.matrix_from_row_lengths(lens.numel(), 6000, lens, 7)
+    T = (fmt.pack_csr if layout == "csr" else fmt.pack_dcsr)(lens.numel(), 6000, rows, cols, vals)
+    say("non-finite alpha=%g layout=%s R=%d variant=%d beta=%g" % (alpha, layout, R, variant, beta))
+    A = comet.from_levels(T.to("cuda")).set_variant(variant)
+    old, given = _old((lens.numel(), R) if R > 1 else (lens.numel(),), beta, 36)
+    C, B = dev(given).clone(), dev(gen.dense_operand(2, 0, (6000, R) if R > 1 else (6000,)))
+    (comet.comet_spmm_axpby if R > 1 else comet.comet_spmv_axpby)(A, alpha, B, beta, C)
+    C = C.cpu()
+    assert torch.equal(C[lens == 0], beta * old[lens == 0] if beta else torch.zeros_like(old[lens == 0]))
+    assert not torch.isfinite(C[lens > 0]).any()
+
+
 def test_accumulating_into_zeros_equals_the_plain_product(comet):
     """beta = 1 on a zero result and alpha = 1, beta = 0 on NaN both give comet_spmm's result bit for bit."""
     (I, J), (rows, cols, vals) = MATRIX_CASES["zipf_rows"]
