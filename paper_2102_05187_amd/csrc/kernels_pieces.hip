@@ -7,8 +7,10 @@
 // spends as few instructions as it can: rows 16 bytes per lane, nonzeros 16 bytes per lane into LDS, from where a lane
 // group reads one with a broadcast, and result rows stored for all groups of a wavefront at once, which pieces of equal
 // length make possible.  A walk that asks at every nonzero whether a segment ends (kernels_rankR.hip) stores few rows at a time.
-// Measured before and after, that walk and this: SpMM on 11.3 M nonzeros within 2000 columns of the diagonal, rank 20,
-// 313 and 157 us; TTM on 8 M nonzeros in 1.6 M fibers, rank 32, 181 and 127 us; 200 000 nonzeros, rank 16, 29 and 14 us.
+// Measured before and after, that walk and this, for whole calls whose inputs change from call to call: SpMM on 11.3 M
+// nonzeros within 2000 columns of the diagonal, rank 20, added to the old result, 358 and 236 us; TTM on 8 M nonzeros in
+// 1.6 M fibers, rank 32, 180 and 172 us (the result's 415 MB and nonzeros that come from memory leave little to gain);
+// 200 000 nonzeros, rank 16, 29 and 14 us.
 #include "pieces.hpp"
 #include "stream_common.hpp"
 
@@ -22,7 +24,7 @@ struct Item { unsigned off, pad; double val; };                   // a nonzero: 
 __host__ __device__ inline int lds_pieces_at(int units) { return (tile_items(units) + 7) * (int)sizeof(Item); }
 __host__ __device__ inline int lds_parts_at(int units) { return lds_pieces_at(units) + ((tile_pieces(units) + 3) & ~3) * 4; }
 
-// stream: the nonzeros are read around the caches, and neighbouring tiles go to different XCDs (see kLargeNnz)
+// stream: the nonzeros are read around the caches (kStreamNnz)
 template <int L, int E, int NL, bool FULL, bool BIG, bool ROWMAP>
 __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, const uint32_t *__restrict__ pieces,
                                                 const uint32_t *__restrict__ joins, int units, int stream,
@@ -38,35 +40,42 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
     uint32_t *piece = reinterpret_cast<uint32_t *>(lds + lds_pieces_at(units));
     double *part = reinterpret_cast<double *>(lds + lds_parts_at(units));
     // Workgroups go to the eight XCDs in turn.  Each XCD gets a contiguous eighth of the tiles, so that operand rows which
-    // neighbouring segments share are shared in its L2 (banded matrix above: 177 -> 167 us).
-    const int n8 = stream ? 0 : (int)gridDim.x / 8;
+    // neighbouring segments share are shared in its L2 (12 M nonzeros within 2000 columns, rank 32: 403 -> 284 us).
+    const int n8 = (int)gridDim.x / 8;
     const int t = (int)blockIdx.x < 8 * n8 ? ((int)blockIdx.x & 7) * n8 + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
     const int4 t0 = tiles[t], t1 = tiles[t + 1];
     const int np = t1.z - t0.z, nj = t1.w - t0.w;
     const unsigned unit = (unsigned)R * (BIG ? 1u : 8u);          // row offsets: bytes, or doubles for operands of 4 GiB and more
     // nonzeros of the tile from the 16-byte boundary in front of them
     const int p0 = t0.x & ~3, lead = t0.x - p0, n_items = t1.x - p0;
-    for (int i = (int)threadIdx.x * 4; i < n_items; i += 1024) {
-        int c[4];
-        double a[4];
-        if ((int64_t)p0 + i + 4 <= nnz) {
-            typedef int v4i __attribute__((ext_vector_type(4)));
-            typedef double v2d __attribute__((ext_vector_type(2)));
-            const v4i *pc = reinterpret_cast<const v4i *>(crd + p0 + i);
-            const v2d *pv = reinterpret_cast<const v2d *>(vals + p0 + i);
-            v4i cv;
-            v2d x, y;
-            if (stream) { cv = __builtin_nontemporal_load(pc); x = __builtin_nontemporal_load(pv); y = __builtin_nontemporal_load(pv + 1); }
-            else { cv = pc[0]; x = pv[0]; y = pv[1]; }
-            c[0] = cv.x; c[1] = cv.y; c[2] = cv.z; c[3] = cv.w;
-            a[0] = x.x; a[1] = x.y; a[2] = y.x; a[3] = y.y;
-        } else {
+    // (two loops: the compiler folds a plain and a non-temporal load of one address into a plain one)
+    auto stage = [&](auto around) {
+        for (int i = (int)threadIdx.x * 4; i < n_items; i += 1024) {
+            int c[4];
+            double a[4];
+            if ((int64_t)p0 + i + 4 <= nnz) {
+                typedef int v4i __attribute__((ext_vector_type(4)));
+                typedef double v2d __attribute__((ext_vector_type(2)));
+                const v4i *pc = reinterpret_cast<const v4i *>(crd + p0 + i);
+                const v2d *pv = reinterpret_cast<const v2d *>(vals + p0 + i);
+                v4i cv;
+                v2d x, y;
+                if constexpr (decltype(around)::value) {
+                    cv = __builtin_nontemporal_load(pc); x = __builtin_nontemporal_load(pv); y = __builtin_nontemporal_load(pv + 1);
+                } else {
+                    cv = pc[0]; x = pv[0]; y = pv[1];
+                }
+                c[0] = cv.x; c[1] = cv.y; c[2] = cv.z; c[3] = cv.w;
+                a[0] = x.x; a[1] = x.y; a[2] = y.x; a[3] = y.y;
+            } else {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { const bool in = i + u < n_items; c[u] = in ? crd[p0 + i + u] : 0; a[u] = in ? vals[p0 + i + u] : 0.0; }
+                for (int u = 0; u < 4; ++u) { const bool in = i + u < n_items; c[u] = in ? crd[p0 + i + u] : 0; a[u] = in ? vals[p0 + i + u] : 0.0; }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) item[i + u] = Item{(unsigned)c[u] * unit, 0u, a[u]};
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) item[i + u] = Item{(unsigned)c[u] * unit, 0u, a[u]};
-    }
+    };
+    if (stream) stage(IntC<1>{}); else stage(IntC<0>{});
     for (int i = threadIdx.x; i < np; i += 256) piece[i] = pieces[t0.z + i];
     __syncthreads();
 
@@ -248,7 +257,7 @@ struct PieceArgs {
 
 template <int L, int E, int NL, bool FULL, bool BIG>
 hipError_t launch_pieces(const PieceArgs &a) {
-    const int lds = lds_parts_at(a.plan.units) + tile_parts(a.plan.units) * L * E * NL * 8;
+    const int lds = lds_parts_at(a.plan.units) + a.plan.max_parts * L * E * NL * 8;
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)a.plan.ntiles), dim3(256), (unsigned)lds, a.st, (const int4 *)a.plan.tiles->ptr,
                            (const uint32_t *)a.plan.pieces->ptr, (const uint32_t *)a.plan.joins->ptr, a.plan.units, a.plan.units == kUnitsLarge,

@@ -619,7 +619,7 @@ hipError_t stream_segreduce(const Schedule &sc, const int32_t *pos, const int32_
         // Which walk: the pieces, except for narrow rows of full width over many nonzeros, where memory bounds both and
         // the walk over whole tiles of nonzeros keeps more of the list in flight (TTM at rank 16, 36 M nonzeros in 6.5 M
         // fibers: 485 us against 535; level at 12 M nonzeros, behind by 1.3 to 2 at 5 M and below).
-        const bool long_list = sc.nnz >= kLargeNnz && (R == 8 || R == 16);
+        const bool long_list = sc.nnz >= kWalkNnz && (R == 8 || R == 16);
         if (!long_list)
             return piece_rows(sc.pieces, crd, vals, sc.nnz, rowmap, Dn, dense_rows, (int)R, out, scratch, st, ep);
         e = stream_segreduce_rankR(sc, pos, crd, vals, rowmap, Dn, (int)R, out, scratch, st, ep);

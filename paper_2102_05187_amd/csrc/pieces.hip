@@ -34,8 +34,8 @@ __global__ void __launch_bounds__(256) k_piece_tiles(const int32_t *__restrict__
 // The pieces and joins of tile t; FILL = false only counts them.
 template <bool FILL>
 __global__ void __launch_bounds__(256) k_piece_fill(const int32_t *__restrict__ pos, int64_t nseg, int64_t ntiles, int4 *__restrict__ tiles,
-                                                    uint64_t *__restrict__ counts, uint32_t *__restrict__ pieces,
-                                                    uint32_t *__restrict__ joins) {
+                                                    uint64_t *__restrict__ counts, int *__restrict__ max_parts,
+                                                    uint32_t *__restrict__ pieces, uint32_t *__restrict__ joins) {
     __shared__ int bin[64], npart, njoin;
     const int64_t t = blockIdx.x;
     const int4 a = tiles[t], b = tiles[t + 1];
@@ -59,6 +59,7 @@ __global__ void __launch_bounds__(256) k_piece_fill(const int32_t *__restrict__ 
              const int np = (n + kPiece - 1) / kPiece;
              for (int q = 0; q < np; ++q) atomicAdd(&bin[(int)((int64_t)n * (q + 1) / np) - (int)((int64_t)n * q / np)], 1);
              atomicAdd(&njoin, 1);
+             atomicAdd(&npart, np);
          });
     __syncthreads();
     if (!FILL) {
@@ -66,6 +67,8 @@ __global__ void __launch_bounds__(256) k_piece_fill(const int32_t *__restrict__ 
             int total = 0;
             for (int i = 0; i < 64; ++i) total += bin[i];
             counts[t] = (uint64_t)(uint32_t)total | ((uint64_t)(uint32_t)njoin << 32);
+            // few tiles raise the maximum; atomics of all of them on one address would queue up
+            if (npart > __hip_atomic_load(max_parts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(max_parts, npart);
         }
         return;
     }
@@ -74,6 +77,7 @@ __global__ void __launch_bounds__(256) k_piece_fill(const int32_t *__restrict__ 
         for (int i = 63; i >= 0; --i) { const int n = bin[i]; bin[i] = at; at += n; }      // longest first
         tiles[t].z = (int)(uint32_t)counts[t];
         tiles[t].w = (int)(uint32_t)(counts[t] >> 32);
+        npart = 0;
         njoin = 0;
     }
     __syncthreads();
@@ -123,22 +127,22 @@ unsigned grid_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, int64_t nnz, PiecePlan &plan, hipStream_t st) {
     plan = PiecePlan();
     if (nseg < 1 || nnz < 1) return hipSuccess;
-    const int units = nnz >= kLargeNnz ? kUnitsLarge : kUnitsSmall;
+    const int units = nnz >= kStreamNnz ? kUnitsLarge : kUnitsSmall;
     const int64_t ntiles = (nnz + nseg + units - 1) / units;
     auto fail = [&](hipError_t e) { plan = PiecePlan(); return e; };
     plan.tiles = dev_alloc(sizeof(int4) * (ntiles + 1));
     plan.cuts = dev_alloc(sizeof(int4) * ntiles);
     DevRef counts = dev_alloc(sizeof(uint64_t) * (ntiles + 1)), before = dev_alloc(sizeof(uint64_t) * (ntiles + 1));
-    DevRef counters = dev_alloc(2 * sizeof(int));
+    DevRef counters = dev_alloc(3 * sizeof(int));   // short cuts, long cuts, most partial sums in a tile
     if (!plan.tiles || !plan.cuts || !counts || !before || !counters) return fail(hipErrorOutOfMemory);
     int4 *tiles = (int4 *)plan.tiles->ptr;
     uint64_t *cn = (uint64_t *)counts->ptr, *bf = (uint64_t *)before->ptr;
     hipLaunchKernelGGL(k_piece_tiles, dim3(grid_for(ntiles + 1)), dim3(256), 0, st, pos, nseg, nnz, units, ntiles, tiles);
     hipError_t e = hipMemsetAsync(cn + ntiles, 0, sizeof(uint64_t), st);
-    if (e == hipSuccess) e = hipMemsetAsync(counters->ptr, 0, 2 * sizeof(int), st);
+    if (e == hipSuccess) e = hipMemsetAsync(counters->ptr, 0, 3 * sizeof(int), st);
     if (e != hipSuccess) return fail(e);
-    hipLaunchKernelGGL((k_piece_fill<false>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, tiles, cn, (uint32_t *)nullptr,
-                       (uint32_t *)nullptr);
+    hipLaunchKernelGGL((k_piece_fill<false>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, tiles, cn,
+                       (int *)counters->ptr + 2, (uint32_t *)nullptr, (uint32_t *)nullptr);
     hipLaunchKernelGGL(k_piece_cuts, dim3(grid_for(ntiles)), dim3(256), 0, st, pos, nseg, (const int4 *)tiles, ntiles,
                        (int4 *)plan.cuts->ptr, (int *)counters->ptr);
     size_t tb = 0;
@@ -148,7 +152,7 @@ hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, int64_t nnz, Piece
     if (!temp) return fail(hipErrorOutOfMemory);
     e = reorder_scan_flags(temp->ptr, &tb, cn, bf, ntiles + 1, st);
     uint64_t total = 0;
-    int nc[2] = {0, 0};
+    int nc[3] = {0, 0, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(&total, bf + ntiles, sizeof total, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipMemcpyAsync(nc, counters->ptr, sizeof nc, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -160,11 +164,12 @@ hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, int64_t nnz, Piece
     plan.njoins = (int64_t)(uint32_t)(total >> 32);
     plan.ncut = nc[0];
     plan.ncut_long = nc[1];
+    plan.max_parts = nc[2];
     plan.pieces = dev_alloc(sizeof(uint32_t) * plan.npieces);
     plan.joins = dev_alloc(sizeof(uint32_t) * plan.njoins);
     if (!plan.pieces || !plan.joins) return fail(hipErrorOutOfMemory);
     hipLaunchKernelGGL((k_piece_fill<true>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, tiles, bf,
-                       (uint32_t *)plan.pieces->ptr, (uint32_t *)plan.joins->ptr);
+                       (int *)nullptr, (uint32_t *)plan.pieces->ptr, (uint32_t *)plan.joins->ptr);
     hipLaunchKernelGGL(k_piece_end, dim3(1), dim3(1), 0, st, tiles, ntiles, (int)plan.npieces, (int)plan.njoins);
     e = hipStreamSynchronize(st);                            // the temporaries go out of scope
     return e == hipSuccess ? hipGetLastError() : fail(e);

@@ -15,12 +15,15 @@
 
 namespace comet {
 
-// Units per tile.  Small tiles leave room for more workgroups per compute unit (LDS), which hides the latencies at the start of
-// a tile; that wins while the nonzeros (12 bytes each) fit the 256 MB memory-side cache beside other things.  Beyond,
-// memory bounds the kernel and larger tiles (and loads that do not displace the operand from that cache) are better:
-// TTM at rank 32, 8 M nonzeros 127 us with 768, 148 with 1536; 50 M nonzeros at rank 16 473 and 449 us.
-constexpr int kUnitsSmall = 768, kUnitsLarge = 1536;
-constexpr int64_t kLargeNnz = int64_t(10) << 20;
+// Units per tile, and how the nonzeros are read.  Small tiles leave room for more workgroups per compute unit (LDS), which
+// hides the latencies at the start of a tile; that wins while the nonzeros (12 bytes each) are still in the caches from the
+// pass before.  A list that is not would only push the operand out of them: from kStreamNnz on its loads are non-temporal.
+// TTM at rank 32, 8 M nonzeros in 1.6 M fibers: 177 us, and 192 with plain loads, where four tensors take turns; 184 and 147
+// where one is used again and again; 6 M: 137 and 141, 136 and 112.  15 M: 318 and 352, 317 and 275.
+// Large tiles end at 1472 units so that a tile full of pieces of long segments leaves room for two workgroups per compute
+// unit at rank 128 (1536 units did not: SpMM on 13 M nonzeros in power-law rows 2043 us, now 1940; rank 112 1820 and 1665).
+constexpr int kUnitsSmall = 768, kUnitsLarge = 1472;
+constexpr int64_t kStreamNnz = int64_t(7) << 20;
 constexpr int kWhole = 48;             // longest segment that is taken as one piece
 constexpr int kPiece = 32;             // longest piece of any other segment
 constexpr int kSnap = 32;              // a tile boundary inside a segment of at most this many nonzeros moves to its start

@@ -41,6 +41,8 @@ hipError_t stream_segreduce_rankR(const Schedule &sc, const int32_t *pos, const 
                                   const int32_t *rowmap, const double *Dn, int R, double *out, void *scratch,
                                   hipStream_t st, Epilogue ep = Epilogue());
 
+// Nonzeros from which on ranks 8 and 16 take that walk and not the pieces (see stream_segreduce).
+constexpr int64_t kWalkNnz = int64_t(10) << 20;
 // The same over the piece plan (defined in kernels_pieces.hip).
 hipError_t piece_rows(const PiecePlan &plan, const int32_t *crd, const double *vals, int64_t nnz, const int32_t *rowmap, const double *Dn,
                       int64_t dense_rows, int R, double *out, void *scratch, hipStream_t st, Epilogue ep = Epilogue());

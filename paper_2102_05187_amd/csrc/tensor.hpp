@@ -102,6 +102,7 @@ struct FiberPlan {
 struct PiecePlan {
     int64_t nseg = 0, ntiles = 0, npieces = 0, njoins = 0;
     int     units = 0;                 // units per tile
+    int     max_parts = 0;             // most partial sums in a tile
     int64_t ncut = 0, ncut_long = 0;   // segments cut by tile boundaries: over few tiles, over many
     DevRef  tiles;        // int4 [ntiles + 1]: first nonzero, segment, piece and join of a tile
     DevRef  pieces;       // uint32 [npieces], longest first inside a tile

@@ -1,5 +1,5 @@
 """The rank-R kernel over pieces: segment lengths around its limits (pieces of 32, whole segments of 48, tiles of 768 and
-1536 units), segments over many tiles, empty ones, every row layout, with and without accumulation."""
+1472 units), segments over many tiles, empty ones, every row layout, with and without accumulation."""
 import numpy as np
 import pytest
 import torch
@@ -66,7 +66,7 @@ def test_many_nonzeros_take_large_tiles(comet, R):
 
 @pytest.mark.parametrize("R", [20, 128])
 def test_most_partial_sums_in_a_tile(comet, R):
-    # rows of 65 are three pieces each: 23 whole ones and a cut one at both ends give a large tile 71 partial sums
+    # rows of 65 are three pieces each, more than rows of any other length give: 22 whole ones in a large tile and cut ones at its ends
     n = 165_000
     lens = torch.full((n,), 65, dtype=torch.int64)
     rows, cols, vals = gen.matrix_from_row_lengths(n, 50_000, lens, 7, "cuda")
@@ -77,3 +77,26 @@ def test_most_partial_sums_in_a_tile(comet, R):
     C = comet.comet_spmm(A, B.to("cuda"))
     ref, absum = oracle.spmm(np_(rows.cpu()), np_(cols.cpu()), np_(vals.cpu()), (n, 50_000), np_(B))
     assert_values_close(np_(C), ref, absum, "partial sums R=%d" % R)
+
+
+@pytest.mark.parametrize("R", [20, 32, 33, 64, 128])
+@pytest.mark.parametrize("layout", ["csr", "dcsr"])
+def test_edges_of_large_tiles(comet, layout, R):
+    """The same edges where tiles are large: rows around a whole tile, over few and over many tiles, empty ones."""
+    lens = torch.tensor([1, 0, 31, 32, 33, 47, 48, 49, 64, 65, 97, 1471, 1472, 1473, 2944, 2945, 0, 20000, 30000, 0] + [33, 0, 49, 2] * 200,
+                        dtype=torch.int64)
+    lens = torch.cat([lens, torch.full((200_000,), 37, dtype=torch.int64), lens])
+    I, J = lens.numel(), 40000
+    rows, cols, vals = gen.matrix_from_row_lengths(I, J, lens, 8, "cuda")
+    assert vals.numel() > 7 << 20
+    pack = fmt.pack_csr if layout == "csr" else fmt.pack_dcsr
+    A = comet.from_levels(pack(I, J, rows, cols, vals)).set_variant(2)
+    B, old = gen.dense_operand(3, 0, (J, R)), gen.dense_operand(4, 0, (I, R))
+    print("large tiles %s R=%d nnz=%d" % (layout, R, vals.numel()), flush=True)
+    C = torch.full((I, R), float("nan"), dtype=torch.float64, device="cuda")
+    comet.comet_spmm(A, B.to("cuda"), C)
+    ref, absum = oracle.spmm(np_(rows.cpu()), np_(cols.cpu()), np_(vals.cpu()), (I, J), np_(B))
+    assert_values_close(np_(C), ref, absum, "large tiles %s R=%d" % (layout, R))
+    D = old.to("cuda")
+    comet.comet_spmm_axpby(A, 0.75, B.to("cuda"), -0.5, D)
+    assert_values_close(np_(D), 0.75 * ref - 0.5 * np_(old), 0.75 * absum + 0.5 * np.abs(np_(old)), "axpby R=%d" % R)
