@@ -428,11 +428,19 @@ inline int lanes_per_item(int64_t R) { return R <= 8 ? 4 : 8; }
     }()
 
 // Calls F<L, E, NL, FULL, BIG>(args...) for the row layout that covers rank R (see RowOf).  big: operand rows need 64-bit
-// offsets; rare enough for the general layout to serve them.
+// offsets; rare enough for the ragged layouts to serve them, but with 16 bytes per lane as below (25 M nonzeros in rows of 3,
+// 8.4 M operand rows: rank 66 4364 us, and 5061 with 8 bytes per lane).
 #define COMET_DISPATCH_RANK(F, R, big, ...)                                                \
     [&]() -> hipError_t {                                                                  \
         const int r_ = (int)(R);                                                           \
-        if (big || (r_ & 1)) {                                                             \
+        if (big && !(r_ & 1)) {                                                            \
+            if (r_ <= 16) return F<8, 2, 1, false, true>(__VA_ARGS__);                     \
+            if (r_ <= 32) return F<16, 2, 1, false, true>(__VA_ARGS__);                    \
+            if (r_ <= 64) return F<16, 2, 2, false, true>(__VA_ARGS__);                    \
+            if (r_ <= 96) return F<16, 2, 3, false, true>(__VA_ARGS__);                    \
+            return F<16, 2, 4, false, true>(__VA_ARGS__);                                  \
+        }                                                                                  \
+        if (r_ & 1) {                                                                      \
             if (big) {                                                                     \
                 if (r_ <= 16) return F<16, 1, 1, false, true>(__VA_ARGS__);                \
                 if (r_ <= 32) return F<16, 1, 2, false, true>(__VA_ARGS__);                \

@@ -100,3 +100,27 @@ def test_edges_of_large_tiles(comet, layout, R):
     D = old.to("cuda")
     comet.comet_spmm_axpby(A, 0.75, B.to("cuda"), -0.5, D)
     assert_values_close(np_(D), 0.75 * ref - 0.5 * np_(old), 0.75 * absum + 0.5 * np.abs(np_(old)), "axpby R=%d" % R)
+
+
+@pytest.mark.parametrize("R", [2, 16, 18, 33, 34, 64, 66, 96, 100, 128])
+@pytest.mark.parametrize("layout", ["csr", "dcsr"])
+def test_operands_of_4_gib(comet, layout, R):
+    """Row offsets beyond 32 bits in bytes, first and last rows of the operand among them; every layout for such operands."""
+    J = (1 << 32) // (8 * R) + 3
+    lens = torch.tensor([1, 0, 2, 33, 48, 49, 3000, 0, 5] * 20, dtype=torch.int64)
+    rows, cols, vals = gen.matrix_from_row_lengths(lens.numel(), J, lens, 9)
+    start = torch.cumsum(lens, 0) - lens
+    cols[start[lens > 1]] = 0
+    cols[(start + lens - 1)[lens > 1]] = J - 1
+    I = lens.numel()
+    A = comet.from_levels((fmt.pack_csr if layout == "csr" else fmt.pack_dcsr)(I, J, rows, cols, vals).to("cuda")).set_variant(2)
+    print("large operand %s R=%d J=%d" % (layout, R, J), flush=True)
+    B = torch.rand((J, R), dtype=torch.float64, device="cuda")
+    C = torch.full((I, R), float("nan"), dtype=torch.float64, device="cuda")
+    comet.comet_spmm(A, B, C)
+    used, where = torch.unique(cols.long(), return_inverse=True)
+    ref, absum = oracle.spmm(np_(rows), np_(where.int()), np_(vals), (I, used.numel()), np_(B[used.cuda()]))
+    assert_values_close(np_(C), ref, absum, "large operand %s R=%d" % (layout, R))
+    D = torch.ones_like(C)
+    comet.comet_spmm_axpby(A, 0.75, B, -0.5, D)
+    assert_values_close(np_(D), 0.75 * ref - 0.5, 0.75 * absum + 0.5, "large operand axpby R=%d" % R)
