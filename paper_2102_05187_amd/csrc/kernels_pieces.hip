@@ -44,7 +44,9 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
     const int n8 = (int)gridDim.x / 8;
     const int t = (int)blockIdx.x < 8 * n8 ? ((int)blockIdx.x & 7) * n8 + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
     const int4 t0 = tiles[t], t1 = tiles[t + 1];
-    const int np = t1.z - t0.z, nj = t1.w - t0.w;
+    // a level of almost 2^31 segments has more pieces than that: their numbers are unsigned
+    const uint32_t first_piece = (uint32_t)t0.z;
+    const int np = (int)((uint32_t)t1.z - first_piece), nj = t1.w - t0.w;
     const unsigned unit = (unsigned)R * (BIG ? 1u : 8u);          // row offsets: bytes, or doubles for operands of 4 GiB and more
     // nonzeros of the tile from the 16-byte boundary in front of them
     const int p0 = t0.x & ~3, lead = t0.x - p0, n_items = t1.x - p0;
@@ -76,7 +78,7 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
         }
     };
     if (stream) stage(IntC<1>{}); else stage(IntC<0>{});
-    for (int i = threadIdx.x; i < np; i += 256) piece[i] = pieces[t0.z + i];
+    for (int i = threadIdx.x; i < np; i += 256) piece[i] = pieces[(size_t)first_piece + i];
     __syncthreads();
 
     const int k = threadIdx.x % L, gw = (threadIdx.x & 63) / L, wave = threadIdx.x >> 6;

@@ -46,8 +46,8 @@ __global__ void __launch_bounds__(256) k_piece_fill(const int32_t *__restrict__ 
     if (threadIdx.x == 0) { npart = 0; njoin = 0; }
     __syncthreads();
     auto each = [&](auto &&whole, auto &&cut) {
-        for (int s = s0 + (int)threadIdx.x; s < s1; s += 256) {
-            const int sb = pos[s], se = pos[s + 1];
+        for (int i = threadIdx.x; i < s1 - s0; i += 256) {      // a count: segment numbers end just below 2^31
+            const int s = s0 + i, sb = pos[s], se = pos[s + 1];
             const int lo = sb > p0 ? sb : p0, hi = se < p1 ? se : p1, n = hi - lo;
             const bool begins = sb >= p0, ends = se <= p1;
             if (begins && ends && n <= kWhole) whole(s, lo, n);
