@@ -113,7 +113,10 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st) {
         rs = read_i32((const int32_t *)mx->ptr, 1, &h, st);
         if (rs != COMET_OK) return rs;
         sc.empty_segments = h;
-        HIP_TRY(comet::piece_plan_build(t.pos_i(leaf), sc.nseg, sc.nnz, sc.pieces, st));
+        // optional, like the plans of the sweeps below: without the memory for it, what would run on it takes the simple kernels
+        hipError_t ppe = comet::piece_plan_build(t.pos_i(leaf), sc.nseg, sc.nnz, sc.pieces, st);
+        if (ppe == hipErrorOutOfMemory) { (void)hipGetLastError(); ppe = hipSuccess; }
+        HIP_TRY(ppe);
         if (t.levels[0] == COMET_CU) {
             HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
             HIP_TRY(comet::max_coordinate_gap(t.crd_i(0), t.crd_len[0], t.dims[0], (int32_t *)mx->ptr, st));
@@ -734,12 +737,14 @@ static comet_status matrix_product(const comet_tensor *A, const double *Dn, int6
     if (A->fmt != Format::CSR && A->fmt != Format::DCSR) return COMET_ERR_UNSUPPORTED;
     if (R < 1 || R > 1024) return COMET_ERR_UNSUPPORTED;
     const int64_t nseg = A->pos_len[1] - 1, nnz = A->nvals;
-    const bool tiled = nnz > 0 && use_tiled(A, R, Dn, out, A->dims[1], A->sched.max_seg_len);
+    const bool tiled = nnz > 0 && use_tiled(A, R, Dn, out, A->dims[1], A->sched.max_seg_len) &&
+                       comet::segreduce_supports(A->sched, R);
     const size_t carry = tiled ? comet::segreduce_scratch_bytes(A->sched, R) : 0;
     // The heavy-row sweep pays when the dense operand is much larger than the L2 caches (else its rows are
     // cache hits anyway) and the long rows hold a good share of the nonzeros (decided when the plan was built).
     const bool heavy = tiled && !ext_scratch && A->variant != 3 && A->sched.heavy.nunits > 0 &&
-                       A->dims[1] * R * 8 >= (int64_t(16) << 20) && R <= 64 && comet::heavy_supports(A->sched.heavy, R);
+                       A->dims[1] * R * 8 >= (int64_t(16) << 20) && R <= 64 && comet::heavy_supports(A->sched.heavy, R) &&
+                       (!A->light || comet::segreduce_supports(A->light->sched, R));
     const size_t need = carry + (heavy ? comet::heavy_partial_bytes(A->sched.heavy, R) : 0);
     if (ext_scratch && need > ext_bytes) return COMET_ERR_UNSUPPORTED;       // before anything is enqueued
     const int32_t *rowmap = nullptr;
@@ -927,12 +932,13 @@ static comet_status leaf_contract(const comet_tensor *X, int mode, const double 
     if (X->nvals > 0) {
         if (csf || S) {
             const comet_tensor *C = csf ? X : S;                 // the compressed storage the kernels walk
-            if (use_tiled(C, R, Dn, yv, C->dims[2], C->sched.max_seg_len)) {
+            if (use_tiled(C, R, Dn, yv, C->dims[2], C->sched.max_seg_len) && comet::segreduce_supports(C->sched, R)) {
                 // long fibers over a small last mode: their rows come from the heavy-fiber sweep (operand rows in
                 // LDS), all other fibers from the tiled kernel run on the compacted copy of them
                 const comet_tensor *Lh = C->light.get();
                 const bool sweep = kind == 2 && C->variant != 3 && Lh && comet::fiber_supports(C->sched.fibers, R) &&
-                                   Lh->sched.ntiles > 0 && aligned16(Lh->crd_i(1)) && aligned16(Lh->vals_d());
+                                   Lh->sched.ntiles > 0 && comet::segreduce_supports(Lh->sched, R) &&
+                                   aligned16(Lh->crd_i(1)) && aligned16(Lh->vals_d());
                 if (sweep) {
                     rs = ensure_scratch(Lh, comet::segreduce_scratch_bytes(Lh->sched, R));
                     if (rs != COMET_OK) return rs;

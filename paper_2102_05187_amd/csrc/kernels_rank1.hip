@@ -570,6 +570,15 @@ size_t stream_scratch_bytes(int64_t ntiles, int64_t R) {
     return total + 256;
 }
 
+// Which walk: the pieces, except for narrow rows of full width over many nonzeros, where memory bounds both and
+// the walk over whole tiles of nonzeros keeps more of the list in flight (TTM at rank 16, 36 M nonzeros in 6.5 M
+// fibers: 485 us against 535; level at 12 M nonzeros, behind by 1.3 to 2 at 5 M and below).
+static bool takes_walk(const Schedule &sc, int64_t R) { return sc.nnz >= kWalkNnz && (R == 8 || R == 16); }
+
+bool segreduce_supports(const Schedule &sc, int64_t R) {
+    return sc.ntiles <= 0 || R == 1 || takes_walk(sc, R) || sc.pieces.ntiles > 0;
+}
+
 size_t segreduce_scratch_bytes(const Schedule &sc, int64_t R) {
     if (R == 1) return stream_scratch_bytes(sc.nchunks, 1);
     const size_t a = stream_scratch_bytes(sc.ntiles, R), b = piece_scratch_bytes(sc.pieces, R);
@@ -616,11 +625,7 @@ hipError_t stream_segreduce(const Schedule &sc, const int32_t *pos, const int32_
                                rowmap, Dn, out, sc.nnz, sc.ntiles, scratch, ep);
         e = hipGetLastError();
     } else {
-        // Which walk: the pieces, except for narrow rows of full width over many nonzeros, where memory bounds both and
-        // the walk over whole tiles of nonzeros keeps more of the list in flight (TTM at rank 16, 36 M nonzeros in 6.5 M
-        // fibers: 485 us against 535; level at 12 M nonzeros, behind by 1.3 to 2 at 5 M and below).
-        const bool long_list = sc.nnz >= kWalkNnz && (R == 8 || R == 16);
-        if (!long_list)
+        if (!takes_walk(sc, R))
             return piece_rows(sc.pieces, crd, vals, sc.nnz, rowmap, Dn, dense_rows, (int)R, out, scratch, st, ep);
         e = stream_segreduce_rankR(sc, pos, crd, vals, rowmap, Dn, (int)R, out, scratch, st, ep);
     }

@@ -21,6 +21,7 @@ bool   stream_mttkrp_supports_rank(int64_t R);
 bool   stream_supports_coo();
 size_t stream_scratch_bytes(int64_t ntiles, int64_t R);
 size_t piece_scratch_bytes(const PiecePlan &plan, int64_t R);
+bool   segreduce_supports(const Schedule &sc, int64_t R);          // false: stream_segreduce would need a plan that is not there
 size_t segreduce_scratch_bytes(const Schedule &sc, int64_t R);     // what stream_segreduce needs
 size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R);        // what stream_mttkrp needs
 

@@ -124,3 +124,37 @@ def test_operands_of_4_gib(comet, layout, R):
     D = torch.ones_like(C)
     comet.comet_spmm_axpby(A, 0.75, B, -0.5, D)
     assert_values_close(np_(D), 0.75 * ref - 0.5, 0.75 * absum + 0.5, "large operand axpby R=%d" % R)
+
+
+@pytest.mark.parametrize("R", [2, 8])
+def test_without_memory_for_the_plan(comet, R):
+    """A handle whose piece plan (4 bytes per row here) does not fit is made all the same, and its products are right."""
+    I, J, step = 48_000_000, 1000, 12
+    pos = torch.div(torch.arange(I + 1, device="cuda") + step - 1, step, rounding_mode="floor").int()
+    nnz = int(pos[-1])
+    crd = torch.randint(0, J, (nnz,), device="cuda", dtype=torch.int32)
+    vals = torch.rand(nnz, dtype=torch.float64, device="cuda")
+    B = torch.rand((J, R), dtype=torch.float64, device="cuda")
+    C = torch.full((I, R), float("nan"), dtype=torch.float64, device="cuda")
+    size = torch.tensor([I], dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    while True:                                   # all but about 100 MB of the device memory, without touching it
+        free = torch.cuda.mem_get_info()[0] - (100 << 20)
+        if free < 16 << 20 or len(held) > 2000:
+            break
+        try:
+            held.append(torch.empty(min(free // 2 + (8 << 20), 8 << 30), dtype=torch.uint8, device="cuda"))
+        except torch.cuda.OutOfMemoryError:
+            break
+    print("no plan R=%d left=%d MB" % (R, torch.cuda.mem_get_info()[0] >> 20), flush=True)
+    try:
+        A = comet.comet_tensor_create([I, J], [comet.COMET_D, comet.COMET_CU], [size, pos], [None, crd], vals, 0)
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    comet.comet_spmm(A.set_variant(2), B, C)
+    assert torch.equal(C[::step], vals[:, None] * B[crd.long()])
+    C[::step] = 0.0
+    assert torch.count_nonzero(C) == 0
