@@ -261,8 +261,8 @@ template <int L, int E, int NL, bool FULL, bool BIG>
 hipError_t launch_pieces(const PieceArgs &a) {
     const int lds = lds_parts_at(a.plan.units) + a.plan.max_parts * L * E * NL * 8;
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)a.plan.ntiles), dim3(256), (unsigned)lds, a.st, (const int4 *)a.plan.tiles->ptr,
-                           (const uint32_t *)a.plan.pieces->ptr, (const uint32_t *)a.plan.joins->ptr, a.plan.units, a.plan.units == kUnitsLarge,
+        hipLaunchKernelGGL(kernel, dim3((unsigned)a.plan.ntiles), dim3(256), (unsigned)lds, a.st, (const int4 *)a.plan.tiles(),
+                           (const uint32_t *)a.plan.pieces(), (const uint32_t *)a.plan.joins(), a.plan.units, a.plan.units == kUnitsLarge,
                            a.crd, a.vals, a.rowmap, a.Dn, a.out, a.nnz, a.R, a.head, a.tail, a.ep);
     };
     if (lds > 64 * 1024) {
@@ -287,7 +287,7 @@ hipError_t piece_rows(const PiecePlan &plan, const int32_t *crd, const double *v
     const hipError_t e = COMET_DISPATCH_RANK(launch_pieces, R, big, a);
     if (e != hipSuccess || plan.ncut + plan.ncut_long == 0) return e;
     const int64_t narrow = (plan.ncut * R + 255) / 256;
-    hipLaunchKernelGGL(k_piece_cut_sums, dim3((unsigned)(narrow + plan.ncut_long)), dim3(256), 0, st, (const int4 *)plan.cuts->ptr,
+    hipLaunchKernelGGL(k_piece_cut_sums, dim3((unsigned)(narrow + plan.ncut_long)), dim3(256), 0, st, (const int4 *)plan.cuts(),
                        (int)plan.ncut, (int)plan.ncut_long, plan.ntiles, (const double *)head, (const double *)tail, R, rowmap, out, ep);
     return hipGetLastError();
 }

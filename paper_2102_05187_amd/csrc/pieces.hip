@@ -36,14 +36,14 @@ template <bool FILL>
 __global__ void __launch_bounds__(256) k_piece_fill(const int32_t *__restrict__ pos, int64_t nseg, int64_t ntiles, int4 *__restrict__ tiles,
                                                     uint64_t *__restrict__ counts, int *__restrict__ max_parts,
                                                     uint32_t *__restrict__ pieces, uint32_t *__restrict__ joins) {
-    __shared__ int bin[64], npart, njoin;
+    __shared__ int bin[64], nwhole, npart, njoin;
     const int64_t t = blockIdx.x;
     const int4 a = tiles[t], b = tiles[t + 1];
     const int p0 = a.x, p1 = b.x, s0 = a.y;
     // segments of the tile: [s0, s1), the last of them possibly continued
     const int s1 = b.y + (b.y < nseg && pos[b.y] < p1 ? 1 : 0);
     if (threadIdx.x < 64) bin[threadIdx.x] = 0;
-    if (threadIdx.x == 0) { npart = 0; njoin = 0; }
+    if (threadIdx.x == 0) { nwhole = 0; npart = 0; njoin = 0; }
     __syncthreads();
     auto each = [&](auto &&whole, auto &&cut) {
         for (int i = threadIdx.x; i < s1 - s0; i += 256) {      // a count: segment numbers end just below 2^31
@@ -54,42 +54,47 @@ __global__ void __launch_bounds__(256) k_piece_fill(const int32_t *__restrict__ 
             else cut(s, lo, n, ends ? (begins ? kJoinRow : kJoinHead) : (begins ? kJoinTail : kJoinHead));
         }
     };
-    each([&](int, int, int n) { atomicAdd(&bin[n], 1); },
-         [&](int, int, int n, int) {
-             const int np = (n + kPiece - 1) / kPiece;
-             for (int q = 0; q < np; ++q) atomicAdd(&bin[(int)((int64_t)n * (q + 1) / np) - (int)((int64_t)n * q / np)], 1);
-             atomicAdd(&njoin, 1);
-             atomicAdd(&npart, np);
-         });
-    __syncthreads();
     if (!FILL) {
+        each([&](int, int, int) { atomicAdd(&nwhole, 1); },
+             [&](int, int, int n, int) { atomicAdd(&npart, (n + kPiece - 1) / kPiece); atomicAdd(&njoin, 1); });
+        __syncthreads();
         if (threadIdx.x == 0) {
-            int total = 0;
-            for (int i = 0; i < 64; ++i) total += bin[i];
-            counts[t] = (uint64_t)(uint32_t)total | ((uint64_t)(uint32_t)njoin << 32);
+            counts[t] = (uint64_t)(uint32_t)(nwhole + npart) | ((uint64_t)(uint32_t)njoin << 32);
             // few tiles raise the maximum; atomics of all of them on one address would queue up
             if (npart > __hip_atomic_load(max_parts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(max_parts, npart);
         }
         return;
     }
+    // a segment in np pieces: `extra` of them hold base + 1 nonzeros, the others base
+    each([&](int, int, int n) { atomicAdd(&bin[n], 1); },
+         [&](int, int, int n, int) {
+             const int np = (n + kPiece - 1) / kPiece, base = n / np, extra = n - np * base;
+             if (extra) atomicAdd(&bin[base + 1], extra);
+             atomicAdd(&bin[base], np - extra);
+         });
+    __syncthreads();
+    if (threadIdx.x < 64) {                                     // first place of every length, longest first
+        const int lane = threadIdx.x, n = bin[63 - lane];
+        int at = n;
+        for (int d = 1; d < 64; d *= 2) { const int y = __shfl_up(at, d); if (lane >= d) at += y; }
+        bin[63 - lane] = at - n;
+    }
     if (threadIdx.x == 0) {
-        int at = 0;
-        for (int i = 63; i >= 0; --i) { const int n = bin[i]; bin[i] = at; at += n; }      // longest first
         tiles[t].z = (int)(uint32_t)counts[t];
         tiles[t].w = (int)(uint32_t)(counts[t] >> 32);
-        npart = 0;
-        njoin = 0;
     }
     __syncthreads();
     uint32_t *pc = pieces + (uint32_t)counts[t], *jn = joins + (uint32_t)(counts[t] >> 32);
     // an empty segment starts nowhere: behind the tile's last nonzero there is none that its lanes could read beside longer pieces
     each([&](int s, int lo, int n) { pc[atomicAdd(&bin[n], 1)] = piece_pack(n ? lo - p0 : 0, n, s - s0, 0); },
          [&](int s, int lo, int n, int to) {
-             const int np = (n + kPiece - 1) / kPiece;
+             const int np = (n + kPiece - 1) / kPiece, base = n / np, extra = n - np * base;
              const int slot = atomicAdd(&npart, np);
+             int at = lo - p0;
              for (int q = 0; q < np; ++q) {
-                 const int x = (int)((int64_t)n * q / np), y = (int)((int64_t)n * (q + 1) / np);
-                 pc[atomicAdd(&bin[y - x], 1)] = piece_pack(lo - p0 + x, y - x, slot + q, 1);
+                 const int len = base + (q < extra ? 1 : 0);
+                 pc[atomicAdd(&bin[len], 1)] = piece_pack(at, len, slot + q, 1);
+                 at += len;
              }
              jn[atomicAdd(&njoin, 1)] = join_pack(slot, np, s - s0, to);
          });
@@ -127,50 +132,45 @@ unsigned grid_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, int64_t nnz, PiecePlan &plan, hipStream_t st) {
     plan = PiecePlan();
     if (nseg < 1 || nnz < 1) return hipSuccess;
-    const int units = nnz >= kStreamNnz ? kUnitsLarge : kUnitsSmall;
-    const int64_t ntiles = (nnz + nseg + units - 1) / units;
     auto fail = [&](hipError_t e) { plan = PiecePlan(); return e; };
-    plan.tiles = dev_alloc(sizeof(int4) * (ntiles + 1));
-    plan.cuts = dev_alloc(sizeof(int4) * ntiles);
-    DevRef counts = dev_alloc(sizeof(uint64_t) * (ntiles + 1)), before = dev_alloc(sizeof(uint64_t) * (ntiles + 1));
-    DevRef counters = dev_alloc(3 * sizeof(int));   // short cuts, long cuts, most partial sums in a tile
-    if (!plan.tiles || !plan.cuts || !counts || !before || !counters) return fail(hipErrorOutOfMemory);
-    int4 *tiles = (int4 *)plan.tiles->ptr;
-    uint64_t *cn = (uint64_t *)counts->ptr, *bf = (uint64_t *)before->ptr;
-    hipLaunchKernelGGL(k_piece_tiles, dim3(grid_for(ntiles + 1)), dim3(256), 0, st, pos, nseg, nnz, units, ntiles, tiles);
-    hipError_t e = hipMemsetAsync(cn + ntiles, 0, sizeof(uint64_t), st);
-    if (e == hipSuccess) e = hipMemsetAsync(counters->ptr, 0, 3 * sizeof(int), st);
-    if (e != hipSuccess) return fail(e);
-    hipLaunchKernelGGL((k_piece_fill<false>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, tiles, cn,
-                       (int *)counters->ptr + 2, (uint32_t *)nullptr, (uint32_t *)nullptr);
-    hipLaunchKernelGGL(k_piece_cuts, dim3(grid_for(ntiles)), dim3(256), 0, st, pos, nseg, (const int4 *)tiles, ntiles,
-                       (int4 *)plan.cuts->ptr, (int *)counters->ptr);
+    const int64_t units = nnz >= kStreamNnz ? kUnitsLarge : kUnitsSmall, ntiles = (nnz + nseg + units - 1) / units;
+    plan.nseg = nseg;
+    plan.units = (int)units;
+    plan.ntiles = ntiles;
+    plan.tiles_mem = dev_alloc(sizeof(int4) * (2 * ntiles + 1));
+    // temporary: pieces and joins of each tile, their sums before each tile, counters (short cuts, long cuts, most partial
+    // sums in a tile), and what the scan asks for.  One allocation: each costs a small handle's creation 10 us and more
     size_t tb = 0;
-    e = reorder_scan_flags(nullptr, &tb, cn, bf, ntiles + 1, st);
+    hipError_t e = reorder_scan_flags(nullptr, &tb, (uint64_t *)nullptr, (uint64_t *)nullptr, ntiles + 1, st);
     if (e != hipSuccess) return fail(e);
-    DevRef temp = dev_alloc(tb ? tb : 16);
-    if (!temp) return fail(hipErrorOutOfMemory);
-    e = reorder_scan_flags(temp->ptr, &tb, cn, bf, ntiles + 1, st);
-    uint64_t total = 0;
-    int nc[3] = {0, 0, 0};
-    if (e == hipSuccess) e = hipMemcpyAsync(&total, bf + ntiles, sizeof total, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(nc, counters->ptr, sizeof nc, hipMemcpyDeviceToHost, st);
+    const size_t scan_at = ((size_t)(2 * (ntiles + 1) + 2) * sizeof(uint64_t) + 255) & ~(size_t)255;
+    DevRef temp = dev_alloc(scan_at + tb);
+    if (!plan.tiles_mem || !temp) return fail(hipErrorOutOfMemory);
+    uint64_t *cn = (uint64_t *)temp->ptr, *bf = cn + ntiles + 1;
+    int *counters = (int *)(bf + ntiles + 1);
+    hipLaunchKernelGGL(k_piece_tiles, dim3(grid_for(ntiles + 1)), dim3(256), 0, st, pos, nseg, nnz, plan.units, ntiles, plan.tiles());
+    e = hipMemsetAsync(cn + ntiles, 0, sizeof(uint64_t), st);
+    if (e == hipSuccess) e = hipMemsetAsync(counters, 0, 3 * sizeof(int), st);
+    if (e != hipSuccess) return fail(e);
+    hipLaunchKernelGGL((k_piece_fill<false>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, plan.tiles(), cn,
+                       counters + 2, (uint32_t *)nullptr, (uint32_t *)nullptr);
+    hipLaunchKernelGGL(k_piece_cuts, dim3(grid_for(ntiles)), dim3(256), 0, st, pos, nseg, (const int4 *)plan.tiles(), ntiles,
+                       plan.cuts(), counters);
+    e = reorder_scan_flags((char *)temp->ptr + scan_at, &tb, cn, bf, ntiles + 1, st);
+    struct { uint64_t total; int short_cuts, long_cuts, max_parts, unused; } sums = {0, 0, 0, 0, 0};    // bf[ntiles] and the counters
+    if (e == hipSuccess) e = hipMemcpyAsync(&sums, bf + ntiles, sizeof(uint64_t) + 3 * sizeof(int), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(e);
-    plan.nseg = nseg;
-    plan.units = units;
-    plan.ntiles = ntiles;
-    plan.npieces = (int64_t)(uint32_t)total;
-    plan.njoins = (int64_t)(uint32_t)(total >> 32);
-    plan.ncut = nc[0];
-    plan.ncut_long = nc[1];
-    plan.max_parts = nc[2];
-    plan.pieces = dev_alloc(sizeof(uint32_t) * plan.npieces);
-    plan.joins = dev_alloc(sizeof(uint32_t) * plan.njoins);
-    if (!plan.pieces || !plan.joins) return fail(hipErrorOutOfMemory);
-    hipLaunchKernelGGL((k_piece_fill<true>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, tiles, bf,
-                       (int *)nullptr, (uint32_t *)plan.pieces->ptr, (uint32_t *)plan.joins->ptr);
-    hipLaunchKernelGGL(k_piece_end, dim3(1), dim3(1), 0, st, tiles, ntiles, (int)plan.npieces, (int)plan.njoins);
+    plan.npieces = (int64_t)(uint32_t)sums.total;
+    plan.njoins = (int64_t)(uint32_t)(sums.total >> 32);
+    plan.ncut = sums.short_cuts;
+    plan.ncut_long = sums.long_cuts;
+    plan.max_parts = sums.max_parts;
+    plan.pieces_mem = dev_alloc(sizeof(uint32_t) * (plan.npieces + plan.njoins));
+    if (!plan.pieces_mem) return fail(hipErrorOutOfMemory);
+    hipLaunchKernelGGL((k_piece_fill<true>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, plan.tiles(), bf,
+                       (int *)nullptr, plan.pieces(), plan.joins());
+    hipLaunchKernelGGL(k_piece_end, dim3(1), dim3(1), 0, st, plan.tiles(), ntiles, (int)plan.npieces, (int)plan.njoins);
     e = hipStreamSynchronize(st);                            // the temporaries go out of scope
     return e == hipSuccess ? hipGetLastError() : fail(e);
 }

@@ -104,10 +104,15 @@ struct PiecePlan {
     int     units = 0;                 // units per tile
     int     max_parts = 0;             // most partial sums in a tile
     int64_t ncut = 0, ncut_long = 0;   // segments cut by tile boundaries: over few tiles, over many
-    DevRef  tiles;        // int4 [ntiles + 1]: first nonzero, segment, piece and join of a tile
-    DevRef  pieces;       // uint32 [npieces], longest first inside a tile
-    DevRef  joins;        // uint32 [njoins]
-    DevRef  cuts;         // int4 [ntiles]: {segment, first tile, last tile}; the short ones in front, the long ones from the end
+    DevRef  tiles_mem, pieces_mem;
+    // int4 [ntiles + 1]: first nonzero, segment, piece and join of a tile
+    int4 *tiles() const { return tiles_mem ? (int4 *)tiles_mem->ptr : nullptr; }
+    // int4 [ntiles]: {segment, first tile, last tile}; the short ones in front, the long ones from the end
+    int4 *cuts() const { return tiles_mem ? tiles() + ntiles + 1 : nullptr; }
+    // uint32 [npieces], longest first inside a tile
+    uint32_t *pieces() const { return pieces_mem ? (uint32_t *)pieces_mem->ptr : nullptr; }
+    // uint32 [njoins]
+    uint32_t *joins() const { return pieces_mem ? pieces() + npieces : nullptr; }
 };
 
 // Per-tensor schedule for the nonzero-tiled kernels, built once at creation.
