@@ -8,13 +8,14 @@ namespace {
 
 // ROWMAP: segment s writes result row rowmap[s]; the tail map then holds rows, and so do the ids this kernel
 // publishes in its carries (the fix-up takes them as rows).
-template <int L, int V, bool WIDE, bool ROWMAP>
+template <int L, bool ROWMAP>
 __global__ void __launch_bounds__(256) k_stream_rankR(const int32_t *__restrict__ pos, const int32_t *__restrict__ crd,
                                                       const double *__restrict__ vals,
                                                       const int32_t *__restrict__ seg_begin,
                                                       const int32_t *__restrict__ rowmap, const double *__restrict__ Dn,
                                                       double *__restrict__ out, int64_t nnz, int64_t ntiles, int R,
                                                       void *scratch, Epilogue ep) {
+    constexpr int V = 2;                       // columns per lane: R = 2 L, 16 bytes of a row
     constexpr int NW = 256 / L;                // walkers per tile
     constexpr int WI = kTile / NW;             // items per walker
     using RL = RecLayout<L, 2>;                // record = {row offset in doubles, tail id} + value
@@ -37,7 +38,7 @@ __global__ void __launch_bounds__(256) k_stream_rankR(const int32_t *__restrict_
     st.ht = 0; st.first_id = -1;
     int32_t *rec = rec_all + g * RL::kStride;
     const unsigned R8 = 8u * (unsigned)R;
-    const unsigned slot = lane_slot_doubles<L, WIDE>(j), Ru = (unsigned)R;
+    const unsigned slot = 2u * (unsigned)j, Ru = (unsigned)R;    // row offsets: 32-bit counts of doubles, up to 32 GiB
     char *outb = reinterpret_cast<char *>(out);
 
     constexpr int G = StepGroup<V>::value, NG = SB / G;
@@ -63,7 +64,8 @@ __global__ void __launch_bounds__(256) k_stream_rankR(const int32_t *__restrict_
                 const int2 ct = *reinterpret_cast<const int2 *>(rec + 2 * k);
                 b.a = *reinterpret_cast<const double *>(rec + RL::kVal + 2 * k);
                 b.tail = ct.y;
-                grp_load_row_off<L, V, WIDE>(Dn, (unsigned)ct.x + slot, R, j, b.d);
+                const double2 x = *reinterpret_cast<const double2 *>(Dn + (size_t)((unsigned)ct.x + slot));
+                b.d[0] = x.x; b.d[1] = x.y;
             });
         };
         auto consume = [&](auto gc, const RowBuf<V> *bb) {
@@ -79,7 +81,7 @@ __global__ void __launch_bounds__(256) k_stream_rankR(const int32_t *__restrict_
                         st.ht = 1;
                     } else {
                         const unsigned row = (unsigned)b.tail;
-                        grp_store_row_stream<L, V, WIDE>(reinterpret_cast<double *>(outb + (size_t)row * R8), 0, R, j, st.acc, ep);
+                        grp_store_row_stream<L, V, true>(reinterpret_cast<double *>(outb + (size_t)row * R8), 0, R, j, st.acc, ep);
                     }
 #pragma unroll
                     for (int q = 0; q < V; ++q) st.acc[q] = 0.0;
@@ -104,23 +106,23 @@ __global__ void __launch_bounds__(256) k_stream_rankR(const int32_t *__restrict_
     }
     __syncthreads();
     const int64_t first_row = st.ht ? (int64_t)st.first_id : 0;
-    finish_tile_walkers<L, V, WIDE>(wopen, wht, g, j, st.ht, st.first, first_row, st.first_id, st.acc, out, R,
+    finish_tile_walkers<L, V, true>(wopen, wht, g, j, st.ht, st.first, first_row, st.first_id, st.acc, out, R,
                                     carry_view(scratch, ntiles, R), t, ep);
 }
 
-template <int L, int V, bool WIDE, bool ROWMAP>
+template <int L, bool ROWMAP>
 void launch_rankR_one(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals, const int32_t *rowmap,
                       const double *Dn, int R, double *out, void *scratch, hipStream_t st, Epilogue ep) {
-    hipLaunchKernelGGL((k_stream_rankR<L, V, WIDE, ROWMAP>), dim3((unsigned)sc.ntiles), dim3(256), 0, st, pos, crd, vals,
+    hipLaunchKernelGGL((k_stream_rankR<L, ROWMAP>), dim3((unsigned)sc.ntiles), dim3(256), 0, st, pos, crd, vals,
                        (const int32_t *)sc.seg_begin->ptr, rowmap, Dn, out, sc.nnz, sc.ntiles, R, scratch, ep);
 }
 
-template <int L, int V, bool WIDE>
+template <int L>
 hipError_t launch_rankR(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals,
                         const int32_t *rowmap, const double *Dn, int R, double *out, void *scratch, hipStream_t st,
                         Epilogue ep) {
-    if (rowmap) launch_rankR_one<L, V, WIDE, true>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
-    else launch_rankR_one<L, V, WIDE, false>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
+    if (rowmap) launch_rankR_one<L, true>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
+    else launch_rankR_one<L, false>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
     return hipGetLastError();
 }
 
@@ -129,8 +131,8 @@ hipError_t launch_rankR(const Schedule &sc, const int32_t *pos, const int32_t *c
 hipError_t stream_segreduce_rankR(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals,
                                   const int32_t *rowmap, const double *Dn, int R, double *out, void *scratch,
                                   hipStream_t st, Epilogue ep) {
-    if (R == 8) return launch_rankR<4, 2, true>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
-    if (R == 16) return launch_rankR<8, 2, true>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
+    if (R == 8) return launch_rankR<4>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
+    if (R == 16) return launch_rankR<8>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
     return hipErrorNotSupported;
 }
 

@@ -1,5 +1,5 @@
-// Shared device helpers of the nonzero-tiled streaming kernels (included by kernels_rank1.hip,
-// kernels_rankR.hip and kernels_mttkrp.hip; everything here has internal linkage).
+// Shared device helpers of the nonzero-tiled streaming kernels (included by kernels_rank1.hip, kernels_rankR.hip,
+// kernels_mttkrp.hip, kernels_heavy.hip and kernels_pieces.hip; everything here has internal linkage).
 // Nonzero-tiled streaming kernels for gfx950 (wave64).
 //
 // Work is cut by nonzeros, not by rows: tile t owns leaf positions [t*kTile, (t+1)*kTile), whatever
@@ -23,7 +23,8 @@
 //
 // Kernels:  k_stream_rank1_ldsvec  rank 1, dense vector staged in LDS, one wavefront per 1024-item chunk
 //           k_stream_rank1[_coo]   rank 1, vector gathered through L1, tail-id map per 4096-item tile
-//           k_stream_rankR         rank R, lane groups walk item runs, per-item records in LDS
+//           k_pieces               rank R, lane groups walk pieces of segments (cut and carried in a way of their own, pieces.hpp)
+//           k_stream_rankR         ranks 8 and 16 over long lists, lane groups walk item runs, per-item records in LDS
 //           k_stream_mttkrp        rank R, two nested segment levels (fibers inside slices)
 //           k_fixup_level / k_stream_fixup   carry resolution
 #pragma once
@@ -121,8 +122,8 @@ __device__ __forceinline__ double grp_bcast_d(double v) {
 // group then takes the items one at a time: every lane reads the current item's record with a
 // broadcast LDS read (no cross-lane VALU work), adds its own 16-byte slot, and gathers its share of
 // the operand row Dn[crd, :] -- contiguous 16-byte pieces (WIDE, R a multiple of 2L: lane j takes
-// ranks 2L*q+2j, 2L*q+2j+1) or 8-byte pieces (lane j takes ranks L*q+j) -- so a load instruction
-// reads each gathered row as one contiguous run of 16*L bytes.  Gathers run G steps ahead of the
+// ranks 2L*q+2j, 2L*q+2j+1; always so in k_stream_rankR) or, in MTTKRP, 8-byte pieces (lane j takes ranks L*q+j) -- so a
+// load instruction reads each gathered row as one contiguous run of 16*L bytes.  Gathers run G steps ahead of the
 // FMAs (double-buffered in registers).  Row offsets are 32-bit counts of doubles, so an operand must hold fewer than 2^32 values.
 template <int L, int NI>
 struct RecLayout {                                     // per-walker record area, in 4-byte words
@@ -210,7 +211,7 @@ __device__ __forceinline__ void lane_load_items(LaneItems &it, const int32_t *__
     }
 }
 
-template <int V> struct RowBuf { double d[V]; int tail; double a; int boff, mrow; };
+template <int V> struct RowBuf { double d[V]; int tail; double a; };
 
 // Steps per pipeline group: the gathers of group g+1 are in flight while group g is consumed.
 template <int V> struct StepGroup { static constexpr int value = V <= 4 ? 4 : (V <= 8 ? 2 : 1); };
@@ -221,26 +222,6 @@ struct WalkState {
     double first[V];
     int ht, first_id;
 };
-
-// This lane's share of the dense row that starts `off` doubles into Dn (off already includes the
-// lane's own slot).  Offsets are 32-bit counts of doubles, so an operand may hold up to 2^32 values
-// (32 GiB); the sum with the q-th piece is formed in 64 bits.
-template <int L, int V, bool WIDE>
-__device__ __forceinline__ void grp_load_row_off(const double *__restrict__ Dn, unsigned off, int R, int j, double *d) {
-    const double *base = Dn + (size_t)off;
-    if constexpr (WIDE) {
-#pragma unroll
-        for (int q = 0; q < V / 2; ++q) {
-            const double2 x = *reinterpret_cast<const double2 *>(base + 2 * L * q);
-            d[2 * q] = x.x; d[2 * q + 1] = x.y;
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < V; ++q) d[q] = L * q + j < R ? base[L * q] : 0.0;
-    }
-}
-template <int L, bool WIDE>
-__device__ __forceinline__ unsigned lane_slot_doubles(int j) { return WIDE ? 2u * j : (unsigned)j; }
 
 // Close the first segment end of every walker of the tile and publish the tile summary.
 // wopen[(g*L + j)*V + q] holds walker g's open sum, wht[g] its has_tail flag (both already written
