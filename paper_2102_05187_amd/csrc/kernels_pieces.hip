@@ -2,11 +2,10 @@
 //
 // What bounds it.  Every vector memory instruction keeps the texture-address unit of a compute unit busy for 16 clocks and
 // more, however few of its lanes are active, and the vector L1 behind it returns data in order, so that the times for
-// gathering operand rows, reading nonzeros and writing results add up rather than overlap (measured: rows of 128 bytes
-// from L2 132 us for 35 M, streaming 480 MB 82 us, storing 832 MB 157 us; all three at once 394 us).  The kernel therefore
-// spends as few instructions as it can: rows 16 bytes per lane, nonzeros 16 bytes per lane into LDS, from where a lane
-// group reads one with a broadcast, and result rows stored for all groups of a wavefront at once, which pieces of equal
-// length make possible.  A walk that asks at every nonzero whether a segment ends (kernels_rankR.hip) stores few rows at a time.
+// gathering operand rows, reading nonzeros and writing results add up rather than overlap.  The kernel therefore spends as
+// few instructions as it can: rows 16 bytes per lane, nonzeros 16 bytes per lane into LDS, from where a lane group reads one
+// with a broadcast, and result rows stored for all groups of a wavefront at once, which pieces of equal length make possible.
+// A walk that asks at every nonzero whether a segment ends (kernels_rankR.hip) stores few rows at a time.
 // Measured before and after, that walk and this, for whole calls whose inputs change from call to call: SpMM on 11.3 M
 // nonzeros within 2000 columns of the diagonal, rank 20, added to the old result, 358 and 236 us; TTM on 8 M nonzeros in
 // 1.6 M fibers, rank 32, 180 and 172 us (the result's 415 MB and nonzeros that come from memory leave little to gain);

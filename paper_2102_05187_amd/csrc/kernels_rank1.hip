@@ -570,9 +570,11 @@ size_t stream_scratch_bytes(int64_t ntiles, int64_t R) {
     return total + 256;
 }
 
-// Which walk: the pieces, except for narrow rows of full width over many nonzeros, where memory bounds both and
-// the walk over whole tiles of nonzeros keeps more of the list in flight (TTM at rank 16, 36 M nonzeros in 6.5 M
-// fibers: 485 us against 535; level at 12 M nonzeros, behind by 1.3 to 2 at 5 M and below).
+// Which walk: the pieces, except for ranks 8 and 16 over many nonzeros, where the walk over whole tiles of nonzeros keeps more
+// of a list of short segments in flight.  Whole calls on the walk and on the pieces: TTM at rank 16, 100 M nonzeros in 6.5 M
+// fibers (36 M of them off the sweep) 742 and 793 us, in 15 M fibers 999 and 1085; 15 M nonzeros in 3 M fibers 184 and 187.
+// The line sees only the size: SpMM on 11 M nonzeros near the diagonal, rank 16, takes 203 and 145, on 20 M in rows of 40 at
+// random 407 and 397.
 static bool takes_walk(const Schedule &sc, int64_t R) { return sc.nnz >= kWalkNnz && (R == 8 || R == 16); }
 
 bool segreduce_supports(const Schedule &sc, int64_t R) {
