@@ -248,8 +248,9 @@ bool use_tiled(const comet_tensor *t, int64_t R, const void *dense, const void *
     if (!comet::stream_supports_rank(R)) return false;
     if (t->variant == 0 && R == 1 && serial > 0 && serial <= kShortSegment && t->sched.nnz <= kSmallProblemNnz)
         return false;
-    // The same for rank R: a thread per (segment, column) walks its short segment alone (4 against 17 us at
-    // 4096 rows x 10 nonzeros, R = 32; level with the tiled kernel at about 10M multiply-adds).
+    // The same for rank R: a thread per (segment, column) walks its short segment alone.  In a replayed graph, the simple kernel
+    // and the pieces: 4096 rows x 10 nonzeros, R = 32, 4.1 and 8.1 us; 16384 x 10, R = 32, 8.4 and 9.0; 65536 x 8, R = 8, 8.1 and 8.6;
+    // beyond the line 16384 x 10, R = 64, 16.6 and 12.8.  Longer rows are level earlier (30000 x 30, R = 8, 14.6 and 7.9).
     if (t->variant == 0 && R > 1 && serial > 0 && serial <= 64 && t->sched.nnz * R <= (int64_t(8) << 20))
         return false;
     // Far more (empty) segments than nonzeros -- a hypersparse matrix kept in CSR: a tile would spend its
