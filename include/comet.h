@@ -120,8 +120,9 @@ typedef struct {
  * kernels; load imbalance is what Section 8.3 identifies as the main source of slowdown), which
  * is why it synchronises.  On compressed rows or fibers the tables hold 4 bytes and more for each of
  * them, with COMET_LEAN too; without the memory for that part the handle is made all the same, and
- * comet_spmm / comet_ttm run on kernels that do not need it.  Accepted tuples: [D,CU] (CSR), [CU,CU] (DCSR), [CN,S] and [CN,S,S]
- * (COO), [CU,CU,CU] (CSF); results of TTV/TTM may additionally be [CU,CU,D] or [CN,S,D].
+ * comet_spmm / comet_ttm run on kernels that do not need it.
+ * Accepted tuples: [D,CU] (CSR), [CU,CU] (DCSR), [CN,S] and [CN,S,S] (COO), [CU,CU,CU] (CSF); results
+ * of TTV/TTM may additionally be [CU,CU,D] or [CN,S,D].
  */
 comet_status comet_tensor_create(comet_tensor **out, int order,
                                  const int64_t *dims, const comet_level_t *levels,
