@@ -1,5 +1,5 @@
 // Rank-1 kernels of the nonzero-tiled family (SpMV, TTV on CSF and on sorted coordinate lists), the
-// carry fix-up kernels shared by all of them, and the host entry points of the family.
+// carry fix-up kernel shared by all of them, and the host entry points of the family.
 #include <atomic>
 
 #include "pieces.hpp"
@@ -433,105 +433,99 @@ __global__ void __launch_bounds__(256) k_stream_rank1_coo(const int32_t *__restr
 }
 
 // ---- fix-up: finish the first segment end of every tile -------------------------------------------
-// value = first[t] + open[t-1] + open[t-2] + ... up to and including the nearest tile that contains
-// a segment end.  One thread per (tile, r).
-__global__ void __launch_bounds__(256) k_stream_fixup(void *scratch, int64_t ntiles, int R,
-                                                      const int32_t *__restrict__ rowmap, double *__restrict__ out,
-                                                      Epilogue ep) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= ntiles * R) return;
-    const int64_t t = g / R;
-    const int r = (int)(g - t * R);
-    CarryView cb = carry_view(scratch, ntiles, R);
-    if (!cb.has_tail[t]) return;
-    double v = cb.first[t * R + r];
-    for (int64_t u = t - 1; u >= 0; --u) {
-        v += cb.open[u * R + r];
-        if (cb.has_tail[u]) break;
-    }
-    const int32_t id = cb.first_id[t];
-    const int64_t row = rowmap ? (int64_t)rowmap[id] : (int64_t)id;
-    out[row * R + r] = ep_apply(ep, v, out + row * R + r);
-}
-
-
-// One pass of the hierarchical fix-up: thread (g, r) folds the kFixGroup summaries of group g in
-// order.  A segment end whose carry chain starts inside the group is final and is written to out;
-// the group's own summary (first segment end, trailing open sum) goes one level up.
-__global__ void __launch_bounds__(256) k_fixup_level(const double *__restrict__ lo_first, const double *__restrict__ lo_open,
-                                                     const int32_t *__restrict__ lo_ht, const int32_t *__restrict__ lo_id,
-                                                     int64_t n_lo, double *__restrict__ up_first,
-                                                     double *__restrict__ up_open, int32_t *__restrict__ up_ht,
-                                                     int32_t *__restrict__ up_id, int64_t n_up, int R,
-                                                     const int32_t *__restrict__ rowmap, double *__restrict__ out,
-                                                     Epilogue ep) {
-    const int64_t gidx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gidx >= n_up * R) return;
-    const int64_t g = gidx / R;
-    const int r = (int)(gidx - g * R);
-    const int64_t u0 = g * kFixGroup;
-    const int64_t u1 = u0 + kFixGroup < n_lo ? u0 + kFixGroup : n_lo;
-    int rf = 0, gid = -1;
-    double rv = 0.0, gfirst = 0.0;
-    for (int64_t ub = u0; ub < u1; ub += 16) {
-        // 16 summaries at a time: all loads are independent of the fold, so they are issued together
-        int ht[16], id[16];
-        double op[16], fi[16];
+// value = first[t] + open[t-1] + open[t-2] + ... up to and including the nearest tile that contains a segment end: a thread
+// per (tile, r) walks back, eight summaries at a time (their loads do not depend on what they hold).  A chain of more than
+// kFixSerial tiles -- the head slice of a power-law tensor is cut over thousands -- is left to the whole workgroup, its tiles
+// dealt over 1024 / R threads per column.  One launch; folding 64 summaries per thread level by level took three of them, 51 us
+// for 36 600 tiles of the MTTKRP configuration at rank 16 where this takes 28.  T = 256 threads where no chain is that long (a few
+// thousand tiles at rank 1 would otherwise sit on a handful of compute units).
+constexpr int kFixSerial = 64;
+template <int T>
+__global__ void __launch_bounds__(T) k_stream_fixup(void *scratch, int64_t ntiles, int R, const int32_t *__restrict__ rowmap,
+                                                       double *__restrict__ out, Epilogue ep) {
+    __shared__ double sums[T];
+    __shared__ int nlong, list[T], newest;
+    const CarryView cb = carry_view(scratch, ntiles, R);
+    const int lanes = T / R, lane = (int)threadIdx.x / R, r = (int)threadIdx.x - lane * R;
+    if (threadIdx.x == 0) nlong = 0;
+    __syncthreads();
+    auto finish = [&](int64_t t, double v) {
+        const int32_t id = cb.first_id[t];
+        double *o = out + (rowmap ? (int64_t)rowmap[id] : (int64_t)id) * R + r;
+        *o = ep_apply(ep, v, o);
+    };
+    const int64_t t0 = (int64_t)blockIdx.x * lanes, mine = t0 + lane;
+    if (lane < lanes && mine < ntiles && cb.has_tail[mine]) {
+        double v = cb.first[mine * R + r];
+        bool done = false;
+        int64_t u = mine - 1;
+        for (int step = 0; !done && u >= 0 && step < kFixSerial; step += 8) {
+            int ht[8];
+            double op[8];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int64_t u = ub + i;
-            const bool in = u < u1;
-            ht[i] = in ? lo_ht[u] : 0;
-            id[i] = in ? lo_id[u] : -1;
-            op[i] = in ? lo_open[u * R + r] : 0.0;
-            fi[i] = in ? lo_first[u * R + r] : 0.0;
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if (ht[i]) {
-                const double value = rv + fi[i];
-                if (rf) {
-                    const int64_t row = rowmap ? (int64_t)rowmap[id[i]] : (int64_t)id[i];
-                    out[row * R + r] = ep_apply(ep, value, out + row * R + r);
-                } else {
-                    gfirst = value; gid = id[i]; rf = 1;
-                }
-                rv = op[i];
-            } else {
-                rv += op[i];
+            for (int q = 0; q < 8; ++q) {
+                const int64_t w = u - q > 0 ? u - q : 0;
+                ht[q] = cb.has_tail[w];
+                op[q] = cb.open[w * R + r];
             }
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (!done && u - q >= 0) { v += op[q]; done = ht[q] != 0; }
+            u -= 8;
         }
+        if (done || u < 0) finish(mine, v);
+        else if (r == 0) list[atomicAdd(&nlong, 1)] = lane;
     }
-    up_first[g * R + r] = gfirst;
-    up_open[g * R + r] = rv;
-    if (r == 0) { up_ht[g] = rf; up_id[g] = gid; }
+    __syncthreads();
+    const int n = nlong;
+    for (int i = 0; i < n; ++i) {
+        const int64_t t = t0 + list[i];
+        int64_t from = 0;                                         // the nearest tile in front of t that contains a segment end, or the first
+        for (int64_t base = t - 1; base >= 0; base -= T) {
+            __syncthreads();
+            if (threadIdx.x == 0) newest = -1;
+            __syncthreads();
+            const int64_t u = base - threadIdx.x;
+            if (u >= 0 && cb.has_tail[u]) atomicMax(&newest, (int)u);
+            __syncthreads();
+            if (newest >= 0) { from = newest; break; }
+        }
+        double v = 0.0;
+        if (lane < lanes) {
+            int64_t u = from + lane;
+            for (; u + 7 * (int64_t)lanes < t; u += 8 * (int64_t)lanes) {
+                double x[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) x[q] = cb.open[(u + q * (int64_t)lanes) * R + r];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v += x[q];
+            }
+            for (; u < t; u += lanes) v += cb.open[u * R + r];
+        }
+        sums[threadIdx.x] = v;
+        for (int k = lanes; k > 1;) {
+            const int h = (k + 1) / 2;
+            __syncthreads();
+            if (lane < k - h) sums[threadIdx.x] += sums[threadIdx.x + h * R];
+            k = h;
+        }
+        __syncthreads();
+        if (lane == 0) finish(t, cb.first[t * R + r] + sums[threadIdx.x]);
+        __syncthreads();
+    }
 }
 
 
 }  // namespace
 
-// Finish every segment that a tile boundary cut: fold the tile summaries level by level, then
-// walk the few top-level summaries serially.  `max_chain` bounds the number of consecutive tiles
-// one segment can span (0 = unknown); short chains go straight to the serial walk.
-hipError_t run_fixup(void *scratch, int64_t ntiles, int R, const int32_t *rowmap, double *out, int64_t max_chain,
-                     hipStream_t st, Epilogue ep) {
-    char *base = (char *)scratch;
-    int64_t n = ntiles;
-    const bool direct = max_chain > 0 && max_chain <= 24;
-    while (!direct && n > kFixGroup) {
-        const int64_t n_up = (n + kFixGroup - 1) / kFixGroup;
-        CarryView lo = carry_view(base, n, R);
-        char *up_base = base + carry_level_bytes(n, R);
-        CarryView up = carry_view(up_base, n_up, R);
-        const int64_t threads = n_up * R;
-        hipLaunchKernelGGL(k_fixup_level, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, lo.first, lo.open,
-                           lo.has_tail, lo.first_id, n, up.first, up.open, up.has_tail, up.first_id, n_up, R, rowmap, out, ep);
-        base = up_base;
-        n = n_up;
-    }
-    const int64_t threads = n * R;
-    hipLaunchKernelGGL(k_stream_fixup, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, (void *)base, n, R,
-                       rowmap, out, ep);
+// Finish every segment that a tile boundary cut.  max_chain bounds the number of tiles that one of them is cut over (0: unknown).
+hipError_t run_fixup(void *scratch, int64_t ntiles, int R, const int32_t *rowmap, double *out, int64_t max_chain, hipStream_t st,
+                     Epilogue ep) {
+    const bool shorter = max_chain > 0 && max_chain <= kFixSerial;
+    const int64_t per = (shorter ? 256 : 1024) / R;
+    const dim3 grid((unsigned)((ntiles + per - 1) / per));
+    if (shorter) hipLaunchKernelGGL(k_stream_fixup<256>, grid, dim3(256), 0, st, scratch, ntiles, R, rowmap, out, ep);
+    else hipLaunchKernelGGL(k_stream_fixup<1024>, grid, dim3(1024), 0, st, scratch, ntiles, R, rowmap, out, ep);
     return hipGetLastError();
 }
 
@@ -559,16 +553,7 @@ bool stream_supports_rank(int64_t R) { return R >= 1 && R <= 128; }
 bool stream_mttkrp_supports_rank(int64_t R) { return R >= 1 && R <= 128; }
 bool stream_supports_coo() { return true; }
 
-size_t stream_scratch_bytes(int64_t ntiles, int64_t R) {
-    int64_t n = ntiles < 1 ? 1 : ntiles;
-    size_t total = 0;
-    for (;;) {
-        total += carry_level_bytes(n, R);
-        if (n <= kFixGroup) break;
-        n = (n + kFixGroup - 1) / kFixGroup;
-    }
-    return total + 256;
-}
+size_t stream_scratch_bytes(int64_t ntiles, int64_t R) { return carry_bytes(ntiles < 1 ? 1 : ntiles, R) + 256; }
 
 // Which walk: the pieces, except for ranks 8 and 16 over many nonzeros, where the walk over whole tiles of nonzeros keeps more
 // of a list of short segments in flight.  Whole calls on the walk and on the pieces: TTM at rank 16, 100 M nonzeros in 6.5 M

@@ -18,7 +18,7 @@
 //     open        sum of the items after the last segment end (all items if there is none)
 // and two adjacent summaries combine associatively; a segment that closes at the boundary of two
 // units is final once the left unit contains a segment end.  Tile summaries go to a carry buffer
-// and small follow-up kernels finish the segments cut by tile boundaries in a fixed order, so the
+// and a small follow-up kernel finishes the segments cut by tile boundaries in a fixed order, so the
 // results do not depend on scheduling (no atomics).
 //
 // Kernels:  k_stream_rank1_ldsvec  rank 1, dense vector staged in LDS, one wavefront per 1024-item chunk
@@ -26,7 +26,7 @@
 //           k_pieces               rank R, lane groups walk pieces of segments (cut and carried in a way of their own, pieces.hpp)
 //           k_stream_rankR         ranks 8 and 16 over long lists, lane groups walk item runs, per-item records in LDS
 //           k_stream_mttkrp        rank R, two nested segment levels (fibers inside slices)
-//           k_fixup_level / k_stream_fixup   carry resolution
+//           k_stream_fixup         carry resolution
 #pragma once
 
 #include "kernels.hpp"
@@ -50,16 +50,12 @@ hipError_t piece_rows(const PiecePlan &plan, const int32_t *crd, const double *v
 
 namespace {
 
-// Carry-buffer layout inside the per-tensor scratch.  Level 0 holds one summary per tile: first[R],
-// open[R] (fp64), has_tail and first_id (int32).  Level l+1 holds one summary per group of
-// kFixGroup consecutive level-l summaries (same layout), so that a segment cut over thousands of
-// tiles is finished in a few short passes instead of one long serial walk.
-constexpr int kFixGroup = 64;
+// Carry buffer in the per-tensor scratch: one summary per tile, first[R], open[R] (fp64), has_tail and first_id (int32).
 struct CarryView {
     double  *first, *open;
     int32_t *has_tail, *first_id;
 };
-__host__ __device__ inline size_t carry_level_bytes(int64_t n, int64_t R) {
+__host__ __device__ inline size_t carry_bytes(int64_t n, int64_t R) {
     size_t b = (size_t)n * (size_t)R * 2 * sizeof(double) + (size_t)n * 2 * sizeof(int32_t);
     return (b + 255) & ~(size_t)255;
 }
