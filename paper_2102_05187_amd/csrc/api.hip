@@ -117,12 +117,10 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st) {
         hipError_t ppe = comet::piece_plan_build(t.pos_i(leaf), sc.nseg, sc.nnz, sc.pieces, st);
         if (ppe == hipErrorOutOfMemory) { (void)hipGetLastError(); ppe = hipSuccess; }
         HIP_TRY(ppe);
-        if (t.levels[0] == COMET_CU) {
-            HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
-            HIP_TRY(comet::max_coordinate_gap(t.crd_i(0), t.crd_len[0], t.dims[0], (int32_t *)mx->ptr, st));
-            rs = read_i32((const int32_t *)mx->ptr, 1, &h, st);
-            if (rs != COMET_OK) return rs;
-            sc.max_root_gap = h;
+        if (t.levels[0] == COMET_CU && t.crd_len[0] * 2 >= t.dims[0]) {
+            sc.unstored = comet::dev_alloc(sizeof(int32_t) * (t.dims[0] - t.crd_len[0]));
+            if (!sc.unstored) return COMET_ERR_ALLOC;
+            HIP_TRY(comet::list_unstored_rows(t.crd_i(0), t.crd_len[0], t.dims[0], (int32_t *)sc.unstored->ptr, st));
         }
         if ((t.fmt == Format::CSR || t.fmt == Format::DCSR) && !t.lean) {
             // the plans are optional: without the memory for one, the tiled kernel takes everything
@@ -222,12 +220,9 @@ void note_stream(const comet_tensor *t, hipStream_t st) {
 constexpr int64_t kShortSegment = 256;
 constexpr int64_t kSmallProblemNnz = int64_t(4) << 20;
 
-// Clearing only the rows between the stored root coordinates beats clearing the whole dense result when
-// most rows are stored -- but one thread clears one gap, so a long gap (say, an empty lower half) must
-// not be left to it.
-bool gaps_are_short(const comet_tensor *t, int64_t R) {
-    const int64_t nstored = t->crd_len[0];
-    return nstored * 2 >= t->dims[0] && t->sched.max_root_gap >= 0 && t->sched.max_root_gap * R <= 4096;
+// Clearing only the rows that are not stored beats clearing the whole dense result when most rows are stored.
+hipError_t clear_unstored_rows(const comet_tensor *t, int64_t R, double *out, double beta, hipStream_t st) {
+    return comet::clear_rows((const int32_t *)t->sched.unstored->ptr, t->dims[0] - t->crd_len[0], R, out, st, beta);
 }
 
 // The tiled kernels read crd / vals with 16-byte vector loads, so the arrays must be 16-byte aligned
@@ -752,11 +747,10 @@ static comet_status matrix_product(const comet_tensor *A, const double *Dn, int6
     if (A->fmt == Format::DCSR) {
         // Rows absent from the root level hold no nonzeros and must come out as zeros.  Every stored row is
         // written by the kernels below (also one without nonzeros), so when most rows are stored only
-        // the gaps between them are cleared; otherwise, or when there is nothing to run, the whole result.
+        // the others are cleared; otherwise, or when there is nothing to run, the whole result.
         rowmap = A->crd_i(0);
-        const int64_t nstored = A->crd_len[0];
-        if (nnz > 0 && gaps_are_short(A, R)) {
-            HIP_TRY(comet::zero_unstored_rows(rowmap, nstored, A->dims[0], R, out, st, ep.on ? ep.beta : 0.0));
+        if (nnz > 0 && A->sched.unstored) {
+            HIP_TRY(clear_unstored_rows(A, R, out, ep.on ? ep.beta : 0.0, st));
         } else {
             // every element is cleared (scaled by beta) here, so the kernels add to what they find
             HIP_TRY(comet::scale_f64(out, A->dims[0] * R, ep.on ? ep.beta : 0.0, st));
@@ -1012,9 +1006,9 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
                        comet::stream_mttkrp_supports_rank(R);
     // Rows of M whose index is not stored at the root level receive no contribution.  The tiled kernel
     // writes every stored slice's row itself (a slice without nonzeros is cleared in its slice pass), so
-    // when most rows are stored only the gaps between them are cleared; otherwise all of M is.
-    if (tiled && gaps_are_short(X, R)) {
-        HIP_TRY(comet::zero_unstored_rows(X->crd_i(0), nslice, X->dims[0], R, M, st, ep.on ? ep.beta : 0.0));
+    // when most rows are stored only the others are cleared; otherwise all of M is.
+    if (tiled && X->sched.unstored) {
+        HIP_TRY(clear_unstored_rows(X, R, M, ep.on ? ep.beta : 0.0, st));
     } else {
         // every element is cleared (scaled by beta) here, so the kernels add to what they find
         HIP_TRY(comet::scale_f64(M, X->dims[0] * R, ep.on ? ep.beta : 0.0, st));

@@ -27,10 +27,10 @@ __device__ __forceinline__ double ep_empty(const Epilogue &ep, const double *p) 
 hipError_t fill_zero_f64(double *p, int64_t n, hipStream_t st);
 // p[i] = beta * p[i] (beta == 0: p[i] = 0 without reading it).
 hipError_t scale_f64(double *p, int64_t n, double beta, hipStream_t st);
-// out[r, :] = 0 for every row r of [0, nrows) that does not occur in the sorted, duplicate-free list idx[0..n).
-// beta != 0: those rows are multiplied by beta instead.
-hipError_t zero_unstored_rows(const int32_t *idx, int64_t n, int64_t nrows, int64_t R, double *out, hipStream_t st,
-                              double beta = 0.0);
+// rows = the rows of [0, nrows) that do not occur in the sorted, duplicate-free list idx[0..n): nrows - n of them.
+hipError_t list_unstored_rows(const int32_t *idx, int64_t n, int64_t nrows, int32_t *rows, hipStream_t st);
+// out[r, :] = 0 for the listed rows; beta != 0: they are multiplied by beta instead.
+hipError_t clear_rows(const int32_t *rows, int64_t nrows, int64_t R, double *out, hipStream_t st, double beta = 0.0);
 
 // Structure checks; each ORs a bit into *err (device int32, zeroed by the caller) on failure.
 hipError_t check_pos(const int32_t *pos, int64_t n, int64_t last, int32_t *err, hipStream_t st);
