@@ -6,6 +6,7 @@
 #include <new>
 
 #include "kernels.hpp"
+#include "mttkrp_plan.hpp"
 #include "pieces.hpp"
 #include "stream_kernels.hpp"
 #include "tensor.hpp"
@@ -117,10 +118,23 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st) {
         hipError_t ppe = comet::piece_plan_build(t.pos_i(leaf), sc.nseg, sc.nnz, sc.pieces, st);
         if (ppe == hipErrorOutOfMemory) { (void)hipGetLastError(); ppe = hipSuccess; }
         HIP_TRY(ppe);
+        if (t.fmt == Format::CSF3 && sc.nnz <= comet::kMtNarrow) {
+            ppe = comet::mttkrp_plan_build(t.pos_i(1), t.crd_i(0), t.pos_len[1] - 1, t.pos_i(2), t.crd_i(1), sc.nseg, sc.nnz, t.dims[0],
+                                           sc.mttkrp, st);
+            if (ppe == hipErrorOutOfMemory) { (void)hipGetLastError(); ppe = hipSuccess; }
+            HIP_TRY(ppe);
+        }
         if (t.levels[0] == COMET_CU && t.crd_len[0] * 2 >= t.dims[0]) {
             sc.unstored = comet::dev_alloc(sizeof(int32_t) * (t.dims[0] - t.crd_len[0]));
             if (!sc.unstored) return COMET_ERR_ALLOC;
             HIP_TRY(comet::list_unstored_rows(t.crd_i(0), t.crd_len[0], t.dims[0], (int32_t *)sc.unstored->ptr, st));
+        }
+        if (sc.mttkrp.ntiles > 0) {
+            HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
+            HIP_TRY(comet::max_coordinate_gap(t.crd_i(0), t.crd_len[0], t.dims[0], (int32_t *)mx->ptr, st));
+            rs = read_i32((const int32_t *)mx->ptr, 1, &h, st);
+            if (rs != COMET_OK) return rs;
+            sc.max_root_gap = h;
         }
         if ((t.fmt == Format::CSR || t.fmt == Format::DCSR) && !t.lean) {
             // the plans are optional: without the memory for one, the tiled kernel takes everything
@@ -223,6 +237,10 @@ constexpr int64_t kSmallProblemNnz = int64_t(4) << 20;
 // Clearing only the rows that are not stored beats clearing the whole dense result when most rows are stored.
 hipError_t clear_unstored_rows(const comet_tensor *t, int64_t R, double *out, double beta, hipStream_t st) {
     return comet::clear_rows((const int32_t *)t->sched.unstored->ptr, t->dims[0] - t->crd_len[0], R, out, st, beta);
+}
+// MTTKRP over pieces does that itself, a lane group per gap: a long gap (say, an empty lower half) is not left to it.
+bool gaps_are_short(const comet_tensor *t, int64_t R) {
+    return t->sched.unstored && t->sched.max_root_gap >= 0 && t->sched.max_root_gap * R <= 4096;
 }
 
 // The tiled kernels read crd / vals with 16-byte vector loads, so the arrays must be 16-byte aligned
@@ -1000,16 +1018,16 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
     const double *B = factors[X->mode_of_level[1]], *C = factors[X->mode_of_level[2]];
     if (!B || !C) return COMET_ERR_INVALID_ARG;
     hipStream_t st = (hipStream_t)stream;
-    const int64_t nslice = X->pos_len[1] - 1;
     const bool tiled = X->nvals > 0 &&
                        use_tiled(X, R, B, M, 0, X->sched.max_parent_len) && aligned16(C) &&
                        comet::stream_mttkrp_supports_rank(R);
-    // Rows of M whose index is not stored at the root level receive no contribution.  The tiled kernel
-    // writes every stored slice's row itself (a slice without nonzeros is cleared in its slice pass), so
-    // when most rows are stored only the others are cleared; otherwise all of M is.
-    if (tiled && X->sched.unstored) {
+    // Rows of M whose index is not stored at the root level receive no contribution.  The tiled kernels write every stored
+    // slice's row themselves, so when most rows are stored only the gaps between them are cleared (by the kernel over pieces
+    // itself); otherwise all of M is.
+    const bool gaps = tiled && comet::mttkrp_on_pieces(X->sched, R) && gaps_are_short(X, R);
+    if (tiled && !gaps && X->sched.unstored) {
         HIP_TRY(clear_unstored_rows(X, R, M, ep.on ? ep.beta : 0.0, st));
-    } else {
+    } else if (!gaps) {
         // every element is cleared (scaled by beta) here, so the kernels add to what they find
         HIP_TRY(comet::scale_f64(M, X->dims[0] * R, ep.on ? ep.beta : 0.0, st));
         if (ep.on && ep.beta != 0.0) ep.beta = 1.0;
@@ -1018,8 +1036,8 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
     if (tiled) {
         comet_status rs = ensure_scratch(X, comet::mttkrp_scratch_bytes(X->sched, R));
         if (rs != COMET_OK) return rs;
-        HIP_TRY(comet::stream_mttkrp(X->sched, X->pos_i(1), X->crd_i(0), nslice, X->pos_i(2), X->crd_i(1),
-                                     X->crd_i(2), X->vals_d(), B, C, R, M, X->scratch->ptr, st, ep));
+        HIP_TRY(comet::stream_mttkrp(X->sched, X->pos_i(1), X->crd_i(0), X->pos_i(2), X->crd_i(1), X->crd_i(2), X->vals_d(), B, C,
+                                     X->dims[1] > X->dims[2] ? X->dims[1] : X->dims[2], R, M, gaps, X->scratch->ptr, st, ep));
         return COMET_OK;
     }
     HIP_TRY(comet::simple_mttkrp(X->pos_i(1), X->crd_i(0), X->pos_len[1] - 1, X->pos_i(2), X->crd_i(1), X->crd_i(2),

@@ -1,9 +1,265 @@
-// MTTKRP kernel of the nonzero-tiled family: the rank-R walk over two nested segment levels.
+// MTTKRP kernel: lane groups of 4, 8 or 16 walk the pieces of the fibers of a tile (mttkrp_plan.hpp).
+#include "mttkrp_plan.hpp"
 #include "stream_common.hpp"
 
 namespace comet {
 
 namespace {
+
+struct MtItem { unsigned off, pad; double val; };                 // a nonzero: where its row of C starts, and its value
+
+// A workgroup takes a tile and a block of L * E columns.
+template <int L, int E, bool FULL, bool BIG>
+__global__ void __launch_bounds__(256, 3) k_mttkrp_pieces(const int4 *__restrict__ tiles, const uint2 *__restrict__ pieces,
+                                                       const uint2 *__restrict__ recs, int ntiles, int items_cap,
+                                                       const int32_t *__restrict__ crd, const double *__restrict__ vals,
+                                                       const double *__restrict__ Bm, const double *__restrict__ Cm,
+                                                       double *__restrict__ M, int64_t nnz, int R, int gaps, double *__restrict__ head,
+                                                       double *__restrict__ tail, Epilogue ep) {
+    constexpr int V = E, KP = 64 / L, NG = 256 / L, kRow = L * E;
+    constexpr int G = 4;                                          // rows of C in flight per group, next to as many being used
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    MtItem *item = reinterpret_cast<MtItem *>(lds);
+    double *slots = reinterpret_cast<double *>(item + items_cap);
+    const int cb = (int)(blockIdx.x / (unsigned)ntiles), t = (int)(blockIdx.x % (unsigned)ntiles);
+    const int c0 = cb * kRow;
+    const int k = threadIdx.x % L, gw = (threadIdx.x & 63) / L, gid = threadIdx.x / L, wave = threadIdx.x >> 6;
+    const RowOf<L, E, 1, FULL> rw(R - c0 < kRow ? R - c0 : kRow, k);
+    const char *Cl = reinterpret_cast<const char *>(Cm + c0), *Bl = reinterpret_cast<const char *>(Bm + c0);
+    const unsigned unit = (unsigned)R * (BIG ? 1u : 8u);          // row offsets: bytes, or doubles for operands of 4 GiB and more
+    auto from_lane = [&](unsigned v, int lane) { return (unsigned)__shfl((int)v, gw * L + lane); };
+
+    const int4 d0 = tiles[t], d1 = tiles[t + 1];
+    const int p0 = d0.x & ~1, np = (int)((unsigned)d1.y - (unsigned)d0.y), njoin = d0.w;
+    const unsigned nr = (unsigned)d1.z - (unsigned)d0.z, nsum = nr - (unsigned)njoin;
+    const MtItem *items = item + (d0.x - p0);
+    // two nonzeros, a piece and a record per thread; lane k of a group keeps what the group takes in its k-th turn
+    const int pi = (4 * k + wave) * KP + gw;
+    const unsigned ri = (unsigned)(k * NG + gid);
+    const uint2 pcs = pi < np ? pieces[(size_t)(unsigned)d0.y + pi] : make_uint2(0u, 0u);
+    const uint2 rcs = ri < nr ? recs[(size_t)(unsigned)d0.z + ri] : make_uint2(0u, 0u);
+    {
+        const int i = (int)threadIdx.x * 2;
+        if (i < d1.x - p0) {
+            int c[2] = {0, 0};
+            double a[2] = {0.0, 0.0};
+            if ((int64_t)p0 + i + 2 <= nnz) {
+                const int2 cc = *reinterpret_cast<const int2 *>(crd + p0 + i);
+                const double2 x = *reinterpret_cast<const double2 *>(vals + p0 + i);
+                c[0] = cc.x; c[1] = cc.y;
+                a[0] = x.x; a[1] = x.y;
+            } else {
+                c[0] = crd[p0 + i]; a[0] = vals[p0 + i];
+            }
+            item[i] = MtItem{(unsigned)c[0] * unit, 0u, a[0]};
+            item[i + 1] = MtItem{(unsigned)c[1] * unit, 0u, a[1]};
+        }
+    }
+    __syncthreads();
+    // Longest pieces first: a piece per group at a time until the longest of them is short.
+    int m = 0;
+    for (; m < L && (4 * m + wave) * KP < np; ++m) {
+        const int longest = mt_len((unsigned)__builtin_amdgcn_readlane((int)pcs.x, m));
+        if (longest <= 2 * G) break;
+        const unsigned pd = from_lane(pcs.x, m), br = from_lane(pcs.y, m);
+        const int shortest = mt_len((unsigned)__builtin_amdgcn_readlane((int)pcs.x, 64 - L + m));
+        const int len = mt_len(pd), last = len > 0 ? len - 1 : 0;
+        const MtItem *it = items + mt_start(pd);
+        double acc[V], b[V], row[2][G][V], val[2][G];
+        rw.template load<BIG>(Bl, br * unit, b);
+#pragma unroll
+        for (int q = 0; q < V; ++q) acc[q] = 0.0;
+        auto issue = [&](int j, double (*d)[V], double *v) {
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const MtItem x = it[j + u < last ? j + u : last];
+                v[u] = x.val;
+                rw.template load<BIG>(Cl, x.off, d[u]);
+            }
+        };
+        auto consume = [&](int j, const double (*d)[V], const double *v) {
+            if (j + G <= shortest) {
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+#pragma unroll
+                    for (int q = 0; q < V; ++q) acc[q] = fma(v[u], d[u][q], acc[q]);
+            } else {
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+                    if (j + u < len) {
+#pragma unroll
+                        for (int q = 0; q < V; ++q) acc[q] = fma(v[u], d[u][q], acc[q]);
+                    }
+            }
+        };
+        issue(0, row[0], val[0]);
+        for (int j = 0; j < longest; j += 2 * G) {
+            issue(j + G, row[1], val[1]);
+            consume(j, row[0], val[0]);
+            issue(j + 2 * G, row[0], val[0]);
+            consume(j + G, row[1], val[1]);
+        }
+#pragma unroll
+        for (int q = 0; q < V; ++q) acc[q] *= b[q];
+        if (len > 0) rw.put(slots + mt_slot(pd) * kRow, acc);
+    }
+    // Short pieces: several of them per group at the same time.
+    auto short_pieces = [&](auto count) {
+        constexpr int KB = decltype(count)::value;
+        const int longest = mt_len((unsigned)__builtin_amdgcn_readlane((int)pcs.x, m));
+        unsigned pd[KB];
+        int len[KB];
+        double acc[KB][V], b[KB][V], row[2][KB][V], val[2][KB];
+        auto issue = [&](int j, double (*d)[V], double *v) {
+#pragma unroll
+            for (int q = 0; q < KB; ++q) {
+                const MtItem x = items[j < len[q] ? mt_start(pd[q]) + j : 0];
+                v[q] = x.val;
+                rw.template load<BIG>(Cl, x.off, d[q]);
+            }
+        };
+        auto consume = [&](int j, const double (*d)[V], const double *v) {
+#pragma unroll
+            for (int q = 0; q < KB; ++q)
+                if (j < len[q]) {
+#pragma unroll
+                    for (int e = 0; e < V; ++e) acc[q][e] = fma(v[q], d[q][e], acc[q][e]);
+                }
+        };
+#pragma unroll
+        for (int q = 0; q < KB; ++q) {
+            pd[q] = from_lane(pcs.x, m + q);
+            len[q] = mt_len(pd[q]);
+            rw.template load<BIG>(Bl, from_lane(pcs.y, m + q) * unit, b[q]);
+#pragma unroll
+            for (int e = 0; e < V; ++e) acc[q][e] = 0.0;
+        }
+        issue(0, row[0], val[0]);
+        for (int j = 0; j < longest; j += 2) {
+            if (j + 1 < longest) issue(j + 1, row[1], val[1]);
+            consume(j, row[0], val[0]);
+            if (j + 1 >= longest) break;
+            if (j + 2 < longest) issue(j + 2, row[0], val[0]);
+            consume(j + 1, row[1], val[1]);
+        }
+#pragma unroll
+        for (int q = 0; q < KB; ++q)
+            if (len[q] > 0) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) acc[q][e] *= b[q][e];
+                rw.put(slots + mt_slot(pd[q]) * kRow, acc[q]);
+            }
+        m += KB;
+    };
+    const int turns = ((np + KP - 1) / KP - wave + 3) >> 2;    // pieces of this wavefront's groups
+    while (m < turns) {
+        if (turns - m >= 4) short_pieces(IntC<4>{});
+        else if (turns - m >= 2) short_pieces(IntC<2>{});
+        else short_pieces(IntC<1>{});
+    }
+    __syncthreads();
+    auto add_rows = [&](int first, int n, int step, double *s) {
+        for (int i = 0; i < n; i += 4 * step) {
+            double v[4][V];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) rw.get(slots + (first + (i + u * step < n ? i + u * step : i)) * kRow, v[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i + u * step < n) {
+#pragma unroll
+                    for (int q = 0; q < V; ++q) s[q] += v[u][q];
+                }
+        }
+    };
+    auto do_sum = [&](const uint2 r) {
+        const int kind = mt_sum_kind(r.x), first = mt_first(r.x), n = mt_sum_rows(r.x);
+        double s[V];
+#pragma unroll
+        for (int q = 0; q < V; ++q) s[q] = 0.0;
+        add_rows(first, n, 1, s);
+        double *o = M + (int64_t)(int)r.y * R + c0;
+        if (kind == kMtPart) rw.put(slots + first * kRow, s);
+        else if (kind == kMtSlice) rw.store_result(o, s, ep, n == 0);
+        if (gaps)
+            for (int g = mt_sum_gap(r.x); g > 0; --g) {       // rows that are not stored
+#pragma unroll
+                for (int q = 0; q < V; ++q) s[q] = 0.0;
+                rw.store_result(o - (int64_t)g * R, s, ep, true);
+            }
+    };
+    auto do_join = [&](const uint2 r) {
+        const bool cont = mt_join_cont(r.x), open = mt_join_open(r.x);
+        double s[V];
+#pragma unroll
+        for (int q = 0; q < V; ++q) s[q] = 0.0;
+        add_rows(mt_first(r.x), mt_join_rows(r.x), kMtSum, s);
+        const int64_t at = (int64_t)t * R + c0;
+        if (cont) rw.store(head + at, s);
+        else if (open) rw.store(tail + at, s);
+        else rw.store_result(M + (int64_t)(int)r.y * R + c0, s, ep);
+    };
+    auto record = [&](int q) { return make_uint2(from_lane(rcs.x, q), from_lane(rcs.y, q)); };
+    int q = 0;
+    for (; q < L; ++q) {
+        if ((unsigned)(q * NG + gid) >= nsum) break;
+        do_sum(record(q));
+    }
+    for (unsigned i = 256 + gid; i < nsum; i += NG) do_sum(recs[(size_t)(unsigned)d0.z + i]);
+    if (njoin) {
+        __syncthreads();
+        for (; q < L; ++q) {
+            if ((unsigned)(q * NG + gid) >= nr) break;
+            do_join(record(q));
+        }
+        for (unsigned i = 256 + gid; i < nr; i += NG)
+            if (i >= nsum) do_join(recs[(size_t)(unsigned)d0.z + i]);
+    }
+}
+
+// Slices cut by tile boundaries: what the first tile holds of one behind its boundary, then what the following tiles hold in
+// front of theirs.  A thread per (slice, column); the last workgroups take the slices over many tiles, a block of 16 columns
+// each, with the tiles dealt over 64 threads per column.
+__global__ void __launch_bounds__(1024) k_mttkrp_cut_sums(const int4 *__restrict__ cuts, int ncut, int nlong, int64_t ntiles,
+                                                          const double *__restrict__ head, const double *__restrict__ tail, int R,
+                                                          double *__restrict__ M, Epilogue ep) {
+    __shared__ double sums[1024];
+    const int nblocks = (R + 15) / 16, narrow = (int)gridDim.x - nlong * nblocks;
+    if ((int)blockIdx.x < narrow) {
+        const int64_t g = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+        if (g >= (int64_t)ncut * R) return;
+        const int i = (int)(g / R), r = (int)(g - (int64_t)i * R);
+        const int4 c = cuts[i];
+        double s = tail[(int64_t)c.y * R + r];
+        for (int u = c.y + 1; u <= c.z; ++u) s += head[(int64_t)u * R + r];
+        double *o = M + (int64_t)c.x * R + r;
+        *o = ep_apply(ep, s, o);
+        return;
+    }
+    const int w = (int)blockIdx.x - narrow;
+    const int4 c = cuts[ntiles - 1 - w / nblocks];
+    const int lane = threadIdx.x >> 4, r = (w % nblocks) * 16 + (threadIdx.x & 15);
+    double s = 0.0;
+    if (r < R) {
+        if (lane == 0) s = tail[(int64_t)c.y * R + r];
+        int64_t u = c.y + 1 + lane;
+        for (; u + 7 * 64 <= c.z; u += 8 * 64) {
+            double v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = head[(u + 64 * q) * R + r];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s += v[q];
+        }
+        for (; u <= c.z; u += 64) s += head[u * R + r];
+    }
+    sums[threadIdx.x] = s;
+    for (int d = 32; d > 0; d >>= 1) {
+        __syncthreads();
+        if (lane < d) sums[threadIdx.x] += sums[threadIdx.x + 16 * d];
+    }
+    if (lane != 0 || r >= R) return;
+    double *o = M + (int64_t)c.x * R + r;
+    *o = ep_apply(ep, sums[threadIdx.x], o);
+}
 
 // ---- MTTKRP: the same walk, two nested segment levels ---------------------------------------------
 // Inner level: fibers (segments of pos3); the per-fiber sum of vals * C[crd3, :] is scaled by the row
@@ -160,38 +416,81 @@ __global__ void __launch_bounds__(256) k_stream_mttkrp(const int32_t *__restrict
                                     carry_view(scratch, ntiles, R), t, ep);
 }
 
+struct MtArgs {
+    const MttkrpPlan &plan;
+    const int32_t *pos2, *crd1, *pos3, *crd2;
+    const int32_t *crd;
+    const double *vals, *B, *C;
+    double *M;
+    int64_t nnz;
+    int R, gaps;
+    double *head, *tail;
+    hipStream_t st;
+    Epilogue ep;
+};
+
+template <int L, int E, bool FULL, bool BIG>
+hipError_t launch_mttkrp(const MtArgs &a) {
+    constexpr int kRow = L * E;
+    const int nblocks = (a.R + kRow - 1) / kRow, items_cap = a.plan.max_items + 3;
+    const size_t lds = (size_t)items_cap * sizeof(MtItem) + (size_t)a.plan.max_pieces * kRow * 8;
+    hipLaunchKernelGGL((k_mttkrp_pieces<L, E, FULL, BIG>), dim3((unsigned)(a.plan.ntiles * nblocks)), dim3(256), (unsigned)lds, a.st,
+                       (const int4 *)a.plan.tiles(), (const uint2 *)a.plan.pieces(), (const uint2 *)a.plan.recs(), (int)a.plan.ntiles,
+                       items_cap, a.crd, a.vals, a.B, a.C, a.M, a.nnz, a.R, a.gaps, a.head, a.tail, a.ep);
+    return hipGetLastError();
+}
+
 template <int L, int V, bool WIDE>
-hipError_t launch_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, const int32_t *pos3,
-                         const int32_t *crd2, const int32_t *crd3, const double *vals, const double *B, const double *C,
-                         int R, double *M, void *scratch, hipStream_t st, Epilogue ep) {
+hipError_t launch_walk(const MtArgs &a, const Schedule &sc, void *scratch) {
     auto go = [&](auto kernel, int64_t ntiles, const DevRef &fibers, const DevRef &slices) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)ntiles), dim3(256), 0, st, pos2, crd1, pos3, crd2, crd3, vals,
-                           (const int32_t *)fibers->ptr, (const int32_t *)slices->ptr, B, C, M, sc.nnz, sc.nseg, ntiles, R,
-                           scratch, ep);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)ntiles), dim3(256), 0, a.st, a.pos2, a.crd1, a.pos3, a.crd2, a.crd, a.vals,
+                           (const int32_t *)fibers->ptr, (const int32_t *)slices->ptr, a.B, a.C, a.M, sc.nnz, sc.nseg, ntiles, a.R,
+                           scratch, a.ep);
     };
     if (sc.chunk_slice_begin) go(k_stream_mttkrp<L, V, WIDE, kChunk>, sc.nchunks, sc.chunk_seg_begin, sc.chunk_slice_begin);
     else go(k_stream_mttkrp<L, V, WIDE, kTile>, sc.ntiles, sc.seg_begin, sc.slice_begin);
     return hipGetLastError();
 }
 
+// Calls F<L, E, FULL, BIG>(args) for rank R: blocks of 16 columns, 16 bytes per lane where the rank is even.
+#define COMET_DISPATCH_BLOCKS(F, R, big, args)                                \
+    (big ? ((R) & 1 ? F<16, 1, false, true>(args) : F<8, 2, false, true>(args)) \
+     : (R) & 1 ? ((R) <= 4 ? F<4, 1, false, false>(args) : (R) <= 8 ? F<8, 1, false, false>(args) : F<16, 1, false, false>(args)) \
+               : ((R) <= 8 ? F<4, 2, false, false>(args) : (R) % 16 ? F<8, 2, false, false>(args) : F<8, 2, true, false>(args)))
+
 }  // namespace
 
+bool mttkrp_on_pieces(const Schedule &sc, int64_t R) { return sc.mttkrp.ntiles > 0 && mttkrp_takes_pieces(sc.nnz, R); }
+
 size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R) {
-    return stream_scratch_bytes(sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, R);
+    // ranks below R may take the pieces where R does not
+    const size_t a = stream_scratch_bytes(sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, R);
+    const size_t b = (size_t)sc.mttkrp.ntiles * (size_t)R * 2 * sizeof(double);
+    return a > b ? a : b;
 }
 
-hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, int64_t nslice,
-                         const int32_t *pos3, const int32_t *crd2, const int32_t *crd3, const double *vals,
-                         const double *B, const double *C, int64_t R, double *M, void *scratch, hipStream_t st,
-                         Epilogue ep) {
-    (void)nslice;
+hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, const int32_t *pos3, const int32_t *crd2,
+                         const int32_t *crd3, const double *vals, const double *B, const double *C, int64_t dense_rows, int64_t R,
+                         double *M, bool gaps, void *scratch, hipStream_t st, Epilogue ep) {
     if (sc.ntiles <= 0) return hipSuccess;
     if (!stream_mttkrp_supports_rank(R) || !sc.slice_begin) return hipErrorNotSupported;
-    const int r = (int)R;
-    hipError_t e = COMET_DISPATCH_GROUPS(launch_mttkrp, R, sc, pos2, crd1, pos3, crd2, crd3, vals, B, C, r, M, scratch, st, ep);
+    const MttkrpPlan &plan = sc.mttkrp;
+    double *head = (double *)scratch, *tail = head + plan.ntiles * R;
+    const MtArgs a{plan, pos2, crd1, pos3, crd2, crd3, vals, B, C, M, sc.nnz, (int)R, gaps ? 1 : 0, head, tail, st, ep};
+    if (mttkrp_on_pieces(sc, R)) {
+        const bool wide = dense_rows * R * 8 >= (int64_t(1) << 32);   // row offsets in bytes no longer fit 32 bits
+        const hipError_t e = COMET_DISPATCH_BLOCKS(launch_mttkrp, a.R, wide, a);
+        if (e != hipSuccess || plan.ncut + plan.ncut_long == 0) return e;
+        const int64_t narrow = (plan.ncut * R + 1023) / 1024;
+        hipLaunchKernelGGL(k_mttkrp_cut_sums, dim3((unsigned)(narrow + plan.ncut_long * ((R + 15) / 16))), dim3(1024), 0, st,
+                           (const int4 *)plan.cuts(), (int)plan.ncut, (int)plan.ncut_long, plan.ntiles, (const double *)head,
+                           (const double *)tail, (int)R, M, ep);
+        return hipGetLastError();
+    }
+    const hipError_t e = COMET_DISPATCH_GROUPS(launch_walk, a.R, a, sc, scratch);
     if (e != hipSuccess) return e;
     const int tile = sc.chunk_slice_begin ? kChunk : kTile;
-    return run_fixup(scratch, sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, r, nullptr, M,
+    return run_fixup(scratch, sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, (int)R, nullptr, M,
                      sc.max_parent_len > 0 ? sc.max_parent_len / tile + 2 : 0, st, ep);
 }
 

@@ -68,12 +68,15 @@ hipError_t fiber_ttm(const FiberPlan &plan, const int32_t *crd, const double *va
 // Number of compute units of the current device (cached per device).
 int current_device_cu_count();
 
-// M[crd1[s], :] = sum_{f in slice s} B[crd2[f], :] * (sum_{p in fiber f} vals[p] * C[crd3[p], :]).
-// M must have been cleared (or, with an epilogue, scaled by beta) for rows that have no stored slice.
+// M[crd1[s], :] = sum_{f in slice s} B[crd2[f], :] * (sum_{p in fiber f} vals[p] * C[crd3[p], :]) over the schedule sc.
+// dense_rows = the larger number of rows of B and C.
+// Every stored slice's row is written.  gaps: the rows that are not stored are cleared too (scaled by beta), which only the
+// pieces do (mttkrp_on_pieces); otherwise the caller has done that.
 // Every comment above reads "=" as "= alpha * (...) + beta * (old value)" when an epilogue is switched on.
-hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, int64_t nslice,
-                         const int32_t *pos3, const int32_t *crd2, const int32_t *crd3, const double *vals,
-                         const double *B, const double *C, int64_t R, double *M, void *scratch, hipStream_t st,
-                         Epilogue ep = Epilogue());
+hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, const int32_t *pos3, const int32_t *crd2,
+                         const int32_t *crd3, const double *vals, const double *B, const double *C, int64_t dense_rows, int64_t R,
+                         double *M, bool gaps, void *scratch, hipStream_t st, Epilogue ep = Epilogue());
+// Whether the pieces of sc.mttkrp serve this rank; only they clear the rows that are not stored.
+bool mttkrp_on_pieces(const Schedule &sc, int64_t R);
 
 }  // namespace comet

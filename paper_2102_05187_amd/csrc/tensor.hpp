@@ -115,6 +115,19 @@ struct PiecePlan {
     uint32_t *joins() const { return pieces_mem ? pieces() + npieces : nullptr; }
 };
 
+// Plan of MTTKRP (mttkrp_plan.hpp).
+constexpr int kMtLongCut = 16;         // tiles from which on a cut slice is summed by a whole workgroup
+struct MttkrpPlan {
+    int64_t ntiles = 0, npieces = 0, nrecs = 0;
+    int     max_pieces = 0, max_items = 0;   // most pieces and nonzeros in a tile
+    int64_t ncut = 0, ncut_long = 0;   // slices cut by tile boundaries: over few tiles, over many
+    DevRef  tiles_mem, pieces_mem;
+    int4 *tiles() const { return tiles_mem ? (int4 *)tiles_mem->ptr : nullptr; }              // [ntiles + 1]
+    int4 *cuts() const { return tiles_mem ? tiles() + ntiles + 1 : nullptr; }                 // [ntiles]: the short ones in front, the long ones from the end
+    uint2 *pieces() const { return pieces_mem ? (uint2 *)pieces_mem->ptr : nullptr; }         // [npieces], longest first inside a tile
+    uint2 *recs() const { return pieces_mem ? pieces() + npieces : nullptr; }                 // [nrecs]
+};
+
 // Per-tensor schedule for the nonzero-tiled kernels, built once at creation.
 //   The leaf level's nonzeros are cut into tiles of kTile consecutive positions; seg_begin[t] is
 //   the segment (row / fiber) that contains the first nonzero of tile t (seg_begin[0] = 0 and
@@ -134,8 +147,10 @@ struct Schedule {
     int64_t empty_segments = -1;  // leaf segments without a nonzero (-1 = unknown)
     int64_t max_seg_len = 0;      // longest leaf segment, in nonzeros (0 = unknown)
     int64_t max_parent_len = 0;   // CSF3: most nonzeros under one slice (0 = unknown)
+    int64_t max_root_gap = -1;    // with a plan in `mttkrp`: longest run of absent root coordinates (-1 = unknown)
     DevRef  unstored;             // compressed root level that stores at least half of its rows: int32 list of the others
     PiecePlan pieces;
+    MttkrpPlan mttkrp;            // CSF3 of at most kMtNarrow nonzeros only
     HeavyPlan heavy;              // matrices only; nunits = 0 when the sweep does not apply
     FiberPlan fibers;             // CSF3 only; nheavy = 0 when the sweep does not apply
 };

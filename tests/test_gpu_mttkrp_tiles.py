@@ -1,5 +1,6 @@
-"""The MTTKRP walk on both tile sizes: fibers and slices that end just before, at and behind the boundaries of chunks of 1024
-nonzeros, slices over few and over many of them, every lane-group layout, and lists on either side of the size rule."""
+"""MTTKRP on its tile sizes: fibers and slices that end just before, at and behind the boundaries of chunks of 1024
+nonzeros, slices over few and over many of them, every lane-group layout, lists on either side of the size rules, and fibers
+and slices without nonzeros between the pieces' tiles."""
 import numpy as np
 import pytest
 import torch
@@ -65,3 +66,55 @@ def test_both_sides_of_the_size_rule(comet, nnz):
     if nnz - n * sum(each):
         slices = slices + [[nnz - n * sum(each)]]
     _check(comet, slices, 10)
+
+
+@pytest.mark.parametrize("R,nnz", [(8, 9 << 18), (8, (9 << 18) + 1), (33, (9 << 18) // 3), (33, (9 << 18) // 3 + 1), (6, 5 << 20), (6, (5 << 20) + 1)])
+def test_both_sides_of_the_rules_for_pieces(comet, R, nnz):
+    each = [40, 3, 1, 500, 17, 16, 1]
+    n = nnz // sum(each)
+    _check(comet, [each] * n + ([[nnz - n * sum(each)]] if nnz - n * sum(each) else []), R)
+
+
+@pytest.mark.parametrize("R", [1, 6, 16, 35])
+@pytest.mark.parametrize("stored_every", [1, 3])
+def test_fibers_and_slices_without_nonzeros(comet, R, stored_every):
+    """Runs of empty fibers and of slices without fibers, long enough to fill tiles of the pieces, at either end and between
+    nonzeros; with the rows between the stored slices cleared by gaps (1) or all together (3).  An infinite alpha must not
+    reach rows that receive nothing."""
+    g = torch.Generator().manual_seed(R)
+    slices = []
+    for n in (0, 0, 700, 1, 0, 40, 5, 0, 300, 2000, 0):
+        slices.append([0] * n)                                          # empty fibers only, or no fiber at all
+        slices.append([0] * 130 + [int(x) for x in torch.randint(0, 40, (60,), generator=g)] + [0] * (n % 200))
+        slices.append([])
+        slices += [[1], [0, 1], [1, 0]] * 25
+    slices.append([])
+    nfib = torch.tensor([len(x) for x in slices])
+    lens = torch.tensor([n for x in slices for n in x])
+    pos2 = torch.cat([torch.zeros(1, dtype=torch.int64), torch.cumsum(nfib, 0)]).int()
+    pos3 = torch.cat([torch.zeros(1, dtype=torch.int64), torch.cumsum(lens, 0)]).int()
+    crd1 = (stored_every * torch.arange(len(slices)) + stored_every - 1).int()
+    crd2 = (torch.arange(lens.numel()) - (torch.cumsum(nfib, 0) - nfib).repeat_interleave(nfib)).int()
+    fiber = torch.repeat_interleave(torch.arange(lens.numel()), lens)
+    k = (torch.arange(fiber.numel()) - (torch.cumsum(lens, 0) - lens)[fiber]).int()
+    i = crd1[torch.repeat_interleave(torch.arange(len(slices)), nfib)[fiber]]
+    dims = (stored_every * len(slices) + 4, int(nfib.max()) + 1, int(lens.max()) + 1)
+    vals = gen.dense_operand(3, 1, (fiber.numel(), 1)).reshape(-1)
+    print("mttkrp empties R=%d every=%d nnz=%d fibers=%d" % (R, stored_every, vals.numel(), lens.numel()), flush=True)
+    d = lambda t: t.to("cuda").contiguous()
+    X = comet.comet_tensor_create(dims, [comet.COMET_CU] * 3, [d(torch.tensor([0, len(slices)], dtype=torch.int32)), d(pos2), d(pos3)],
+                                  [d(crd1), d(crd2), d(k)], d(vals)).set_variant(2)
+    B, C, old = (gen.dense_operand(5, n, (e, R)) for n, e in ((0, dims[1]), (1, dims[2]), (2, dims[0])))
+    ref, absum = oracle.mttkrp(np_(i), np_(crd2[fiber]), np_(k), np_(vals), dims, np_(B), np_(C))
+    M = torch.full((dims[0], R), float("nan"), dtype=torch.float64, device="cuda")
+    comet.comet_mttkrp(X, 0, [None, d(B), d(C)], M)
+    assert_values_close(np_(M), ref, absum, "empties R=%d" % R)
+    D = old.to("cuda")
+    comet.comet_mttkrp_axpby(X, 0, 0.75, [None, d(B), d(C)], -0.5, D)
+    assert_values_close(np_(D), 0.75 * ref - 0.5 * np_(old), 0.75 * absum + 0.5 * np.abs(np_(old)), "empties axpby R=%d" % R)
+    if stored_every == 1:
+        D = old.to("cuda")
+        comet.comet_mttkrp_axpby(X, 0, float("inf"), [None, d(B), d(C)], -0.5, D)
+        none = np.ones(dims[0], dtype=bool)
+        none[np_(i)] = False
+        assert np.array_equal(np_(D)[none], -0.5 * np_(old)[none])
