@@ -1,5 +1,5 @@
 // Rank-1 kernels of the nonzero-tiled family (SpMV, TTV on CSF and on sorted coordinate lists), the
-// carry fix-up kernel shared by all of them, and the host entry points of the family.
+// carry fix-up kernels shared by all of them, and the host entry points of the family.
 #include <atomic>
 
 #include "pieces.hpp"
@@ -433,20 +433,38 @@ __global__ void __launch_bounds__(256) k_stream_rank1_coo(const int32_t *__restr
 }
 
 // ---- fix-up: finish the first segment end of every tile -------------------------------------------
-// value = first[t] + open[t-1] + open[t-2] + ... up to and including the nearest tile that contains a segment end: a thread
-// per (tile, r) walks back, eight summaries at a time (their loads do not depend on what they hold).  A chain of more than
-// kFixSerial tiles -- the head slice of a power-law tensor is cut over thousands -- is left to the whole workgroup, its tiles
-// dealt over 1024 / R threads per column.  One launch; folding 64 summaries per thread level by level took three of them, 51 us
-// for 36 600 tiles of the MTTKRP configuration at rank 16 where this takes 28.  T = 256 threads where no chain is that long (a few
-// thousand tiles at rank 1 would otherwise sit on a handful of compute units).
+// value = first[t] + open[t-1] + open[t-2] + ... up to and including the nearest tile that contains a segment end.  A thread per
+// (tile, r) walks back; for levels whose segments are cut over kShortChain tiles at most.
+constexpr int kShortChain = 24;
+__global__ void __launch_bounds__(256) k_stream_fixup(void *scratch, int64_t ntiles, int R, const int32_t *__restrict__ rowmap,
+                                                      double *__restrict__ out, Epilogue ep) {
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= ntiles * R) return;
+    const int64_t t = g / R;
+    const int r = (int)(g - t * R);
+    CarryView cb = carry_view(scratch, ntiles, R);
+    if (!cb.has_tail[t]) return;
+    double v = cb.first[t * R + r];
+    for (int64_t u = t - 1; u >= 0; --u) {
+        v += cb.open[u * R + r];
+        if (cb.has_tail[u]) break;
+    }
+    const int32_t id = cb.first_id[t];
+    const int64_t row = rowmap ? (int64_t)rowmap[id] : (int64_t)id;
+    out[row * R + r] = ep_apply(ep, v, out + row * R + r);
+}
+
+// The same for longer chains (the head slice of a power-law tensor is cut over thousands of tiles): eight summaries at a time,
+// whose loads do not depend on what they hold, and from kFixSerial tiles on the whole workgroup, the tiles dealt over 1024 / R
+// threads per column.  One launch; folding 64 summaries per thread level by level took three of them, 51 us for 36 600 tiles of
+// the MTTKRP configuration at rank 16 where this takes 28, 47 us for 4900 tiles at rank 64 where this takes 19.
 constexpr int kFixSerial = 64;
-template <int T>
-__global__ void __launch_bounds__(T) k_stream_fixup(void *scratch, int64_t ntiles, int R, const int32_t *__restrict__ rowmap,
+__global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64_t ntiles, int R, const int32_t *__restrict__ rowmap,
                                                        double *__restrict__ out, Epilogue ep) {
-    __shared__ double sums[T];
-    __shared__ int nlong, list[T], newest;
+    __shared__ double sums[1024];
+    __shared__ int nlong, list[1024], newest;
     const CarryView cb = carry_view(scratch, ntiles, R);
-    const int lanes = T / R, lane = (int)threadIdx.x / R, r = (int)threadIdx.x - lane * R;
+    const int lanes = 1024 / R, lane = (int)threadIdx.x / R, r = (int)threadIdx.x - lane * R;
     if (threadIdx.x == 0) nlong = 0;
     __syncthreads();
     auto finish = [&](int64_t t, double v) {
@@ -481,7 +499,7 @@ __global__ void __launch_bounds__(T) k_stream_fixup(void *scratch, int64_t ntile
     for (int i = 0; i < n; ++i) {
         const int64_t t = t0 + list[i];
         int64_t from = 0;                                         // the nearest tile in front of t that contains a segment end, or the first
-        for (int64_t base = t - 1; base >= 0; base -= T) {
+        for (int64_t base = t - 1; base >= 0; base -= 1024) {
             __syncthreads();
             if (threadIdx.x == 0) newest = -1;
             __syncthreads();
@@ -521,11 +539,13 @@ __global__ void __launch_bounds__(T) k_stream_fixup(void *scratch, int64_t ntile
 // Finish every segment that a tile boundary cut.  max_chain bounds the number of tiles that one of them is cut over (0: unknown).
 hipError_t run_fixup(void *scratch, int64_t ntiles, int R, const int32_t *rowmap, double *out, int64_t max_chain, hipStream_t st,
                      Epilogue ep) {
-    const bool shorter = max_chain > 0 && max_chain <= kFixSerial;
-    const int64_t per = (shorter ? 256 : 1024) / R;
-    const dim3 grid((unsigned)((ntiles + per - 1) / per));
-    if (shorter) hipLaunchKernelGGL(k_stream_fixup<256>, grid, dim3(256), 0, st, scratch, ntiles, R, rowmap, out, ep);
-    else hipLaunchKernelGGL(k_stream_fixup<1024>, grid, dim3(1024), 0, st, scratch, ntiles, R, rowmap, out, ep);
+    if (max_chain > 0 && max_chain <= kShortChain) {
+        hipLaunchKernelGGL(k_stream_fixup, dim3((unsigned)((ntiles * R + 255) / 256)), dim3(256), 0, st, scratch, ntiles, R, rowmap, out, ep);
+    } else {
+        const int64_t per = 1024 / R;
+        hipLaunchKernelGGL(k_stream_fixup_long, dim3((unsigned)((ntiles + per - 1) / per)), dim3(1024), 0, st, scratch, ntiles, R, rowmap,
+                           out, ep);
+    }
     return hipGetLastError();
 }
 
