@@ -10,6 +10,9 @@
 // nonzeros within 2000 columns of the diagonal, rank 20, added to the old result, 358 and 236 us; TTM on 8 M nonzeros in
 // 1.6 M fibers, rank 32, 180 and 172 us (the result's 415 MB and nonzeros that come from memory leave little to gain);
 // 200 000 nonzeros, rank 16, 29 and 14 us.
+// The loads of a long piece: as many as its batch has steps, none under a condition (see the loop).  Three states taking turns,
+// before and after: 3.6 M nonzeros, 12 per row near the diagonal, ranks 8 / 16 / 20 / 32 / 64 / 128, 27 / 37 / 61 / 73 / 142 / 286
+// and 24 / 31 / 48 / 61 / 134 / 250 us; 11.3 M in power-law rows near the diagonal, rank 64, 486 and 381.
 #include "pieces.hpp"
 #include "stream_common.hpp"
 
@@ -32,8 +35,11 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
                                                 double *__restrict__ out, int64_t nnz, int R, double *__restrict__ head,
                                                 double *__restrict__ tail, Epilogue ep) {
     constexpr int V = E * NL, KP = 64 / L, kRow = L * V;          // pieces side by side in a wavefront
-    constexpr int G = V <= 2 ? 4 : (V <= 4 ? 2 : 1);              // gathers of a piece in flight, next to as many being used
-    constexpr int KB = G;                                         // pieces of a group at a time, when they are short
+    // Gathers of a piece in flight, next to as many being used.  More cost wavefronts: with 6 at two values per lane, band of 12 per
+    // row, 3.6 M nonzeros, ranks 16 / 32 go from 31 / 61 us to 50 / 64; with 2 and 1 instead of 3 at four and eight values ranks 64 / 128
+    // of 11.3 M nonzeros near the diagonal and of the band take 396 and 276 instead of 381 and 250.
+    constexpr int G = V <= 2 ? 4 : 3;
+    constexpr int KB = V <= 2 ? 4 : (V <= 4 ? 2 : 1);             // pieces of a group at a time, when they are short
     extern __shared__ __attribute__((aligned(16))) char lds[];
     Item *item = reinterpret_cast<Item *>(lds);
     uint32_t *piece = reinterpret_cast<uint32_t *>(lds + lds_pieces_at(units));
@@ -80,7 +86,7 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
     for (int i = threadIdx.x; i < np; i += 256) piece[i] = pieces[(size_t)first_piece + i];
     __syncthreads();
 
-    const int k = threadIdx.x % L, gw = (threadIdx.x & 63) / L, wave = threadIdx.x >> 6;
+    const int k = threadIdx.x % L, gw = (threadIdx.x & 63) / L, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const RowOf<L, E, NL, FULL> rw(R, k);
     const char *base = reinterpret_cast<const char *>(Dn);
     const Item *items = item + lead;
@@ -95,28 +101,37 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
     // Longest pieces first: batches of one piece per group until the longest piece of a batch is short.
     int b = wave * KP;
     for (; b < np; b += 4 * KP) {
-        const int longest = piece_len(piece[b]);
+        const int longest = __builtin_amdgcn_readfirstlane(piece_len(piece[b]));
         if (longest <= 2 * G) break;
         const bool mine = b + gw < np;
         const uint32_t pd = piece[mine ? b + gw : b];
         const int len = mine ? piece_len(pd) : 0;
-        const int shortest = b + KP <= np ? piece_len(piece[b + KP - 1]) : 0;
+        const int shortest = b + KP <= np ? __builtin_amdgcn_readfirstlane(piece_len(piece[b + KP - 1])) : 0;
         const int r = result_row(pd);
         const Item *it = items + piece_start(pd);
         const int last = len > 0 ? len - 1 : 0;
-        double acc[V], row[2][G][V], val[2][G];
+        const int full = longest / G, left = longest - full * G;
+        double acc[V], row[2][G][V], val[2][G], rrow[G][V], rval[G];
 #pragma unroll
         for (int q = 0; q < V; ++q) acc[q] = 0.0;
-        auto issue = [&](int j, double (*d)[V], double *v) {
+        // the nonzeros that fill no group of G: first in the queue of loads, last in the sum
+#pragma unroll
+        for (int u = 0; u < G - 1; ++u)
+            if (u < left) {
+                const Item x = it[full * G + u < last ? full * G + u : last];
+                rval[u] = x.val;
+                rw.template load<BIG>(base, x.off, rrow[u]);
+            }
+        auto issue = [&](int g, double (*d)[V], double *v) {
 #pragma unroll
             for (int u = 0; u < G; ++u) {
-                const Item x = it[j + u < last ? j + u : last];
+                const Item x = it[g * G + u < last ? g * G + u : last];
                 v[u] = x.val;
                 rw.template load<BIG>(base, x.off, d[u]);
             }
         };
-        auto consume = [&](int j, const double (*d)[V], const double *v) {
-            if (j + G <= shortest) {
+        auto consume = [&](int g, const double (*d)[V], const double *v) {
+            if (g * G + G <= shortest) {
 #pragma unroll
                 for (int u = 0; u < G; ++u)
 #pragma unroll
@@ -124,24 +139,40 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
             } else {
 #pragma unroll
                 for (int u = 0; u < G; ++u)
-                    if (j + u < len) {
+                    if (g * G + u < len) {
 #pragma unroll
                         for (int q = 0; q < V; ++q) acc[q] = fma(v[u], d[u][q], acc[q]);
                     }
             }
         };
+        // a group is in flight while the one before it is used; none of these loads is under a condition, which would make
+        // the wait for a group cover the next one too
         issue(0, row[0], val[0]);
-        for (int j = 0; j < longest; j += 2 * G) {
-            issue(j + G, row[1], val[1]);
-            consume(j, row[0], val[0]);
-            issue(j + 2 * G, row[0], val[0]);
-            consume(j + G, row[1], val[1]);
+        int g = 0;
+        for (; g + 2 < full; g += 2) {
+            issue(g + 1, row[1], val[1]);
+            consume(g, row[0], val[0]);
+            issue(g + 2, row[0], val[0]);
+            consume(g + 1, row[1], val[1]);
         }
+        if (g + 1 < full) {
+            issue(g + 1, row[1], val[1]);
+            consume(g, row[0], val[0]);
+            consume(g + 1, row[1], val[1]);
+        } else {
+            consume(g, row[0], val[0]);
+        }
+#pragma unroll
+        for (int u = 0; u < G - 1; ++u)
+            if (u < left && full * G + u < len) {
+#pragma unroll
+                for (int q = 0; q < V; ++q) acc[q] = fma(rval[u], rrow[u][q], acc[q]);
+            }
         if (mine) finish(pd, r, acc);
     }
     // Short pieces: KB of them per group at the same time.
     for (; b < np; b += 4 * KP * KB) {
-        const int longest = piece_len(piece[b]);
+        const int longest = __builtin_amdgcn_readfirstlane(piece_len(piece[b]));
         uint32_t pd[KB];
         int len[KB], r[KB];
         double acc[KB][V];
