@@ -197,7 +197,8 @@ comet_status comet_tensor_convert(const comet_tensor *X, const int32_t *mode_ord
 comet_status comet_spmv(const comet_tensor *A, const double *x, double *y, void *stream);
 
 /* SpMV for callers that cannot allocate device memory: code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc.  Same result as comet_spmv (the same kernels run), but the
+ * loops, harnesses that forbid hipMalloc.  Same result as comet_spmv (the same kernels run, but for matrices whose long rows
+ * comet_spmv takes from a sweep over a vector of 655 360 and more entries: there the sums are formed in another order), but the
  * kernels' carry scratch is a static device array of COMET_STATIC_SCRATCH_BYTES inside the library
  * (one copy per GPU, held until the process ends) instead of memory owned by the handle, and the call
  * makes no hipMalloc / hipFree or other allocating call.

@@ -234,6 +234,14 @@ void note_stream(const comet_tensor *t, hipStream_t st) {
 constexpr int64_t kShortSegment = 256;
 constexpr int64_t kSmallProblemNnz = int64_t(4) << 20;
 
+// SpMV: the sweep over the long rows copies the vector into the LDS of every compute unit of an XCD once, which their nonzeros have
+// to earn.  Whole calls without and with it, power-law matrices: 1 M columns, 13.8 / 10.3 / 9.6 / 6.7 / 6.1 M nonzeros in long rows,
+// 194 / 160 / 149 / 118 / 119 and 145 / 135 / 131 / 114 / 125 us; 900 000, 8.7 M, 126 and 113; 800 000, 11.1 M, 131 and 117;
+// 700 000, 14.2 M, 138 and 118; 600 000 (most of the vector stays in an L2), 8.5 M, 90 and 89; 400 000, 5.5 M, 55 and 70.
+bool long_vector_sweep_pays(const comet_tensor *A) {
+    return A->dims[1] >= (int64_t(5) << 17) && A->sched.heavy.heavy_nnz >= 4 * A->dims[1] + (int64_t(4) << 20);
+}
+
 // Clearing only the rows that are not stored beats clearing the whole dense result when most rows are stored.
 hipError_t clear_unstored_rows(const comet_tensor *t, int64_t R, double *out, double beta, hipStream_t st) {
     return comet::clear_rows((const int32_t *)t->sched.unstored->ptr, t->dims[0] - t->crd_len[0], R, out, st, beta);
@@ -757,7 +765,8 @@ static comet_status matrix_product(const comet_tensor *A, const double *Dn, int6
     // The heavy-row sweep pays when the dense operand is much larger than the L2 caches (else its rows are
     // cache hits anyway) and the long rows hold a good share of the nonzeros (decided when the plan was built).
     const bool heavy = tiled && !ext_scratch && A->variant != 3 && A->sched.heavy.nunits > 0 &&
-                       A->dims[1] * R * 8 >= (int64_t(16) << 20) && R <= 64 && comet::heavy_supports(A->sched.heavy, R) &&
+                       (R == 1 ? long_vector_sweep_pays(A)
+                               : A->dims[1] * R * 8 >= (int64_t(16) << 20) && R <= 64 && comet::heavy_supports(A->sched.heavy, R)) &&
                        (!A->light || comet::segreduce_supports(A->light->sched, R));
     const size_t need = carry + (heavy ? comet::heavy_partial_bytes(A->sched.heavy, R) : 0);
     if (ext_scratch && need > ext_bytes) return COMET_ERR_UNSUPPORTED;       // before anything is enqueued
@@ -796,7 +805,8 @@ static comet_status matrix_product(const comet_tensor *A, const double *Dn, int6
                 HIP_TRY(comet::stream_segreduce(Lh->sched, Lh->pos_i(1), Lh->crd_i(1), Lh->vals_d(), Lh->crd_i(0), Dn,
                                                 A->dims[1], R, out, Lh->scratch->ptr, false, st, ep));
             }
-            HIP_TRY(comet::heavy_spmm(A->sched.heavy, rowmap, Dn, R, out, (char *)scr + carry, st, ep));
+            if (R == 1) HIP_TRY(comet::heavy_spmv(A->sched.heavy, rowmap, Dn, A->dims[1], out, (char *)scr + carry, st, ep));
+            else HIP_TRY(comet::heavy_spmm(A->sched.heavy, rowmap, Dn, R, out, (char *)scr + carry, st, ep));
             return COMET_OK;
         }
         HIP_TRY(comet::stream_segreduce(A->sched, A->pos_i(1), A->crd_i(1), A->vals_d(), rowmap, Dn, A->dims[1], R, out,

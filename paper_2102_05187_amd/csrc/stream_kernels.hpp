@@ -52,6 +52,10 @@ size_t heavy_partial_bytes(const HeavyPlan &plan, int64_t R);
 hipError_t heavy_spmm(const HeavyPlan &plan, const int32_t *rowmap, const double *Dn, int64_t R, double *out, void *partial,
                       hipStream_t st, Epilogue ep = Epilogue());
 
+// The same for one column; `partial` holds heavy_partial_bytes(plan, 1).
+hipError_t heavy_spmv(const HeavyPlan &plan, const int32_t *rowmap, const double *x, int64_t ncols, double *out, void *partial,
+                      hipStream_t st, Epilogue ep = Epilogue());
+
 // ---- heavy-fiber sweep of TTM (kernels_heavy.hip) --------------------------------------------------
 // Builds the plan for the leaf level of a [CU,CU,CU] tensor (pos over nseg fibers, crd with coordinates < ncols);
 // leaves plan.nheavy = 0 when the operand rows do not fit a few LDS windows or the long fibers hold too small a

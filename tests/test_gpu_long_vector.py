@@ -1,0 +1,68 @@
+"""SpMV with the sweep over long rows: long vectors on either side of the rule, an odd number of columns (the last interval of the
+vector is ragged), rows around the sweep's length, rows cut into several units, pieces of one nonzero and of many, empty rows."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from synth import formats as fmt
+from synth import generate as gen
+from util import assert_values_close, np_
+
+pytestmark = pytest.mark.gpu
+
+MIN_COLS = 5 << 17
+MIN_NNZ = 4 * MIN_COLS + (4 << 20)          # nonzeros in rows of 128 and more from which on the sweep runs at that many columns
+
+
+@pytest.fixture(scope="module")
+def comet():
+    from paper_2102_05187_amd import build
+    build.build_if_missing()
+    import paper_2102_05187_amd as c
+    return c
+
+
+def _matrix(ncols, clustered, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    lens = torch.cat([torch.tensor([0, 127, 128, 129, 4095, 4096, 4097, 8193, 60_000, 0, 1]), torch.randint(0, 127, (30_000,)),
+                      torch.full((MIN_NNZ // 900 + 50,), 900), torch.tensor([0, 5, 0])]).cuda()
+    rows = torch.repeat_interleave(lens)
+    # distinct columns of a row: its nonzeros in equal strides from a random start; clustered rows lie in a sixteenth of the columns
+    k = torch.arange(rows.numel(), device="cuda") - (torch.cumsum(lens, 0) - lens)[rows]
+    width = torch.full_like(lens, ncols)
+    if clustered:
+        width[torch.rand(lens.numel(), device="cuda", generator=g) < 0.05] = ncols // 8
+    start = (torch.rand(lens.numel(), device="cuda", generator=g, dtype=torch.float64) * ncols).long()
+    cols = (start[rows] + k * (width // lens.clamp(min=1))[rows]) % ncols
+    keys = torch.sort(rows * ncols + cols).values
+    rows, cols = torch.div(keys, ncols, rounding_mode="floor"), keys % ncols
+    vals = torch.rand(rows.numel(), dtype=torch.float64, device="cuda", generator=g) * 2 - 1
+    return lens.numel(), rows.int(), cols.int(), vals
+
+
+@pytest.mark.parametrize("layout", ["csr", "dcsr"])
+@pytest.mark.parametrize("ncols,clustered", [(MIN_COLS, False), (MIN_COLS - 1, False), (700_001, True), (MIN_COLS + 4099, False)])
+def test_sweep_against_the_oracle(comet, layout, ncols, clustered):
+    n, rows, cols, vals = _matrix(ncols, clustered, ncols)
+    A = comet.from_levels((fmt.pack_csr if layout == "csr" else fmt.pack_dcsr)(n, ncols, rows, cols, vals))
+    print("spmv sweep %s ncols=%d nnz=%d heavy=%s" % (layout, ncols, vals.numel(), A.heavy_plan()), flush=True)
+    assert A.heavy_plan()[1] >= MIN_NNZ
+    x = gen.dense_operand(3, 0, (ncols, 1)).reshape(-1)
+    old = gen.dense_operand(4, 0, (n, 1)).reshape(-1)
+    ref, absum = oracle.spmv(np_(rows), np_(cols), np_(vals), (n, ncols), np_(x))
+    y = torch.full((n,), float("nan"), dtype=torch.float64, device="cuda")
+    comet.comet_spmv(A, x.cuda(), y)
+    assert_values_close(np_(y), ref, absum, "spmv sweep")
+    for _ in range(3):
+        assert torch.equal(y, comet.comet_spmv(A, x.cuda())), "two runs differ"
+    z = old.cuda()
+    comet.comet_spmv_axpby(A, 0.75, x.cuda(), -0.5, z)
+    assert_values_close(np_(z), 0.75 * ref - 0.5 * np_(old), 0.75 * absum + 0.5 * np.abs(np_(old)), "spmv sweep axpby")
+    # a value that no nonzero reads must not reach the result, wherever the kernels touch the vector
+    unused = torch.ones(ncols, dtype=torch.bool, device="cuda")
+    unused[cols.long()] = False
+    w = x.cuda()
+    w[unused] = float("nan")
+    w[0] = x[0] if not bool(unused[0]) else float("inf")
+    assert torch.equal(y, comet.comet_spmv(A, w))
