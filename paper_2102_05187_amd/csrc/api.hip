@@ -1034,7 +1034,8 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
     // Rows of M whose index is not stored at the root level receive no contribution.  The tiled kernels write every stored
     // slice's row themselves, so when most rows are stored only the gaps between them are cleared (by the kernel over pieces
     // itself); otherwise all of M is.
-    const bool gaps = tiled && comet::mttkrp_on_pieces(X->sched, R) && gaps_are_short(X, R);
+    const int64_t dense_rows = X->dims[1] > X->dims[2] ? X->dims[1] : X->dims[2];
+    const bool gaps = tiled && comet::mttkrp_on_pieces(X->sched, dense_rows, R) && gaps_are_short(X, R);
     if (tiled && !gaps && X->sched.unstored) {
         HIP_TRY(clear_unstored_rows(X, R, M, ep.on ? ep.beta : 0.0, st));
     } else if (!gaps) {
@@ -1047,7 +1048,7 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
         comet_status rs = ensure_scratch(X, comet::mttkrp_scratch_bytes(X->sched, R));
         if (rs != COMET_OK) return rs;
         HIP_TRY(comet::stream_mttkrp(X->sched, X->pos_i(1), X->crd_i(0), X->pos_i(2), X->crd_i(1), X->crd_i(2), X->vals_d(), B, C,
-                                     X->dims[1] > X->dims[2] ? X->dims[1] : X->dims[2], R, M, gaps, X->scratch->ptr, st, ep));
+                                     dense_rows, R, M, gaps, X->scratch->ptr, st, ep));
         return COMET_OK;
     }
     HIP_TRY(comet::simple_mttkrp(X->pos_i(1), X->crd_i(0), X->pos_len[1] - 1, X->pos_i(2), X->crd_i(1), X->crd_i(2),

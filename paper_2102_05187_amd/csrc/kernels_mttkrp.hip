@@ -460,7 +460,10 @@ hipError_t launch_walk(const MtArgs &a, const Schedule &sc, void *scratch) {
 
 }  // namespace
 
-bool mttkrp_on_pieces(const Schedule &sc, int64_t R) { return sc.mttkrp.ntiles > 0 && mttkrp_takes_pieces(sc.nnz, R); }
+bool mttkrp_on_pieces(const Schedule &sc, int64_t dense_rows, int64_t R) {
+    // row offsets of the pieces are 32-bit counts of doubles; the walk forms 64-bit addresses
+    return sc.mttkrp.ntiles > 0 && mttkrp_takes_pieces(sc.nnz, R) && dense_rows * R < (int64_t(1) << 32);
+}
 
 size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R) {
     // ranks below R may take the pieces where R does not
@@ -477,7 +480,7 @@ hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t 
     const MttkrpPlan &plan = sc.mttkrp;
     double *head = (double *)scratch, *tail = head + plan.ntiles * R;
     const MtArgs a{plan, pos2, crd1, pos3, crd2, crd3, vals, B, C, M, sc.nnz, (int)R, gaps ? 1 : 0, head, tail, st, ep};
-    if (mttkrp_on_pieces(sc, R)) {
+    if (mttkrp_on_pieces(sc, dense_rows, R)) {
         const bool wide = dense_rows * R * 8 >= (int64_t(1) << 32);   // row offsets in bytes no longer fit 32 bits
         const hipError_t e = COMET_DISPATCH_BLOCKS(launch_mttkrp, a.R, wide, a);
         if (e != hipSuccess || plan.ncut + plan.ncut_long == 0) return e;

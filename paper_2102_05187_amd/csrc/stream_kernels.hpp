@@ -80,7 +80,7 @@ int current_device_cu_count();
 hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, const int32_t *pos3, const int32_t *crd2,
                          const int32_t *crd3, const double *vals, const double *B, const double *C, int64_t dense_rows, int64_t R,
                          double *M, bool gaps, void *scratch, hipStream_t st, Epilogue ep = Epilogue());
-// Whether the pieces of sc.mttkrp serve this rank; only they clear the rows that are not stored.
-bool mttkrp_on_pieces(const Schedule &sc, int64_t R);
+// Whether the pieces of sc.mttkrp serve this rank and factors of up to dense_rows rows; only they clear the rows that are not stored.
+bool mttkrp_on_pieces(const Schedule &sc, int64_t dense_rows, int64_t R);
 
 }  // namespace comet

@@ -118,3 +118,33 @@ def test_fibers_and_slices_without_nonzeros(comet, R, stored_every):
         none = np.ones(dims[0], dtype=bool)
         none[np_(i)] = False
         assert np.array_equal(np_(D)[none], -0.5 * np_(old)[none])
+
+
+@pytest.mark.parametrize("values", [1 << 29, 1 << 32])
+@pytest.mark.parametrize("level", [1, 2])
+@pytest.mark.parametrize("R", [4, 5])
+def test_factors_whose_offsets_leave_32_bits(comet, R, level, values):
+    """A factor just above 2^29 values (row offsets in bytes) and 2^32 values (in doubles), its first and last rows among
+    those that are read."""
+    wide = values // R + 3
+    dims = (50, 7, 9)
+    g = torch.Generator().manual_seed(R)
+    i, j, k = torch.meshgrid(torch.arange(dims[0]), torch.arange(dims[1]), torch.arange(dims[2]), indexing="ij")
+    keep = torch.rand(i.shape, generator=g) < 0.6
+    i, j, k = (x[keep].int() for x in (i, j, k))
+    vals = torch.rand(i.numel(), dtype=torch.float64, generator=g) * 2 - 1
+    spread = torch.linspace(0, wide - 1, dims[level], dtype=torch.float64).long()        # where the coordinates of the level go
+    spread[-1] = wide - 1
+    far = spread[(j if level == 1 else k).long()].int()
+    tdims = (dims[0], wide, dims[2]) if level == 1 else (dims[0], dims[1], wide)
+    X = comet.from_levels(fmt.pack_csf3(tdims, i, far if level == 1 else j, far if level == 2 else k, vals).to("cuda")).set_variant(2)
+    small = [gen.dense_operand(5, n, (d, R)) for n, d in ((0, dims[1]), (1, dims[2]))]
+    F = torch.empty((wide, R), dtype=torch.float64, device="cuda")
+    F[spread.cuda()] = small[level - 1].cuda()
+    BC = [s.cuda() for s in small]
+    BC[level - 1] = F
+    print("mttkrp wide factor R=%d level=%d rows=%d nnz=%d" % (R, level, wide, vals.numel()), flush=True)
+    M = torch.full((dims[0], R), float("nan"), dtype=torch.float64, device="cuda")
+    comet.comet_mttkrp(X, 0, [None] + BC, M)
+    ref, absum = oracle.mttkrp(np_(i), np_(j), np_(k), np_(vals), dims, np_(small[0]), np_(small[1]))
+    assert_values_close(np_(M), ref, absum, "wide factor R=%d level=%d" % (R, level))
