@@ -124,10 +124,10 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st) {
             if (ppe == hipErrorOutOfMemory) { (void)hipGetLastError(); ppe = hipSuccess; }
             HIP_TRY(ppe);
         }
+        // (optional too: without the memory for the list the whole result is cleared)
         if (t.levels[0] == COMET_CU && t.crd_len[0] * 2 >= t.dims[0]) {
             sc.unstored = comet::dev_alloc(sizeof(int32_t) * (t.dims[0] - t.crd_len[0]));
-            if (!sc.unstored) return COMET_ERR_ALLOC;
-            HIP_TRY(comet::list_unstored_rows(t.crd_i(0), t.crd_len[0], t.dims[0], (int32_t *)sc.unstored->ptr, st));
+            if (sc.unstored) HIP_TRY(comet::list_unstored_rows(t.crd_i(0), t.crd_len[0], t.dims[0], (int32_t *)sc.unstored->ptr, st));
         }
         if (sc.mttkrp.ntiles > 0) {
             HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
