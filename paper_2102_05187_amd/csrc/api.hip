@@ -124,9 +124,14 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st) {
             if (ppe == hipErrorOutOfMemory) { (void)hipGetLastError(); ppe = hipSuccess; }
             HIP_TRY(ppe);
         }
-        // (optional too: without the memory for the list the whole result is cleared)
-        if (t.levels[0] == COMET_CU && t.crd_len[0] * 2 >= t.dims[0]) {
-            sc.unstored = comet::dev_alloc(sizeof(int32_t) * (t.dims[0] - t.crd_len[0]));
+        // (optional too: without the memory for the list the whole result is cleared, and so it is where the stored rows do not
+        // increase, which only the validating checks refuse)
+        if (t.levels[0] == COMET_CU && t.crd_len[0] <= t.dims[0] && t.crd_len[0] * 2 >= t.dims[0]) {
+            HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
+            HIP_TRY(comet::check_cu_sorted(t.pos_i(0), 1, t.crd_i(0), t.crd_len[0], (int32_t *)mx->ptr, st));
+            rs = read_i32((const int32_t *)mx->ptr, 1, &h, st);
+            if (rs != COMET_OK) return rs;
+            if (h == 0) sc.unstored = comet::dev_alloc(sizeof(int32_t) * (t.dims[0] - t.crd_len[0]));
             if (sc.unstored) HIP_TRY(comet::list_unstored_rows(t.crd_i(0), t.crd_len[0], t.dims[0], (int32_t *)sc.unstored->ptr, st));
         }
         if (sc.mttkrp.ntiles > 0) {

@@ -29,6 +29,16 @@ hipError_t fill_zero_f64(double *p, int64_t n, hipStream_t st);
 hipError_t scale_f64(double *p, int64_t n, double beta, hipStream_t st);
 // rows = the rows of [0, nrows) that do not occur in the sorted, duplicate-free list idx[0..n): nrows - n of them.
 hipError_t list_unstored_rows(const int32_t *idx, int64_t n, int64_t nrows, int32_t *rows, hipStream_t st);
+// Where row r goes in that list; -1 if it is stored.  Inside [0, nrows - n) or -1 whatever idx holds.
+__host__ __device__ inline int64_t unstored_place(const int32_t *idx, int64_t n, int64_t nrows, int64_t r) {
+    int64_t lo = 0, hi = n;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if ((int64_t)idx[mid] < r) lo = mid + 1; else hi = mid;
+    }
+    if (lo < n && (int64_t)idx[lo] == r) return -1;
+    return r >= lo && r - lo < nrows - n ? r - lo : -1;
+}
 // out[r, :] = 0 for the listed rows; beta != 0: they are multiplied by beta instead.
 hipError_t clear_rows(const int32_t *rows, int64_t nrows, int64_t R, double *out, hipStream_t st, double beta = 0.0);
 

@@ -120,18 +120,16 @@ __global__ void __launch_bounds__(256) k_mt_fill(const int32_t *__restrict__ pos
             hi = hi < lo ? lo : (hi > nf ? nf : hi);
             const int r0 = before[lo], n = before[hi] - r0, row = crd1[s];
             const bool cn = cont && q == 0, op = q == nend;
-            int64_t gap = op ? 0 : (int64_t)row - (s > 0 ? crd1[s - 1] : -1) - 1;
-            if (gap > 65535) gap = 65535;
-            if (!cn && !op && n <= kMtSum) { sum(mt_sum(r0, n, kMtSlice, (int)gap), row); continue; }
-            if (gap > 0) sum(mt_sum(0, 0, kMtGap, (int)gap), row);
+            const int gap = op ? 0 : mt_gap(s > 0 ? crd1[s - 1] : -1, row);
+            if (!cn && !op && n <= kMtSum) { sum(mt_sum(r0, n, kMtSlice, gap), row); continue; }
+            if (gap > 0) sum(mt_sum(0, 0, kMtGap, gap), row);
             for (int c = 0; c < n; c += kMtSum)
                 if (n - c > 1) sum(mt_sum(r0 + c, n - c < kMtSum ? n - c : kMtSum, kMtPart, 0), row);
             join(mt_join(r0, n, cn, op), row);
         }
         if (threadIdx.x == 0 && t == ntiles - 1) {             // rows of M behind the last stored one
-            int64_t gap = dim0 - 1 - crd1[nslice - 1];
-            if (gap > 65535) gap = 65535;
-            if (gap > 0) sum(mt_sum(0, 0, kMtGap, (int)gap), (int)dim0);
+            const int gap = mt_gap(crd1[nslice - 1], dim0);
+            if (gap > 0) sum(mt_sum(0, 0, kMtGap, gap), (int)dim0);
         }
     };
     each([&](unsigned, int) { atomicAdd(&nsum, 1); }, [&](unsigned, int) { atomicAdd(&njoin, 1); });

@@ -61,6 +61,11 @@ __host__ __device__ inline unsigned mt_sum(int first, int rows, int kind, int ga
 __device__ __forceinline__ int mt_sum_rows(unsigned r) { return (int)((r >> 9) & 31u); }
 __device__ __forceinline__ int mt_sum_kind(unsigned r) { return (int)((r >> 14) & 3u); }
 __device__ __forceinline__ int mt_sum_gap(unsigned r) { return (int)(r >> 16); }
+// Rows of M between two stored ones (from = -1: in front of the first); none where the coordinates do not increase.
+__host__ __device__ inline int mt_gap(int64_t from, int64_t to) {
+    const int64_t gap = to - from - 1;
+    return gap < 0 ? 0 : (gap > 65535 ? 65535 : (int)gap);
+}
 // Then the joins: first row (9 bits), rows (9), whether the slice began in front of the tile, whether it goes on behind it.
 __host__ __device__ inline unsigned mt_join(int first, int rows, bool cont, bool open) {
     return (unsigned)first | ((unsigned)rows << 9) | (cont ? 1u << 18 : 0u) | (open ? 1u << 19 : 0u);

@@ -303,13 +303,8 @@ hipError_t count_empty_segments(const int32_t *pos, int64_t nseg, int32_t *out_c
 __global__ void __launch_bounds__(256) k_list_unstored(const int32_t *__restrict__ idx, int64_t n, int64_t nrows, int32_t *__restrict__ rows) {
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (r >= nrows) return;
-    int64_t lo = 0, hi = n;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if ((int64_t)idx[mid] < r) lo = mid + 1; else hi = mid;
-    }
-    // (a list that is not sorted, which only the validating checks refuse, must not lead out of the array)
-    if ((lo == n || (int64_t)idx[lo] != r) && r - lo < nrows - n) rows[r - lo] = (int32_t)r;
+    const int64_t place = unstored_place(idx, n, nrows, r);
+    if (place >= 0) rows[place] = (int32_t)r;
 }
 
 hipError_t list_unstored_rows(const int32_t *idx, int64_t n, int64_t nrows, int32_t *rows, hipStream_t st) {
