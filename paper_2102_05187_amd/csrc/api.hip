@@ -115,7 +115,7 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st) {
         if (rs != COMET_OK) return rs;
         sc.empty_segments = h;
         // optional, like the plans of the sweeps below: without the memory for it, what would run on it takes the simple kernels
-        hipError_t ppe = comet::piece_plan_build(t.pos_i(leaf), sc.nseg, sc.nnz, sc.pieces, st);
+        hipError_t ppe = comet::piece_plan_build(t.pos_i(leaf), sc.nseg, t.crd_i(leaf), sc.nnz, sc.pieces, st);
         if (ppe == hipErrorOutOfMemory) { (void)hipGetLastError(); ppe = hipSuccess; }
         HIP_TRY(ppe);
         if (t.fmt == Format::CSF3 && sc.nnz <= comet::kMtNarrow) {

@@ -10,9 +10,12 @@
 // nonzeros within 2000 columns of the diagonal, rank 20, added to the old result, 358 and 236 us; TTM on 8 M nonzeros in
 // 1.6 M fibers, rank 32, 180 and 172 us (the result's 415 MB and nonzeros that come from memory leave little to gain);
 // 200 000 nonzeros, rank 16, 29 and 14 us.
-// The loads of a long piece: as many as its batch has steps, none under a condition (see the loop).  Three states taking turns,
-// before and after: 3.6 M nonzeros, 12 per row near the diagonal, ranks 8 / 16 / 20 / 32 / 64 / 128, 27 / 37 / 61 / 73 / 142 / 286
-// and 24 / 31 / 48 / 61 / 134 / 250 us; 11.3 M in power-law rows near the diagonal, rank 64, 486 and 381.
+// The loads of a long piece.  Where a part of the list comes back to the same operand rows, as many as its batch has steps:
+// 3.6 M nonzeros, 12 per row near the diagonal, three states taking turns, ranks 20 / 32 / 128, 59 / 75 / 260 us, and 72 / 86 / 292
+// with up to eight loads behind its end; 9 M, nine per row, rank 32, 210 and 260; 11.3 M in power-law rows, rank 64, 367 and 402.
+// Where almost every row is a new one from memory it is the other way round: nine nonzeros per row at random, 7.2 M, ranks 10 / 32,
+// 198 and 192, 296 and 280 us; 1 to 120 per row, rank 64, 531 and 519.  The loads behind the end read the piece's last row again;
+// other rows there, fewer wavefronts or fewer loads in flight do not give the same, and why it does was not found (spread_rows).
 #include "pieces.hpp"
 #include "stream_common.hpp"
 
@@ -26,10 +29,10 @@ struct Item { unsigned off, pad; double val; };                   // a nonzero: 
 __host__ __device__ inline int lds_pieces_at(int units) { return (tile_items(units) + 7) * (int)sizeof(Item); }
 __host__ __device__ inline int lds_parts_at(int units) { return lds_pieces_at(units) + ((tile_pieces(units) + 3) & ~3) * 4; }
 
-// stream: the nonzeros are read around the caches (kStreamNnz)
+// stream: the nonzeros are read around the caches (kStreamNnz); spread: spread_rows
 template <int L, int E, int NL, bool FULL, bool BIG, bool ROWMAP>
 __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, const uint32_t *__restrict__ pieces,
-                                                const uint32_t *__restrict__ joins, int units, int stream,
+                                                const uint32_t *__restrict__ joins, int units, int stream, int spread,
                                                 const int32_t *__restrict__ crd, const double *__restrict__ vals,
                                                 const int32_t *__restrict__ rowmap, const double *__restrict__ Dn,
                                                 double *__restrict__ out, int64_t nnz, int R, double *__restrict__ head,
@@ -86,7 +89,7 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
     for (int i = threadIdx.x; i < np; i += 256) piece[i] = pieces[(size_t)first_piece + i];
     __syncthreads();
 
-    const int k = threadIdx.x % L, gw = (threadIdx.x & 63) / L, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int k = threadIdx.x % L, gw = (threadIdx.x & 63) / L, wave = threadIdx.x >> 6;
     const RowOf<L, E, NL, FULL> rw(R, k);
     const char *base = reinterpret_cast<const char *>(Dn);
     const Item *items = item + lead;
@@ -110,18 +113,31 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
         const int r = result_row(pd);
         const Item *it = items + piece_start(pd);
         const int last = len > 0 ? len - 1 : 0;
-        const int full = longest / G, left = longest - full * G;
+        // Groups of loads, and the nonzeros that fill none: wide rows have them first in the queue of loads, narrow ones, whose
+        // kernels would lose a wavefront per SIMD to the registers that costs, last.
+        constexpr bool kEarly = V > 2;
+        const int full = spread ? 2 * ((longest + 2 * G - 1) / (2 * G)) + 1 : longest / G, left = spread ? 0 : longest - full * G;
         double acc[V], row[2][G][V], val[2][G], rrow[G][V], rval[G];
 #pragma unroll
         for (int q = 0; q < V; ++q) acc[q] = 0.0;
-        // the nonzeros that fill no group of G: first in the queue of loads, last in the sum
+        auto issue_left = [&](double (*d)[V], double *v) {
 #pragma unroll
-        for (int u = 0; u < G - 1; ++u)
-            if (u < left) {
-                const Item x = it[full * G + u < last ? full * G + u : last];
-                rval[u] = x.val;
-                rw.template load<BIG>(base, x.off, rrow[u]);
-            }
+            for (int u = 0; u < G - 1; ++u)
+                if (u < left) {
+                    const Item x = it[full * G + u < last ? full * G + u : last];
+                    v[u] = x.val;
+                    rw.template load<BIG>(base, x.off, d[u]);
+                }
+        };
+        auto consume_left = [&](const double (*d)[V], const double *v) {
+#pragma unroll
+            for (int u = 0; u < G - 1; ++u)
+                if (u < left && full * G + u < len) {
+#pragma unroll
+                    for (int q = 0; q < V; ++q) acc[q] = fma(v[u], d[u][q], acc[q]);
+                }
+        };
+        if constexpr (kEarly) issue_left(rrow, rval);
         auto issue = [&](int g, double (*d)[V], double *v) {
 #pragma unroll
             for (int u = 0; u < G; ++u) {
@@ -158,21 +174,20 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
         if (g + 1 < full) {
             issue(g + 1, row[1], val[1]);
             consume(g, row[0], val[0]);
+            if constexpr (!kEarly) issue_left(row[0], val[0]);
             consume(g + 1, row[1], val[1]);
+            if constexpr (!kEarly) consume_left(row[0], val[0]);
         } else {
+            if constexpr (!kEarly) issue_left(row[1], val[1]);
             consume(g, row[0], val[0]);
+            if constexpr (!kEarly) consume_left(row[1], val[1]);
         }
-#pragma unroll
-        for (int u = 0; u < G - 1; ++u)
-            if (u < left && full * G + u < len) {
-#pragma unroll
-                for (int q = 0; q < V; ++q) acc[q] = fma(rval[u], rrow[u][q], acc[q]);
-            }
+        if constexpr (kEarly) consume_left(rrow, rval);
         if (mine) finish(pd, r, acc);
     }
     // Short pieces: KB of them per group at the same time.
     for (; b < np; b += 4 * KP * KB) {
-        const int longest = __builtin_amdgcn_readfirstlane(piece_len(piece[b]));
+        const int longest = piece_len(piece[b]);
         uint32_t pd[KB];
         int len[KB], r[KB];
         double acc[KB][V];
@@ -281,7 +296,7 @@ struct PieceArgs {
     const double *Dn;
     double *out;
     int64_t nnz;
-    int R;
+    int R, spread;
     double *head, *tail;
     hipStream_t st;
     Epilogue ep;
@@ -293,7 +308,7 @@ hipError_t launch_pieces(const PieceArgs &a) {
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)a.plan.ntiles), dim3(256), (unsigned)lds, a.st, (const int4 *)a.plan.tiles(),
                            (const uint32_t *)a.plan.pieces(), (const uint32_t *)a.plan.joins(), a.plan.units, a.plan.units == kUnitsLarge,
-                           a.crd, a.vals, a.rowmap, a.Dn, a.out, a.nnz, a.R, a.head, a.tail, a.ep);
+                           a.spread, a.crd, a.vals, a.rowmap, a.Dn, a.out, a.nnz, a.R, a.head, a.tail, a.ep);
     };
     if (lds > 64 * 1024) {
         static const hipError_t allowed[2] = {
@@ -305,6 +320,16 @@ hipError_t launch_pieces(const PieceArgs &a) {
     return hipGetLastError();
 }
 
+// Whether a part of the list as long as an XCD works on at a time reads more of the operand than its L2 gives back, so that most
+// rows come from behind it; in whole lines of 128 bytes.  With the loads behind the pieces' ends and without: nine nonzeros per row
+// at random, rank 32, 100 000 columns (24 MB by this count) 37.7 and 36.5 us, 150 000 (32 MB) 53.3 and 54.0, 300 000 105 and 110;
+// rank 10, 300 000 (35 MB) 68.9 and 69.0, 500 000 118 and 120; 1 M columns, rank 32, at most 20 000 from the diagonal (18 MB) 278 and 253,
+// 100 000 (38 MB) 323 and 338; TTM over 400 000 rows that follow a power law (25 MB and less) 242 and 240, 199 and 193.
+int spread_rows(const PiecePlan &plan, int R) {
+    const int64_t row = R % 16 ? R * 8 + 120 : R * 8;
+    return plan.distinct * row >= int64_t(30) << 20;
+}
+
 }  // namespace
 
 size_t piece_scratch_bytes(const PiecePlan &plan, int64_t R) { return (size_t)plan.ntiles * (size_t)R * 2 * sizeof(double); }
@@ -312,7 +337,7 @@ size_t piece_scratch_bytes(const PiecePlan &plan, int64_t R) { return (size_t)pl
 hipError_t piece_rows(const PiecePlan &plan, const int32_t *crd, const double *vals, int64_t nnz, const int32_t *rowmap, const double *Dn,
                       int64_t dense_rows, int R, double *out, void *scratch, hipStream_t st, Epilogue ep) {
     double *head = (double *)scratch, *tail = head + plan.ntiles * R;
-    const PieceArgs a{plan, crd, vals, rowmap, Dn, out, nnz, R, head, tail, st, ep};
+    const PieceArgs a{plan, crd, vals, rowmap, Dn, out, nnz, R, spread_rows(plan, R), head, tail, st, ep};
     const bool big = dense_rows * R * 8 >= (int64_t(1) << 32);    // row offsets in bytes no longer fit 32 bits
     const hipError_t e = COMET_DISPATCH_RANK(launch_pieces, R, big, a);
     if (e != hipSuccess || plan.ncut + plan.ncut_long == 0) return e;

@@ -1,6 +1,8 @@
 // Builds the piece plan of a compressed level (see pieces.hpp); runs once per tensor.
 #include "pieces.hpp"
 
+#include <cmath>
+
 #include "kernels.hpp"
 
 namespace comet {
@@ -125,11 +127,31 @@ __global__ void __launch_bounds__(256) k_piece_cuts(const int32_t *__restrict__ 
     else cuts[ntiles - 1 - atomicAdd(&counters[1], 1)] = c;
 }
 
+// Sets a bit per coordinate of a sample (samples spread evenly over the list) and adds up the bits that are set.
+constexpr int kSampleBits = 1 << 18;
+__global__ void __launch_bounds__(1024) k_piece_distinct(const int32_t *__restrict__ crd, int64_t nnz, int *__restrict__ set) {
+    __shared__ uint32_t bits[kSampleBits / 32];
+    for (int i = threadIdx.x; i < kSampleBits / 32; i += 1024) bits[i] = 0u;
+    __syncthreads();
+    const int64_t n = nnz < kSampleNnz ? nnz : kSampleNnz;
+    const int64_t begin = gridDim.x > 1 ? (nnz - n) / (gridDim.x - 1) * blockIdx.x : 0;
+#pragma unroll 8
+    for (int64_t i = threadIdx.x; i < n; i += 1024) {
+        const uint32_t h = ((uint32_t)crd[begin + i] * 0x9E3779B1u) >> 14;
+        atomicOr(&bits[h >> 5], 1u << (h & 31u));
+    }
+    __syncthreads();
+    int sum = 0;
+    for (int i = threadIdx.x; i < kSampleBits / 32; i += 1024) sum += __popc(bits[i]);
+    for (int d = 32; d > 0; d >>= 1) sum += __shfl_down(sum, d);
+    if ((threadIdx.x & 63) == 0) atomicAdd(set, sum);
+}
+
 unsigned grid_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
-hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, int64_t nnz, PiecePlan &plan, hipStream_t st) {
+hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd, int64_t nnz, PiecePlan &plan, hipStream_t st) {
     plan = PiecePlan();
     if (nseg < 1 || nnz < 1) return hipSuccess;
     auto fail = [&](hipError_t e) { plan = PiecePlan(); return e; };
@@ -139,7 +161,7 @@ hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, int64_t nnz, Piece
     plan.ntiles = ntiles;
     plan.tiles_mem = dev_alloc(sizeof(int4) * (2 * ntiles + 1));
     // temporary: pieces and joins of each tile, their sums before each tile, counters (short cuts, long cuts, most partial
-    // sums in a tile), and what the scan asks for.  One allocation: each costs a small handle's creation 10 us and more
+    // sums in a tile, bits set by the samples), and what the scan asks for.  One allocation: each costs a small handle's creation 10 us and more
     size_t tb = 0;
     hipError_t e = reorder_scan_flags(nullptr, &tb, (uint64_t *)nullptr, (uint64_t *)nullptr, ntiles + 1, st);
     if (e != hipSuccess) return fail(e);
@@ -150,15 +172,17 @@ hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, int64_t nnz, Piece
     int *counters = (int *)(bf + ntiles + 1);
     hipLaunchKernelGGL(k_piece_tiles, dim3(grid_for(ntiles + 1)), dim3(256), 0, st, pos, nseg, nnz, plan.units, ntiles, plan.tiles());
     e = hipMemsetAsync(cn + ntiles, 0, sizeof(uint64_t), st);
-    if (e == hipSuccess) e = hipMemsetAsync(counters, 0, 3 * sizeof(int), st);
+    if (e == hipSuccess) e = hipMemsetAsync(counters, 0, 4 * sizeof(int), st);
     if (e != hipSuccess) return fail(e);
     hipLaunchKernelGGL((k_piece_fill<false>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, plan.tiles(), cn,
                        counters + 2, (uint32_t *)nullptr, (uint32_t *)nullptr);
     hipLaunchKernelGGL(k_piece_cuts, dim3(grid_for(ntiles)), dim3(256), 0, st, pos, nseg, (const int4 *)plan.tiles(), ntiles,
                        plan.cuts(), counters);
+    const int samples = nnz > kSampleNnz ? 4 : 1;
+    hipLaunchKernelGGL(k_piece_distinct, dim3(samples), dim3(1024), 0, st, crd, nnz, counters + 3);
     e = reorder_scan_flags((char *)temp->ptr + scan_at, &tb, cn, bf, ntiles + 1, st);
-    struct { uint64_t total; int short_cuts, long_cuts, max_parts, unused; } sums = {0, 0, 0, 0, 0};    // bf[ntiles] and the counters
-    if (e == hipSuccess) e = hipMemcpyAsync(&sums, bf + ntiles, sizeof(uint64_t) + 3 * sizeof(int), hipMemcpyDeviceToHost, st);
+    struct { uint64_t total; int short_cuts, long_cuts, max_parts, set; } sums = {0, 0, 0, 0, 0};    // bf[ntiles] and the counters
+    if (e == hipSuccess) e = hipMemcpyAsync(&sums, bf + ntiles, sizeof sums, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(e);
     plan.npieces = (int64_t)(uint32_t)sums.total;
@@ -166,6 +190,9 @@ hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, int64_t nnz, Piece
     plan.ncut = sums.short_cuts;
     plan.ncut_long = sums.long_cuts;
     plan.max_parts = sums.max_parts;
+    // m coordinates set kSampleBits * (1 - exp(-m / kSampleBits)) bits
+    const double unset = 1.0 - (double)sums.set / ((double)samples * kSampleBits);
+    plan.distinct = unset > 0.0 ? (int64_t)(-std::log(unset) * kSampleBits) : kSampleNnz;
     plan.pieces_mem = dev_alloc(sizeof(uint32_t) * (plan.npieces + plan.njoins));
     if (!plan.pieces_mem) return fail(hipErrorOutOfMemory);
     hipLaunchKernelGGL((k_piece_fill<true>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, plan.tiles(), bf,

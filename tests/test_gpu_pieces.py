@@ -158,3 +158,23 @@ def test_without_memory_for_the_plan(comet, R):
     assert torch.equal(C[::step], vals[:, None] * B[crd.long()])
     C[::step] = 0.0
     assert torch.count_nonzero(C) == 0
+
+
+@pytest.mark.parametrize("R", [10, 20, 32, 33, 48, 64, 100, 128])
+def test_rows_spread_over_a_large_operand(comet, R):
+    """Nonzeros that hardly ever come back to an operand row take another number of loads per piece; the same edges."""
+    lens = torch.tensor(([n for n in EDGES if n < 100] + list(range(1, 50))) * 120 + [5000, 20000], dtype=torch.int64)
+    I, J = lens.numel(), 1_000_000 if R < 32 else 400_000
+    rows, cols, vals = gen.matrix_from_row_lengths(I, J, lens, 8)
+    part = torch.unique(cols[:1 << 18]).numel()
+    print("spread R=%d nnz=%d distinct=%d" % (R, vals.numel(), part), flush=True)
+    assert vals.numel() > 1 << 18 and part * (R * 8 if R % 16 == 0 else R * 8 + 120) > 33 << 20
+    A = comet.from_levels(fmt.pack_csr(I, J, rows, cols, vals).to("cuda"), comet.COMET_LEAN).set_variant(2)
+    B, old = gen.dense_operand(3, 0, (J, R)), gen.dense_operand(4, 0, (I, R))
+    C = torch.full((I, R), float("nan"), dtype=torch.float64, device="cuda")
+    comet.comet_spmm(A, B.to("cuda"), C)
+    ref, absum = oracle.spmm(np_(rows), np_(cols), np_(vals), (I, J), np_(B))
+    assert_values_close(np_(C), ref, absum, "spread R=%d" % R)
+    D = old.to("cuda")
+    comet.comet_spmm_axpby(A, 0.75, B.to("cuda"), -0.5, D)
+    assert_values_close(np_(D), 0.75 * ref - 0.5 * np_(old), 0.75 * absum + 0.5 * np.abs(np_(old)), "spread axpby R=%d" % R)
