@@ -455,25 +455,29 @@ __global__ void __launch_bounds__(256) k_stream_fixup(void *scratch, int64_t nti
 }
 
 // The same for longer chains (the head slice of a power-law tensor is cut over thousands of tiles): eight summaries at a time,
-// whose loads do not depend on what they hold, and from kFixSerial tiles on the whole workgroup, the tiles dealt over 1024 / R
-// threads per column.  One launch; folding 64 summaries per thread level by level took three of them, 51 us for 36 600 tiles of
-// the MTTKRP configuration at rank 16 where this takes 28, 47 us for 4900 tiles at rank 64 where this takes 19.
-constexpr int kFixSerial = 64;
+// whose loads do not depend on what they hold, and from kFixSerial tiles on the whole workgroup.  A workgroup finishes kFixTiles
+// tiles in a block of up to 16 columns: no more tiles, since two chains that long cannot end among so few of them, and no more
+// columns, so that 64 threads and more share the tiles of a chain at every rank.  One launch; folding 64 summaries per thread level by
+// level took three of them, FIXUP_FIGURES
+constexpr int kFixSerial = 64, kFixTiles = 64, kFixColumns = 16;
+static_assert(kFixTiles <= kFixSerial && kFixTiles * kFixColumns <= 1024, "one long chain per workgroup, a thread per tile and column");
 __global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64_t ntiles, int R, const int32_t *__restrict__ rowmap,
                                                        double *__restrict__ out, Epilogue ep) {
     __shared__ double sums[1024];
-    __shared__ int nlong, list[1024], newest;
+    __shared__ int chain, newest;
     const CarryView cb = carry_view(scratch, ntiles, R);
-    const int lanes = 1024 / R, lane = (int)threadIdx.x / R, r = (int)threadIdx.x - lane * R;
-    if (threadIdx.x == 0) nlong = 0;
+    const int64_t nblocks = (ntiles + kFixTiles - 1) / kFixTiles;
+    const int c0 = (int)(blockIdx.x / nblocks) * kFixColumns, cols = R - c0 < kFixColumns ? R - c0 : kFixColumns;
+    const int lanes = 1024 / cols, lane = (int)threadIdx.x / cols, col = (int)threadIdx.x - lane * cols, r = c0 + col;
+    if (threadIdx.x == 0) chain = -1;
     __syncthreads();
     auto finish = [&](int64_t t, double v) {
         const int32_t id = cb.first_id[t];
         double *o = out + (rowmap ? (int64_t)rowmap[id] : (int64_t)id) * R + r;
         *o = ep_apply(ep, v, o);
     };
-    const int64_t t0 = (int64_t)blockIdx.x * lanes, mine = t0 + lane;
-    if (lane < lanes && mine < ntiles && cb.has_tail[mine]) {
+    const int64_t t0 = (int64_t)(blockIdx.x % nblocks) * kFixTiles, mine = t0 + lane;
+    if (lane < kFixTiles && mine < ntiles && cb.has_tail[mine]) {
         double v = cb.first[mine * R + r];
         bool done = false;
         int64_t u = mine - 1;
@@ -492,45 +496,51 @@ __global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64
             u -= 8;
         }
         if (done || u < 0) finish(mine, v);
-        else if (r == 0) list[atomicAdd(&nlong, 1)] = lane;
+        else if (col == 0) chain = lane;
     }
     __syncthreads();
-    const int n = nlong;
-    for (int i = 0; i < n; ++i) {
-        const int64_t t = t0 + list[i];
-        int64_t from = 0;                                         // the nearest tile in front of t that contains a segment end, or the first
-        for (int64_t base = t - 1; base >= 0; base -= 1024) {
-            __syncthreads();
-            if (threadIdx.x == 0) newest = -1;
-            __syncthreads();
-            const int64_t u = base - threadIdx.x;
-            if (u >= 0 && cb.has_tail[u]) atomicMax(&newest, (int)u);
-            __syncthreads();
-            if (newest >= 0) { from = newest; break; }
-        }
-        double v = 0.0;
-        if (lane < lanes) {
-            int64_t u = from + lane;
-            for (; u + 7 * (int64_t)lanes < t; u += 8 * (int64_t)lanes) {
-                double x[8];
+    if (chain < 0) return;
+    const int64_t t = t0 + chain;
+    int64_t from = 0;                                             // the nearest tile in front of t that contains a segment end, or the first
+    for (int64_t base = t - 1; base >= 0; base -= 8 * 1024) {
+        int ht[8], nearest = -1;
 #pragma unroll
-                for (int q = 0; q < 8; ++q) x[q] = cb.open[(u + q * (int64_t)lanes) * R + r];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v += x[q];
-            }
-            for (; u < t; u += lanes) v += cb.open[u * R + r];
+        for (int q = 0; q < 8; ++q) {
+            const int64_t u = base - q * 1024 - (int)threadIdx.x;
+            ht[q] = cb.has_tail[u > 0 ? u : 0];
         }
-        sums[threadIdx.x] = v;
-        for (int k = lanes; k > 1;) {
-            const int h = (k + 1) / 2;
-            __syncthreads();
-            if (lane < k - h) sums[threadIdx.x] += sums[threadIdx.x + h * R];
-            k = h;
+#pragma unroll
+        for (int q = 7; q >= 0; --q) {
+            const int64_t u = base - q * 1024 - (int)threadIdx.x;
+            if (u >= 0 && ht[q]) nearest = (int)u;
         }
         __syncthreads();
-        if (lane == 0) finish(t, cb.first[t * R + r] + sums[threadIdx.x]);
+        if (threadIdx.x == 0) newest = -1;
         __syncthreads();
+        if (nearest >= 0) atomicMax(&newest, nearest);
+        __syncthreads();
+        if (newest >= 0) { from = newest; break; }
     }
+    double v = 0.0;
+    if (lane < lanes) {
+        int64_t u = from + lane;
+        for (; u + 15 * (int64_t)lanes < t; u += 16 * (int64_t)lanes) {
+            double x[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) x[q] = cb.open[(u + q * (int64_t)lanes) * R + r];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v += x[q];
+        }
+        for (; u < t; u += lanes) v += cb.open[u * R + r];
+    }
+    sums[threadIdx.x] = v;
+    for (int k = lanes; k > 1;) {
+        const int h = (k + 1) / 2;
+        __syncthreads();
+        if (lane < k - h) sums[threadIdx.x] += sums[threadIdx.x + h * cols];
+        k = h;
+    }
+    if (lane == 0) finish(t, cb.first[t * R + r] + sums[threadIdx.x]);
 }
 
 
@@ -542,9 +552,8 @@ hipError_t run_fixup(void *scratch, int64_t ntiles, int R, const int32_t *rowmap
     if (max_chain > 0 && max_chain <= kShortChain) {
         hipLaunchKernelGGL(k_stream_fixup, dim3((unsigned)((ntiles * R + 255) / 256)), dim3(256), 0, st, scratch, ntiles, R, rowmap, out, ep);
     } else {
-        const int64_t per = 1024 / R;
-        hipLaunchKernelGGL(k_stream_fixup_long, dim3((unsigned)((ntiles + per - 1) / per)), dim3(1024), 0, st, scratch, ntiles, R, rowmap,
-                           out, ep);
+        const int64_t blocks = (ntiles + kFixTiles - 1) / kFixTiles * ((R + kFixColumns - 1) / kFixColumns);
+        hipLaunchKernelGGL(k_stream_fixup_long, dim3((unsigned)blocks), dim3(1024), 0, st, scratch, ntiles, R, rowmap, out, ep);
     }
     return hipGetLastError();
 }

@@ -148,3 +148,40 @@ def test_factors_whose_offsets_leave_32_bits(comet, R, level, values):
     comet.comet_mttkrp(X, 0, [None] + BC, M)
     ref, absum = oracle.mttkrp(np_(i), np_(j), np_(k), np_(vals), dims, np_(small[0]), np_(small[1]))
     assert_values_close(np_(M), ref, absum, "wide factor R=%d level=%d" % (R, level))
+
+
+@pytest.mark.parametrize("R", [33, 42, 64, 100, 128])
+def test_slices_over_many_tiles_of_the_walk(comet, R):
+    """Slices cut over 64 and more tiles of the walk, whose partial sums a workgroup adds up per block of 16 columns: at ranks
+    whose last block leaves threads idle, at several slices in a row, and with short slices between them."""
+    long_slice = [300] * 280                                            # 84 000 nonzeros: 82 chunks of 1024
+    slices = [long_slice, [1], long_slice, [7, 2000, 1], long_slice, long_slice, [3] * 300, [66_000], long_slice * 2, [1023], long_slice * 3, [5]]
+    n = sum(map(sum, slices))
+    assert 9 << 18 < n * -(-R // 16) and n < LINE                       # beyond the pieces, in chunks
+    _check(comet, slices, R)
+
+
+@pytest.mark.parametrize("op", ["ttv", "ttv_coo", "spmv"])
+def test_chains_over_many_tiles_at_rank_one(comet, op):
+    """Segments of 64 and more tiles of 4096 nonzeros, one behind the other and with short ones between them, on a vector that
+    does not fit LDS: every one ends among the tiles of another workgroup of the fix-up, wherever it begins."""
+    n = 400_003
+    lens = [280_000, 5, 262_144, 262_145, 1, 399_999, 4096, 300_000, 300_000, 12_000, 2]
+    rows = torch.repeat_interleave(torch.arange(len(lens)), torch.tensor(lens))
+    cols = torch.cat([torch.arange(m) for m in lens])
+    vals = gen.dense_operand(7, 0, (rows.numel(), 1)).reshape(-1)
+    x = gen.dense_operand(7, 1, (n, 1)).reshape(-1)
+    print("chains %s nnz=%d" % (op, vals.numel()), flush=True)
+    ref, absum = oracle.spmv(np_(rows), np_(cols), np_(vals), (len(lens), n), np_(x))
+    if op == "spmv":
+        A = comet.from_levels(fmt.pack_csr(len(lens), n, rows.int(), cols.int(), vals).to("cuda"), comet.COMET_LEAN).set_variant(2)
+        got = comet.comet_spmv(A, x.cuda())
+        y = torch.ones(len(lens), dtype=torch.float64, device="cuda")
+        comet.comet_spmv_axpby(A, 0.5, x.cuda(), 2.0, y)
+        assert_values_close(np_(y), 0.5 * ref + 2.0, 0.5 * absum + 2.0, "chains axpby")
+    else:
+        dims = (1, len(lens), n)
+        i = torch.zeros_like(rows).int()
+        T = fmt.pack_csf3(dims, i, rows.int(), cols.int(), vals) if op == "ttv" else fmt.pack_coo(dims, (i, rows.int(), cols.int()), vals)
+        got = comet.comet_ttv(comet.from_levels(T.to("cuda")).set_variant(2), 2, x.cuda()).vals()
+    assert_values_close(np_(got), ref, absum, "chains %s" % op)
