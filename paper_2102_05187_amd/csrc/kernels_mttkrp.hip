@@ -1,4 +1,8 @@
-// MTTKRP kernel: lane groups of 4, 8 or 16 walk the pieces of the fibers of a tile (mttkrp_plan.hpp).
+// MTTKRP kernels.  Short lists: lane groups of 4, 8 or 16 walk the pieces of the fibers of a tile (k_mttkrp_pieces, mttkrp_plan.hpp);
+// a tile is a chain of dependent loads -- its descriptor, its nonzeros, rows of B and C, the sums -- and what bounds the kernel is how
+// many of them are in flight.  All others: lane groups walk runs of nonzeros over two nested segment levels (k_stream_mttkrp).
+// A piece loads rows of C in groups of four, none behind its batch's last group; with up to seven more rows per piece, fibers of 12 / 30 /
+// 200 nonzeros, rank 10, 2.3 M, took 39 / 40 / 37 us instead of 36 / 35 / 32, rank 33 107 / 117 / 108 instead of 90 / 87 / 79.
 #include "mttkrp_plan.hpp"
 #include "stream_common.hpp"
 
@@ -92,12 +96,21 @@ __global__ void __launch_bounds__(256, 3) k_mttkrp_pieces(const int4 *__restrict
                     }
             }
         };
+        // one group in flight behind the one being used, none behind the batch's last one
         issue(0, row[0], val[0]);
-        for (int j = 0; j < longest; j += 2 * G) {
+        int j = 0;
+        for (; j + 2 * G < longest; j += 2 * G) {
             issue(j + G, row[1], val[1]);
             consume(j, row[0], val[0]);
             issue(j + 2 * G, row[0], val[0]);
             consume(j + G, row[1], val[1]);
+        }
+        if (j + G < longest) {
+            issue(j + G, row[1], val[1]);
+            consume(j, row[0], val[0]);
+            consume(j + G, row[1], val[1]);
+        } else {
+            consume(j, row[0], val[0]);
         }
 #pragma unroll
         for (int q = 0; q < V; ++q) acc[q] *= b[q];
@@ -458,11 +471,55 @@ hipError_t launch_walk(const MtArgs &a, const Schedule &sc, void *scratch) {
      : (R) & 1 ? ((R) <= 4 ? F<4, 1, false, false>(args) : (R) <= 8 ? F<8, 1, false, false>(args) : F<16, 1, false, false>(args)) \
                : ((R) <= 8 ? F<4, 2, false, false>(args) : (R) % 16 ? F<8, 2, false, false>(args) : F<8, 2, true, false>(args)))
 
+// Tiles that the slices of the walk are cut over at most.
+int64_t mttkrp_chain(const Schedule &sc) { return sc.max_parent_len / (sc.chunk_slice_begin ? kChunk : kTile) + 2; }
+
+// Which lists and ranks take the pieces; all others the walk over tiles of nonzeros, which keeps more rows in flight once its tiles
+// fill the chip, while a tile of pieces needs several rounds of loads one after the other.  Calls of the walk and of the pieces in us,
+// three tensors taking turns.  Power: power-law modes, 2.5 to 4 nonzeros per fiber, slices cut over many tiles, for which the walk's
+// carry fix-up is longer; ones: uniform modes, a nonzero per fiber, so that the pieces read a row of B for each; fives, thirties: so
+// many per fiber, short slices.
+//   nonzeros         rank 8     16        32        64         10        20        7         9         33        40
+//   0.2 M power      27   19   29   25   37   35   61   64    30   22   39   30   28   19   30   22   55   42   59   46
+//         ones       18   15   20   17   24   23   35   37    25   17   30   25   20   15   25   17   41   38   40   33
+//         fives      15   15   15   15   15   16   16   24    15   15   18   15   15   15   15   15   24   20   24   20
+//         thirties   15   15   15   15   15   16   16   23    16   15   18   16   16   15   16   14   22   19   22   19
+//   0.6 M power      37   25   42   34   66   59  101  103    44   30   67   48   38   26   44   35  102   88  109   83
+//         ones       25   22   26   27   45   45   83   94    34   29   52   49   30   24   33   32   74   86   75   69
+//         fives      15   15   15   16   23   24   30   38    21   16   32   24   16   15   21   18   43   32   43   30
+//         thirties   18   15   17   15   22   21   27   33    22   15   28   20   20   15   23   16   36   29   36   27
+//   1.2 M power      42   34   49   49   89   88  136  158    55   43   93   79   47   34   54   51  141  140  146  124
+//         ones       34   34   37   43   71   82  135  159    47   46   73   83   41   37   47   54  111  158  114  124
+//         fives      17   21   20   25   32   41   46   74    29   25   46   41   21   21   30   27   64   60   64   57
+//         thirties   22   17   21   22   31   34   40   58    30   21   41   34   25   19   30   24   53   49   53   46
+//   2.3 M power      55   51   67   75  122  133  193  252    76   68  144  127   60   50   76   82  206  228  213  192
+//         ones       53   57   56   76  117  149  248  286    72   78  114  154   64   62   72   96  179  291  182  228
+//         fives      28   33   30   40   53   72   77  136    46   40   75   72   33   32   47   43  107  105  108  103
+//         thirties   29   27   30   34   49   59   64  108    46   35   67   59   35   28   47   37   87   87   87   84
+//   4.9 M power      88   98  124  131  198  239  327  460   154  127  253  234  107   97  151  153  370  425  379  350
+//         ones      108  119  126  153  244  292  538  574   157  162  244  317  137  127  155  190  372  609  385  466
+//         fives      47   62   63   75   95  145  152  285    95   76  142  143   61   58   97   78  210  213  210  212
+//         thirties   48   47   61   62   73  116  109  224    92   63  106  116   62   50   92   67  151  174  152  170
+// Ranks 2 and 4 go with 8, 48 with 32, 96 and 128 with 64; 1, 3, 6 with 7; 12 with 10; 15 with 9; 17 between 9 and 33; 24 with 20; 80 with 40.
+bool mttkrp_takes_pieces(const Schedule &sc, int64_t R) {
+    const int64_t n = sc.nnz, blocks = (R + 15) / 16;
+    const bool long_slices = sc.max_parent_len <= 0 || mttkrp_chain(sc) > kShortChain;
+    // ranks whose rows the walk reads 16 bytes per lane, with no lane idle
+    if (R == 2 || R == 4 || R == 8 || R % 16 == 0) {
+        if (long_slices) return R <= 48 && n <= (R <= 8 ? int64_t(9) << 18 : int64_t(9) << 17) && n * blocks <= int64_t(9) << 18;
+        return R <= 32 && n * (R > 8 ? R : 8) <= int64_t(25) << 18;
+    }
+    if (n < 2 * sc.nseg) return n * (R % 2 ? blocks : (R + 31) / 32) <= int64_t(3) << 18;
+    if (R > 32 || (R % 2 && R > 16)) return n * blocks <= int64_t(9) << 18;
+    if (R % 2 && R > 8) return n <= (long_slices ? int64_t(5) << 18 : int64_t(9) << 18);
+    return R < 16 || long_slices || n <= int64_t(9) << 18;
+}
+
 }  // namespace
 
 bool mttkrp_on_pieces(const Schedule &sc, int64_t dense_rows, int64_t R) {
     // row offsets of the pieces are 32-bit counts of doubles; the walk forms 64-bit addresses
-    return sc.mttkrp.ntiles > 0 && mttkrp_takes_pieces(sc.nnz, R) && dense_rows * R < (int64_t(1) << 32);
+    return sc.mttkrp.ntiles > 0 && mttkrp_takes_pieces(sc, R) && dense_rows * R < (int64_t(1) << 32);
 }
 
 size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R) {
@@ -492,9 +549,8 @@ hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t 
     }
     const hipError_t e = COMET_DISPATCH_GROUPS(launch_walk, a.R, a, sc, scratch);
     if (e != hipSuccess) return e;
-    const int tile = sc.chunk_slice_begin ? kChunk : kTile;
     return run_fixup(scratch, sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, (int)R, nullptr, M,
-                     sc.max_parent_len > 0 ? sc.max_parent_len / tile + 2 : 0, st, ep);
+                     sc.max_parent_len > 0 ? mttkrp_chain(sc) : 0, st, ep);
 }
 
 }  // namespace comet

@@ -435,7 +435,6 @@ __global__ void __launch_bounds__(256) k_stream_rank1_coo(const int32_t *__restr
 // ---- fix-up: finish the first segment end of every tile -------------------------------------------
 // value = first[t] + open[t-1] + open[t-2] + ... up to and including the nearest tile that contains a segment end.  A thread per
 // (tile, r) walks back; for levels whose segments are cut over kShortChain tiles at most.
-constexpr int kShortChain = 24;
 __global__ void __launch_bounds__(256) k_stream_fixup(void *scratch, int64_t ntiles, int R, const int32_t *__restrict__ rowmap,
                                                       double *__restrict__ out, Epilogue ep) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -15,22 +15,8 @@
 
 namespace comet {
 
-// Lists that take the pieces; all others the walk over tiles of nonzeros, which keeps more rows in flight once its tiles fill
-// the chip, while a tile of pieces needs several rounds of loads one after the other.  Where the walk reads rows 16 bytes per
-// lane (and at odd ranks, which neither can) the line is nonzeros times blocks of 16 columns; the other ranks below 32 are read
-// 8 bytes per lane by the walk and go to the pieces much longer.  Walk and pieces, power-law tensors, whole calls in us:
-//   nonzeros  rank 8      10         16         32         33         64         4          12         20
-//   0.1 M     24   19    27   20    26   22    33   31    50   33    50   50
-//   0.4 M     46   24    50   28    48   30    58   45    79   63    91   83
-//   1 M       51   32    64   40    57   43    84   76    122  124   132  145   47   29    62   41    86   66
-//   2.5 M     68   55    97   71    78   78    137  145   228  257   213  277   61   53    94   73    155  135
-//   5 M       100  99    165  130   130  137   209  250   382  452   337  480   98   87    163  134   257  244
-//   8 M                                                                         112  141   213  197   347  361
-constexpr int64_t kMtWork = int64_t(9) << 18, kMtNarrow = int64_t(5) << 20;
-inline bool mttkrp_takes_pieces(int64_t nnz, int64_t R) {
-    const bool narrow = R < 32 && R != 8 && R != 16 && (R % 2 == 0 || R < 8);
-    return narrow ? nnz <= kMtNarrow : nnz * ((R + 15) / 16) <= kMtWork;
-}
+// Lists of up to this many nonzeros have a plan (kernels_mttkrp.hip says which ranks use it).
+constexpr int64_t kMtNarrow = int64_t(5) << 20;
 // Units per tile: with 448 the items and sums of a tile take at most 39 KB of LDS at rank 16, so that four workgroups share a
 // compute unit.  Short lists take smaller tiles, down to 128 units, so that there are about 1024 of them.
 constexpr int kMtUnitsMin = 128, kMtUnitsMax = 448;
@@ -38,7 +24,7 @@ constexpr int kMtWhole = 16;           // longest fiber that is taken as one pie
 constexpr int kMtPiece = 12;           // longest piece of any other fiber
 constexpr int kMtSnap = 32;            // a tile boundary inside a fiber of at most this many nonzeros moves to its start
 constexpr int kMtSum = 16;             // rows of sums that one lane group adds up at a time
-// A fiber of n >= 1 nonzeros is n + 1 units and gives one piece, or about n / 32; the fibers at either end may be cut.
+// A fiber of n >= 1 nonzeros is n + 1 units and gives one piece, or n / 12 and a part of one; the fibers at either end may be cut.
 constexpr int kMtItems = kMtUnitsMax + kMtSnap + 1, kMtPieces = kMtItems / 2 + 8;
 static_assert(kMtPieces <= 256, "a thread holds one piece");
 

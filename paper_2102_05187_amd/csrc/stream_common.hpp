@@ -35,6 +35,7 @@
 namespace comet {
 
 // Finishes every segment that a tile boundary cut (defined in kernels_rank1.hip).
+constexpr int kShortChain = 24;        // tiles that a segment is cut over, up to which a thread finishes it alone
 hipError_t run_fixup(void *scratch, int64_t ntiles, int R, const int32_t *rowmap, double *out, int64_t max_chain,
                      hipStream_t st, Epilogue ep = Epilogue());
 // Rank-R part of stream_segreduce (defined in kernels_rankR.hip).

@@ -68,11 +68,20 @@ def test_both_sides_of_the_size_rule(comet, nnz):
     _check(comet, slices, 10)
 
 
-@pytest.mark.parametrize("R,nnz", [(8, 9 << 18), (8, (9 << 18) + 1), (33, (9 << 18) // 3), (33, (9 << 18) // 3 + 1), (6, 5 << 20), (6, (5 << 20) + 1)])
-def test_both_sides_of_the_rules_for_pieces(comet, R, nnz):
-    each = [40, 3, 1, 500, 17, 16, 1]
-    n = nnz // sum(each)
-    _check(comet, [each] * n + ([[nnz - n * sum(each)]] if nnz - n * sum(each) else []), R)
+# nonzeros up to which lists take the pieces, by what the rule sees: short slices of several nonzeros per fiber, the same behind a
+# slice cut over many tiles, and a nonzero per fiber
+LINES = [("short", 8, 25 << 15), ("short", 16, 25 << 14), ("short", 33, 3 << 18), ("short", 20, 9 << 18), ("short", 9, 9 << 18), ("short", 6, 5 << 20),
+         ("long", 8, 9 << 18), ("long", 32, 9 << 17), ("long", 11, 5 << 18), ("ones", 10, 3 << 18), ("ones", 33, 1 << 18), ("ones", 24, 3 << 18)]
+
+
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("shape,R,line", LINES)
+def test_both_sides_of_the_rules_for_pieces(comet, shape, R, line, more):
+    each = [1] * 7 if shape == "ones" else [40, 3, 1, 500, 17, 16, 1]
+    first = [[300] * 100] if shape == "long" else []                    # 30 chunks
+    rest = line + more - sum(map(sum, first))
+    n = rest // sum(each)
+    _check(comet, first + [each] * n + ([[rest - n * sum(each)]] if rest - n * sum(each) else []), R)
 
 
 @pytest.mark.parametrize("R", [1, 6, 16, 35])
