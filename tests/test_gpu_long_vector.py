@@ -12,7 +12,11 @@ from util import assert_values_close, np_
 pytestmark = pytest.mark.gpu
 
 MIN_COLS = 5 << 17
-MIN_NNZ = 4 * MIN_COLS + (4 << 20)          # nonzeros in rows of 128 and more from which on the sweep runs at that many columns
+
+
+def _line(ncols):
+    """Nonzeros in rows of 128 and more from which on the sweep runs."""
+    return 4 * ncols + (4 << 20)
 
 
 @pytest.fixture(scope="module")
@@ -26,9 +30,9 @@ def comet():
 def _matrix(ncols, clustered, seed):
     g = torch.Generator(device="cuda").manual_seed(seed)
     lens = torch.cat([torch.tensor([0, 127, 128, 129, 4095, 4096, 4097, 8193, 60_000, 0, 1]), torch.randint(0, 127, (30_000,)),
-                      torch.full((MIN_NNZ // 900 + 50,), 900), torch.tensor([0, 5, 0])]).cuda()
+                      torch.full((_line(ncols) // 900 + 50,), 900), torch.tensor([0, 5, 0])]).cuda()
     rows = torch.repeat_interleave(lens)
-    # distinct columns of a row: its nonzeros in equal strides from a random start; clustered rows lie in a sixteenth of the columns
+    # distinct columns of a row: its nonzeros in equal strides from a random start; clustered rows lie in an eighth of the columns
     k = torch.arange(rows.numel(), device="cuda") - (torch.cumsum(lens, 0) - lens)[rows]
     width = torch.full_like(lens, ncols)
     if clustered:
@@ -47,7 +51,7 @@ def test_sweep_against_the_oracle(comet, layout, ncols, clustered):
     n, rows, cols, vals = _matrix(ncols, clustered, ncols)
     A = comet.from_levels((fmt.pack_csr if layout == "csr" else fmt.pack_dcsr)(n, ncols, rows, cols, vals))
     print("spmv sweep %s ncols=%d nnz=%d heavy=%s" % (layout, ncols, vals.numel(), A.heavy_plan()), flush=True)
-    assert A.heavy_plan()[1] >= MIN_NNZ
+    assert A.heavy_plan()[1] >= _line(ncols)           # so that the sweep runs from MIN_COLS columns on
     x = gen.dense_operand(3, 0, (ncols, 1)).reshape(-1)
     old = gen.dense_operand(4, 0, (n, 1)).reshape(-1)
     ref, absum = oracle.spmv(np_(rows), np_(cols), np_(vals), (n, ncols), np_(x))
@@ -56,6 +60,10 @@ def test_sweep_against_the_oracle(comet, layout, ncols, clustered):
     assert_values_close(np_(y), ref, absum, "spmv sweep")
     for _ in range(3):
         assert torch.equal(y, comet.comet_spmv(A, x.cuda())), "two runs differ"
+    # on the sweep the sums are formed in another order than in the plain kernel, which tells the two apart; below it they are the same
+    plain = comet.comet_spmv(A.set_variant(3), x.cuda())
+    A.set_variant(0)
+    assert torch.equal(y, plain) == (ncols < MIN_COLS)
     z = old.cuda()
     comet.comet_spmv_axpby(A, 0.75, x.cuda(), -0.5, z)
     assert_values_close(np_(z), 0.75 * ref - 0.5 * np_(old), 0.75 * absum + 0.5 * np.abs(np_(old)), "spmv sweep axpby")
@@ -66,3 +74,25 @@ def test_sweep_against_the_oracle(comet, layout, ncols, clustered):
     w[unused] = float("nan")
     w[0] = x[0] if not bool(unused[0]) else float("inf")
     assert torch.equal(y, comet.comet_spmv(A, w))
+
+
+def test_sweep_replays_from_a_captured_graph(comet):
+    """After reserve a call only launches kernels; replays, with eager work between them, give the eager result bit for bit."""
+    n, rows, cols, vals = _matrix(MIN_COLS, False, 8)
+    A = comet.from_levels(fmt.pack_csr(n, MIN_COLS, rows, cols, vals))
+    assert A.heavy_plan()[1] >= _line(MIN_COLS)
+    A.reserve(1)
+    x = gen.dense_operand(6, 0, (MIN_COLS, 1)).reshape(-1).cuda()
+    y = torch.empty(n, dtype=torch.float64, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(g, stream=side):
+        comet.comet_spmv(A, x, y)
+    want = comet.comet_spmv(A, x)
+    for rep in range(3):
+        y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want), "replay %d differs from the eager result" % rep
