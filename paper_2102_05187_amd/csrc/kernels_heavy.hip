@@ -28,7 +28,7 @@
 // rows of B gathered a few positions ahead of the multiply-adds, a sum flushed into LDS where a unit's piece
 // ends -- and the 16 wavefronts of a compute unit meet at a barrier where a window ends (no data is
 // exchanged there; it only keeps them on the same rows of B).  Each (unit, XCD) pair yields one partial row;
-// a second kernel adds the partial rows of a heavy row in a fixed order (no atomics anywhere: results are
+// a second kernel adds the partial rows of a heavy row in a fixed order (no sum depends on scheduling: results are
 // reproducible run to run).
 #include <algorithm>
 #include <atomic>
@@ -382,23 +382,24 @@ __global__ void __launch_bounds__(kHeavyThreads) k_heavy_sweep(const int32_t *__
 // workgroup copies the part of x that an interval of the streams reads into LDS (128 KB) and gathers from there; a position behind
 // the interval's end, in a super-block that crosses it, is gathered from memory.  A lane multiplies the four positions that it holds,
 // adds up what it can by itself, and a segmented scan over the eight lanes of its group joins the rest; finished pieces are added to
-// the unit's sum in LDS.  (Two lanes of a group may finish pieces of one unit in the same instruction, hence the LDS atomic; a unit's
-// sum is touched by one wavefront only, in program order.)
+// the lane's own sum of the unit in LDS, and the eight of a unit are added up in lane order at the end: no two lanes share an
+// address, so that the order of every sum is the program's (the atomic is only the form of an add that nothing waits for).
 // 1 M x 1 M, 18.5 M nonzeros, 13.9 M of them in 13 700 rows: 78 us here, 60 for the other rows, 145 a call where the walk through the
 // vector L1 alone takes 194; gathering through the L1 here too, from the eighth of x in the XCD's L2, took 106.  Reading the next
 // interval's part ahead into registers (81), or super-blocks three ahead (91), costs more than it hides.
 constexpr int kSpmvColumns = kSync * kWindow;                      // of an interval
+static_assert((kSpmvColumns + kMaxUnitsPerGroup * kHeavyThreads) * sizeof(double) <= 160 * 1024, "LDS of a compute unit");
 __global__ void __launch_bounds__(kHeavyThreads) k_heavy_spmv(const int32_t *__restrict__ scrd, const int32_t *__restrict__ scode,
                                                               const double *__restrict__ sval, const int32_t *__restrict__ block_start,
                                                               const int32_t *__restrict__ wend, int nsx, int nwx, int nu,
                                                               const int4 *__restrict__ units, int nunits, const double *__restrict__ xv,
                                                               int64_t ncols, double *__restrict__ partial) {
-    extern __shared__ __attribute__((aligned(16))) double xs[];    // [kSpmvColumns], then the units' sums [nu][groups]
+    extern __shared__ __attribute__((aligned(16))) double xs[];    // [kSpmvColumns], then the units' sums [nu][threads]
     double *accs = xs + kSpmvColumns;
     const int x = blockIdx.x % kXcd, wg = blockIdx.x / kXcd;
     const int g = threadIdx.x >> 3, j = threadIdx.x & 7, gl = g & 7;
     const int wave = x * kWaves + wg * (kHeavyThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (j < nu) accs[j * kHeavyGroups + g] = 0.0;
+    for (int k = 0; k < nu; ++k) accs[k * kHeavyThreads + threadIdx.x] = 0.0;
     const int nsb = block_start[wave + 1] - block_start[wave];
     const int64_t base = (int64_t)block_start[wave] * (8 * kBlock) + gl * kBlock + 4 * j;
     const int32_t *we = wend + (int64_t)wave * (nsx + 1);
@@ -412,7 +413,7 @@ __global__ void __launch_bounds__(kHeavyThreads) k_heavy_spmv(const int32_t *__r
         it.a = __builtin_nontemporal_load(reinterpret_cast<const v2d *>(sval + i));
         it.b = __builtin_nontemporal_load(reinterpret_cast<const v2d *>(sval + i + 2));
     };
-    auto add = [&](int slot, double v) { atomicAdd(&accs[slot * kHeavyGroups + g], v); };
+    auto add = [&](int slot, double v) { atomicAdd(&accs[slot * kHeavyThreads + threadIdx.x], v); };
     double carry = 0.0;                        // of the piece that the group's positions so far leave open
     auto use = [&](const Items &it, int lo, auto crosses) {
         const int c[4] = {it.c.x, it.c.y, it.c.z, it.c.w}, code[4] = {it.d.x, it.d.y, it.d.z, it.d.w};
@@ -482,9 +483,15 @@ __global__ void __launch_bounds__(kHeavyThreads) k_heavy_spmv(const int32_t *__r
             cur = nxt;
         }
     }
-    __builtin_amdgcn_wave_barrier();           // a group's sums are written and read by its own lanes only
+    __syncthreads();
     const int u = j < nu ? unit_of_slot(g * kSlots + wg, j) : nunits;
-    if (u < nunits) partial[(int64_t)x * nunits + units[u].w] = accs[j * kHeavyGroups + g];
+    if (u < nunits) {
+        const double *of = accs + j * kHeavyThreads + g * 8;
+        double s = of[0];
+#pragma unroll
+        for (int l = 1; l < 8; ++l) s += of[l];
+        partial[(int64_t)x * nunits + units[u].w] = s;
+    }
 }
 
 // out[row(h), r] = sum over the units of heavy row h, and over the column ranges, of the partial rows
@@ -673,7 +680,7 @@ hipError_t heavy_spmv(const HeavyPlan &plan, const int32_t *rowmap, const double
     if (attr != hipSuccess) return attr;
     const int nwx = (plan.nwin + kXcd - 1) / kXcd, nsx = (nwx + kSync - 1) / kSync;
     double *pp = (double *)partial;
-    hipLaunchKernelGGL(k_heavy_spmv, dim3(kXcd * kSlots), dim3(kHeavyThreads), (kSpmvColumns + plan.nu * kHeavyGroups) * sizeof(double), st,
+    hipLaunchKernelGGL(k_heavy_spmv, dim3(kXcd * kSlots), dim3(kHeavyThreads), (kSpmvColumns + plan.nu * kHeavyThreads) * sizeof(double), st,
                        (const int32_t *)plan.scrd->ptr, (const int32_t *)plan.scode->ptr, (const double *)plan.sval->ptr,
                        (const int32_t *)plan.block_start->ptr, (const int32_t *)plan.wend->ptr, nsx, nwx, plan.nu,
                        (const int4 *)plan.units->ptr, (int)plan.nunits, xv, ncols, pp);

@@ -76,6 +76,22 @@ def test_sweep_against_the_oracle(comet, layout, ncols, clustered):
     assert torch.equal(y, comet.comet_spmv(A, w))
 
 
+def test_order_of_the_sums_is_fixed(comet):
+    """Sums that rounding tells apart: the nonzeros of a row are large and of both signs, so that another order of the additions
+    gives another result.  The order is the program's, whatever else runs on the device."""
+    n, rows, cols, vals = _matrix(MIN_COLS, True, 7)
+    vals = torch.where(torch.arange(vals.numel(), device="cuda") % 3 == 0, 1e8, 1.0) * vals
+    A = comet.from_levels(fmt.pack_csr(n, MIN_COLS, rows, cols, vals))
+    x = gen.dense_operand(5, 0, (MIN_COLS, 1)).reshape(-1).cuda()
+    y = comet.comet_spmv(A, x)
+    side, noise = torch.cuda.Stream(), torch.ones(1 << 24, device="cuda")
+    for _ in range(20):
+        with torch.cuda.stream(side):
+            noise = noise * 1.0000001
+        assert torch.equal(y, comet.comet_spmv(A, x))
+    side.synchronize()
+
+
 def test_sweep_replays_from_a_captured_graph(comet):
     """After reserve a call only launches kernels; replays, with eager work between them, give the eager result bit for bit."""
     n, rows, cols, vals = _matrix(MIN_COLS, False, 8)
