@@ -191,7 +191,7 @@ __device__ inline void piece_of(const int4 *__restrict__ units, const int32_t *_
 // windows: the most nonzeros any of its 8 groups has there
 __global__ void __launch_bounds__(256) k_window_lengths(const int4 *__restrict__ units, int nunits, int nu,
                                                         const int32_t *__restrict__ wstart, int nwin, int nwx, int nsx,
-                                                        int32_t *__restrict__ wmax) {
+                                                        int32_t *__restrict__ wmax, int *__restrict__ unsorted) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (int64_t)kXcd * kWaves * nsx) return;
     const int iv = (int)(t % nsx), wv = (int)((t / nsx) % kWaves), x = (int)(t / ((int64_t)nsx * kWaves));
@@ -207,6 +207,7 @@ __global__ void __launch_bounds__(256) k_window_lengths(const int4 *__restrict__
                 if (u >= nunits) continue;
                 int lo, hi;
                 piece_of(units, wstart, nwin, u, wabs, &lo, &hi);
+                if (hi < lo) *unsorted = 1;
                 total += hi - lo;
             }
         }
@@ -234,7 +235,7 @@ __global__ void __launch_bounds__(256) k_fill_streams(const int32_t *__restrict_
                                                       const int32_t *__restrict__ wstart, int nwin, int nwx, int nsx,
                                                       const int32_t *__restrict__ wend, const int32_t *__restrict__ block_start,
                                                       int32_t *__restrict__ scrd, int32_t *__restrict__ scode,
-                                                      double *__restrict__ sval) {
+                                                      double *__restrict__ sval, int *__restrict__ unsorted) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (int64_t)kXcd * kWaves * nsx * 8) return;
     const int gl = (int)(t % 8), iv = (int)((t / 8) % nsx), wv = (int)((t / (8 * (int64_t)nsx)) % kWaves),
@@ -256,7 +257,10 @@ __global__ void __launch_bounds__(256) k_fill_streams(const int32_t *__restrict_
             if (u >= nunits) continue;
             int lo, hi;
             piece_of(units, wstart, nwin, u, wabs, &lo, &hi);
-            for (int i = lo; i < hi; ++i, ++p) put(p, crd[i], i + 1 == hi ? k : kNoFlush, vals[i]);
+            for (int i = lo; i < hi; ++i, ++p) {
+                if (crd[i] / kWindow != wabs) *unsorted = 1;
+                put(p, crd[i], i + 1 == hi ? k : kNoFlush, vals[i]);
+            }
         }
     }
     int pend = we[iv + 1];
@@ -542,10 +546,10 @@ hipError_t heavy_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd
     plan = HeavyPlan();
     // worth it only when the dense operand is far larger than the caches and there is real work
     if (nnz < (int64_t(1) << 20) || ncols < (int64_t(1) << 16) || nseg < 1) return hipSuccess;
-    DevRef counters = dev_alloc(3 * sizeof(unsigned long long));
+    DevRef counters = dev_alloc(4 * sizeof(unsigned long long));
     if (!counters) return hipErrorOutOfMemory;
     unsigned long long *cn = (unsigned long long *)counters->ptr;
-    hipError_t e = hipMemsetAsync(cn, 0, 3 * sizeof(unsigned long long), st);
+    hipError_t e = hipMemsetAsync(cn, 0, 4 * sizeof(unsigned long long), st);
     if (e != hipSuccess) return e;
     const unsigned grid = (unsigned)((nseg + 255) / 256);
     hipLaunchKernelGGL(k_count_heavy, dim3(grid), dim3(256), 0, st, pos, nseg, (int32_t)kHeavyLen, cn);
@@ -615,13 +619,18 @@ hipError_t heavy_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd
                        (const int32_t *)plan.hseg->ptr, nheavy, (int)nwin, (int)kWindow, (int32_t *)wstart->ptr);
     const int64_t nlen = (int64_t)nwaves * nsx;
     hipLaunchKernelGGL(k_window_lengths, dim3((unsigned)((nlen + 255) / 256)), dim3(256), 0, st, (const int4 *)plan.units->ptr,
-                       (int)nunits, nu, (const int32_t *)wstart->ptr, (int)nwin, nwx, nsx, (int32_t *)wmax->ptr);
+                       (int)nunits, nu, (const int32_t *)wstart->ptr, (int)nwin, nwx, nsx, (int32_t *)wmax->ptr, (int *)(cn + 3));
     hipLaunchKernelGGL(k_window_ends, dim3((unsigned)((nwaves + 255) / 256)), dim3(256), 0, st, (const int32_t *)wmax->ptr, nsx,
                        (int32_t *)plan.wend->ptr, (int32_t *)nblocks->ptr);
     std::vector<int32_t> nb((size_t)nwaves), bs((size_t)nwaves + 1);
     e = hipMemcpyAsync(nb.data(), nblocks->ptr, sizeof(int32_t) * nwaves, hipMemcpyDeviceToHost, st);
+    // Rows whose columns do not increase, which only the validating checks refuse, cannot be cut into windows: the tiled kernels,
+    // which take them in any order, then do the whole matrix.
+    int unsorted = 0;
+    auto read_unsorted = [&] { return hipMemcpyAsync(&unsorted, cn + 3, sizeof unsorted, hipMemcpyDeviceToHost, st); };
+    if (e == hipSuccess) e = read_unsorted();
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) { plan = HeavyPlan(); return e; }
+    if (e != hipSuccess || unsorted) { plan = HeavyPlan(); return e; }
     int64_t total_blocks = 0;
     for (int k = 0; k < nwaves; ++k) { bs[(size_t)k] = (int32_t)total_blocks; total_blocks += nb[(size_t)k]; }
     bs[(size_t)nwaves] = (int32_t)total_blocks;
@@ -657,9 +666,10 @@ hipError_t heavy_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd
     hipLaunchKernelGGL(k_fill_streams, dim3((unsigned)((nfill + 255) / 256)), dim3(256), 0, st, crd, vals,
                        (const int4 *)plan.units->ptr, (int)nunits, nu, (const int32_t *)wstart->ptr, (int)nwin, nwx, nsx,
                        (const int32_t *)plan.wend->ptr, (const int32_t *)plan.block_start->ptr, (int32_t *)plan.scrd->ptr,
-                       (int32_t *)plan.scode->ptr, (double *)plan.sval->ptr);
-    e = hipStreamSynchronize(st);                                          // the host vectors and the temporaries go out of scope
-    if (e != hipSuccess) { plan = HeavyPlan(); return e; }
+                       (int32_t *)plan.scode->ptr, (double *)plan.sval->ptr, (int *)(cn + 3));
+    e = read_unsorted();
+    if (e == hipSuccess) e = hipStreamSynchronize(st);                     // the host vectors and the temporaries go out of scope
+    if (e != hipSuccess || unsorted) { plan = HeavyPlan(); return e; }
     // all other rows, copied out as a matrix (a matrix made of long rows only needs none)
     if (nseg - nheavy > 0 && nnz - heavy_nnz > 0) {
         e = light_copy_build(pos, nseg, crd, vals, (int32_t)kHeavyLen, rowmap, nseg - nheavy, nnz - heavy_nnz, plan.light, st);

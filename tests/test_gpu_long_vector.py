@@ -112,3 +112,22 @@ def test_sweep_replays_from_a_captured_graph(comet):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, want), "replay %d differs from the eager result" % rep
+
+
+@pytest.mark.parametrize("R", [1, 32])
+def test_columns_in_any_order(comet, R):
+    """The default creation does not check that the columns of a row increase.  Long rows in another order have no windows: the
+    kernels that take any order run, and the result is right."""
+    n, rows, cols, vals = _matrix(MIN_COLS, False, 9)
+    lens = torch.bincount(rows.long(), minlength=n)
+    end = torch.cumsum(lens, 0)
+    p = torch.arange(rows.numel(), device="cuda")
+    back = end[rows.long()] - 1 - (p - (end - lens)[rows.long()])           # every row back to front
+    L = fmt.pack_csr(n, MIN_COLS, rows, cols, vals)
+    L.crd[1], L.vals = cols[back].contiguous(), vals[back].contiguous()
+    A = comet.from_levels(L, comet.COMET_BORROW)
+    assert A.heavy_plan() == (0, 0)
+    B = gen.dense_operand(3, 0, (MIN_COLS, R))
+    got = comet.comet_spmv(A, B.reshape(-1).cuda()) if R == 1 else comet.comet_spmm(A, B.cuda())
+    ref, absum = oracle.spmm(np_(rows), np_(cols), np_(vals), (n, MIN_COLS), np_(B))
+    assert_values_close(np_(got).reshape(n, R), ref, absum, "columns back to front R=%d" % R)
