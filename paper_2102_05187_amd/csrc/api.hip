@@ -20,6 +20,12 @@ using comet::Format;
         if (e_ != hipSuccess) { (void)hipGetLastError(); return COMET_ERR_DEVICE; } \
     } while (0)
 
+// comet_tensor_create; part: the handle holds a part of another one's rows, so that nothing clears the rows it does not store.
+static comet_status create_tensor(comet_tensor **out, int order, const int64_t *dims, const comet_level_t *levels,
+                                  const int32_t *const *pos, const int64_t *pos_len,
+                                  const int32_t *const *crd, const int64_t *crd_len,
+                                  const double *vals, int64_t nvals, unsigned flags, hipStream_t st, bool part);
+
 namespace {
 
 Format classify(int order, const int32_t *lv) {
@@ -63,14 +69,14 @@ static comet_status make_light_handle(comet_tensor &t, const comet::LightCopy &l
     const int32_t *cc[2] = {(const int32_t *)lc.rows->ptr, (const int32_t *)lc.crd->ptr};
     const int64_t pl[2] = {2, lc.nrows + 1}, cl[2] = {lc.nrows, lc.nnz};
     comet_tensor *lh = nullptr;
-    comet_status ls = comet_tensor_create(&lh, 2, dims2, lv, pp, pl, cc, cl, (const double *)lc.vals->ptr, lc.nnz, COMET_LEAN, st);
+    comet_status ls = create_tensor(&lh, 2, dims2, lv, pp, pl, cc, cl, (const double *)lc.vals->ptr, lc.nnz, COMET_LEAN, st, true);
     if (ls != COMET_OK) return ls;
     t.light.reset(lh);
     return COMET_OK;
 }
 
 // Builds the tile tables of the nonzero-tiled kernels for the formats that have them.
-comet_status build_schedule(comet_tensor &t, hipStream_t st) {
+comet_status build_schedule(comet_tensor &t, hipStream_t st, bool part = false) {
     comet::Schedule &sc = t.sched;
     const int tile = comet::kTile;
     int leaf = -1;
@@ -126,7 +132,7 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st) {
         }
         // (optional too: without the memory for the list the whole result is cleared, and so it is where the stored rows do not
         // increase, which only the validating checks refuse)
-        if (t.levels[0] == COMET_CU && t.crd_len[0] <= t.dims[0] && t.crd_len[0] * 2 >= t.dims[0]) {
+        if (!part && t.levels[0] == COMET_CU && t.crd_len[0] <= t.dims[0] && t.crd_len[0] * 2 >= t.dims[0]) {
             HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
             HIP_TRY(comet::check_cu_sorted(t.pos_i(0), 1, t.crd_i(0), t.crd_len[0], (int32_t *)mx->ptr, st));
             rs = read_i32((const int32_t *)mx->ptr, 1, &h, st);
@@ -321,10 +327,10 @@ const char *comet_status_string(comet_status s) {
     return "unknown status";
 }
 
-comet_status comet_tensor_create(comet_tensor **out, int order, const int64_t *dims, const comet_level_t *levels,
-                                 const int32_t *const *pos, const int64_t *pos_len,
-                                 const int32_t *const *crd, const int64_t *crd_len,
-                                 const double *vals, int64_t nvals, unsigned flags, void *stream) {
+static comet_status create_tensor(comet_tensor **out, int order, const int64_t *dims, const comet_level_t *levels,
+                                  const int32_t *const *pos, const int64_t *pos_len,
+                                  const int32_t *const *crd, const int64_t *crd_len,
+                                  const double *vals, int64_t nvals, unsigned flags, hipStream_t st, bool part) {
     if (!out) return COMET_ERR_INVALID_ARG;
     *out = nullptr;
     if (!dims || !levels || !pos || !pos_len || !crd || !crd_len) return COMET_ERR_INVALID_ARG;
@@ -332,7 +338,6 @@ comet_status comet_tensor_create(comet_tensor **out, int order, const int64_t *d
     if (nvals < 0 || nvals >= (int64_t(1) << 31)) return COMET_ERR_INVALID_ARG;
     if (nvals > 0 && !vals) return COMET_ERR_INVALID_ARG;
     if (flags & ~(COMET_COPY | COMET_VALIDATE | COMET_LEAN)) return COMET_ERR_INVALID_ARG;
-    hipStream_t st = (hipStream_t)stream;
 
     comet_tensor *t = new (std::nothrow) comet_tensor();
     if (!t) return COMET_ERR_ALLOC;
@@ -422,10 +427,17 @@ comet_status comet_tensor_create(comet_tensor **out, int order, const int64_t *d
         if (rs != COMET_OK) return rs;
         if (h) return COMET_ERR_BAD_FORMAT;
     }
-    comet_status rs = build_schedule(*t, st);
+    comet_status rs = build_schedule(*t, st, part);
     if (rs != COMET_OK) return rs;
     *out = guard.release();
     return COMET_OK;
+}
+
+comet_status comet_tensor_create(comet_tensor **out, int order, const int64_t *dims, const comet_level_t *levels,
+                                 const int32_t *const *pos, const int64_t *pos_len,
+                                 const int32_t *const *crd, const int64_t *crd_len,
+                                 const double *vals, int64_t nvals, unsigned flags, void *stream) {
+    return create_tensor(out, order, dims, levels, pos, pos_len, crd, crd_len, vals, nvals, flags, (hipStream_t)stream, false);
 }
 
 // Work that uses the handle's arrays may still be in flight: wait for the streams its operations were
