@@ -1049,8 +1049,8 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
                        use_tiled(X, R, B, M, 0, X->sched.max_parent_len) && aligned16(C) &&
                        comet::stream_mttkrp_supports_rank(R);
     // Rows of M whose index is not stored at the root level receive no contribution.  The tiled kernels write every stored
-    // slice's row themselves, so when most rows are stored only the gaps between them are cleared (by the kernel over pieces
-    // itself); otherwise all of M is.
+    // slice's row themselves, so when most rows are stored only the others are cleared: by the kernel over pieces itself where the
+    // gaps between stored rows are short, else from the list made at creation.  Without a list all of M is cleared.
     const int64_t dense_rows = X->dims[1] > X->dims[2] ? X->dims[1] : X->dims[2];
     const bool gaps = tiled && comet::mttkrp_on_pieces(X->sched, dense_rows, R) && gaps_are_short(X, R);
     if (tiled && !gaps && X->sched.unstored) {
@@ -1062,7 +1062,8 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
     }
     if (X->nvals == 0) return COMET_OK;
     if (tiled) {
-        comet_status rs = ensure_scratch(X, comet::mttkrp_scratch_bytes(X->sched, R));
+        // (only what this call takes: on a new handle 2 MB and more cost 100 us that a list on the walk need not pay)
+        comet_status rs = ensure_scratch(X, comet::mttkrp_call_bytes(X->sched, dense_rows, R));
         if (rs != COMET_OK) return rs;
         HIP_TRY(comet::stream_mttkrp(X->sched, X->pos_i(1), X->crd_i(0), X->pos_i(2), X->crd_i(1), X->crd_i(2), X->vals_d(), B, C,
                                      dense_rows, R, M, gaps, X->scratch->ptr, st, ep));

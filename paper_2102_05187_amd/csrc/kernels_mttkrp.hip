@@ -522,6 +522,11 @@ bool mttkrp_on_pieces(const Schedule &sc, int64_t dense_rows, int64_t R) {
     return sc.mttkrp.ntiles > 0 && mttkrp_takes_pieces(sc, R) && dense_rows * R < (int64_t(1) << 32);
 }
 
+size_t mttkrp_call_bytes(const Schedule &sc, int64_t dense_rows, int64_t R) {
+    if (mttkrp_on_pieces(sc, dense_rows, R)) return (size_t)sc.mttkrp.ntiles * (size_t)R * 2 * sizeof(double);
+    return stream_scratch_bytes(sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, R);
+}
+
 size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R) {
     // ranks below R may take the pieces where R does not
     const size_t a = stream_scratch_bytes(sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, R);

@@ -19,14 +19,15 @@
 // and two adjacent summaries combine associatively; a segment that closes at the boundary of two
 // units is final once the left unit contains a segment end.  Tile summaries go to a carry buffer
 // and a small follow-up kernel finishes the segments cut by tile boundaries in a fixed order, so the
-// results do not depend on scheduling (no atomics).
+// results do not depend on scheduling.
 //
 // Kernels:  k_stream_rank1_ldsvec  rank 1, dense vector staged in LDS, one wavefront per 1024-item chunk
 //           k_stream_rank1[_coo]   rank 1, vector gathered through L1, tail-id map per 4096-item tile
 //           k_pieces               rank R, lane groups walk pieces of segments (cut and carried in a way of their own, pieces.hpp)
 //           k_stream_rankR         ranks 8 and 16 over long lists, lane groups walk item runs, per-item records in LDS
 //           k_stream_mttkrp        rank R, two nested segment levels (fibers inside slices)
-//           k_stream_fixup         carry resolution
+//           k_mttkrp_pieces        the same over short lists, lane groups walk pieces of fibers (mttkrp_plan.hpp)
+//           k_stream_fixup, k_stream_fixup_long   carry resolution, for segments over few and over many tiles
 #pragma once
 
 #include "kernels.hpp"
@@ -34,8 +35,8 @@
 
 namespace comet {
 
-// Finishes every segment that a tile boundary cut (defined in kernels_rank1.hip).
 constexpr int kShortChain = 24;        // tiles that a segment is cut over, up to which a thread finishes it alone
+// Finishes every segment that a tile boundary cut (defined in kernels_rank1.hip).
 hipError_t run_fixup(void *scratch, int64_t ntiles, int R, const int32_t *rowmap, double *out, int64_t max_chain,
                      hipStream_t st, Epilogue ep = Epilogue());
 // Rank-R part of stream_segreduce (defined in kernels_rankR.hip).

@@ -4,7 +4,7 @@
 // The leaf level's nonzeros are processed in tiles of kTile consecutive positions regardless of
 // where segment (row / fiber / slice) boundaries fall, so a power-law head segment is spread
 // over many workgroups.  Partial sums of segments cut by a tile boundary go through a small
-// carry buffer in `scratch` and are completed by a fix-up kernel in a fixed order (no atomics,
+// carry buffer in `scratch` and are completed by a fix-up kernel in a fixed order (no sum depends on scheduling,
 // results are reproducible run to run).
 #pragma once
 
@@ -23,7 +23,8 @@ size_t stream_scratch_bytes(int64_t ntiles, int64_t R);
 size_t piece_scratch_bytes(const PiecePlan &plan, int64_t R);
 bool   segreduce_supports(const Schedule &sc, int64_t R);          // false: stream_segreduce would need a plan that is not there
 size_t segreduce_scratch_bytes(const Schedule &sc, int64_t R);     // what stream_segreduce needs
-size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R);        // what stream_mttkrp needs
+size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R);        // what stream_mttkrp needs at ranks up to R
+size_t mttkrp_call_bytes(const Schedule &sc, int64_t dense_rows, int64_t R);   // ... at rank R, with factors of up to dense_rows rows
 
 // out[row(s), :] = sum_{p in segment s} vals[p] * Dn[crd[p], :],  row(s) = rowmap ? rowmap[s] : s.
 // Every segment of the level is written (empty ones with zeros).  dense_rows = number of rows of Dn.
