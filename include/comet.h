@@ -63,8 +63,9 @@ typedef enum {
 #define COMET_COPY     1u   /* the library copies pos/crd/vals into memory it owns              */
 #define COMET_VALIDATE 2u   /* run the device-side structure check (see below)                  */
 #define COMET_LEAN     4u   /* keep no copies of parts of the tensor: the heavy-row sweep of    */
-                            /* comet_spmm and the heavy-fiber sweep of comet_ttm are not planned */
-                            /* (same results from the nonzero-tiled kernels alone, less memory) */
+                            /* comet_spmm and comet_spmv and the heavy-fiber sweep of comet_ttm */
+                            /* are not planned (results from the nonzero-tiled kernels alone,   */
+                            /* the same up to summation order; less memory)                     */
 
 typedef struct comet_tensor comet_tensor;   /* opaque, library-owned */
 
@@ -82,7 +83,8 @@ typedef struct {
     int32_t        mode_of_level[COMET_MAX_ORDER];  /* tensor mode stored at each level: 0,1,2,..
                                                  * unless comet_tensor_reorder chose another order;
                                                  * dims / levels / pos / crd above are per LEVEL    */
-    int64_t        heavy_rows;                /* schedule: rows that comet_spmm hands to its heavy-row sweep  */
+    int64_t        heavy_rows;                /* schedule: rows that comet_spmm hands to its heavy-row sweep, */
+                                              /* and comet_spmv on long vectors when they hold enough nonzeros */
                                               /* (order 3: fibers that comet_ttm hands to its heavy-fiber sweep) */
     int64_t        heavy_nnz;                 /* ... and the nonzeros they hold (both 0: no sweep planned)   */
     int64_t        heavy_stream_bytes;        /* device memory of the sweep's re-ordered copy of those rows   */
@@ -119,8 +121,10 @@ typedef struct {
  * The call also builds the per-tensor schedule (nonzero-balanced tile tables used by the
  * kernels; load imbalance is what Section 8.3 identifies as the main source of slowdown), which
  * is why it synchronises.  On compressed rows or fibers the tables hold 4 bytes and more for each of
- * them, with COMET_LEAN too; without the memory for that part the handle is made all the same, and
- * comet_spmm / comet_ttm run on kernels that do not need it.
+ * them, a [CU,CU,CU] tensor of up to 5 Mi nonzeros has 8 more per fiber (comet_mttkrp), and a compressed
+ * root level that stores at least half of its rows has 4 for each of the others, with COMET_LEAN too;
+ * without the memory for these the handle is made all the same, and the operations run on kernels that
+ * do not need them.
  * Accepted tuples: [D,CU] (CSR), [CU,CU] (DCSR), [CN,S] and [CN,S,S] (COO), [CU,CU,CU] (CSF); results
  * of TTV/TTM may additionally be [CU,CU,D] or [CN,S,D].
  */
@@ -197,15 +201,14 @@ comet_status comet_tensor_convert(const comet_tensor *X, const int32_t *mode_ord
 comet_status comet_spmv(const comet_tensor *A, const double *x, double *y, void *stream);
 
 /* SpMV for callers that cannot allocate device memory: code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc.  Same result as comet_spmv (the same kernels run, but for matrices whose long rows
- * comet_spmv takes from a sweep over a vector of 655 360 and more entries: there the sums are formed in another order), but the
+ * loops, harnesses that forbid hipMalloc.  Same result as comet_spmv (the same kernels run), but the
  * kernels' carry scratch is a static device array of COMET_STATIC_SCRATCH_BYTES inside the library
- * (one copy per GPU, held until the process ends) instead of memory owned by the handle, and the call
- * makes no hipMalloc / hipFree or other allocating call.
+ * (one copy per GPU, held until the process ends, with 1 MiB more for the partial sums of long rows)
+ * instead of memory owned by the handle, and the call makes no hipMalloc / hipFree or other allocating call.
  *   A   order-2 handle, [D,CU] or [CU,CU]; a coordinate list gives COMET_ERR_UNSUPPORTED (its compressed
  *       copy would have to be allocated).
- *   The kernels need about 24.4 bytes of scratch per 1024 nonzeros, so the array covers matrices of up
- *   to about 88 M nonzeros; a larger one gives COMET_ERR_UNSUPPORTED and nothing is enqueued.
+ *   The kernels need about 24 bytes of scratch per 1024 nonzeros, so the array covers matrices of up
+ *   to about 89 M nonzeros; a larger one gives COMET_ERR_UNSUPPORTED and nothing is enqueued.
  *   All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different
  *   streams, different threads) race -- serialise them.  Nothing in the array has to be cleared between
  *   calls (every entry that is read was written by the same call).  The first call on each device looks

@@ -758,7 +758,8 @@ static comet_status ensure_shadow(const comet_tensor *X, hipStream_t st) {
 }
 
 // ---- SpMV / SpMM: the last level is compressed; rows come from a dense or compressed root -------
-// ext_scratch != nullptr: the caller supplies the carry scratch (ext_bytes of it) and nothing may be allocated.
+// ext_scratch != nullptr (R = 1 only): the caller supplies the carry scratch (ext_bytes of it, and kHeavySpmvSums more behind them for
+// the sweep's partial sums) and nothing may be allocated.
 // ep: what the kernels do with a finished element (off: out = A * Dn; on: out = alpha * A * Dn + beta * out).
 static comet_status matrix_product(const comet_tensor *A, const double *Dn, int64_t R, double *out, hipStream_t st,
                                    void *ext_scratch = nullptr, size_t ext_bytes = 0,
@@ -781,12 +782,12 @@ static comet_status matrix_product(const comet_tensor *A, const double *Dn, int6
     const size_t carry = tiled ? comet::segreduce_scratch_bytes(A->sched, R) : 0;
     // The heavy-row sweep pays when the dense operand is much larger than the L2 caches (else its rows are
     // cache hits anyway) and the long rows hold a good share of the nonzeros (decided when the plan was built).
-    const bool heavy = tiled && !ext_scratch && A->variant != 3 && A->sched.heavy.nunits > 0 &&
+    const bool heavy = tiled && A->variant != 3 && A->sched.heavy.nunits > 0 &&
                        (R == 1 ? long_vector_sweep_pays(A)
                                : A->dims[1] * R * 8 >= (int64_t(16) << 20) && R <= 64 && comet::heavy_supports(A->sched.heavy, R)) &&
                        (!A->light || comet::segreduce_supports(A->light->sched, R));
     const size_t need = carry + (heavy ? comet::heavy_partial_bytes(A->sched.heavy, R) : 0);
-    if (ext_scratch && need > ext_bytes) return COMET_ERR_UNSUPPORTED;       // before anything is enqueued
+    if (ext_scratch && carry > ext_bytes) return COMET_ERR_UNSUPPORTED;      // before anything is enqueued
     const int32_t *rowmap = nullptr;
     if (A->fmt == Format::DCSR) {
         // Rows absent from the root level hold no nonzeros and must come out as zeros.  Every stored row is
@@ -817,13 +818,18 @@ static comet_status matrix_product(const comet_tensor *A, const double *Dn, int6
             // (whose rows carry their result rows, DCSR's included)
             const comet_tensor *Lh = A->light.get();
             if (Lh && Lh->sched.ntiles > 0) {
-                comet_status rs = ensure_scratch(Lh, comet::segreduce_scratch_bytes(Lh->sched, R));
-                if (rs != COMET_OK) return rs;
+                void *light_scr = ext_scratch;                     // (the copy has no more chunks than the matrix, and A's carry is not used)
+                if (!ext_scratch) {
+                    comet_status rs = ensure_scratch(Lh, comet::segreduce_scratch_bytes(Lh->sched, R));
+                    if (rs != COMET_OK) return rs;
+                    light_scr = Lh->scratch->ptr;
+                }
                 HIP_TRY(comet::stream_segreduce(Lh->sched, Lh->pos_i(1), Lh->crd_i(1), Lh->vals_d(), Lh->crd_i(0), Dn,
-                                                A->dims[1], R, out, Lh->scratch->ptr, false, st, ep));
+                                                A->dims[1], R, out, light_scr, false, st, ep));
             }
-            if (R == 1) HIP_TRY(comet::heavy_spmv(A->sched.heavy, rowmap, Dn, A->dims[1], out, (char *)scr + carry, st, ep));
-            else HIP_TRY(comet::heavy_spmm(A->sched.heavy, rowmap, Dn, R, out, (char *)scr + carry, st, ep));
+            void *sums = (char *)scr + (ext_scratch ? ext_bytes : carry);
+            if (R == 1) HIP_TRY(comet::heavy_spmv(A->sched.heavy, rowmap, Dn, A->dims[1], out, sums, st, ep));
+            else HIP_TRY(comet::heavy_spmm(A->sched.heavy, rowmap, Dn, R, out, sums, st, ep));
             return COMET_OK;
         }
         HIP_TRY(comet::stream_segreduce(A->sched, A->pos_i(1), A->crd_i(1), A->vals_d(), rowmap, Dn, A->dims[1], R, out,
@@ -873,10 +879,11 @@ comet_status comet_spmm_axpby(const comet_tensor *A, double alpha, const double 
 }
 
 // ---- SpMV for callers that cannot allocate --------------------------------------------------------
-// The carry scratch of the tiled kernels lives in this array instead of in memory owned by the handle.
+// The carry scratch of the tiled kernels, and behind it the partial sums of the sweep over long rows, live in this array instead
+// of in memory owned by the handle.
 // Every GPU the library runs on holds its own copy at its own address: host code must go through the
 // address that hipGetSymbolAddress returns for the current device, never through the array's name.
-static __device__ __align__(256) unsigned char g_static_scratch[COMET_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char g_static_scratch[COMET_STATIC_SCRATCH_BYTES + comet::kHeavySpmvSums];
 
 static void *static_scratch_of_current_device(hipError_t *err) {
     static std::mutex mu;

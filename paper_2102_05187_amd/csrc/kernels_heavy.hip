@@ -392,6 +392,7 @@ __global__ void __launch_bounds__(kHeavyThreads) k_heavy_sweep(const int32_t *__
 // vector L1 alone takes 194; gathering through the L1 here too, from the eighth of x in the XCD's L2, took 106.  Reading the next
 // interval's part ahead into registers (81), or super-blocks three ahead (91), costs more than it hides.
 constexpr int kSpmvColumns = kSync * kWindow;                      // of an interval
+static_assert((size_t)kXcd * kMaxUnitsPerGroup * kGroupSlots * sizeof(double) <= kHeavySpmvSums, "partial sums of all units");
 static_assert((kSpmvColumns + kMaxUnitsPerGroup * kHeavyThreads) * sizeof(double) <= 160 * 1024, "LDS of a compute unit");
 __global__ void __launch_bounds__(kHeavyThreads) k_heavy_spmv(const int32_t *__restrict__ scrd, const int32_t *__restrict__ scode,
                                                               const double *__restrict__ sval, const int32_t *__restrict__ block_start,

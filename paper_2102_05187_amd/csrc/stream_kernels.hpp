@@ -53,7 +53,8 @@ size_t heavy_partial_bytes(const HeavyPlan &plan, int64_t R);
 hipError_t heavy_spmm(const HeavyPlan &plan, const int32_t *rowmap, const double *Dn, int64_t R, double *out, void *partial,
                       hipStream_t st, Epilogue ep = Epilogue());
 
-// The same for one column; `partial` holds heavy_partial_bytes(plan, 1).
+// The same for one column; `partial` holds heavy_partial_bytes(plan, 1), which is never more than kHeavySpmvSums.
+constexpr size_t kHeavySpmvSums = 1 << 20;
 hipError_t heavy_spmv(const HeavyPlan &plan, const int32_t *rowmap, const double *x, int64_t ncols, double *out, void *partial,
                       hipStream_t st, Epilogue ep = Epilogue());
 

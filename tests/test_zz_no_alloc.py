@@ -10,6 +10,8 @@ import torch
 import oracle
 from synth import formats as fmt
 from synth import generate as gen
+from test_gpu_long_vector import MIN_COLS, _line
+from test_gpu_long_vector import _matrix as _sweep_matrix
 from util import assert_values_close, np_
 
 pytestmark = pytest.mark.gpu
@@ -67,6 +69,35 @@ def test_small_problem_on_the_automatic_path(comet):
     torch.cuda.synchronize()
     ref, absum = oracle.spmv(np_(rows), np_(cols), np_(vals), (n, n), np_(c["x"]))
     assert_values_close(np_(y), ref, absum, "spmv_static config 1")
+
+
+@pytest.mark.parametrize("layout", ["csr", "dcsr"])
+def test_long_rows_take_the_same_kernels(comet, layout):
+    """Matrices whose long rows comet_spmv takes from a sweep over a long vector: bit for bit the same here, and nothing is
+    allocated, which a capture on a new handle would refuse."""
+    ncols = MIN_COLS
+    n, rows, cols, vals = _sweep_matrix(ncols, False, 11)
+    L = (fmt.pack_csr if layout == "csr" else fmt.pack_dcsr)(n, ncols, rows, cols, vals)
+    x = gen.dense_operand(3, 0, (ncols, 1)).reshape(-1).to(DEV)
+    A = comet.from_levels(L)
+    assert A.heavy_plan()[1] >= _line(ncols)
+    got = torch.full((n,), float("nan"), dtype=torch.float64, device=DEV)
+    small = comet.from_levels(fmt.pack_csr(2, 2, torch.tensor([0, 1], device=DEV), torch.tensor([0, 1], device=DEV), torch.ones(2, dtype=torch.float64, device=DEV)))
+    comet.comet_spmv_static(small, torch.ones(2, dtype=torch.float64, device=DEV), torch.zeros(2, dtype=torch.float64, device=DEV))
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        comet.comet_spmv_static(A, x, got)
+    want = comet.comet_spmv(A, x)
+    plain = comet.comet_spmv(A.set_variant(3), x)
+    assert not torch.equal(want, plain)                # the sweep ran
+    for rep in range(3):
+        got.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), "replay %d" % rep
 
 
 def test_rejects_what_does_not_fit_and_coordinate_lists(comet):
