@@ -289,7 +289,8 @@ const char *comet_status_string(comet_status s);
 /* Choose the kernel family used by later operations on this handle: 0 = automatic,
  * 1 = the simple one-lane-group-per-segment kernels, 2 = the nonzero-tiled streaming kernels with
  * all their specialisations, 3 = the nonzero-tiled kernels in their plain per-tile form only (no
- * operand staging in LDS, no heavy-row sweep): the baseline the specialisations are measured against.
+ * operand staging in LDS, no heavy-row sweep, MTTKRP by the walk over nonzeros at every size): the
+ * baseline the specialisations are measured against.
  * For testing and measurement; results are the same up to summation order. */
 comet_status comet_tensor_set_variant(comet_tensor *t, int variant);
 

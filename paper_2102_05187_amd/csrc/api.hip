@@ -1059,7 +1059,8 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
     // slice's row themselves, so when most rows are stored only the others are cleared: by the kernel over pieces itself where the
     // gaps between stored rows are short, else from the list made at creation.  Without a list all of M is cleared.
     const int64_t dense_rows = X->dims[1] > X->dims[2] ? X->dims[1] : X->dims[2];
-    const bool gaps = tiled && comet::mttkrp_on_pieces(X->sched, dense_rows, R) && gaps_are_short(X, R);
+    const bool pieces = tiled && X->variant != 3 && comet::mttkrp_on_pieces(X->sched, dense_rows, R);
+    const bool gaps = pieces && gaps_are_short(X, R);
     if (tiled && !gaps && X->sched.unstored) {
         HIP_TRY(clear_unstored_rows(X, R, M, ep.on ? ep.beta : 0.0, st));
     } else if (!gaps) {
@@ -1070,10 +1071,10 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
     if (X->nvals == 0) return COMET_OK;
     if (tiled) {
         // (only what this call takes: on a new handle 2 MB and more cost 100 us that a list on the walk need not pay)
-        comet_status rs = ensure_scratch(X, comet::mttkrp_call_bytes(X->sched, dense_rows, R));
+        comet_status rs = ensure_scratch(X, comet::mttkrp_call_bytes(X->sched, R, pieces));
         if (rs != COMET_OK) return rs;
         HIP_TRY(comet::stream_mttkrp(X->sched, X->pos_i(1), X->crd_i(0), X->pos_i(2), X->crd_i(1), X->crd_i(2), X->vals_d(), B, C,
-                                     dense_rows, R, M, gaps, X->scratch->ptr, st, ep));
+                                     dense_rows, R, M, pieces, gaps, X->scratch->ptr, st, ep));
         return COMET_OK;
     }
     HIP_TRY(comet::simple_mttkrp(X->pos_i(1), X->crd_i(0), X->pos_len[1] - 1, X->pos_i(2), X->crd_i(1), X->crd_i(2),

@@ -522,8 +522,8 @@ bool mttkrp_on_pieces(const Schedule &sc, int64_t dense_rows, int64_t R) {
     return sc.mttkrp.ntiles > 0 && mttkrp_takes_pieces(sc, R) && dense_rows * R < (int64_t(1) << 32);
 }
 
-size_t mttkrp_call_bytes(const Schedule &sc, int64_t dense_rows, int64_t R) {
-    if (mttkrp_on_pieces(sc, dense_rows, R)) return (size_t)sc.mttkrp.ntiles * (size_t)R * 2 * sizeof(double);
+size_t mttkrp_call_bytes(const Schedule &sc, int64_t R, bool pieces) {
+    if (pieces) return (size_t)sc.mttkrp.ntiles * (size_t)R * 2 * sizeof(double);
     return stream_scratch_bytes(sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, R);
 }
 
@@ -536,13 +536,13 @@ size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R) {
 
 hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, const int32_t *pos3, const int32_t *crd2,
                          const int32_t *crd3, const double *vals, const double *B, const double *C, int64_t dense_rows, int64_t R,
-                         double *M, bool gaps, void *scratch, hipStream_t st, Epilogue ep) {
+                         double *M, bool pieces, bool gaps, void *scratch, hipStream_t st, Epilogue ep) {
     if (sc.ntiles <= 0) return hipSuccess;
     if (!stream_mttkrp_supports_rank(R) || !sc.slice_begin) return hipErrorNotSupported;
     const MttkrpPlan &plan = sc.mttkrp;
     double *head = (double *)scratch, *tail = head + plan.ntiles * R;
     const MtArgs a{plan, pos2, crd1, pos3, crd2, crd3, vals, B, C, M, sc.nnz, (int)R, gaps ? 1 : 0, head, tail, st, ep};
-    if (mttkrp_on_pieces(sc, dense_rows, R)) {
+    if (pieces) {
         const bool wide = dense_rows * R * 8 >= (int64_t(1) << 32);   // row offsets in bytes no longer fit 32 bits
         const hipError_t e = COMET_DISPATCH_BLOCKS(launch_mttkrp, a.R, wide, a);
         if (e != hipSuccess || plan.ncut + plan.ncut_long == 0) return e;

@@ -38,10 +38,10 @@ def _tensor(slices):
     return dims, (2 * slice_of + 1)[fiber].int(), (3 * f_in)[fiber].int(), k.int(), vals
 
 
-def _check(comet, slices, R):
+def _check(comet, slices, R, variant=2):
     dims, i, j, k, vals = _tensor(slices)
     print("mttkrp tiles R=%d nnz=%d" % (R, vals.numel()), flush=True)
-    X = comet.from_levels(fmt.pack_csf3(dims, i, j, k, vals).to("cuda")).set_variant(2)
+    X = comet.from_levels(fmt.pack_csf3(dims, i, j, k, vals).to("cuda")).set_variant(variant)
     B, C, old = (gen.dense_operand(5, n, (d, R)) for n, d in ((0, dims[1]), (1, dims[2]), (2, dims[0])))
     ref, absum = oracle.mttkrp(np_(i), np_(j), np_(k), np_(vals), dims, np_(B), np_(C))
     M = torch.full((dims[0], R), float("nan"), dtype=torch.float64, device="cuda")
@@ -53,19 +53,21 @@ def _check(comet, slices, R):
     assert_values_close(np_(D), 0.75 * ref - 0.5 * np_(old), 0.75 * absum + 0.5 * np.abs(np_(old)), "axpby R=%d" % R)
 
 
+@pytest.mark.parametrize("variant", [2, 3])                              # pieces up to rank 33, and the walk
 @pytest.mark.parametrize("R", [1, 3, 8, 10, 16, 20, 32, 33, 48, 64, 96, 128])
-def test_edges_of_chunks(comet, R):
-    _check(comet, EDGES, R)
+def test_edges_of_chunks(comet, R, variant):
+    _check(comet, EDGES, R, variant)
 
 
+@pytest.mark.parametrize("variant", [2, 3])                              # the line is the walk's; at this rank pieces take both sides
 @pytest.mark.parametrize("nnz", [LINE - 1, LINE])
-def test_both_sides_of_the_size_rule(comet, nnz):
+def test_both_sides_of_the_size_rule(comet, nnz, variant):
     each = [700, 3, 1, 5000, 40]
     n = nnz // sum(each)
     slices = [each] * n
     if nnz - n * sum(each):
         slices = slices + [[nnz - n * sum(each)]]
-    _check(comet, slices, 10)
+    _check(comet, slices, 10, variant)
 
 
 # nonzeros up to which lists take the pieces, by what the rule sees: short slices of several nonzeros per fiber, the same behind a
@@ -159,15 +161,14 @@ def test_factors_whose_offsets_leave_32_bits(comet, R, level, values):
     assert_values_close(np_(M), ref, absum, "wide factor R=%d level=%d" % (R, level))
 
 
-@pytest.mark.parametrize("R", [33, 42, 64, 100, 128])
+@pytest.mark.parametrize("R", [1, 7, 16, 20, 33, 42, 64, 100, 128])
 def test_slices_over_many_tiles_of_the_walk(comet, R):
     """Slices cut over 64 and more tiles of the walk, whose partial sums a workgroup adds up per block of 16 columns: at ranks
     whose last block leaves threads idle, at several slices in a row, and with short slices between them."""
     long_slice = [300] * 280                                            # 84 000 nonzeros: 82 chunks of 1024
     slices = [long_slice, [1], long_slice, [7, 2000, 1], long_slice, long_slice, [3] * 300, [66_000], long_slice * 2, [1023], long_slice * 3, [5]]
-    n = sum(map(sum, slices))
-    assert 9 << 18 < n * -(-R // 16) and n < LINE                       # beyond the pieces, in chunks
-    _check(comet, slices, R)
+    assert sum(map(sum, slices)) < LINE                                 # in chunks
+    _check(comet, slices, R, 3)
 
 
 @pytest.mark.parametrize("op", ["ttv", "ttv_coo", "spmv"])

@@ -522,7 +522,7 @@ def test_empty_slices_and_fibers_are_accepted_and_contribute_nothing(comet):
 def test_operations_replay_from_a_captured_graph(comet):
     """After a first (allocating) call every operation only enqueues kernels, so it can be captured into a
     HIP graph; each replay -- with eager work and synchronisations in between -- must reproduce the eager
-    result bit for bit (the kernels use no atomics and clear their scratch themselves)."""
+    result bit for bit (no sum depends on scheduling, and the kernels clear their scratch themselves)."""
     (n, m), (rows, cols, vals) = MATRIX_CASES["zipf_rows"]
     A = comet.from_levels(fmt.pack_csr(n, m, rows, cols, vals).to("cuda"))
     dims, (i, j, k, tv) = TENSOR_CASES["zipf_mttkrp"]
