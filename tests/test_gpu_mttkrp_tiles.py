@@ -25,21 +25,23 @@ def comet():
     return c
 
 
-def _tensor(slices):
-    """Slice s is stored at coordinate 2 s + 1; fiber f of a slice at 3 f; coordinates of a fiber are consecutive."""
+def _tensor(slices, root=None):
+    """Slice s is stored at coordinate 2 s + 1, or at root[s] of root[-1] rows; fiber f of a slice at 3 f; coordinates of a fiber are
+    consecutive.  Half of the rows are stored, which is when the others are cleared one by one."""
     nfib = torch.tensor([len(s) for s in slices])
     lens = torch.tensor([n for s in slices for n in s])
     slice_of = torch.repeat_interleave(torch.arange(len(slices)), nfib)
     f_in = torch.arange(lens.numel()) - (torch.cumsum(nfib, 0) - nfib)[slice_of]
     fiber = torch.repeat_interleave(torch.arange(lens.numel()), lens)
     k = torch.arange(fiber.numel()) - (torch.cumsum(lens, 0) - lens)[fiber]
-    dims = (2 * len(slices) + 1, 3 * int(nfib.max()), int(lens.max()))
+    root = torch.cat([2 * torch.arange(len(slices)) + 1, torch.tensor([2 * len(slices)])]) if root is None else torch.tensor(root)
+    dims = (int(root[-1]), 3 * int(nfib.max()), int(lens.max()))
     vals = gen.dense_operand(9, 0, (fiber.numel(), 1)).reshape(-1)
-    return dims, (2 * slice_of + 1)[fiber].int(), (3 * f_in)[fiber].int(), k.int(), vals
+    return dims, root[slice_of][fiber].int(), (3 * f_in)[fiber].int(), k.int(), vals
 
 
-def _check(comet, slices, R, variant=2):
-    dims, i, j, k, vals = _tensor(slices)
+def _check(comet, slices, R, variant=2, root=None):
+    dims, i, j, k, vals = _tensor(slices, root)
     print("mttkrp tiles R=%d nnz=%d" % (R, vals.numel()), flush=True)
     X = comet.from_levels(fmt.pack_csf3(dims, i, j, k, vals).to("cuda")).set_variant(variant)
     B, C, old = (gen.dense_operand(5, n, (d, R)) for n, d in ((0, dims[1]), (1, dims[2]), (2, dims[0])))
@@ -86,11 +88,40 @@ def test_both_sides_of_the_rules_for_pieces(comet, shape, R, line, more):
     _check(comet, first + [each] * n + ([[rest - n * sum(each)]] if rest - n * sum(each) else []), R)
 
 
+@pytest.mark.parametrize("variant", [2, 3])
+@pytest.mark.parametrize("R", [1, 6, 10, 16, 35])
+@pytest.mark.parametrize("longest", [40, 600])
+def test_rows_between_stored_slices(comet, R, longest, variant):
+    """Rows that are not stored, in runs of 1, 2, 40 and more, in front of the first slice, behind the last, and in front of slices of
+    every kind: in one record, in several (more than 16 pieces), cut by a tile boundary, over many tiles.  With beta each of them has
+    to be scaled exactly once, and an infinite alpha must not reach them.  (longest 600: too long a run for the kernel over pieces
+    to clear at ranks from 10 on.)"""
+    kinds = [[3], [1] * 20, [40, 1, 2], [1] * 50, [300, 7], [17, 16, 33, 1], [1], [2] * 200]
+    slices = [kinds[(s * s + s // 3) % len(kinds)] for s in range(1200)] + [[500] * 40, [1] * 3, [90] * 9]
+    gaps = [longest if s == 77 else 40 if s == 400 else (0, 0, 1, 0, 2, 0, 0)[s % 7] for s in range(len(slices))]
+    gaps[0], gaps[-3] = 3, 2
+    root, at = [], -1
+    for gap in gaps:
+        at += gap + 1
+        root.append(at)
+    root.append(at + 1 + 5)                                             # rows of M
+    assert 2 * len(slices) >= root[-1]
+    _check(comet, slices, R, variant, root)
+    dims, i, j, k, vals = _tensor(slices, root)
+    X = comet.from_levels(fmt.pack_csf3(dims, i, j, k, vals).to("cuda")).set_variant(variant)
+    B, C, old = (gen.dense_operand(5, n, (d, R)) for n, d in ((0, dims[1]), (1, dims[2]), (2, dims[0])))
+    D = old.to("cuda")
+    comet.comet_mttkrp_axpby(X, 0, float("inf"), [None, B.to("cuda"), C.to("cuda")], -0.5, D)
+    none = np.ones(dims[0], dtype=bool)
+    none[root[:-1]] = False
+    assert np.array_equal(np_(D)[none], -0.5 * np_(old)[none])
+
+
 @pytest.mark.parametrize("R", [1, 6, 16, 35])
 @pytest.mark.parametrize("stored_every", [1, 3])
 def test_fibers_and_slices_without_nonzeros(comet, R, stored_every):
     """Runs of empty fibers and of slices without fibers, long enough to fill tiles of the pieces, at either end and between
-    nonzeros; with the rows between the stored slices cleared by gaps (1) or all together (3).  An infinite alpha must not
+    nonzeros; with the rows behind the last slice cleared by a gap (1), or all rows together (3).  An infinite alpha must not
     reach rows that receive nothing."""
     g = torch.Generator().manual_seed(R)
     slices = []
