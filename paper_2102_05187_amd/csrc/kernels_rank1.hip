@@ -586,10 +586,10 @@ bool stream_supports_coo() { return true; }
 size_t stream_scratch_bytes(int64_t ntiles, int64_t R) { return carry_bytes(ntiles < 1 ? 1 : ntiles, R) + 256; }
 
 // Which walk: the pieces, except for ranks 8 and 16 over many nonzeros, where the walk over whole tiles of nonzeros keeps more
-// of a list of short segments in flight.  Whole calls on the walk and on the pieces: TTM at rank 16, 100 M nonzeros in 6.5 M
-// fibers (36 M of them off the sweep) 742 and 793 us, in 15 M fibers 999 and 1085; 15 M nonzeros in 3 M fibers 184 and 187.
-// The line sees only the size: SpMM on 11 M nonzeros near the diagonal, rank 16, takes 203 and 145, on 20 M in rows of 40 at
-// random 407 and 397.
+// of a list of short fibers in flight.  Whole calls on the walk and on the pieces, rank 16: TTM on 100 M nonzeros in 6.5 M fibers
+// (36 M of them off the sweep) 734 and 768 us, 15 M 198 and 198.  The line sees only the size, and lists with longer segments or with
+// reuse lose by it: SpMM, ranks 8 and 16, 11 M nonzeros, 12 per row, within 2000 columns of the diagonal 187 / 224 and 86 / 131, anywhere
+// 240 / 250 and 218 / 239; 16 M in 1 to 100 per row 333 / 343 and 307 / 333; 19 M in power-law rows near the diagonal 158 / 228 and 134 / 161.
 static bool takes_walk(const Schedule &sc, int64_t R) { return sc.nnz >= kWalkNnz && (R == 8 || R == 16); }
 
 bool segreduce_supports(const Schedule &sc, int64_t R) {
