@@ -523,17 +523,17 @@ __global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64
         if (newest >= 0) { from = newest; break; }
     }
     double v = 0.0;
-    if (lane < lanes) {
-        int64_t u = from + lane;
-        for (; u + 15 * (int64_t)lanes < t; u += 16 * (int64_t)lanes) {
+    if (lane < lanes)
+        for (int64_t u = from + lane; u < t; u += 16 * (int64_t)lanes) {
             double x[16];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) x[q] = cb.open[(u + q * (int64_t)lanes) * R + r];
+            for (int q = 0; q < 16; ++q) {                        // (none under a condition: a last round would go one by one)
+                const int64_t w = u + q * (int64_t)lanes;
+                x[q] = cb.open[(w < t ? w : t - 1) * R + r];
+            }
 #pragma unroll
-            for (int q = 0; q < 16; ++q) v += x[q];
+            for (int q = 0; q < 16; ++q) v += u + q * (int64_t)lanes < t ? x[q] : 0.0;
         }
-        for (; u < t; u += lanes) v += cb.open[u * R + r];
-    }
     sums[threadIdx.x] = v;
     for (int k = lanes; k > 1;) {
         const int h = (k + 1) / 2;
