@@ -390,7 +390,8 @@ __global__ void __launch_bounds__(kHeavyThreads) k_heavy_sweep(const int32_t *__
 // address, so that the order of every sum is the program's (the atomic is only the form of an add that nothing waits for).
 // 1 M x 1 M, 18.5 M nonzeros, 13.9 M of them in 13 700 rows: 78 us here, 60 for the other rows, 145 a call where the walk through the
 // vector L1 alone takes 194; gathering through the L1 here too, from the eighth of x in the XCD's L2, took 106.  Reading the next
-// interval's part ahead into registers (81), or super-blocks three ahead (91), costs more than it hides.
+// interval's part ahead into registers (81), or super-blocks three ahead (91), costs more than it hides.  The LDS is at work for a
+// fifth of the kernel's cycles, a ninth of those for bank conflicts; 40 % of the wavefronts' time goes into waiting for loads.
 constexpr int kSpmvColumns = kSync * kWindow;                      // of an interval
 static_assert((size_t)kXcd * kMaxUnitsPerGroup * kGroupSlots * sizeof(double) <= kHeavySpmvSums, "partial sums of all units");
 static_assert((kSpmvColumns + kMaxUnitsPerGroup * kHeavyThreads) * sizeof(double) <= 160 * 1024, "LDS of a compute unit");

@@ -454,21 +454,24 @@ __global__ void __launch_bounds__(256) k_stream_fixup(void *scratch, int64_t nti
 }
 
 // The same for longer chains (the head slice of a power-law tensor is cut over thousands of tiles): eight summaries at a time,
-// whose loads do not depend on what they hold, and from kFixSerial tiles on the whole workgroup.  A workgroup finishes kFixTiles
-// tiles in a block of up to 16 columns: no more tiles, since two chains that long cannot end among so few of them, and no more
-// columns, so that 64 threads and more share the tiles of a chain at every rank.  Whole calls with a launch per level of 64 summaries,
-// which took two to four, with workgroups of 1024 threads' worth of tiles and all columns, and now: TTV of 12 M nonzeros in 40
-// fibers 70 / 103 / 67.5 us; MTTKRP at rank 64, one slice of 37 M, 1581 / 1630 / 1590; rank 128, two slices of 18 M in all, 2042 / 2047 /
-// 2030; 20 M in power-law slices, rank 64, 815 / 771 / 772.
+// whose loads do not depend on what they hold, and from kFixSerial tiles on the whole workgroup, sixteen at a time per thread.
+// A workgroup finishes up to kFixTiles tiles, among which no two chains that long can end, in a block of columns: whole rows (150 M
+// nonzeros, rank 64, 36 600 tiles: 59 us, in blocks of 16 columns 69), but 16 columns where one chain may hold an eighth of all
+// tiles, so that 64 threads and more share it at every rank.  Whole calls with a launch per level of 64 summaries, which took two
+// to four, with workgroups of 1024 threads' worth of tiles in whole rows always, and now: TTV of 12 M nonzeros in 40 fibers
+// 69 / 103 / 67 us; MTTKRP at rank 64, one slice of 37 M, 1575 / 1630 / 1581; rank 128, two slices of 18 M in all, 2024 / 2047 / 2017;
+// 20 M in power-law slices, rank 64, 815 / 771 / 773; 150 M, rank 16, 1641 / 1605 / 1605.
 constexpr int kFixSerial = 64, kFixTiles = 64, kFixColumns = 16;
-static_assert(kFixTiles <= kFixSerial && kFixTiles * kFixColumns <= 1024, "one long chain per workgroup, a thread per tile and column");
-__global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64_t ntiles, int R, const int32_t *__restrict__ rowmap,
-                                                       double *__restrict__ out, Epilogue ep) {
+static_assert(kFixTiles <= kFixSerial, "one long chain per workgroup");
+__host__ __device__ inline int fix_tiles(int block) { return 1024 / block < kFixTiles ? 1024 / block : kFixTiles; }   // a thread per tile and column
+__global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64_t ntiles, int R, int block,
+                                                       const int32_t *__restrict__ rowmap, double *__restrict__ out, Epilogue ep) {
     __shared__ double sums[1024];
     __shared__ int chain, newest;
     const CarryView cb = carry_view(scratch, ntiles, R);
-    const int64_t nblocks = (ntiles + kFixTiles - 1) / kFixTiles;
-    const int c0 = (int)(blockIdx.x / nblocks) * kFixColumns, cols = R - c0 < kFixColumns ? R - c0 : kFixColumns;
+    const int tiles = fix_tiles(block);
+    const int64_t nblocks = (ntiles + tiles - 1) / tiles;
+    const int c0 = (int)(blockIdx.x / nblocks) * block, cols = R - c0 < block ? R - c0 : block;
     const int lanes = 1024 / cols, lane = (int)threadIdx.x / cols, col = (int)threadIdx.x - lane * cols, r = c0 + col;
     if (threadIdx.x == 0) chain = -1;
     __syncthreads();
@@ -477,8 +480,8 @@ __global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64
         double *o = out + (rowmap ? (int64_t)rowmap[id] : (int64_t)id) * R + r;
         *o = ep_apply(ep, v, o);
     };
-    const int64_t t0 = (int64_t)(blockIdx.x % nblocks) * kFixTiles, mine = t0 + lane;
-    if (lane < kFixTiles && mine < ntiles && cb.has_tail[mine]) {
+    const int64_t t0 = (int64_t)(blockIdx.x % nblocks) * tiles, mine = t0 + lane;
+    if (lane < tiles && mine < ntiles && cb.has_tail[mine]) {
         double v = cb.first[mine * R + r];
         bool done = false;
         int64_t u = mine - 1;
@@ -553,8 +556,9 @@ hipError_t run_fixup(void *scratch, int64_t ntiles, int R, const int32_t *rowmap
     if (max_chain > 0 && max_chain <= kShortChain) {
         hipLaunchKernelGGL(k_stream_fixup, dim3((unsigned)((ntiles * R + 255) / 256)), dim3(256), 0, st, scratch, ntiles, R, rowmap, out, ep);
     } else {
-        const int64_t blocks = (ntiles + kFixTiles - 1) / kFixTiles * ((R + kFixColumns - 1) / kFixColumns);
-        hipLaunchKernelGGL(k_stream_fixup_long, dim3((unsigned)blocks), dim3(1024), 0, st, scratch, ntiles, R, rowmap, out, ep);
+        const int block = max_chain <= 0 || max_chain * 8 > ntiles ? kFixColumns : R, tiles = fix_tiles(block);
+        const int64_t blocks = (ntiles + tiles - 1) / tiles * ((R + block - 1) / block);
+        hipLaunchKernelGGL(k_stream_fixup_long, dim3((unsigned)blocks), dim3(1024), 0, st, scratch, ntiles, R, block, rowmap, out, ep);
     }
     return hipGetLastError();
 }
