@@ -456,11 +456,11 @@ __global__ void __launch_bounds__(256) k_stream_fixup(void *scratch, int64_t nti
 // The same for longer chains (the head slice of a power-law tensor is cut over thousands of tiles): eight summaries at a time,
 // whose loads do not depend on what they hold, and from kFixSerial tiles on the whole workgroup, sixteen at a time per thread.
 // A workgroup finishes up to kFixTiles tiles, among which no two chains that long can end, in a block of columns: whole rows (150 M
-// nonzeros, rank 64, 36 600 tiles: 59 us, in blocks of 16 columns 69), but 16 columns where one chain may hold an eighth of all
+// nonzeros, rank 64, 36 600 tiles: 58 us, in blocks of 16 columns 69), but 16 columns where one chain may hold an eighth of all
 // tiles, so that 64 threads and more share it at every rank.  Whole calls with a launch per level of 64 summaries, which took two
 // to four, with workgroups of 1024 threads' worth of tiles in whole rows always, and now: TTV of 12 M nonzeros in 40 fibers
 // 69 / 103 / 67 us; MTTKRP at rank 64, one slice of 37 M, 1575 / 1630 / 1581; rank 128, two slices of 18 M in all, 2024 / 2047 / 2017;
-// 20 M in power-law slices, rank 64, 815 / 771 / 773; 150 M, rank 16, 1641 / 1605 / 1605.
+// 20 M in power-law slices, rank 64, 815 / 774 / 772; 150 M, rank 16, 1641 / 1603 / 1601.
 constexpr int kFixSerial = 64, kFixTiles = 64, kFixColumns = 16;
 static_assert(kFixTiles <= kFixSerial, "one long chain per workgroup");
 __host__ __device__ inline int fix_tiles(int block) { return 1024 / block < kFixTiles ? 1024 / block : kFixTiles; }   // a thread per tile and column
@@ -469,9 +469,7 @@ __global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64
     __shared__ double sums[1024];
     __shared__ int chain, newest;
     const CarryView cb = carry_view(scratch, ntiles, R);
-    const int tiles = fix_tiles(block);
-    const int64_t nblocks = (ntiles + tiles - 1) / tiles;
-    const int c0 = (int)(blockIdx.x / nblocks) * block, cols = R - c0 < block ? R - c0 : block;
+    const int tiles = fix_tiles(block), c0 = (int)blockIdx.y * block, cols = R - c0 < block ? R - c0 : block;
     const int lanes = 1024 / cols, lane = (int)threadIdx.x / cols, col = (int)threadIdx.x - lane * cols, r = c0 + col;
     if (threadIdx.x == 0) chain = -1;
     __syncthreads();
@@ -480,7 +478,7 @@ __global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64
         double *o = out + (rowmap ? (int64_t)rowmap[id] : (int64_t)id) * R + r;
         *o = ep_apply(ep, v, o);
     };
-    const int64_t t0 = (int64_t)(blockIdx.x % nblocks) * tiles, mine = t0 + lane;
+    const int64_t t0 = (int64_t)blockIdx.x * tiles, mine = t0 + lane;
     if (lane < tiles && mine < ntiles && cb.has_tail[mine]) {
         double v = cb.first[mine * R + r];
         bool done = false;
@@ -506,15 +504,16 @@ __global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64
     if (chain < 0) return;
     const int64_t t = t0 + chain;
     int64_t from = 0;                                             // the nearest tile in front of t that contains a segment end, or the first
-    for (int64_t base = t - 1; base >= 0; base -= 8 * 1024) {
-        int ht[8], nearest = -1;
+    auto look = [&](auto count, int64_t base) {                   // among count * 1024 tiles up to base
+        constexpr int N = decltype(count)::value;
+        int ht[N], nearest = -1;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
+        for (int q = 0; q < N; ++q) {
             const int64_t u = base - q * 1024 - (int)threadIdx.x;
             ht[q] = cb.has_tail[u > 0 ? u : 0];
         }
 #pragma unroll
-        for (int q = 7; q >= 0; --q) {
+        for (int q = N - 1; q >= 0; --q) {
             const int64_t u = base - q * 1024 - (int)threadIdx.x;
             if (u >= 0 && ht[q]) nearest = (int)u;
         }
@@ -523,8 +522,11 @@ __global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64
         __syncthreads();
         if (nearest >= 0) atomicMax(&newest, nearest);
         __syncthreads();
-        if (newest >= 0) { from = newest; break; }
-    }
+        if (newest >= 0) from = newest;
+        return newest >= 0;
+    };
+    if (!look(IntC<1>{}, t - 1))
+        for (int64_t base = t - 1 - 1024; base >= 0 && !look(IntC<8>{}, base); base -= 8 * 1024) {}
     double v = 0.0;
     if (lane < lanes)
         for (int64_t u = from + lane; u < t; u += 16 * (int64_t)lanes) {
@@ -557,8 +559,7 @@ hipError_t run_fixup(void *scratch, int64_t ntiles, int R, const int32_t *rowmap
         hipLaunchKernelGGL(k_stream_fixup, dim3((unsigned)((ntiles * R + 255) / 256)), dim3(256), 0, st, scratch, ntiles, R, rowmap, out, ep);
     } else {
         const int block = max_chain <= 0 || max_chain * 8 > ntiles ? kFixColumns : R, tiles = fix_tiles(block);
-        const int64_t blocks = (ntiles + tiles - 1) / tiles * ((R + block - 1) / block);
-        hipLaunchKernelGGL(k_stream_fixup_long, dim3((unsigned)blocks), dim3(1024), 0, st, scratch, ntiles, R, block, rowmap, out, ep);
+        hipLaunchKernelGGL(k_stream_fixup_long, dim3((unsigned)((ntiles + tiles - 1) / tiles), (unsigned)((R + block - 1) / block)), dim3(1024), 0, st, scratch, ntiles, R, block, rowmap, out, ep);
     }
     return hipGetLastError();
 }
