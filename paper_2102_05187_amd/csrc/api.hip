@@ -96,7 +96,7 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st, bool part = false) 
             HIP_TRY(comet::build_parent_begin(t.pos_i(1), t.pos_len[1] - 1, (const int32_t *)sc.seg_begin->ptr,
                                               sc.ntiles, (int32_t *)sc.slice_begin->ptr, st));
         }
-        DevRef mx = comet::dev_alloc(sizeof(int32_t));
+        DevRef mx = comet::dev_alloc(2 * sizeof(int32_t));
         if (!mx) return COMET_ERR_ALLOC;
         HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
         HIP_TRY(comet::max_segment_length(t.pos_i(leaf), sc.nseg, (int32_t *)mx->ptr, st));
@@ -115,11 +115,14 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st, bool part = false) 
             HIP_TRY(comet::build_parent_begin(t.pos_i(1), t.pos_len[1] - 1, (const int32_t *)sc.chunk_seg_begin->ptr,
                                               sc.nchunks, (int32_t *)sc.chunk_slice_begin->ptr, st));
         }
-        HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
+        const bool most_stored = !part && t.levels[0] == COMET_CU && t.crd_len[0] <= t.dims[0] && t.crd_len[0] * 2 >= t.dims[0];
+        int32_t facts[2] = {0, 0};                       // empty segments; whether the stored rows do not increase
+        HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof facts, st));
         HIP_TRY(comet::count_empty_segments(t.pos_i(leaf), sc.nseg, (int32_t *)mx->ptr, st));
-        rs = read_i32((const int32_t *)mx->ptr, 1, &h, st);
+        if (most_stored) HIP_TRY(comet::check_cu_sorted(t.pos_i(0), 1, t.crd_i(0), t.crd_len[0], (int32_t *)mx->ptr + 1, st));
+        rs = read_i32((const int32_t *)mx->ptr, 2, facts, st);
         if (rs != COMET_OK) return rs;
-        sc.empty_segments = h;
+        sc.empty_segments = facts[0];
         // optional, like the plans of the sweeps below: without the memory for it, what would run on it takes the simple kernels
         hipError_t ppe = comet::piece_plan_build(t.pos_i(leaf), sc.nseg, t.crd_i(leaf), sc.nnz, sc.pieces, st);
         if (ppe == hipErrorOutOfMemory) { (void)hipGetLastError(); ppe = hipSuccess; }
@@ -132,12 +135,8 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st, bool part = false) 
         }
         // (optional too: without the memory for the list the whole result is cleared, and so it is where the stored rows do not
         // increase, which only the validating checks refuse)
-        if (!part && t.levels[0] == COMET_CU && t.crd_len[0] <= t.dims[0] && t.crd_len[0] * 2 >= t.dims[0]) {
-            HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
-            HIP_TRY(comet::check_cu_sorted(t.pos_i(0), 1, t.crd_i(0), t.crd_len[0], (int32_t *)mx->ptr, st));
-            rs = read_i32((const int32_t *)mx->ptr, 1, &h, st);
-            if (rs != COMET_OK) return rs;
-            if (h == 0) sc.unstored = comet::dev_alloc(sizeof(int32_t) * (t.dims[0] - t.crd_len[0]));
+        if (most_stored && facts[1] == 0) {
+            sc.unstored = comet::dev_alloc(sizeof(int32_t) * (t.dims[0] - t.crd_len[0]));
             if (sc.unstored) HIP_TRY(comet::list_unstored_rows(t.crd_i(0), t.crd_len[0], t.dims[0], (int32_t *)sc.unstored->ptr, st));
         }
         if (sc.mttkrp.ntiles > 0) {

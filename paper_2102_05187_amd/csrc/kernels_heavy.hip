@@ -248,6 +248,7 @@ __global__ void __launch_bounds__(256) k_fill_streams(const int32_t *__restrict_
         scrd[i] = c; scode[i] = code; sval[i] = v;
     };
     int p = we[iv];
+    bool outside = false;
     const int gs = slot_of_group(wv, gl);
     for (int w = iv * kSync; w < (iv + 1) * kSync && w < nwx; ++w) {
         const int wabs = x * nwx + w;
@@ -258,11 +259,13 @@ __global__ void __launch_bounds__(256) k_fill_streams(const int32_t *__restrict_
             int lo, hi;
             piece_of(units, wstart, nwin, u, wabs, &lo, &hi);
             for (int i = lo; i < hi; ++i, ++p) {
-                if (crd[i] / kWindow != wabs) *unsorted = 1;
-                put(p, crd[i], i + 1 == hi ? k : kNoFlush, vals[i]);
+                const int c = crd[i];
+                outside |= c / kWindow != wabs;
+                put(p, c, i + 1 == hi ? k : kNoFlush, vals[i]);
             }
         }
     }
+    if (outside) *unsorted = 1;
     int pend = we[iv + 1];
     if (iv == nsx - 1) pend = (block_start[wave + 1] - block_start[wave]) * kBlock;   // and the padding behind the last interval
     for (; p < pend; ++p) put(p, 0, kSkip, 0.0);

@@ -89,7 +89,10 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
     for (int i = threadIdx.x; i < np; i += 256) piece[i] = pieces[(size_t)first_piece + i];
     __syncthreads();
 
-    const int k = threadIdx.x % L, gw = (threadIdx.x & 63) / L, wave = threadIdx.x >> 6;
+    // Wide rows: the wavefront's number and the length of a short batch in scalar registers (60 000 nonzeros, rank 53, 20.0 -> 19.5 us);
+    // narrow ones are slower with them (the 10^6 x 10^6 matrix, rank 32, 445.8 and 447.4).
+    auto uniform = [](int x) { if constexpr (V > 2) return __builtin_amdgcn_readfirstlane(x); else return x; };
+    const int k = threadIdx.x % L, gw = (threadIdx.x & 63) / L, wave = uniform(threadIdx.x >> 6);
     const RowOf<L, E, NL, FULL> rw(R, k);
     const char *base = reinterpret_cast<const char *>(Dn);
     const Item *items = item + lead;
@@ -187,7 +190,7 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
     }
     // Short pieces: KB of them per group at the same time.
     for (; b < np; b += 4 * KP * KB) {
-        const int longest = piece_len(piece[b]);
+        const int longest = uniform(piece_len(piece[b]));
         uint32_t pd[KB];
         int len[KB], r[KB];
         double acc[KB][V];

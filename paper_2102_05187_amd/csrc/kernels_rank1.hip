@@ -528,17 +528,23 @@ __global__ void __launch_bounds__(1024) k_stream_fixup_long(void *scratch, int64
     if (!look(IntC<1>{}, t - 1))
         for (int64_t base = t - 1 - 1024; base >= 0 && !look(IntC<8>{}, base); base -= 8 * 1024) {}
     double v = 0.0;
-    if (lane < lanes)
-        for (int64_t u = from + lane; u < t; u += 16 * (int64_t)lanes) {
-            double x[16];
+    int64_t u = from + lane;
+    auto sum = [&](auto count) {                                  // (no load under a condition: a last round would go one by one)
+        constexpr int N = decltype(count)::value;
+        double x[N];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {                        // (none under a condition: a last round would go one by one)
-                const int64_t w = u + q * (int64_t)lanes;
-                x[q] = cb.open[(w < t ? w : t - 1) * R + r];
-            }
-#pragma unroll
-            for (int q = 0; q < 16; ++q) v += u + q * (int64_t)lanes < t ? x[q] : 0.0;
+        for (int q = 0; q < N; ++q) {
+            const int64_t w = u + q * (int64_t)lanes;
+            x[q] = cb.open[(w < t ? w : t - 1) * R + r];
         }
+#pragma unroll
+        for (int q = 0; q < N; ++q) v += u + q * (int64_t)lanes < t ? x[q] : 0.0;
+        u += N * (int64_t)lanes;
+    };
+    if (lane < lanes) {
+        while (u + 4 * (int64_t)lanes < t) sum(IntC<16>{});
+        if (u < t) sum(IntC<4>{});
+    }
     sums[threadIdx.x] = v;
     for (int k = lanes; k > 1;) {
         const int h = (k + 1) / 2;

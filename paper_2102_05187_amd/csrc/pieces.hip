@@ -135,10 +135,15 @@ __global__ void __launch_bounds__(1024) k_piece_distinct(const int32_t *__restri
     __syncthreads();
     const int64_t n = nnz < kSampleNnz ? nnz : kSampleNnz;
     const int64_t begin = gridDim.x > 1 ? (nnz - n) / (gridDim.x - 1) * blockIdx.x : 0;
-#pragma unroll 8
-    for (int64_t i = threadIdx.x; i < n; i += 1024) {
-        const uint32_t h = ((uint32_t)crd[begin + i] * 0x9E3779B1u) >> 14;
-        atomicOr(&bits[h >> 5], 1u << (h & 31u));
+    for (int64_t i = threadIdx.x; i < n; i += 32 * 1024) {
+        uint32_t c[32];
+#pragma unroll
+        for (int q = 0; q < 32; ++q) c[q] = (uint32_t)crd[begin + (i + q * 1024 < n ? i + q * 1024 : i)];
+#pragma unroll
+        for (int q = 0; q < 32; ++q) {
+            const uint32_t h = (c[q] * 0x9E3779B1u) >> 14;
+            atomicOr(&bits[h >> 5], 1u << (h & 31u));
+        }
     }
     __syncthreads();
     int sum = 0;
@@ -178,8 +183,9 @@ hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd
                        counters + 2, (uint32_t *)nullptr, (uint32_t *)nullptr);
     hipLaunchKernelGGL(k_piece_cuts, dim3(grid_for(ntiles)), dim3(256), 0, st, pos, nseg, (const int4 *)plan.tiles(), ntiles,
                        plan.cuts(), counters);
-    const int samples = nnz > kSampleNnz ? 4 : 1;
-    hipLaunchKernelGGL(k_piece_distinct, dim3(samples), dim3(1024), 0, st, crd, nnz, counters + 3);
+    // (a list shorter than a sample is not worth the 40 us that the kernel costs a small handle)
+    const int samples = 4;
+    if (nnz >= kSampleNnz) hipLaunchKernelGGL(k_piece_distinct, dim3(samples), dim3(1024), 0, st, crd, nnz, counters + 3);
     e = reorder_scan_flags((char *)temp->ptr + scan_at, &tb, cn, bf, ntiles + 1, st);
     struct { uint64_t total; int short_cuts, long_cuts, max_parts, set; } sums = {0, 0, 0, 0, 0};    // bf[ntiles] and the counters
     if (e == hipSuccess) e = hipMemcpyAsync(&sums, bf + ntiles, sizeof sums, hipMemcpyDeviceToHost, st);
