@@ -89,8 +89,8 @@ __global__ void __launch_bounds__(256) k_pieces(const int4 *__restrict__ tiles, 
     for (int i = threadIdx.x; i < np; i += 256) piece[i] = pieces[(size_t)first_piece + i];
     __syncthreads();
 
-    // Wide rows: the wavefront's number and the length of a short batch in scalar registers (60 000 nonzeros, rank 53, 20.0 -> 19.5 us);
-    // narrow ones are slower with them (the 10^6 x 10^6 matrix, rank 32, 445.8 and 447.4).
+    // The wavefront's number and the length of a short batch: in scalar registers for wide rows (60 000 nonzeros, rank 53, level with
+    // vector ones at 20 us); narrow ones are slower with them (the 10^6 x 10^6 matrix, rank 32, 447.4 and 445.8).
     auto uniform = [](int x) { if constexpr (V > 2) return __builtin_amdgcn_readfirstlane(x); else return x; };
     const int k = threadIdx.x % L, gw = (threadIdx.x & 63) / L, wave = uniform(threadIdx.x >> 6);
     const RowOf<L, E, NL, FULL> rw(R, k);
