@@ -96,7 +96,7 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st, bool part = false) 
             HIP_TRY(comet::build_parent_begin(t.pos_i(1), t.pos_len[1] - 1, (const int32_t *)sc.seg_begin->ptr,
                                               sc.ntiles, (int32_t *)sc.slice_begin->ptr, st));
         }
-        DevRef mx = comet::dev_alloc(2 * sizeof(int32_t));
+        DevRef mx = comet::dev_alloc(3 * sizeof(int32_t));
         if (!mx) return COMET_ERR_ALLOC;
         HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof(int32_t), st));
         HIP_TRY(comet::max_segment_length(t.pos_i(leaf), sc.nseg, (int32_t *)mx->ptr, st));
@@ -109,20 +109,22 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st, bool part = false) 
         if (!sc.chunk_seg_begin) return COMET_ERR_ALLOC;
         HIP_TRY(comet::build_seg_begin(t.pos_i(leaf), sc.nseg, sc.nnz, comet::kChunk, sc.nchunks,
                                        (int32_t *)sc.chunk_seg_begin->ptr, st));
-        if (t.fmt == Format::CSF3 && sc.nnz < comet::kChunkWalkNnz) {
+        if (t.fmt == Format::CSF3) {
             sc.chunk_slice_begin = comet::dev_alloc(sizeof(int32_t) * (sc.nchunks + 1));
             if (!sc.chunk_slice_begin) return COMET_ERR_ALLOC;
             HIP_TRY(comet::build_parent_begin(t.pos_i(1), t.pos_len[1] - 1, (const int32_t *)sc.chunk_seg_begin->ptr,
                                               sc.nchunks, (int32_t *)sc.chunk_slice_begin->ptr, st));
         }
         const bool most_stored = !part && t.levels[0] == COMET_CU && t.crd_len[0] <= t.dims[0] && t.crd_len[0] * 2 >= t.dims[0];
-        int32_t facts[2] = {0, 0};                       // empty segments; whether the stored rows do not increase
+        int32_t facts[3] = {0, 0, 0};                    // empty segments; whether the stored rows do not increase; empty slices
         HIP_TRY(hipMemsetAsync(mx->ptr, 0, sizeof facts, st));
         HIP_TRY(comet::count_empty_segments(t.pos_i(leaf), sc.nseg, (int32_t *)mx->ptr, st));
         if (most_stored) HIP_TRY(comet::check_cu_sorted(t.pos_i(0), 1, t.crd_i(0), t.crd_len[0], (int32_t *)mx->ptr + 1, st));
-        rs = read_i32((const int32_t *)mx->ptr, 2, facts, st);
+        if (t.fmt == Format::CSF3) HIP_TRY(comet::count_empty_segments(t.pos_i(1), t.pos_len[1] - 1, (int32_t *)mx->ptr + 2, st));
+        rs = read_i32((const int32_t *)mx->ptr, 3, facts, st);
         if (rs != COMET_OK) return rs;
         sc.empty_segments = facts[0];
+        if (t.fmt == Format::CSF3) sc.empty_slices = facts[2];
         // optional, like the plans of the sweeps below: without the memory for it, what would run on it takes the simple kernels
         hipError_t ppe = comet::piece_plan_build(t.pos_i(leaf), sc.nseg, t.crd_i(leaf), sc.nnz, sc.pieces, st);
         if (ppe == hipErrorOutOfMemory) { (void)hipGetLastError(); ppe = hipSuccess; }
@@ -1058,8 +1060,8 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
     // slice's row themselves, so when most rows are stored only the others are cleared: by the kernel over pieces itself where the
     // gaps between stored rows are short, else from the list made at creation.  Without a list all of M is cleared.
     const int64_t dense_rows = X->dims[1] > X->dims[2] ? X->dims[1] : X->dims[2];
-    const bool pieces = tiled && X->variant != 3 && comet::mttkrp_on_pieces(X->sched, dense_rows, R);
-    const bool gaps = pieces && gaps_are_short(X, R);
+    const comet::MttkrpRoute route = comet::mttkrp_route(X->sched, dense_rows, R, X->variant == 3);
+    const bool gaps = tiled && route == comet::MttkrpRoute::kPieces && gaps_are_short(X, R);
     if (tiled && !gaps && X->sched.unstored) {
         HIP_TRY(clear_unstored_rows(X, R, M, ep.on ? ep.beta : 0.0, st));
     } else if (!gaps) {
@@ -1070,10 +1072,10 @@ static comet_status mttkrp_impl(const comet_tensor *X, int mode, const double *c
     if (X->nvals == 0) return COMET_OK;
     if (tiled) {
         // (only what this call takes: on a new handle 2 MB and more cost 100 us that a list on the walk need not pay)
-        comet_status rs = ensure_scratch(X, comet::mttkrp_call_bytes(X->sched, R, pieces));
+        comet_status rs = ensure_scratch(X, comet::mttkrp_call_bytes(X->sched, R, route));
         if (rs != COMET_OK) return rs;
-        HIP_TRY(comet::stream_mttkrp(X->sched, X->pos_i(1), X->crd_i(0), X->pos_i(2), X->crd_i(1), X->crd_i(2), X->vals_d(), B, C,
-                                     dense_rows, R, M, pieces, gaps, X->scratch->ptr, st, ep));
+        HIP_TRY(comet::stream_mttkrp(X->sched, X->pos_i(1), X->crd_i(0), X->pos_len[1] - 1, X->pos_i(2), X->crd_i(1), X->crd_i(2), X->vals_d(), B, C,
+                                     dense_rows, R, M, route, gaps, X->scratch->ptr, st, ep));
         return COMET_OK;
     }
     HIP_TRY(comet::simple_mttkrp(X->pos_i(1), X->crd_i(0), X->pos_len[1] - 1, X->pos_i(2), X->crd_i(1), X->crd_i(2),

@@ -1,4 +1,4 @@
-// MTTKRP kernels.  Short lists: lane groups of 4, 8 or 16 walk the pieces of the fibers of a tile (k_mttkrp_pieces, mttkrp_plan.hpp);
+// MTTKRP kernels and the choice among them (the third one is in kernels_mttkrp_wave.hip).  Short lists: lane groups of 4, 8 or 16 walk the pieces of the fibers of a tile (k_mttkrp_pieces, mttkrp_plan.hpp);
 // a tile is a chain of dependent loads -- its descriptor, its nonzeros, rows of B and C, the sums -- and what bounds the kernel is how
 // many of them are in flight.  All others: lane groups walk runs of nonzeros over two nested segment levels (k_stream_mttkrp).
 // A piece loads rows of C in groups of four, none behind its batch's last group; with up to seven more rows per piece, fibers of 12 / 30 /
@@ -460,7 +460,7 @@ hipError_t launch_walk(const MtArgs &a, const Schedule &sc, void *scratch) {
                            (const int32_t *)fibers->ptr, (const int32_t *)slices->ptr, a.B, a.C, a.M, sc.nnz, sc.nseg, ntiles, a.R,
                            scratch, a.ep);
     };
-    if (sc.chunk_slice_begin) go(k_stream_mttkrp<L, V, WIDE, kChunk>, sc.nchunks, sc.chunk_seg_begin, sc.chunk_slice_begin);
+    if (sc.nnz < kChunkWalkNnz) go(k_stream_mttkrp<L, V, WIDE, kChunk>, sc.nchunks, sc.chunk_seg_begin, sc.chunk_slice_begin);
     else go(k_stream_mttkrp<L, V, WIDE, kTile>, sc.ntiles, sc.seg_begin, sc.slice_begin);
     return hipGetLastError();
 }
@@ -472,7 +472,7 @@ hipError_t launch_walk(const MtArgs &a, const Schedule &sc, void *scratch) {
                : ((R) <= 8 ? F<4, 2, false, false>(args) : (R) % 16 ? F<8, 2, false, false>(args) : F<8, 2, true, false>(args)))
 
 // Tiles that the slices of the walk are cut over at most.
-int64_t mttkrp_chain(const Schedule &sc) { return sc.max_parent_len / (sc.chunk_slice_begin ? kChunk : kTile) + 2; }
+int64_t mttkrp_chain(const Schedule &sc) { return sc.max_parent_len / (sc.nnz < kChunkWalkNnz ? kChunk : kTile) + 2; }
 
 // Which lists and ranks take the pieces; all others the walk over tiles of nonzeros, which keeps more rows in flight once its tiles
 // fill the chip, while a tile of pieces needs several rounds of loads one after the other.  Calls of the walk and of the pieces in us,
@@ -515,34 +515,62 @@ bool mttkrp_takes_pieces(const Schedule &sc, int64_t R) {
     return R < 16 || long_slices || n <= int64_t(9) << 18;
 }
 
-}  // namespace
-
-bool mttkrp_on_pieces(const Schedule &sc, int64_t dense_rows, int64_t R) {
-    // row offsets of the pieces are 32-bit counts of doubles; the walk forms 64-bit addresses
-    return sc.mttkrp.ntiles > 0 && mttkrp_takes_pieces(sc, R) && dense_rows * R < (int64_t(1) << 32);
+// Of the lists that do not take the pieces, those that k_mttkrp_wave serves faster than the walk.  It reads every row 16 bytes per lane, the
+// walk only at ranks 8, 16, 32, 48, 64, 96 and 128; it reads a row of B once per fiber and block, which is nothing gained where almost every
+// nonzero is a fiber; and it adds up a block's products in 64-column passes at most, so that wide rows over long fibers stay with the walk.
+// Whole calls, walk and wavefronts, us; the tensors of the table above:
+//   nonzeros          rank 10     16          20          32          40          64          9           96          128
+//    10 M power       169  129   126  125    258  208    216  208    418  327    385  378    166  159    477  446*   694  584*
+//         ones        316  312   248  266    482  638    528  555    834  994   1203 1118    313  328   1344 1300   1884 1568
+//         fives       229  166   147  143    364  311    259  248    552  450    531  514    229  197    676  608   1013  798
+//         thirties    198  140   129  131    247  256    210  226    404  414    421  457    195  168    489  516    757  687
+//    60 M power       491  353   354  322    881  685    680  597   1336 1032   1164 1133    488  430   1325 1287*  2104 1713*
+//         ones       1836 1870  1493 1541   2900 4073   3339 3445   5092 6401   7354 6869   1796 1859   7690 7698  10455 9105
+//         fives      1021  781   643  643   1752 1541   1274 1308   2773 2378   3402 2648   1023  909   3810 2901   5477 3605
+//         thirties    985  678   574  563   1245 1305    972 1049   1921 2024   2457 2116    988  814   2950 2203   4402 2919
+//   (* ranks 96 and 128: 7 M and 40 M).  150 M power, rank 16: 1601 and 1393; 20 M, rank 64: 771 and 740.  2.5 M, ranks 34 / 62, power 167 and 149 /
+//   253 and 238, ones 224 and 342 / 391 and 529.  Ranks 2 and 8, 60 M power: 190 and 198, 258 and 276.
+bool mttkrp_takes_wave(const Schedule &sc, int64_t R) {
+    const int64_t n = sc.nnz;
+    const bool few = n <= 8 * sc.nseg;                            // nonzeros per fiber
+    if (n < 2 * sc.nseg || R <= 8) return false;
+    if (R == 16) return n >= int64_t(40) << 20;
+    if (R < 16) return n >= int64_t(5) << 20;
+    if (R % 32 == 0) return few && n >= int64_t(10) << 20;
+    return few && R % 2 == 0 && R < 64 && R != 48 && n >= (R > 32 ? int64_t(1) << 20 : int64_t(5) << 19);
 }
 
-size_t mttkrp_call_bytes(const Schedule &sc, int64_t R, bool pieces) {
-    if (pieces) return (size_t)sc.mttkrp.ntiles * (size_t)R * 2 * sizeof(double);
-    return stream_scratch_bytes(sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, R);
+}  // namespace
+
+MttkrpRoute mttkrp_route(const Schedule &sc, int64_t dense_rows, int64_t R, bool plain) {
+    // row offsets of the pieces and of the wavefronts are 32-bit counts of doubles; the walk forms 64-bit addresses
+    if (plain || dense_rows * R >= (int64_t(1) << 32)) return MttkrpRoute::kWalk;
+    if (sc.mttkrp.ntiles > 0 && mttkrp_takes_pieces(sc, R)) return MttkrpRoute::kPieces;
+    return sc.empty_segments == 0 && sc.empty_slices == 0 && mttkrp_takes_wave(sc, R) ? MttkrpRoute::kWave : MttkrpRoute::kWalk;
+}
+
+static int64_t walk_tiles(const Schedule &sc) { return sc.nnz < kChunkWalkNnz ? sc.nchunks : sc.ntiles; }
+
+size_t mttkrp_call_bytes(const Schedule &sc, int64_t R, MttkrpRoute route) {
+    if (route == MttkrpRoute::kPieces) return (size_t)sc.mttkrp.ntiles * (size_t)R * 2 * sizeof(double);
+    return stream_scratch_bytes(route == MttkrpRoute::kWave ? sc.nchunks : walk_tiles(sc), R);
 }
 
 size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R) {
-    // ranks below R may take the pieces where R does not
-    const size_t a = stream_scratch_bytes(sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, R);
-    const size_t b = (size_t)sc.mttkrp.ntiles * (size_t)R * 2 * sizeof(double);
+    // ranks below R may take another route than R does
+    const size_t a = stream_scratch_bytes(sc.nchunks, R), b = (size_t)sc.mttkrp.ntiles * (size_t)R * 2 * sizeof(double);
     return a > b ? a : b;
 }
 
-hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, const int32_t *pos3, const int32_t *crd2,
+hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, int64_t nslice, const int32_t *pos3, const int32_t *crd2,
                          const int32_t *crd3, const double *vals, const double *B, const double *C, int64_t dense_rows, int64_t R,
-                         double *M, bool pieces, bool gaps, void *scratch, hipStream_t st, Epilogue ep) {
+                         double *M, MttkrpRoute route, bool gaps, void *scratch, hipStream_t st, Epilogue ep) {
     if (sc.ntiles <= 0) return hipSuccess;
     if (!stream_mttkrp_supports_rank(R) || !sc.slice_begin) return hipErrorNotSupported;
     const MttkrpPlan &plan = sc.mttkrp;
     double *head = (double *)scratch, *tail = head + plan.ntiles * R;
     const MtArgs a{plan, pos2, crd1, pos3, crd2, crd3, vals, B, C, M, sc.nnz, (int)R, gaps ? 1 : 0, head, tail, st, ep};
-    if (pieces) {
+    if (route == MttkrpRoute::kPieces) {
         const bool wide = dense_rows * R * 8 >= (int64_t(1) << 32);   // row offsets in bytes no longer fit 32 bits
         const hipError_t e = COMET_DISPATCH_BLOCKS(launch_mttkrp, a.R, wide, a);
         if (e != hipSuccess || plan.ncut + plan.ncut_long == 0) return e;
@@ -552,9 +580,11 @@ hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t 
                            (const double *)tail, (int)R, M, ep);
         return hipGetLastError();
     }
+    if (route == MttkrpRoute::kWave)
+        return mttkrp_wave(sc, pos2, nslice, crd1, pos3, crd2, crd3, vals, B, C, dense_rows * R * 8 >= (int64_t(1) << 32), (int)R, M, scratch, st, ep);
     const hipError_t e = COMET_DISPATCH_GROUPS(launch_walk, a.R, a, sc, scratch);
     if (e != hipSuccess) return e;
-    return run_fixup(scratch, sc.chunk_slice_begin ? sc.nchunks : sc.ntiles, (int)R, nullptr, M,
+    return run_fixup(scratch, walk_tiles(sc), (int)R, nullptr, M,
                      sc.max_parent_len > 0 ? mttkrp_chain(sc) : 0, st, ep);
 }
 

@@ -27,6 +27,7 @@
 //           k_stream_rankR         ranks 8 and 16 over long lists, lane groups walk item runs, per-item records in LDS
 //           k_stream_mttkrp        rank R, two nested segment levels (fibers inside slices)
 //           k_mttkrp_pieces        the same over short lists, lane groups walk pieces of fibers (mttkrp_plan.hpp)
+//           k_mttkrp_wave          the same over long lists, a wavefront takes blocks of nonzeros (kernels_mttkrp_wave.hip)
 //           k_stream_fixup, k_stream_fixup_long   carry resolution, for segments over few and over many tiles
 #pragma once
 
@@ -49,6 +50,11 @@ constexpr int64_t kWalkNnz = int64_t(10) << 20;
 // The same over the piece plan (defined in kernels_pieces.hip).
 hipError_t piece_rows(const PiecePlan &plan, const int32_t *crd, const double *vals, int64_t nnz, const int32_t *rowmap, const double *Dn,
                       int64_t dense_rows, int R, double *out, void *scratch, hipStream_t st, Epilogue ep = Epilogue());
+
+// MTTKRP by wavefronts over runs of kChunk nonzeros (defined in kernels_mttkrp_wave.hip); big: row offsets in bytes do not fit 32 bits.
+hipError_t mttkrp_wave(const Schedule &sc, const int32_t *pos2, int64_t nslice, const int32_t *crd1, const int32_t *pos3, const int32_t *crd2,
+                       const int32_t *crd3, const double *vals, const double *B, const double *C, bool big, int R, double *M, void *scratch,
+                       hipStream_t st, Epilogue ep);
 
 namespace {
 

@@ -24,7 +24,8 @@ size_t piece_scratch_bytes(const PiecePlan &plan, int64_t R);
 bool   segreduce_supports(const Schedule &sc, int64_t R);          // false: stream_segreduce would need a plan that is not there
 size_t segreduce_scratch_bytes(const Schedule &sc, int64_t R);     // what stream_segreduce needs
 size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R);        // what stream_mttkrp needs at ranks up to R
-size_t mttkrp_call_bytes(const Schedule &sc, int64_t R, bool pieces);   // ... at rank R
+enum class MttkrpRoute { kWalk, kPieces, kWave };
+size_t mttkrp_call_bytes(const Schedule &sc, int64_t R, MttkrpRoute route);   // ... at rank R
 
 // out[row(s), :] = sum_{p in segment s} vals[p] * Dn[crd[p], :],  row(s) = rowmap ? rowmap[s] : s.
 // Every segment of the level is written (empty ones with zeros).  dense_rows = number of rows of Dn.
@@ -76,13 +77,13 @@ int current_device_cu_count();
 
 // M[crd1[s], :] = sum_{f in slice s} B[crd2[f], :] * (sum_{p in fiber f} vals[p] * C[crd3[p], :]) over the schedule sc.
 // dense_rows = the larger number of rows of B and C.
-// pieces: mttkrp_on_pieces, or false.  Every stored slice's row is written.  gaps: the rows that are not stored are cleared too (scaled by beta), which only the
+// route: from mttkrp_route.  Every stored slice's row is written.  gaps: the rows that are not stored are cleared too (scaled by beta), which only the
 // pieces do; otherwise the caller has done that.
 // Every comment above reads "=" as "= alpha * (...) + beta * (old value)" when an epilogue is switched on.
-hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, const int32_t *pos3, const int32_t *crd2,
+hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, int64_t nslice, const int32_t *pos3, const int32_t *crd2,
                          const int32_t *crd3, const double *vals, const double *B, const double *C, int64_t dense_rows, int64_t R,
-                         double *M, bool pieces, bool gaps, void *scratch, hipStream_t st, Epilogue ep = Epilogue());
-// Whether the pieces of sc.mttkrp serve this rank and factors of up to dense_rows rows; only they clear the rows that are not stored.
-bool mttkrp_on_pieces(const Schedule &sc, int64_t dense_rows, int64_t R);
+                         double *M, MttkrpRoute route, bool gaps, void *scratch, hipStream_t st, Epilogue ep = Epilogue());
+// Which kernel takes this rank over factors of up to dense_rows rows (plain: the walk); only the pieces clear the rows that are not stored.
+MttkrpRoute mttkrp_route(const Schedule &sc, int64_t dense_rows, int64_t R, bool plain);
 
 }  // namespace comet

@@ -143,9 +143,10 @@ struct Schedule {
     int64_t nruns = 0;     // COO3: number of distinct (i,j) pairs
     DevRef  chunk_seg_begin;   // int32 [nchunks + 1]: seg_begin at kChunk granularity
     DevRef  chunk_run_base;    // int32 [nchunks + 1]: run_base at kChunk granularity (COO3 only)
-    DevRef  chunk_slice_begin; // int32 [nchunks + 1]: slice_begin at kChunk granularity (CSF3 below kChunkWalkNnz only)
+    DevRef  chunk_slice_begin; // int32 [nchunks + 1]: slice_begin at kChunk granularity (CSF3 only)
     int64_t nchunks = 0;
     int64_t empty_segments = -1;  // leaf segments without a nonzero (-1 = unknown)
+    int64_t empty_slices = -1;    // CSF3: slices without a fiber (-1 = unknown)
     int64_t max_seg_len = 0;      // longest leaf segment, in nonzeros (0 = unknown)
     int64_t max_parent_len = 0;   // CSF3: most nonzeros under one slice (0 = unknown)
     int64_t max_root_gap = -1;    // with a plan in `mttkrp`: longest run of absent root coordinates (-1 = unknown)

@@ -1,0 +1,151 @@
+"""MTTKRP on lists long enough for wavefronts that take blocks of nonzeros: fibers and slices that end at every place of a block, a
+lane group and a run of 1024 nonzeros, blocks with as many fibers or slices as nonzeros, every layout of the rows, both sides of
+the size rules, operands whose row offsets need 64 bits, and lists that keep the walk because a fiber or a slice is empty."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from synth import formats as fmt
+from synth import generate as gen
+from util import assert_values_close, np_
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def comet():
+    from paper_2102_05187_amd import build
+    build.build_if_missing()
+    import paper_2102_05187_amd as c
+    return c
+
+
+def _lists(nnz):
+    """Fiber lengths and the fibers of each slice: 2 to 8 nonzeros per fiber in all, exactly nnz of them."""
+    g = np.random.default_rng(7)
+    fibers, slices = [], []
+
+    def add(of):
+        slices.append(len(of))
+        fibers.extend(of)
+
+    total = 0
+    while total < nnz:
+        start = len(fibers)
+        for n in (1023, 1024, 1025, 31, 32, 33, 63, 64, 65, 7, 8, 9):
+            add([n])                                                    # a slice of one fiber
+        add([1] * 700)                                                  # as many fibers as nonzeros, no slice ends for 700
+        for _ in range(400):
+            add([1])                                                    # every nonzero is a slice
+        for _ in range(150):
+            add(list(g.integers(1, 4, int(g.integers(1, 6)))))          # several slices in a lane group
+        add([64] * 40 + [1] * 130 + [8] * 300 + [16] * 64)
+        add(list(g.integers(1, 12, 3000)))                              # one slice over many runs
+        add(list(g.integers(1, 12, int(g.integers(100, 400)))))
+        total += sum(fibers[start:])
+    over = total - nnz
+    while over:
+        cut = min(over, fibers[-1] - 1) if slices[-1] == 1 or fibers[-1] > 1 else 0
+        if cut:
+            fibers[-1] -= cut
+            over -= cut
+        elif slices[-1] > 1:
+            fibers.pop()
+            slices[-1] -= 1
+            over -= 1
+        else:
+            fibers.pop()
+            slices.pop()
+            over -= 1
+    assert sum(fibers) == nnz and 2 * len(fibers) <= nnz <= 8 * len(fibers)
+    return torch.tensor(np.array(fibers)), torch.tensor(slices)
+
+
+def _tensor(nnz):
+    lens, nfib = _lists(nnz)
+    fiber = torch.repeat_interleave(torch.arange(lens.numel()), lens)
+    slice_of = torch.repeat_interleave(torch.arange(nfib.numel()), nfib)
+    j = torch.arange(lens.numel()) - (torch.cumsum(nfib, 0) - nfib)[slice_of]
+    k = torch.arange(fiber.numel()) - (torch.cumsum(lens, 0) - lens)[fiber]
+    dims = (nfib.numel() * 4 // 3 + 5, int(nfib.max()) + 2, int(lens.max()) + 1)
+    i = slice_of + slice_of // 3                                        # three of four rows are stored
+    return dims, i[fiber].int(), j[fiber].int(), k.int(), gen.dense_operand(9, 0, (nnz, 1)).reshape(-1)
+
+
+_kept = {}
+
+
+def _case(nnz):
+    if nnz not in _kept:
+        _kept.clear()
+        _kept[nnz] = _tensor(nnz)
+    return _kept[nnz]
+
+
+SMALL = 1 << 20                                                         # from here on at even ranks above 32
+CASES = [(SMALL, 34), (SMALL + 1, 40), (SMALL + 63, 50), (SMALL + 700, 62), (SMALL - 1, 40), (5 << 19, 20), ((5 << 19) + 31, 30), ((5 << 19) - 1, 20),
+         ((5 << 20) + 1, 9), ((5 << 20) + 1, 10), ((5 << 20) + 1, 15), ((10 << 20) + 5, 32)]
+
+
+@pytest.mark.parametrize("nnz,R", CASES)
+def test_blocks(comet, nnz, R):
+    dims, i, j, k, vals = _case(nnz)
+    print("mttkrp blocks R=%d nnz=%d" % (R, nnz), flush=True)
+    X = comet.from_levels(fmt.pack_csf3(dims, i, j, k, vals).to("cuda")).set_variant(2)
+    B, C, old = (gen.dense_operand(5, n, (d, R)) for n, d in ((0, dims[1]), (1, dims[2]), (2, dims[0])))
+    ref, absum = oracle.mttkrp(np_(i), np_(j), np_(k), np_(vals), dims, np_(B), np_(C))
+    M = torch.full((dims[0], R), float("nan"), dtype=torch.float64, device="cuda")
+    comet.comet_mttkrp(X, 0, [None, B.to("cuda"), C.to("cuda")], M)
+    assert_values_close(np_(M), ref, absum, "mttkrp R=%d" % R)
+    assert torch.equal(M, comet.comet_mttkrp(X, 0, [None, B.to("cuda"), C.to("cuda")])), "two runs differ"
+    D = old.to("cuda")
+    comet.comet_mttkrp_axpby(X, 0, 0.75, [None, B.to("cuda"), C.to("cuda")], -0.5, D)
+    assert_values_close(np_(D), 0.75 * ref - 0.5 * np_(old), 0.75 * absum + 0.5 * np.abs(np_(old)), "axpby R=%d" % R)
+
+
+@pytest.mark.parametrize("level", [1, 2])
+@pytest.mark.parametrize("nnz,R", [(SMALL, 34), ((5 << 20) + 1, 11)])
+def test_row_offsets_beyond_4_gib(comet, nnz, R, level):
+    """The coordinates of a level spread over more than 4 GiB of operand rows, the last row among them."""
+    dims, i, j, k, vals = _case(nnz)
+    wide = (1 << 29) // R + 7
+    spread = torch.linspace(0, wide - 1, dims[level], dtype=torch.float64).long()
+    spread[-1] = wide - 1
+    crd = [i, j, k]
+    crd[level] = spread[crd[level].long()].int()
+    tdims = list(dims)
+    tdims[level] = wide
+    X = comet.from_levels(fmt.pack_csf3(tdims, *crd, vals).to("cuda")).set_variant(2)
+    small = [gen.dense_operand(5, n, (dims[n + 1], R)) for n in (0, 1)]
+    F = torch.empty((wide, R), dtype=torch.float64, device="cuda")
+    F[spread.cuda()] = small[level - 1].cuda()
+    BC = [s.cuda() for s in small]
+    BC[level - 1] = F
+    print("mttkrp blocks wide R=%d level=%d rows=%d" % (R, level, wide), flush=True)
+    M = comet.comet_mttkrp(X, 0, [None] + BC)
+    ref, absum = oracle.mttkrp(np_(i), np_(j), np_(k), np_(vals), dims, np_(small[0]), np_(small[1]))
+    assert_values_close(np_(M), ref, absum, "wide R=%d level=%d" % (R, level))
+
+
+@pytest.mark.parametrize("empty", ["fiber", "slice"])
+def test_lists_with_something_empty(comet, empty):
+    """One fiber, or slice, without nonzeros behind the others: its row receives nothing."""
+    dims, i, j, k, vals = _case(SMALL)
+    R = 34
+    T = fmt.pack_csf3(dims, i, j, k, vals)
+    last_row = int(T.crd[0][-1])
+    if empty == "fiber":
+        T.crd[1] = torch.cat([T.crd[1], torch.tensor([dims[1] - 1], dtype=torch.int32)])
+        T.pos[2] = torch.cat([T.pos[2], T.pos[2][-1:]])
+        T.pos[1][-1] += 1
+    else:
+        T.crd[0] = torch.cat([T.crd[0], torch.tensor([last_row + 1], dtype=torch.int32)])
+        T.pos[1] = torch.cat([T.pos[1], T.pos[1][-1:]])
+        T.pos[0][-1] += 1
+    X = comet.from_levels(T.to("cuda")).set_variant(2)
+    B, C = (gen.dense_operand(5, n, (d, R)) for n, d in ((0, dims[1]), (1, dims[2])))
+    ref, absum = oracle.mttkrp(np_(i), np_(j), np_(k), np_(vals), dims, np_(B), np_(C))
+    M = torch.full((dims[0], R), float("nan"), dtype=torch.float64, device="cuda")
+    comet.comet_mttkrp(X, 0, [None, B.to("cuda"), C.to("cuda")], M)
+    assert_values_close(np_(M), ref, absum, "empty %s" % empty)
