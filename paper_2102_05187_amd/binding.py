@@ -99,9 +99,18 @@ def _check(status: int, where: str):
         raise CometError(status, where)
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+# The current stream's address without a Stream object around it, which takes 2.8 us to make: 4096 rows x 10 nonzeros, one call
+# among others, SpMV 7.7 -> 4.8 us, SpMM with 32 columns 8.3 -> 5.5.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _stream(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _raw_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_raw_device())
 
 
 def _dev(t: Optional[torch.Tensor], dtype, what: str) -> Optional[torch.Tensor]:
@@ -136,6 +145,7 @@ class Tensor:
         self._keep = list(keep)
         self._parent = parent      # a result shares level arrays with its input
         self._dims = None
+        self._mode_dims = None
 
     @property
     def handle(self) -> ctypes.c_void_p:
@@ -159,7 +169,7 @@ class Tensor:
         return [int(inf.levels[l]) for l in range(inf.order)]
 
     def dims(self) -> List[int]:
-        # sizes per level never change for a handle: looked up once (the products are launch-bound on small inputs)
+        # sizes never change for a handle: looked up once (the products are launch-bound on small inputs)
         if self._dims is None:
             inf = self.info()
             self._dims = [int(inf.dims[l]) for l in range(inf.order)]
@@ -180,11 +190,13 @@ class Tensor:
 
     def mode_dims(self) -> List[int]:
         """Sizes indexed by tensor mode (dims() is indexed by level)."""
-        inf = self.info()
-        out = [0] * inf.order
-        for l in range(inf.order):
-            out[int(inf.mode_of_level[l])] = int(inf.dims[l])
-        return out
+        if self._mode_dims is None:
+            inf = self.info()
+            out = [0] * inf.order
+            for l in range(inf.order):
+                out[int(inf.mode_of_level[l])] = int(inf.dims[l])
+            self._mode_dims = out
+        return list(self._mode_dims)
 
     def pos(self, l: int) -> Optional[torch.Tensor]:
         inf = self.info()
@@ -272,9 +284,10 @@ def comet_tensor_convert(X: Tensor, mode_order: Sequence[int], levels: Sequence[
 
 def comet_spmv(A: Tensor, x: torch.Tensor, y: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     x = _dev(x, torch.float64, "x")
-    if len(A.dims()) != 2:
+    dims = A.dims()
+    if len(dims) != 2:
         raise CometError(4, "comet_spmv")
-    I, J = A.dims()
+    I, J = dims
     if x.numel() != J:
         raise CometError(3, "comet_spmv")
     if y is None:
@@ -339,9 +352,10 @@ def comet_calibrate_gather(table: torch.Tensor, gathers: int, sink: torch.Tensor
 
 def comet_spmm(A: Tensor, B: torch.Tensor, C: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     B = _dev(B, torch.float64, "B")
-    if len(A.dims()) != 2:
+    dims = A.dims()
+    if len(dims) != 2:
         raise CometError(4, "comet_spmm")
-    I, J = A.dims()
+    I, J = dims
     if B.dim() != 2 or B.shape[0] != J:
         raise CometError(3, "comet_spmm")
     R = B.shape[1]
