@@ -227,20 +227,25 @@ __global__ void __launch_bounds__(256) k_stream_rank1(const int32_t *__restrict_
     finish_tile_rank1<ROWMAP>(wsum_ht, wsum_open, wsum_first, wsum_first_id, rowmap, out, carry_view(scratch, ntiles, 1), t, ep);
 }
 
-// ---- rank-1 kernel with the dense vector staged in LDS ----------------------------------------------
-// When x (SpMV) / v (TTV) fits in the 160 KB of LDS next to a few hundred bytes of bookkeeping, one
-// workgroup of 16 wavefronts per CU copies it in once and every gather x[crd] becomes an LDS read: the
-// L1 / texture-address path, which handles only about one scattered 8-byte gather per clock per CU,
-// is then left to the streaming loads.  Each wavefront works alone on 1024-item chunks (no workgroup
-// barrier after the staging): it marks the segment ends of its chunk in a private 1024-bit mask,
+// ---- rank-1 kernel over chunks -------------------------------------------------------------------------
+// Each wavefront works alone on 1024-item chunks: it marks the segment ends of its chunk in a private 1024-bit mask,
 // gets the segment id of an end as (first segment of the chunk) + (ends before it) -- valid because
 // this kernel is only used when the level has no empty segment -- and writes the chunk summary
 // straight to the carry buffer (one entry per chunk).
+// LDSVEC: where x (SpMV) / v (TTV) fits in the 160 KB of LDS next to a few hundred bytes of bookkeeping, one
+// workgroup of 16 wavefronts per CU copies it in once and every gather x[crd] becomes an LDS read: the
+// L1 / texture-address path, which handles only about one scattered 8-byte gather every two clocks per CU,
+// is then left to the streaming loads.
+// Otherwise the vector is gathered through L1, a chunk per wavefront; coordinate lists only, whose runs are found here with all loads
+// of eight rows of 64 items under way at once, and none behind a comparison: 5 M nonzeros, 60 013 values in the vector, 47.4 us a call with a
+// load of both coordinates and both predecessors per item behind branches, and 44.3 with five wavefronts per SIMD (a third of the time are the gathers,
+// the rest a chunk's chain of loads); 46.1 with all 16 rows unrolled (three per SIMD), 58.7 with six. Compressed levels keep
+// k_stream_rank1 there: 4.7 M nonzeros in short rows, 59 us, and 62 here.
 // COO = true: the input is a sorted coordinate list [CN,S,S]; segment ends come from neighbour
 // comparisons of (c0, c1) instead of pos, the id of a run is (runs started before the chunk) + (runs
 // started earlier in the chunk), and the result's coordinate arrays y0 / y1 are written here too.
-template <bool ROWMAP, bool COO>
-__global__ void __launch_bounds__(1024) k_stream_rank1_ldsvec(const int32_t *__restrict__ pos, const int32_t *__restrict__ crd,
+template <bool ROWMAP, bool COO, bool LDSVEC>
+__global__ void __launch_bounds__(LDSVEC ? 1024 : 256, LDSVEC ? 4 : 5) k_stream_rank1_chunk(const int32_t *__restrict__ pos, const int32_t *__restrict__ crd,
                                                               const double *__restrict__ vals,
                                                               const int32_t *__restrict__ chunk_begin,
                                                               const int32_t *__restrict__ rowmap,
@@ -249,29 +254,32 @@ __global__ void __launch_bounds__(1024) k_stream_rank1_ldsvec(const int32_t *__r
                                                               void *scratch, const int32_t *__restrict__ c0,
                                                               const int32_t *__restrict__ c1, int32_t *__restrict__ y0,
                                                               int32_t *__restrict__ y1, Epilogue ep) {
+    constexpr int NW = LDSVEC ? 16 : kWaves;
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    const int64_t xpad = (ncols + 1) & ~(int64_t)1;
+    const int64_t xpad = LDSVEC ? (ncols + 1) & ~(int64_t)1 : 0;
     double *xs = reinterpret_cast<double *>(lds_raw);
-    unsigned *bits_all = reinterpret_cast<unsigned *>(lds_raw + xpad * 8);            // [16][32]
-    double *wfirst_all = reinterpret_cast<double *>(lds_raw + xpad * 8 + 16 * 128);   // [16]
-    int *wfirst_id_all = reinterpret_cast<int *>(lds_raw + xpad * 8 + 16 * 128 + 16 * 8);   // [16]
+    unsigned *bits_all = reinterpret_cast<unsigned *>(lds_raw + xpad * 8);            // [NW][32]
+    double *wfirst_all = reinterpret_cast<double *>(lds_raw + xpad * 8 + NW * 128);   // [NW]
+    int *wfirst_id_all = reinterpret_cast<int *>(lds_raw + xpad * 8 + NW * 128 + NW * 8);   // [NW]
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     unsigned *bits = bits_all + w * 32;
-    const int64_t stride = (int64_t)gridDim.x * 16;
-    int64_t c = (int64_t)blockIdx.x * 16 + w;
+    const int64_t stride = (int64_t)gridDim.x * NW;
+    int64_t c = (int64_t)blockIdx.x * NW + w;
     Rank1Half h0;
     if (c < nchunks) rank1_load_half(h0, crd, vals, c * kChunk, lane, nnz);          // in flight during the staging
-    for (int64_t i = (int64_t)threadIdx.x * 2; i + 1 < ncols; i += 2048)
-        *reinterpret_cast<double2 *>(xs + i) = *reinterpret_cast<const double2 *>(x + i);
-    if ((ncols & 1) && threadIdx.x == 0) xs[ncols - 1] = x[ncols - 1];
-    __syncthreads();
+    if constexpr (LDSVEC) {
+        for (int64_t i = (int64_t)threadIdx.x * 2; i + 1 < ncols; i += 2048)
+            *reinterpret_cast<double2 *>(xs + i) = *reinterpret_cast<const double2 *>(x + i);
+        if ((ncols & 1) && threadIdx.x == 0) xs[ncols - 1] = x[ncols - 1];
+        __syncthreads();
+    }
     CarryView cb = carry_view(scratch, nchunks, 1);
     const unsigned long long lt_mask = (1ull << lane) - 1ull;
     for (; c < nchunks; c += stride) {
         const int64_t cbeg = c * kChunk;
         int base_id;
         if constexpr (COO) {
-            constexpr int kRows = kChunk / 64, kBatch = 4;
+            constexpr int kRows = kChunk / 64, kBatch = LDSVEC ? 4 : 8;
             // run starts of a row of 64 items (hm), and the same with items past the end counted as starts (hx);
             // the mask of run ENDS of row r-1 is written as soon as row r is known, so only one row is kept
             unsigned long long hx_prev = 0ull;
@@ -291,8 +299,8 @@ __global__ void __launch_bounds__(1024) k_stream_rank1_ldsvec(const int32_t *__r
                 const unsigned long long tmask = ((hx_r >> 1) | (nextbit << 63)) & exist;
                 if (lane == 0) *reinterpret_cast<unsigned long long *>(bits + 2 * r) = tmask;
             };
-#pragma unroll
-            for (int rb = 0; rb < kRows; rb += kBatch) {          // batches of rows keep the register count down
+#pragma unroll 1
+            for (int rb = 0; rb < kRows; rb += kBatch) {          // (a loop: unrolled it keeps more loads in flight than there are registers)
                 int a0[kBatch], a1[kBatch];
 #pragma unroll
                 for (int q = 0; q < kBatch; ++q) {
@@ -350,7 +358,10 @@ __global__ void __launch_bounds__(1024) k_stream_rank1_ldsvec(const int32_t *__r
         };
         auto gather = [&](const Rank1Half &h, double2 *xv) {
 #pragma unroll
-            for (int b = 0; b < 4; ++b) { xv[b].x = xs[h.c[b].x]; xv[b].y = xs[h.c[b].y]; }
+            for (int b = 0; b < 4; ++b) {
+                if constexpr (LDSVEC) { xv[b].x = xs[h.c[b].x]; xv[b].y = xs[h.c[b].y]; }
+                else { xv[b].x = x[h.c[b].x]; xv[b].y = x[h.c[b].y]; }
+            }
         };
         double2 xv[4];
         int2 tt[4];
@@ -372,64 +383,6 @@ __global__ void __launch_bounds__(1024) k_stream_rank1_ldsvec(const int32_t *__r
         }
         __builtin_amdgcn_wave_barrier();
     }
-}
-
-// ---- rank-1 kernel for sorted coordinate lists [CN,S,S] -------------------------------------------
-// A segment is a run of equal (c0, c1).  The root level keeps every coordinate and the lower levels
-// are singletons (one coordinate per position), so run ends are found by comparing neighbours.  The
-// result's own coordinate arrays are written here too: run number n (run_base[t] + runs started
-// earlier in the tile) gets y0[n], y1[n] from the run's first nonzero.
-__global__ void __launch_bounds__(256) k_stream_rank1_coo(const int32_t *__restrict__ c0, const int32_t *__restrict__ c1,
-                                                          const int32_t *__restrict__ c2, const double *__restrict__ vals,
-                                                          const int32_t *__restrict__ run_base,
-                                                          const double *__restrict__ v, int32_t *__restrict__ y0,
-                                                          int32_t *__restrict__ y1, double *__restrict__ yv, int64_t nnz,
-                                                          int64_t ntiles, void *scratch) {
-    __shared__ __attribute__((aligned(16))) int32_t ts[kTile];
-    __shared__ int wsum_ht[kWaves], wsum_first_id[kWaves], wcount[kWaves];
-    __shared__ double wsum_open[kWaves], wsum_first[kWaves];
-    const int64_t t = blockIdx.x;
-    const int64_t tb = t * (int64_t)kTile;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t wb = tb + (int64_t)w * kWaveItems;
-    Rank1Half h0;
-    rank1_load_half(h0, c2, vals, wb, lane, nnz);
-    constexpr int kRows = kWaveItems / 64;
-    unsigned long long hm[kRows];
-    int count = 0;
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-        const int64_t i = wb + 64 * r + lane;
-        bool head = false;
-        if (i < nnz) head = i == 0 || c0[i] != c0[i - 1] || c1[i] != c1[i - 1];
-        hm[r] = __ballot(head);
-        count += __popcll(hm[r]);
-    }
-    // does the item right after this wavefront's range start a run (or lie past the end)?
-    const int64_t inext = wb + kWaveItems;
-    const bool next_head = inext >= nnz || c0[inext] != c0[inext - 1] || c1[inext] != c1[inext - 1];
-    if (lane == 0) wcount[w] = count;
-    __syncthreads();
-    int running = run_base[t];
-    for (int u = 0; u < w; ++u) running += wcount[u];
-    const unsigned long long le_mask = (2ull << lane) - 1ull;
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-        const int64_t i = wb + 64 * r + lane;
-        const int id = running + __popcll(hm[r] & le_mask) - 1;
-        const bool head = (hm[r] >> lane) & 1ull;
-        bool tail;
-        if (lane < 63) tail = (hm[r] >> (lane + 1)) & 1ull;
-        else tail = r + 1 < kRows ? (hm[r + 1] & 1ull) != 0 : next_head;
-        if (i + 1 >= nnz) tail = true;
-        if (head) { y0[id] = c0[i]; y1[id] = c1[i]; }
-        ts[i - tb] = (i < nnz && tail) ? id : -1;
-        running += __popcll(hm[r]);
-    }
-    __syncthreads();
-    walk_rank1<false>(h0, ts, c2, vals, v, nullptr, yv, tb, nnz, wsum_ht, wsum_open, wsum_first, wsum_first_id);
-    __syncthreads();
-    finish_tile_rank1<false>(wsum_ht, wsum_open, wsum_first, wsum_first_id, nullptr, yv, carry_view(scratch, ntiles, 1), t);
 }
 
 // ---- fix-up: finish the first segment end of every tile -------------------------------------------
@@ -590,6 +543,43 @@ int current_device_cu_count() {
     return n;
 }
 
+namespace {
+
+struct Rank1Args {
+    const int32_t *pos, *crd;
+    const double *vals;
+    const int32_t *chunk_begin, *rowmap;
+    const double *x;
+    int64_t ncols;
+    double *out;
+    int64_t nnz, nchunks;
+    void *scratch;
+    const int32_t *c0, *c1;
+    int32_t *y0, *y1;
+    hipStream_t st;
+    Epilogue ep;
+};
+
+constexpr size_t kChunkWaveLds = 128 + 8 + 4;                     // per wavefront
+size_t rank1_lds(int64_t ncols) { return (size_t)((ncols + 1) & ~(int64_t)1) * 8 + 16 * kChunkWaveLds; }
+// There is a workgroup's worth of chunks, and the vector fits in LDS.
+bool vector_in_lds(int64_t nchunks, int64_t ncols) { return nchunks >= 16 && rank1_lds(ncols) <= 160 * 1024; }
+
+template <bool ROWMAP, bool COO, bool LDSVEC>
+hipError_t launch_rank1_chunks(const Rank1Args &a) {
+    const int64_t nw = LDSVEC ? 16 : kWaves, want = (a.nchunks + nw - 1) / nw, ncu = LDSVEC ? current_device_cu_count() : want;
+    if (LDSVEC) {
+        const hipError_t e = allow_full_lds<k_stream_rank1_chunk<ROWMAP, COO, LDSVEC>>();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_stream_rank1_chunk<ROWMAP, COO, LDSVEC>), dim3((unsigned)(want < ncu ? want : ncu)), dim3((unsigned)(64 * nw)),
+                       (unsigned)(LDSVEC ? rank1_lds(a.ncols) : kWaves * kChunkWaveLds), a.st, a.pos, a.crd, a.vals, a.chunk_begin, a.rowmap, a.x,
+                       a.ncols, a.out, a.nnz, a.nchunks, a.scratch, a.c0, a.c1, a.y0, a.y1, a.ep);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 bool stream_supports_rank(int64_t R) { return R >= 1 && R <= 128; }
 bool stream_mttkrp_supports_rank(int64_t R) { return R >= 1 && R <= 128; }
 bool stream_supports_coo() { return true; }
@@ -621,27 +611,11 @@ hipError_t stream_segreduce(const Schedule &sc, const int32_t *pos, const int32_
     const int32_t *sb = (const int32_t *)sc.seg_begin->ptr;
     hipError_t e = hipSuccess;
     if (R == 1) {
-        const size_t lds_bytes = (size_t)((dense_rows + 1) & ~(int64_t)1) * 8 + 16 * 128 + 16 * 8 + 16 * 4;
-        if (sc.empty_segments == 0 && sc.chunk_seg_begin && sc.nchunks >= 16 && lds_bytes <= 160 * 1024 && !plain) {
+        if (sc.empty_segments == 0 && sc.chunk_seg_begin && !plain && vector_in_lds(sc.nchunks, dense_rows)) {
             // the dense vector fits in LDS and every segment holds a nonzero: wavefront-per-chunk kernel
-            const int ncu = current_device_cu_count();
-            const int64_t want = (sc.nchunks + 15) / 16;
-            const unsigned grid = (unsigned)(want < ncu ? want : ncu);
-            const int32_t *csb = (const int32_t *)sc.chunk_seg_begin->ptr;
-            if (rowmap) {
-                e = allow_full_lds<k_stream_rank1_ldsvec<true, false>>();
-                if (e != hipSuccess) return e;
-                hipLaunchKernelGGL((k_stream_rank1_ldsvec<true, false>), dim3(grid), dim3(1024), lds_bytes, st, pos, crd, vals,
-                                   csb, rowmap, Dn, dense_rows, out, sc.nnz, sc.nchunks, scratch, (const int32_t *)nullptr,
-                                   (const int32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr, ep);
-            } else {
-                e = allow_full_lds<k_stream_rank1_ldsvec<false, false>>();
-                if (e != hipSuccess) return e;
-                hipLaunchKernelGGL((k_stream_rank1_ldsvec<false, false>), dim3(grid), dim3(1024), lds_bytes, st, pos, crd, vals,
-                                   csb, rowmap, Dn, dense_rows, out, sc.nnz, sc.nchunks, scratch, (const int32_t *)nullptr,
-                                   (const int32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr, ep);
-            }
-            e = hipGetLastError();
+            const Rank1Args a{pos, crd, vals, (const int32_t *)sc.chunk_seg_begin->ptr, rowmap, Dn, dense_rows, out, sc.nnz, sc.nchunks, scratch,
+                              nullptr, nullptr, nullptr, nullptr, st, ep};
+            e = rowmap ? launch_rank1_chunks<true, false, true>(a) : launch_rank1_chunks<false, false, true>(a);
             if (e != hipSuccess) return e;
             return run_fixup(scratch, sc.nchunks, 1, rowmap, out, sc.max_seg_len / kChunk + 2, st, ep);
         }
@@ -668,23 +642,11 @@ hipError_t stream_ttv_coo(const Schedule &sc, const int32_t *c0, const int32_t *
     if (sc.ntiles <= 0) return hipSuccess;
     // a run of equal (c0, c1) holds at most one nonzero per coordinate of the last mode
     const int64_t max_run = dense_rows;
-    const size_t lds_bytes = (size_t)((dense_rows + 1) & ~(int64_t)1) * 8 + 16 * 128 + 16 * 8 + 16 * 4;
-    if (sc.chunk_run_base && sc.nchunks >= 16 && lds_bytes <= 160 * 1024 && !plain) {
-        const int ncu = current_device_cu_count();
-        const int64_t want = (sc.nchunks + 15) / 16;
-        const unsigned grid = (unsigned)(want < ncu ? want : ncu);
-        hipError_t e = allow_full_lds<k_stream_rank1_ldsvec<false, true>>();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_stream_rank1_ldsvec<false, true>), dim3(grid), dim3(1024), lds_bytes, st,
-                           (const int32_t *)nullptr, c2, vals, (const int32_t *)sc.chunk_run_base->ptr,
-                           (const int32_t *)nullptr, v, dense_rows, yv, sc.nnz, sc.nchunks, scratch, c0, c1, y0, y1, Epilogue());
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        return run_fixup(scratch, sc.nchunks, 1, nullptr, yv, max_run / kChunk + 2, st);
-    }
-    hipLaunchKernelGGL(k_stream_rank1_coo, dim3((unsigned)sc.ntiles), dim3(256), 0, st, c0, c1, c2, vals,
-                       (const int32_t *)sc.run_base->ptr, v, y0, y1, yv, sc.nnz, sc.ntiles, scratch);
-    return run_fixup(scratch, sc.ntiles, 1, nullptr, yv, max_run / kTile + 2, st);
+    const Rank1Args a{nullptr, c2, vals, (const int32_t *)sc.chunk_run_base->ptr, nullptr, v, dense_rows, yv, sc.nnz, sc.nchunks, scratch,
+                      c0, c1, y0, y1, st, Epilogue()};
+    const hipError_t e = !plain && vector_in_lds(sc.nchunks, dense_rows) ? launch_rank1_chunks<false, true, true>(a) : launch_rank1_chunks<false, true, false>(a);
+    if (e != hipSuccess) return e;
+    return run_fixup(scratch, sc.nchunks, 1, nullptr, yv, max_run / kChunk + 2, st);
 }
 
 }  // namespace comet

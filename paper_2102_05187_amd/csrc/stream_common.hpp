@@ -21,8 +21,8 @@
 // and a small follow-up kernel finishes the segments cut by tile boundaries in a fixed order, so the
 // results do not depend on scheduling.
 //
-// Kernels:  k_stream_rank1_ldsvec  rank 1, dense vector staged in LDS, one wavefront per 1024-item chunk
-//           k_stream_rank1[_coo]   rank 1, vector gathered through L1, tail-id map per 4096-item tile
+// Kernels:  k_stream_rank1_chunk   rank 1, one wavefront per 1024-item chunk, dense vector staged in LDS (coordinate lists also through L1)
+//           k_stream_rank1         rank 1, vector gathered through L1, tail-id map per 4096-item tile
 //           k_pieces               rank R, lane groups walk pieces of segments (cut and carried in a way of their own, pieces.hpp)
 //           k_stream_rankR         ranks 8 and 16 over long lists, lane groups walk item runs, per-item records in LDS
 //           k_stream_mttkrp        rank R, two nested segment levels (fibers inside slices)

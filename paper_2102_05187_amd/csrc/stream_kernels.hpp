@@ -29,7 +29,7 @@ size_t mttkrp_call_bytes(const Schedule &sc, int64_t R, MttkrpRoute route);   //
 
 // out[row(s), :] = sum_{p in segment s} vals[p] * Dn[crd[p], :],  row(s) = rowmap ? rowmap[s] : s.
 // Every segment of the level is written (empty ones with zeros).  dense_rows = number of rows of Dn.
-// plain = true keeps rank-1 work on the per-tile kernel that gathers the vector through L1 (measurement
+// plain = true keeps rank-1 work on the kernels that gather the vector through L1 (measurement
 // baseline) instead of the kernel that stages it in LDS.
 hipError_t stream_segreduce(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals,
                             const int32_t *rowmap, const double *Dn, int64_t dense_rows, int64_t R, double *out,
