@@ -32,6 +32,7 @@
 // reproducible run to run).
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 #include <vector>
 
 #include "stream_common.hpp"
@@ -733,12 +734,20 @@ hipError_t heavy_spmm(const HeavyPlan &plan, const int32_t *rowmap, const double
 // contracted mode is small (a few thousand coordinates) U is cut into windows of rows that fill LDS (128 KB:
 // 1024 rows of 16 doubles or 512 rows of 32), every compute unit keeps ONE window for the whole kernel, and the
 // long fibers are handled piecewise: the nonzeros of a fiber are sorted by coordinate, so those inside window w
-// are the consecutive positions wstart[h][w] .. wstart[h][w+1].  A lane group of 8 takes such pieces one after
+// are the consecutive positions wstart[h][w] .. wstart[h][w+1].  A lane group of 16 takes such pieces one after
 // the other (pieces of window w are dealt back and forth over the lane groups of the compute units that hold
-// w, longest fibers first), gathers the operand rows from LDS -- 16 bytes per lane, a whole 128-byte row per
-// group and instruction, at LDS rather than L1 / texture-address cost -- and writes one partial row per
-// (fiber, window); a second kernel adds the windows of a fiber in a fixed order.  The remaining fibers stay with
-// the nonzero-tiled kernel, which skips the heavy ones.
+// w, longest fibers first), gathers the operand rows from LDS -- a whole row per group and instruction, at LDS
+// rather than L1 / texture-address cost -- and writes one partial row per (fiber, window); a second kernel adds
+// the windows of a fiber in a fixed order.  The remaining fibers stay with the nonzero-tiled kernel, which skips
+// the heavy ones.
+//
+// What bounds it is the issue of vector instructions, with the reads of LDS close behind.  Groups of 16 because the
+// hardware broadcasts a lane over a row of 16 inside an addition or a multiplication: a step is three instructions
+// per row of four items, and was eleven per eight with groups of 8, whose broadcasts are moves.  A block always takes
+// 16 items, those behind a piece's end with a row of zeros, so that no step asks whether the piece goes on (with that
+// question 243 us where this takes 196).  65 M nonzeros in 55 K fibers, rank 16: 270 us before, 196 now
+// (780 MB of nonzeros at 4 TB/s); whole calls of TTM on 100 M nonzeros, rank 16, 733 and 667; 60 M, 5000 rows of
+// rank 32, 719 and 673; 4 M in half a million fibers, rank 16, 97 and 59.
 namespace {
 
 constexpr int kFiberLen = 256;         // a fiber with at least this many nonzeros is heavy
@@ -746,13 +755,35 @@ constexpr int kFiberLdsBytes = 128 * 1024;
 constexpr int kFiberMaxWindows = 16;
 constexpr int kFiberThreads = 1024;
 
-template <int L, int V>                // L lanes per group, V doubles per lane; rank = L * V
-__global__ void __launch_bounds__(kFiberThreads) k_fiber_sweep(const int32_t *__restrict__ crd, const double *__restrict__ vals,
-                                                               const int32_t *__restrict__ wstart, int nheavy, int nwin,
-                                                               int window, const double *__restrict__ U, int ncols,
-                                                               double *__restrict__ partial) {
-    extern __shared__ __attribute__((aligned(16))) double2 urows[];          // [window][R / 2]
-    constexpr int R = L * V, R2 = R / 2, kGroups = kFiberThreads / L;
+template <int S>                       // lane S of each row of 16 lanes, in all of them
+__device__ __forceinline__ int row_bcast(int v) { return __builtin_amdgcn_mov_dpp(v, 0x150 + S, 0xf, 0xf, true); }
+
+// acc += a of lanes S .. S + 7 of the row times u0 .. u7, in this order.  The compiler spends a move on every broadcast of a
+// double; the multiplication can do it itself.  (s_nop: a register that a vector instruction has just written can be
+// read across lanes two cycles later.)
+template <int S>
+__device__ __forceinline__ void fma8(double &acc, double a, double u0, double u1, double u2, double u3, double u4, double u5, double u6,
+                                     double u7) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%c10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %3 row_newbcast:%c11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %4 row_newbcast:%c12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %5 row_newbcast:%c13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %6 row_newbcast:%c14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %7 row_newbcast:%c15 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %8 row_newbcast:%c16 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %9 row_newbcast:%c17 row_mask:0xf bank_mask:0xf"
+        : "+&v"(acc)
+        : "v"(a), "v"(u0), "v"(u1), "v"(u2), "v"(u3), "v"(u4), "v"(u5), "v"(u6), "v"(u7), "n"(S), "n"(S + 1), "n"(S + 2), "n"(S + 3),
+          "n"(S + 4), "n"(S + 5), "n"(S + 6), "n"(S + 7));
+}
+
+template <int V>                       // lane groups of 16, V doubles per lane; rank = 16 * V
+__global__ void __launch_bounds__(kFiberThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))   // (LDS leaves one workgroup per compute unit)
+k_fiber_sweep(const int32_t *__restrict__ crd, const double *__restrict__ vals, const int32_t *__restrict__ wstart, int nheavy, int nwin,
+              int window, const double *__restrict__ U, int ncols, double *__restrict__ partial) {
+    extern __shared__ __attribute__((aligned(16))) double2 urows[];          // [window + 1][R / 2]
+    constexpr int L = 16, R = L * V, R2 = R / 2, kGroups = kFiberThreads / L, D = 4;
     const int w = (int)(blockIdx.x % (unsigned)nwin), cw = (int)(blockIdx.x / (unsigned)nwin);
     const int ncw = ((int)gridDim.x - w + nwin - 1) / nwin;                  // workgroups that hold window w
     const int k0 = w * window, k1 = k0 + window < ncols ? k0 + window : ncols;
@@ -760,57 +791,81 @@ __global__ void __launch_bounds__(kFiberThreads) k_fiber_sweep(const int32_t *__
         const int n2 = (k1 - k0) * R2;
         const double2 *src = reinterpret_cast<const double2 *>(U + (size_t)k0 * R);
         for (int i = threadIdx.x; i < n2; i += kFiberThreads) urows[i] = src[i];
+        if (threadIdx.x < R2) urows[window * R2 + threadIdx.x] = make_double2(0.0, 0.0);      // a row of zeros behind the window
     }
     __syncthreads();
     const int g = threadIdx.x / L, j = threadIdx.x % L;
+    using Share = std::conditional_t<V == 1, double, double2>;              // a lane's part of a row
+    const char *mycols = reinterpret_cast<const char *>(urows) + j * sizeof(Share);
     const int Gw = ncw * kGroups, mine = cw * kGroups + g;
     const int per = nwin + 1;
     auto piece_of = [&](int t) { return t * Gw + ((t & 1) ? Gw - 1 - mine : mine); };
     const int rounds = (nheavy + Gw - 1) / Gw;
-    // bounds of the first piece
-    int h = piece_of(0), p0 = 0, p1 = 0;
-    if (rounds > 0 && h < nheavy) { p0 = wstart[(size_t)h * per + w]; p1 = wstart[(size_t)h * per + w + 1]; }
-    for (int t = 0; t < rounds; ++t) {
-        // bounds of the next piece: in flight during this one
-        const int hn = piece_of(t + 1);
-        int p0n = 0, p1n = 0;
-        if (t + 1 < rounds && hn < nheavy) { p0n = wstart[(size_t)hn * per + w]; p1n = wstart[(size_t)hn * per + w + 1]; }
-        double acc[V];
+    // The group's pieces as one sequence of blocks of L items, each block inside one piece.  D blocks are in flight across
+    // the ends of the pieces, so none of their loads is under a condition; the pieces' bounds, which are, come L pieces at
+    // a time, one per lane.
+    int bounds0 = 0, bounds1 = 0, tf = -1, pf = 0, ef = 0;                  // of the L pieces around tf; rest of piece tf
+    auto next_piece = [&] {
+        ++tf;
+        if (tf % L == 0) {
+            const int h = piece_of(tf + j);
+            const size_t at = (size_t)(h < nheavy ? h : 0) * per + w;
+            const int b0 = wstart[at], b1 = wstart[at + 1];
+            bounds0 = b0;
+            bounds1 = h < nheavy ? b1 : b0;
+        }
+        pf = __shfl(bounds0, tf % L, L);
+        ef = __shfl(bounds1, tf % L, L);
+    };
+    int c[D], left[D];                                                      // of a block: the lane's item; items of the piece from the block on
+    double a[D];
+    auto fetch = [&](int &cd, double &ad, int &ld) {
+        ld = ef - pf;
+        int i = pf + (j < ld ? j : ld - 1);                                 // behind the piece's last item, that item again
+        i = i > 0 ? i : 0;
+        cd = crd[i];
+        ad = vals[i];
+        if (ld > L) pf += L; else next_piece();
+    };
+    next_piece();
 #pragma unroll
-        for (int q = 0; q < V; ++q) acc[q] = 0.0;
-        int c_cur = 0;
-        double a_cur = 0.0;
-        if (p0 + j < p1) { c_cur = crd[p0 + j]; a_cur = vals[p0 + j]; }
-        int p = p0;
-        auto block = [&](auto checked) {                                   // L items: one per lane, taken one by one
-            int c_nxt = 0;
-            double a_nxt = 0.0;
-            if (p + L + j < p1) { c_nxt = crd[p + L + j]; a_nxt = vals[p + L + j]; }
-            const int rowoff = (c_cur - k0) * R2;                          // of this lane's item, in 16-byte pieces
-            static_for<0, L>([&](auto sc) {
-                constexpr int s_ = decltype(sc)::value;
-                if (!decltype(checked)::value || p + s_ < p1) {             // the same for the whole group
-                    const int o = grp_bcast_i<L, s_>(rowoff) + j;
-                    const double a = grp_bcast_d<L, s_>(a_cur);
+    for (int d = 0; d < D; ++d) fetch(c[d], a[d], left[d]);
+    double acc[V];
 #pragma unroll
-                    for (int q = 0; q < V / 2; ++q) {
-                        const double2 d = urows[o + L * q];
-                        acc[2 * q] = fma(a, d.x, acc[2 * q]);
-                        acc[2 * q + 1] = fma(a, d.y, acc[2 * q + 1]);
-                    }
+    for (int q = 0; q < V; ++q) acc[q] = 0.0;
+    for (int t = 0; t < rounds;) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            // behind the piece's last item, zero times the row of zeros
+            const bool in = j < left[d];
+            const int rowoff = in ? (c[d] - k0) * (R * 8) : window * (R * 8);
+            const double ad = in ? a[d] : 0.0;
+            static_for<0, L / 8>([&](auto bc) {                             // eight rows are read before the first of them is used
+                constexpr int s0 = decltype(bc)::value * 8;
+                Share u[8];
+                static_for<0, 8>([&](auto sc) {
+                    constexpr int s_ = decltype(sc)::value;
+                    u[s_] = *reinterpret_cast<const Share *>(mycols + row_bcast<s0 + s_>(rowoff));
+                });
+                if constexpr (V == 1) {
+                    fma8<s0>(acc[0], ad, u[0], u[1], u[2], u[3], u[4], u[5], u[6], u[7]);
+                } else {
+                    fma8<s0>(acc[0], ad, u[0].x, u[1].x, u[2].x, u[3].x, u[4].x, u[5].x, u[6].x, u[7].x);
+                    fma8<s0>(acc[1], ad, u[0].y, u[1].y, u[2].y, u[3].y, u[4].y, u[5].y, u[6].y, u[7].y);
                 }
             });
-            c_cur = c_nxt; a_cur = a_nxt;
-            p += L;
-        };
-        while (p + L <= p1) block(IntC<0>{});
-        if (p < p1) block(IntC<1>{});
-        if (h < nheavy) {
-            double2 *dst = reinterpret_cast<double2 *>(partial + ((size_t)h * nwin + w) * R) + j;
+            if (left[d] <= L) {
+                const int h = piece_of(t);
+                if (t < rounds && h < nheavy) {
+                    Share *dst = reinterpret_cast<Share *>(partial + ((size_t)h * nwin + w) * R) + j;
+                    if constexpr (V == 1) *dst = acc[0]; else *dst = make_double2(acc[0], acc[1]);
+                }
 #pragma unroll
-            for (int q = 0; q < V / 2; ++q) dst[L * q] = make_double2(acc[2 * q], acc[2 * q + 1]);
+                for (int q = 0; q < V; ++q) acc[q] = 0.0;
+                ++t;
+            }
+            fetch(c[d], a[d], left[d]);
         }
-        h = hn; p0 = p0n; p1 = p1n;
     }
 }
 
@@ -907,18 +962,18 @@ hipError_t fiber_ttm(const FiberPlan &plan, const int32_t *crd, const double *va
     const int k = fiber_plan_index(R);
     const int ncu = current_device_cu_count();
     const unsigned grid = (unsigned)(ncu < plan.nwin[k] ? plan.nwin[k] : ncu);      // every window needs a workgroup
-    const size_t lds = (size_t)plan.window[k] * (size_t)R * sizeof(double);
+    const size_t lds = (size_t)(plan.window[k] + 1) * (size_t)R * sizeof(double);      // and a row of zeros
     double *pp = (double *)partial;
     hipError_t e;
     if (R == 16) {
-        static hipError_t attr = hipFuncSetAttribute((const void *)k_fiber_sweep<8, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        static hipError_t attr = hipFuncSetAttribute((const void *)k_fiber_sweep<1>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if ((e = attr) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_fiber_sweep<8, 2>), dim3(grid), dim3(kFiberThreads), lds, st, crd, vals, (const int32_t *)plan.wstart[k]->ptr,
+        hipLaunchKernelGGL(k_fiber_sweep<1>, dim3(grid), dim3(kFiberThreads), lds, st, crd, vals, (const int32_t *)plan.wstart[k]->ptr,
                            (int)plan.nheavy, (int)plan.nwin[k], (int)plan.window[k], Dn, (int)ncols, pp);
     } else {
-        static hipError_t attr = hipFuncSetAttribute((const void *)k_fiber_sweep<8, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        static hipError_t attr = hipFuncSetAttribute((const void *)k_fiber_sweep<2>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if ((e = attr) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_fiber_sweep<8, 4>), dim3(grid), dim3(kFiberThreads), lds, st, crd, vals, (const int32_t *)plan.wstart[k]->ptr,
+        hipLaunchKernelGGL(k_fiber_sweep<2>, dim3(grid), dim3(kFiberThreads), lds, st, crd, vals, (const int32_t *)plan.wstart[k]->ptr,
                            (int)plan.nheavy, (int)plan.nwin[k], (int)plan.window[k], Dn, (int)ncols, pp);
     }
     e = hipGetLastError();
