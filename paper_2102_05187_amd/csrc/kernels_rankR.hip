@@ -1,5 +1,5 @@
-// Rank-R kernel of the nonzero-tiled family (SpMM, TTM): lane groups walk runs of consecutive nonzeros.  Serves ranks 8 and
-// 16 over long lists; see stream_segreduce for where the line to the piece kernel lies.
+// Rank-R kernel of the nonzero-tiled family (SpMM, TTM): lane groups walk runs of consecutive nonzeros.  Serves rank 16
+// over long lists of short segments; see stream_segreduce for where the line to the piece kernel lies.
 #include "stream_common.hpp"
 
 namespace comet {
@@ -110,30 +110,16 @@ __global__ void __launch_bounds__(256) k_stream_rankR(const int32_t *__restrict_
                                     carry_view(scratch, ntiles, R), t, ep);
 }
 
-template <int L, bool ROWMAP>
-void launch_rankR_one(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals, const int32_t *rowmap,
-                      const double *Dn, int R, double *out, void *scratch, hipStream_t st, Epilogue ep) {
-    hipLaunchKernelGGL((k_stream_rankR<L, ROWMAP>), dim3((unsigned)sc.ntiles), dim3(256), 0, st, pos, crd, vals,
-                       (const int32_t *)sc.seg_begin->ptr, rowmap, Dn, out, sc.nnz, sc.ntiles, R, scratch, ep);
-}
-
-template <int L>
-hipError_t launch_rankR(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals,
-                        const int32_t *rowmap, const double *Dn, int R, double *out, void *scratch, hipStream_t st,
-                        Epilogue ep) {
-    if (rowmap) launch_rankR_one<L, true>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
-    else launch_rankR_one<L, false>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
-    return hipGetLastError();
-}
-
 }  // namespace
 
-hipError_t stream_segreduce_rankR(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals,
-                                  const int32_t *rowmap, const double *Dn, int R, double *out, void *scratch,
-                                  hipStream_t st, Epilogue ep) {
-    if (R == 8) return launch_rankR<4>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
-    if (R == 16) return launch_rankR<8>(sc, pos, crd, vals, rowmap, Dn, R, out, scratch, st, ep);
-    return hipErrorNotSupported;
+hipError_t stream_segreduce_rank16(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals,
+                                   const int32_t *rowmap, const double *Dn, double *out, void *scratch, hipStream_t st, Epilogue ep) {
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)sc.ntiles), dim3(256), 0, st, pos, crd, vals, (const int32_t *)sc.seg_begin->ptr, rowmap,
+                           Dn, out, sc.nnz, sc.ntiles, 16, scratch, ep);
+    };
+    if (rowmap) go(k_stream_rankR<8, true>); else go(k_stream_rankR<8, false>);
+    return hipGetLastError();
 }
 
 }  // namespace comet

@@ -1,5 +1,5 @@
-"""SpMM over more than 10 M nonzeros at ranks 8 and 16, which a walk over tiles of 4096 nonzeros takes: rows that end around the
-boundaries of walkers (64 and 128 nonzeros) and tiles, rows over many tiles, empty rows, plain and accumulating."""
+"""SpMM over more than 10 M nonzeros at ranks 8 and 16: rows that end around multiples of 64, 128 and 4096 nonzeros (lists of
+short rows that a walk over tiles of 4096 takes are in test_gpu_rank16_walk.py), rows over many tiles, empty rows, plain and accumulating."""
 import numpy as np
 import pytest
 import torch
