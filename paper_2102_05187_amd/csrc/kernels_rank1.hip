@@ -590,7 +590,7 @@ size_t stream_scratch_bytes(int64_t ntiles, int64_t R) { return carry_bytes(ntil
 // nonzeros keeps more in flight.  Whole calls on the walk and on the pieces, rank 16: TTM on 100 M nonzeros (35 M of them, 5 per
 // fiber, off the sweep) 667 and 700 us; 30 M at random, 7.5 per fiber, 347 and 356, 4 per fiber 420 and 420.  Fewer nonzeros: 15 M,
 // 5 and 2.5 per fiber, 212 and 205, 281 and 266.  Longer segments: SpMM on 12 M, 12 per row near the diagonal, 229 and 137; 11 M
-// anywhere 243 and 233; 16 M in 1 to 100 per row 343 and 333.  Rank 8, where half of a wide load's lanes have no column on either:
+// anywhere 243 and 233; 16 M in 1 to 100 per row 343 and 333.  Rank 8:
 // 30 M, 7.5 and 4 per fiber, 285 and 258, 340 and 297; 100 M in 6.5 M fibers 732 and 699; SpMM on 30 M, 30 per row, 602 and 557.
 static bool takes_walk(const Schedule &sc, int64_t R) { return R == 16 && sc.nnz >= kWalkNnz && sc.nnz <= 8 * sc.nseg; }
 
