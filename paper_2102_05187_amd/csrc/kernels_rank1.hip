@@ -3,6 +3,7 @@
 #include <atomic>
 
 #include "pieces.hpp"
+#include "routes.hpp"
 #include "stream_common.hpp"
 
 namespace comet {
@@ -586,16 +587,8 @@ bool stream_supports_coo() { return true; }
 
 size_t stream_scratch_bytes(int64_t ntiles, int64_t R) { return carry_bytes(ntiles < 1 ? 1 : ntiles, R) + 256; }
 
-// Which walk: the pieces, except for rank 16 over very many nonzeros in short segments, of which the walk over whole tiles of
-// nonzeros keeps more in flight.  Whole calls on the walk and on the pieces, rank 16: TTM on 100 M nonzeros (35 M of them, 5 per
-// fiber, off the sweep) 667 and 700 us; 30 M at random, 7.5 per fiber, 347 and 356, 4 per fiber 420 and 420.  Fewer nonzeros: 15 M,
-// 5 and 2.5 per fiber, 212 and 205, 281 and 266.  Longer segments: SpMM on 12 M, 12 per row near the diagonal, 229 and 137; 11 M
-// anywhere 243 and 233; 16 M in 1 to 100 per row 343 and 333.  Rank 8:
-// 30 M, 7.5 and 4 per fiber, 285 and 258, 340 and 297; 100 M in 6.5 M fibers 732 and 699; SpMM on 30 M, 30 per row, 602 and 557.
-static bool takes_walk(const Schedule &sc, int64_t R) { return R == 16 && sc.nnz >= kWalkNnz && sc.nnz <= 8 * sc.nseg; }
-
 bool segreduce_supports(const Schedule &sc, int64_t R) {
-    return sc.ntiles <= 0 || R == 1 || takes_walk(sc, R) || sc.pieces.ntiles > 0;
+    return sc.ntiles <= 0 || R == 1 || segreduce_takes_walk(sc, R) || sc.pieces.ntiles > 0;
 }
 
 size_t segreduce_scratch_bytes(const Schedule &sc, int64_t R) {
@@ -628,12 +621,12 @@ hipError_t stream_segreduce(const Schedule &sc, const int32_t *pos, const int32_
                                rowmap, Dn, out, sc.nnz, sc.ntiles, scratch, ep);
         e = hipGetLastError();
     } else {
-        if (!takes_walk(sc, R))
+        if (!segreduce_takes_walk(sc, R))
             return piece_rows(sc.pieces, crd, vals, sc.nnz, rowmap, Dn, dense_rows, (int)R, out, scratch, st, ep);
-        e = stream_segreduce_rank16(sc, pos, crd, vals, rowmap, Dn, out, scratch, st, ep);
+        e = stream_segreduce_rankR(sc, pos, crd, vals, rowmap, Dn, (int)R, out, scratch, st, ep);
     }
     if (e != hipSuccess) return e;
-    // the rank-16 kernel publishes result rows as ids, the rank-1 kernel segment numbers
+    // the rank-R kernel publishes result rows as ids, the rank-1 kernel segment numbers
     return run_fixup(scratch, sc.ntiles, (int)R, R == 1 ? rowmap : nullptr, out, sc.max_seg_len / kTile + 2, st, ep);
 }
 

@@ -1,5 +1,5 @@
-// Rank-R kernel of the nonzero-tiled family (SpMM, TTM): lane groups walk runs of consecutive nonzeros.  Serves rank 16
-// over long lists of short segments; see stream_segreduce for where the line to the piece kernel lies.
+// Rank-R kernel of the nonzero-tiled family (SpMM, TTM): lane groups walk runs of consecutive nonzeros.  Serves ranks 8 and
+// 16 over long lists; routes.hpp says over which, and which take the piece kernel.
 #include "stream_common.hpp"
 
 namespace comet {
@@ -112,14 +112,16 @@ __global__ void __launch_bounds__(256) k_stream_rankR(const int32_t *__restrict_
 
 }  // namespace
 
-hipError_t stream_segreduce_rank16(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals,
-                                   const int32_t *rowmap, const double *Dn, double *out, void *scratch, hipStream_t st, Epilogue ep) {
+hipError_t stream_segreduce_rankR(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals, const int32_t *rowmap,
+                                  const double *Dn, int R, double *out, void *scratch, hipStream_t st, Epilogue ep) {
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)sc.ntiles), dim3(256), 0, st, pos, crd, vals, (const int32_t *)sc.seg_begin->ptr, rowmap,
-                           Dn, out, sc.nnz, sc.ntiles, 16, scratch, ep);
+                           Dn, out, sc.nnz, sc.ntiles, R, scratch, ep);
+        return hipGetLastError();
     };
-    if (rowmap) go(k_stream_rankR<8, true>); else go(k_stream_rankR<8, false>);
-    return hipGetLastError();
+    if (R == 8) return rowmap ? go(k_stream_rankR<4, true>) : go(k_stream_rankR<4, false>);
+    if (R == 16) return rowmap ? go(k_stream_rankR<8, true>) : go(k_stream_rankR<8, false>);
+    return hipErrorNotSupported;
 }
 
 }  // namespace comet

@@ -127,29 +127,35 @@ __global__ void __launch_bounds__(256) k_piece_cuts(const int32_t *__restrict__ 
     else cuts[ntiles - 1 - atomicAdd(&counters[1], 1)] = c;
 }
 
-// Sets a bit per coordinate of a sample (samples spread evenly over the list) and adds up the bits that are set.
+// Sets a bit per coordinate of a sample (samples spread evenly over the list).  sums[0]: the bits that are set, of all samples
+// together; sums[1]: how many of the first kSampleLook nonzeros of the sample behind find theirs set.
 constexpr int kSampleBits = 1 << 18;
-__global__ void __launch_bounds__(1024) k_piece_distinct(const int32_t *__restrict__ crd, int64_t nnz, int *__restrict__ set) {
+__global__ void __launch_bounds__(1024) k_piece_sample(const int32_t *__restrict__ crd, int64_t nnz, int *__restrict__ sums) {
     __shared__ uint32_t bits[kSampleBits / 32];
     for (int i = threadIdx.x; i < kSampleBits / 32; i += 1024) bits[i] = 0u;
     __syncthreads();
     const int64_t n = nnz < kSampleNnz ? nnz : kSampleNnz;
-    const int64_t begin = gridDim.x > 1 ? (nnz - n) / (gridDim.x - 1) * blockIdx.x : 0;
-    for (int64_t i = threadIdx.x; i < n; i += 32 * 1024) {
+    auto begin = [&](unsigned s) { return (nnz - n) / (kSamples - 1) * (s % kSamples); };
+    auto batch = [&](int64_t at, int64_t i, auto use) {          // nonzeros i, i + 1024, ... of the sample that begins at `at`
         uint32_t c[32];
 #pragma unroll
-        for (int q = 0; q < 32; ++q) c[q] = (uint32_t)crd[begin + (i + q * 1024 < n ? i + q * 1024 : i)];
+        for (int q = 0; q < 32; ++q) c[q] = (uint32_t)crd[at + (i + q * 1024 < n ? i + q * 1024 : i)];
 #pragma unroll
-        for (int q = 0; q < 32; ++q) {
-            const uint32_t h = (c[q] * 0x9E3779B1u) >> 14;
-            atomicOr(&bits[h >> 5], 1u << (h & 31u));
-        }
-    }
+        for (int q = 0; q < 32; ++q) use((c[q] * 0x9E3779B1u) >> 14);
+    };
+    auto add_up = [&](int v, int *to) {
+        for (int d = 32; d > 0; d >>= 1) v += __shfl_down(v, d);
+        if ((threadIdx.x & 63) == 0) atomicAdd(to, v);
+    };
+    for (int64_t i = threadIdx.x; i < n; i += 32 * 1024)
+        batch(begin(blockIdx.x), i, [&](uint32_t h) { atomicOr(&bits[h >> 5], 1u << (h & 31u)); });
     __syncthreads();
-    int sum = 0;
-    for (int i = threadIdx.x; i < kSampleBits / 32; i += 1024) sum += __popc(bits[i]);
-    for (int d = 32; d > 0; d >>= 1) sum += __shfl_down(sum, d);
-    if ((threadIdx.x & 63) == 0) atomicAdd(set, sum);
+    int set = 0, found = 0;
+    for (int i = threadIdx.x; i < kSampleBits / 32; i += 1024) set += __popc(bits[i]);
+    static_assert(kSampleLook == 32 * 1024, "one batch");
+    if (threadIdx.x < n) batch(begin(blockIdx.x + 1), threadIdx.x, [&](uint32_t h) { found += (bits[h >> 5] >> (h & 31u)) & 1u; });
+    add_up(set, &sums[0]);
+    add_up(found, &sums[1]);
 }
 
 unsigned grid_for(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -166,28 +172,27 @@ hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd
     plan.ntiles = ntiles;
     plan.tiles_mem = dev_alloc(sizeof(int4) * (2 * ntiles + 1));
     // temporary: pieces and joins of each tile, their sums before each tile, counters (short cuts, long cuts, most partial
-    // sums in a tile, bits set by the samples), and what the scan asks for.  One allocation: each costs a small handle's creation 10 us and more
+    // sums in a tile, bits set by the samples and found in them), and what the scan asks for.  One allocation: each costs a small handle's creation 10 us and more
     size_t tb = 0;
     hipError_t e = reorder_scan_flags(nullptr, &tb, (uint64_t *)nullptr, (uint64_t *)nullptr, ntiles + 1, st);
     if (e != hipSuccess) return fail(e);
-    const size_t scan_at = ((size_t)(2 * (ntiles + 1) + 2) * sizeof(uint64_t) + 255) & ~(size_t)255;
+    const size_t scan_at = ((size_t)(2 * (ntiles + 1) + 3) * sizeof(uint64_t) + 255) & ~(size_t)255;
     DevRef temp = dev_alloc(scan_at + tb);
     if (!plan.tiles_mem || !temp) return fail(hipErrorOutOfMemory);
     uint64_t *cn = (uint64_t *)temp->ptr, *bf = cn + ntiles + 1;
     int *counters = (int *)(bf + ntiles + 1);
     hipLaunchKernelGGL(k_piece_tiles, dim3(grid_for(ntiles + 1)), dim3(256), 0, st, pos, nseg, nnz, plan.units, ntiles, plan.tiles());
     e = hipMemsetAsync(cn + ntiles, 0, sizeof(uint64_t), st);
-    if (e == hipSuccess) e = hipMemsetAsync(counters, 0, 4 * sizeof(int), st);
+    if (e == hipSuccess) e = hipMemsetAsync(counters, 0, 6 * sizeof(int), st);
     if (e != hipSuccess) return fail(e);
     hipLaunchKernelGGL((k_piece_fill<false>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, plan.tiles(), cn,
                        counters + 2, (uint32_t *)nullptr, (uint32_t *)nullptr);
     hipLaunchKernelGGL(k_piece_cuts, dim3(grid_for(ntiles)), dim3(256), 0, st, pos, nseg, (const int4 *)plan.tiles(), ntiles,
                        plan.cuts(), counters);
     // (a list shorter than a sample is not worth the 40 us that the kernel costs a small handle)
-    const int samples = 4;
-    if (nnz >= kSampleNnz) hipLaunchKernelGGL(k_piece_distinct, dim3(samples), dim3(1024), 0, st, crd, nnz, counters + 3);
+    if (nnz >= kSampleNnz) hipLaunchKernelGGL(k_piece_sample, dim3(kSamples), dim3(1024), 0, st, crd, nnz, counters + 3);
     e = reorder_scan_flags((char *)temp->ptr + scan_at, &tb, cn, bf, ntiles + 1, st);
-    struct { uint64_t total; int short_cuts, long_cuts, max_parts, set; } sums = {0, 0, 0, 0, 0};    // bf[ntiles] and the counters
+    struct { uint64_t total; int short_cuts, long_cuts, max_parts, set, found, pad; } sums = {};    // bf[ntiles] and the counters
     if (e == hipSuccess) e = hipMemcpyAsync(&sums, bf + ntiles, sizeof sums, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(e);
@@ -196,9 +201,10 @@ hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd
     plan.ncut = sums.short_cuts;
     plan.ncut_long = sums.long_cuts;
     plan.max_parts = sums.max_parts;
-    // m coordinates set kSampleBits * (1 - exp(-m / kSampleBits)) bits
-    const double unset = 1.0 - (double)sums.set / ((double)samples * kSampleBits);
+    // m coordinates set kSampleBits * (1 - exp(-m / kSampleBits)) bits, and as large a share of the others finds a bit set by chance
+    const double unset = 1.0 - (double)sums.set / ((double)kSamples * kSampleBits);
     plan.distinct = unset > 0.0 ? (int64_t)(-std::log(unset) * kSampleBits) : kSampleNnz;
+    plan.common = unset > 0.0 ? 1.0 - (1.0 - (double)sums.found / ((double)kSamples * kSampleLook)) / unset : 0.0;
     plan.pieces_mem = dev_alloc(sizeof(uint32_t) * (plan.npieces + plan.njoins));
     if (!plan.pieces_mem) return fail(hipErrorOutOfMemory);
     hipLaunchKernelGGL((k_piece_fill<true>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, plan.tiles(), bf,

@@ -40,12 +40,11 @@ constexpr int kShortChain = 24;        // tiles that a segment is cut over, up t
 // Finishes every segment that a tile boundary cut (defined in kernels_rank1.hip).
 hipError_t run_fixup(void *scratch, int64_t ntiles, int R, const int32_t *rowmap, double *out, int64_t max_chain,
                      hipStream_t st, Epilogue ep = Epilogue());
-// The walk of stream_segreduce at rank 16 (defined in kernels_rankR.hip).
-hipError_t stream_segreduce_rank16(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals,
-                                   const int32_t *rowmap, const double *Dn, double *out, void *scratch, hipStream_t st, Epilogue ep = Epilogue());
+// The walk of stream_segreduce at ranks 8 and 16 (defined in kernels_rankR.hip).
+hipError_t stream_segreduce_rankR(const Schedule &sc, const int32_t *pos, const int32_t *crd, const double *vals,
+                                  const int32_t *rowmap, const double *Dn, int R, double *out, void *scratch,
+                                  hipStream_t st, Epilogue ep = Epilogue());
 
-// Nonzeros from which on rank 16 takes that walk and not the pieces, if the segments are short (see stream_segreduce).
-constexpr int64_t kWalkNnz = int64_t(24) << 20;
 // The same over the piece plan (defined in kernels_pieces.hip).
 hipError_t piece_rows(const PiecePlan &plan, const int32_t *crd, const double *vals, int64_t nnz, const int32_t *rowmap, const double *Dn,
                       int64_t dense_rows, int R, double *out, void *scratch, hipStream_t st, Epilogue ep = Epilogue());

@@ -104,7 +104,10 @@ struct PiecePlan {
     int     units = 0;                 // units per tile
     int     max_parts = 0;             // most partial sums in a tile
     int64_t ncut = 0, ncut_long = 0;   // segments cut by tile boundaries: over few tiles, over many
-    int64_t distinct = 0;              // different coordinates among kSampleNnz consecutive nonzeros, about
+    // of samples of the list, about: different coordinates among kSampleNnz consecutive nonzeros, and which share of a sample's nonzeros have
+    // a coordinate that the sample in front of it has (0 while unknown)
+    int64_t distinct = 0;
+    double  common = 0.0;
     DevRef  tiles_mem, pieces_mem;
     // int4 [ntiles + 1]: first nonzero, segment, piece and join of a tile
     int4 *tiles() const { return tiles_mem ? (int4 *)tiles_mem->ptr : nullptr; }

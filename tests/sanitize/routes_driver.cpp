@@ -1,0 +1,28 @@
+// Host check of the rules that choose a kernel by what a list's plan has counted: prints the route of each list given on stdin.
+//   segreduce RANK nnz segments pieces distinct common joins    -> walk | pieces
+#include <cstdio>
+#include <cstring>
+
+#include "../../paper_2102_05187_amd/csrc/routes.hpp"
+
+int main() {
+    char op[32];
+    while (scanf("%31s", op) == 1) {
+        comet::Schedule sc;
+        long rank, nnz, nseg, ntiles, distinct, joins;
+        double common;
+        if (!strcmp(op, "segreduce")) {
+            if (scanf("%ld %ld %ld %ld %ld %lf %ld", &rank, &nnz, &nseg, &ntiles, &distinct, &common, &joins) != 7) return 1;
+            sc.nnz = nnz;
+            sc.nseg = nseg;
+            sc.pieces.ntiles = ntiles;
+            sc.pieces.distinct = distinct;
+            sc.pieces.common = common;
+            sc.pieces.njoins = joins;
+            printf("%s\n", comet::segreduce_takes_walk(sc, rank) ? "walk" : "pieces");
+        } else {
+            return 1;
+        }
+    }
+    return 0;
+}

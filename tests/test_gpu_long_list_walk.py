@@ -1,5 +1,7 @@
-"""SpMM over more than 10 M nonzeros at ranks 8 and 16: rows that end around multiples of 64, 128 and 4096 nonzeros (lists of
-short rows that a walk over tiles of 4096 takes are in test_gpu_rank16_walk.py), rows over many tiles, empty rows, plain and accumulating."""
+"""SpMM at ranks 8 and 16 over lists that a walk over tiles of 4096 nonzeros takes, because their rows differ in length and all
+parts of the list use the same operand rows (from 10 M nonzeros on; very long lists of short rows are in
+test_gpu_rank16_walk.py): rows that end around the boundaries of walkers (64 and 128 nonzeros) and tiles, rows over many tiles, empty rows, plain and
+accumulating."""
 import numpy as np
 import pytest
 import torch

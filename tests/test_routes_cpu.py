@@ -1,0 +1,57 @@
+"""Which kernel a list takes: lists for which both kernels were timed, by what their plans counted, take the faster one, and a list
+whose plan there was no memory for keeps a kernel that needs none.  Runs on the host."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+M = 1_000_000
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("routes") / "routes")
+    cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip", "-O1", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature",
+           "-Xclang", "-packed-fp32-ops", os.path.join(ROOT, "tests", "sanitize", "routes_driver.cpp"), "-o", exe]
+    built = subprocess.run(cmd, capture_output=True, text=True)
+    assert built.returncode == 0, built.stderr
+
+    def ask(*fields):
+        res = subprocess.run([exe], input=" ".join(str(f) for f in fields) + "\n", capture_output=True, text=True)
+        assert res.returncode == 0, res.stderr
+        return res.stdout.strip()
+    return ask
+
+
+# rank, nonzeros, nonzeros per segment, different coordinates and common share of a sample, share of the segments that are cut up
+@pytest.mark.parametrize("rank,nnz,per,distinct,common,cut,route", [
+    (16, 11 * M, 20, 30_000, 1.0, 0.08, "walk"),           # uneven rows over rows that an L2 holds: 100 us, and 112 on the pieces
+    (16, 40 * M, 20, 59_000, 0.99, 0.08, "walk"),          # 434 and 451
+    (16, 34 * M, 13.5, 58_000, 0.85, 0.03, "walk"),        # power-law columns: 290 and 357
+    (16, 40 * M, 150, 30_000, 1.0, 0.9, "walk"),           # 277 and 303
+    (16, 40 * M, 16, 106_000, 0.9, 0.05, "pieces"),        # 608 and 603
+    (16, 11 * M, 12, 24_000, 0.02, 0.02, "pieces"),        # near the diagonal: 229 and 137
+    (16, 24 * M, 9, 30_000, 1.0, 0.0, "pieces"),           # rows of one length: 253 and 231
+    (16, 40 * M, 3, 30_000, 1.0, 0.0, "walk"),             # very many in short segments
+    (16, 15 * M, 3, 30_000, 1.0, 0.0, "pieces"),
+    (16, 10 * M, 20, 30_000, 1.0, 0.08, "pieces"),         # short lists
+    (8, 40 * M, 20, 30_000, 1.0, 0.08, "walk"),            # 295 and 309
+    (8, 31 * M, 15, 62_000, 0.85, 0.05, "walk"),           # power-law columns: 258 and 287
+    (8, 11 * M, 20, 30_000, 1.0, 0.08, "walk"),            # 90 and 91
+    (8, 10 * M, 20, 30_000, 1.0, 0.08, "pieces"),
+    (8, 40 * M, 32, 30_000, 1.0, 0.2, "pieces"),           # 281 and 269
+    (8, 40 * M, 20, 30_000, 1.0, 0.0, "pieces"),           # 292 and 248
+    (8, 40 * M, 16, 106_000, 0.9, 0.05, "pieces"),         # 458 and 444
+    (8, 40 * M, 3, 30_000, 1.0, 0.0, "pieces"),
+    (32, 40 * M, 20, 30_000, 1.0, 0.08, "pieces"),
+])
+def test_segments_take_the_faster_kernel(routes, rank, nnz, per, distinct, common, cut, route):
+    nseg = int(nnz / per)
+    assert routes("segreduce", rank, nnz, nseg, nnz // 1400, distinct, common, int(cut * nseg)) == route
+
+
+@pytest.mark.parametrize("rank,nnz,route", [(8, 11 * M, "walk"), (16, 11 * M, "walk"), (16, 10 * M, "pieces"), (32, 40 * M, "pieces")])
+def test_segments_without_a_plan(routes, rank, nnz, route):
+    """"pieces" means that the caller finds no plan and takes the kernels that need none."""
+    assert routes("segreduce", rank, nnz, nnz // 30, 0, 0, 0.0, 0) == route
