@@ -4,6 +4,7 @@
 // A piece loads rows of C in groups of four, none behind its batch's last group; with up to seven more rows per piece, fibers of 12 / 30 /
 // 200 nonzeros, rank 10, 2.3 M, took 39 / 40 / 37 us instead of 36 / 35 / 32, rank 33 107 / 117 / 108 instead of 90 / 87 / 79.
 #include "mttkrp_plan.hpp"
+#include "routes.hpp"
 #include "stream_common.hpp"
 
 namespace comet {
@@ -482,7 +483,7 @@ hipError_t launch_walk(const MtArgs &a, const Schedule &sc, void *scratch) {
 // Tiles that the slices of the walk are cut over at most.
 int64_t mttkrp_chain(const Schedule &sc) { return sc.max_parent_len / (sc.nnz < kChunkWalkNnz ? kChunk : kTile) + 2; }
 
-// Which lists and ranks take the pieces; all others the walk over tiles of nonzeros, which keeps more rows in flight once its tiles
+// Which lists and ranks take the pieces; all others the walk over tiles of nonzeros or the wavefronts (routes.hpp), which keep more rows in flight once their tiles
 // fill the chip, while a tile of pieces needs several rounds of loads one after the other.  Calls of the walk and of the pieces in us,
 // three tensors taking turns.  Power: power-law modes, 2.5 to 4 nonzeros per fiber, slices cut over many tiles, for which the walk's
 // carry fix-up is longer; ones: uniform modes, a nonzero per fiber, so that the pieces read a row of B for each; fives, thirties: so
@@ -521,31 +522,6 @@ bool mttkrp_takes_pieces(const Schedule &sc, int64_t R) {
     if (R > 32 || (R % 2 && R > 16)) return n * blocks <= int64_t(9) << 18;
     if (R % 2 && R > 8) return n <= (long_slices ? int64_t(5) << 18 : int64_t(9) << 18);
     return R < 16 || long_slices || n <= int64_t(9) << 18;
-}
-
-// Of the lists that do not take the pieces, those that k_mttkrp_wave serves faster than the walk.  It reads every row 16 bytes per lane, the
-// walk only at ranks 8, 16, 32, 48, 64, 96 and 128; it reads a row of B once per fiber and block, which is nothing gained where almost every
-// nonzero is a fiber; and it adds up a block's products in 64-column passes at most, so that wide rows over long fibers stay with the walk.
-// Whole calls, walk and wavefronts, us; the tensors of the table above:
-//   nonzeros          rank 10     16          20          32          40          64          9           96          128
-//    10 M power       169  129   126  125    258  208    216  208    418  327    385  378    166  159    477  446*   694  584*
-//         ones        316  312   248  266    482  638    528  555    834  994   1203 1118    313  328   1344 1300   1884 1568
-//         fives       229  166   147  143    364  311    259  248    552  450    531  514    229  197    676  608   1013  798
-//         thirties    198  140   129  131    247  256    210  226    404  414    421  457    195  168    489  516    757  687
-//    60 M power       491  353   354  322    881  685    680  597   1336 1032   1164 1133    488  430   1325 1287*  2104 1713*
-//         ones       1836 1870  1493 1541   2900 4073   3339 3445   5092 6401   7354 6869   1796 1859   7690 7698  10455 9105
-//         fives      1021  781   643  643   1752 1541   1274 1308   2773 2378   3402 2648   1023  909   3810 2901   5477 3605
-//         thirties    985  678   574  563   1245 1305    972 1049   1921 2024   2457 2116    988  814   2950 2203   4402 2919
-//   (* ranks 96 and 128: 7 M and 40 M).  150 M power, rank 16: 1601 and 1393; 20 M, rank 64: 771 and 740.  2.5 M, ranks 34 / 62, power 167 and 149 /
-//   253 and 238, ones 224 and 342 / 391 and 529.  Ranks 2 and 8, 60 M power: 190 and 198, 258 and 276.
-bool mttkrp_takes_wave(const Schedule &sc, int64_t R) {
-    const int64_t n = sc.nnz;
-    const bool few = n <= 8 * sc.nseg;                            // nonzeros per fiber
-    if (n < 2 * sc.nseg || R <= 8) return false;
-    if (R == 16) return n >= int64_t(40) << 20;
-    if (R < 16) return n >= int64_t(5) << 20;
-    if (R % 32 == 0) return few && n >= int64_t(10) << 20;
-    return few && R % 2 == 0 && R < 64 && R != 48 && n >= (R > 32 ? int64_t(1) << 20 : int64_t(5) << 19);
 }
 
 }  // namespace

@@ -127,15 +127,20 @@ __global__ void __launch_bounds__(256) k_piece_cuts(const int32_t *__restrict__ 
     else cuts[ntiles - 1 - atomicAdd(&counters[1], 1)] = c;
 }
 
-// Sets a bit per coordinate of a sample (samples spread evenly over the list).  sums[0]: the bits that are set, of all samples
-// together; sums[1]: how many of the first kSampleLook nonzeros of the sample behind find theirs set.
+// A workgroup sets a bit per coordinate of a sample (samples spread evenly over the list).  kSamples of kSampleNnz nonzeros, of all
+// together, sums[0]: the bits that are set; sums[1]: how many of the first kSampleLook of the sample behind find theirs set.  Behind these, kLooks
+// of kSampleLook, sums[2]: the bits that are set; and as many of the coordinates `parent` of the segments, sums[3].
 constexpr int kSampleBits = 1 << 18;
-__global__ void __launch_bounds__(1024) k_piece_sample(const int32_t *__restrict__ crd, int64_t nnz, int *__restrict__ sums) {
+__global__ void __launch_bounds__(1024) k_piece_sample(const int32_t *__restrict__ leaf, int64_t nnz, const int32_t *__restrict__ parent, int64_t nseg,
+                                                       int *__restrict__ sums) {
     __shared__ uint32_t bits[kSampleBits / 32];
+    const int look = (int)blockIdx.x - kSamples;                 // negative: one of the large samples
+    const int32_t *crd = look < kLooks ? leaf : parent;
+    const int64_t total = look < kLooks ? nnz : nseg, most = look < 0 ? kSampleNnz : kSampleLook, n = total < most ? total : most;
+    const int samples = look < 0 ? kSamples : kLooks, mine = look < 0 ? (int)blockIdx.x : look % kLooks;
     for (int i = threadIdx.x; i < kSampleBits / 32; i += 1024) bits[i] = 0u;
     __syncthreads();
-    const int64_t n = nnz < kSampleNnz ? nnz : kSampleNnz;
-    auto begin = [&](unsigned s) { return (nnz - n) / (kSamples - 1) * (s % kSamples); };
+    auto begin = [&](int s) { return (total - n) / (samples - 1) * (s % samples); };
     auto batch = [&](int64_t at, int64_t i, auto use) {          // nonzeros i, i + 1024, ... of the sample that begins at `at`
         uint32_t c[32];
 #pragma unroll
@@ -148,13 +153,14 @@ __global__ void __launch_bounds__(1024) k_piece_sample(const int32_t *__restrict
         if ((threadIdx.x & 63) == 0) atomicAdd(to, v);
     };
     for (int64_t i = threadIdx.x; i < n; i += 32 * 1024)
-        batch(begin(blockIdx.x), i, [&](uint32_t h) { atomicOr(&bits[h >> 5], 1u << (h & 31u)); });
+        batch(begin(mine), i, [&](uint32_t h) { atomicOr(&bits[h >> 5], 1u << (h & 31u)); });
     __syncthreads();
     int set = 0, found = 0;
     for (int i = threadIdx.x; i < kSampleBits / 32; i += 1024) set += __popc(bits[i]);
+    add_up(set, &sums[look < 0 ? 0 : look < kLooks ? 2 : 3]);
+    if (look >= 0) return;
     static_assert(kSampleLook == 32 * 1024, "one batch");
-    if (threadIdx.x < n) batch(begin(blockIdx.x + 1), threadIdx.x, [&](uint32_t h) { found += (bits[h >> 5] >> (h & 31u)) & 1u; });
-    add_up(set, &sums[0]);
+    if (threadIdx.x < n) batch(begin(mine + 1), threadIdx.x, [&](uint32_t h) { found += (bits[h >> 5] >> (h & 31u)) & 1u; });
     add_up(found, &sums[1]);
 }
 
@@ -162,7 +168,7 @@ unsigned grid_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
-hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd, int64_t nnz, PiecePlan &plan, hipStream_t st) {
+hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd, int64_t nnz, const int32_t *parent, PiecePlan &plan, hipStream_t st) {
     plan = PiecePlan();
     if (nseg < 1 || nnz < 1) return hipSuccess;
     auto fail = [&](hipError_t e) { plan = PiecePlan(); return e; };
@@ -176,23 +182,24 @@ hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd
     size_t tb = 0;
     hipError_t e = reorder_scan_flags(nullptr, &tb, (uint64_t *)nullptr, (uint64_t *)nullptr, ntiles + 1, st);
     if (e != hipSuccess) return fail(e);
-    const size_t scan_at = ((size_t)(2 * (ntiles + 1) + 3) * sizeof(uint64_t) + 255) & ~(size_t)255;
+    const size_t scan_at = ((size_t)(2 * (ntiles + 1) + 4) * sizeof(uint64_t) + 255) & ~(size_t)255;
     DevRef temp = dev_alloc(scan_at + tb);
     if (!plan.tiles_mem || !temp) return fail(hipErrorOutOfMemory);
     uint64_t *cn = (uint64_t *)temp->ptr, *bf = cn + ntiles + 1;
     int *counters = (int *)(bf + ntiles + 1);
     hipLaunchKernelGGL(k_piece_tiles, dim3(grid_for(ntiles + 1)), dim3(256), 0, st, pos, nseg, nnz, plan.units, ntiles, plan.tiles());
     e = hipMemsetAsync(cn + ntiles, 0, sizeof(uint64_t), st);
-    if (e == hipSuccess) e = hipMemsetAsync(counters, 0, 6 * sizeof(int), st);
+    if (e == hipSuccess) e = hipMemsetAsync(counters, 0, 8 * sizeof(int), st);
     if (e != hipSuccess) return fail(e);
     hipLaunchKernelGGL((k_piece_fill<false>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, plan.tiles(), cn,
                        counters + 2, (uint32_t *)nullptr, (uint32_t *)nullptr);
     hipLaunchKernelGGL(k_piece_cuts, dim3(grid_for(ntiles)), dim3(256), 0, st, pos, nseg, (const int4 *)plan.tiles(), ntiles,
                        plan.cuts(), counters);
     // (a list shorter than a sample is not worth the 40 us that the kernel costs a small handle)
-    if (nnz >= kSampleNnz) hipLaunchKernelGGL(k_piece_sample, dim3(kSamples), dim3(1024), 0, st, crd, nnz, counters + 3);
+    if (nnz >= kSampleNnz)
+        hipLaunchKernelGGL(k_piece_sample, dim3(kSamples + (parent ? 2 : 1) * kLooks), dim3(1024), 0, st, crd, nnz, parent, nseg, counters + 3);
     e = reorder_scan_flags((char *)temp->ptr + scan_at, &tb, cn, bf, ntiles + 1, st);
-    struct { uint64_t total; int short_cuts, long_cuts, max_parts, set, found, pad; } sums = {};    // bf[ntiles] and the counters
+    struct { uint64_t total; int short_cuts, long_cuts, max_parts, set, found, few, parent_few, pad; } sums = {};    // bf[ntiles] and the counters
     if (e == hipSuccess) e = hipMemcpyAsync(&sums, bf + ntiles, sizeof sums, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(e);
@@ -202,9 +209,14 @@ hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd
     plan.ncut_long = sums.long_cuts;
     plan.max_parts = sums.max_parts;
     // m coordinates set kSampleBits * (1 - exp(-m / kSampleBits)) bits, and as large a share of the others finds a bit set by chance
-    const double unset = 1.0 - (double)sums.set / ((double)kSamples * kSampleBits);
-    plan.distinct = unset > 0.0 ? (int64_t)(-std::log(unset) * kSampleBits) : kSampleNnz;
-    plan.common = unset > 0.0 ? 1.0 - (1.0 - (double)sums.found / ((double)kSamples * kSampleLook)) / unset : 0.0;
+    if (nnz >= kSampleNnz) {
+        auto unset = [](int set, int samples) { return 1.0 - (double)set / ((double)samples * kSampleBits); };
+        const double left = unset(sums.set, kSamples);
+        plan.distinct = left > 0.0 ? (int64_t)(-std::log(left) * kSampleBits) : kSampleNnz;
+        plan.common = left > 0.0 ? 1.0 - (1.0 - (double)sums.found / ((double)kSamples * kSampleLook)) / left : 0.0;
+        plan.few = (int64_t)(-std::log(unset(sums.few, kLooks)) * kSampleBits);      // (an eighth of the bits at most)
+        if (parent) plan.parent_few = (int64_t)(-std::log(unset(sums.parent_few, kLooks)) * kSampleBits);
+    }
     plan.pieces_mem = dev_alloc(sizeof(uint32_t) * (plan.npieces + plan.njoins));
     if (!plan.pieces_mem) return fail(hipErrorOutOfMemory);
     hipLaunchKernelGGL((k_piece_fill<true>), dim3((unsigned)ntiles), dim3(256), 0, st, pos, nseg, ntiles, plan.tiles(), bf,

@@ -57,11 +57,8 @@ __device__ __forceinline__ int join_count(unsigned j) { return (int)((j >> 7) & 
 __device__ __forceinline__ int join_seg(unsigned j) { return (int)((j >> 14) & 2047u); }
 __device__ __forceinline__ int join_to(unsigned j) { return (int)(j >> 25); }
 
-// The different coordinates in a part of the list are counted in four samples of it, each about what one XCD works on at a time,
-// and kSampleLook nonzeros of each are looked up in the sample in front of it.
-constexpr int kSampleNnz = 1 << 18, kSamples = 4, kSampleLook = 1 << 15;
-
-// Builds the plan for a level of nseg segments over nnz nonzeros with coordinates crd.  Synchronises with st.
-hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd, int64_t nnz, PiecePlan &plan, hipStream_t st);
+// Builds the plan for a level of nseg segments over nnz nonzeros with coordinates crd; parent: coordinates of the segments, if they are
+// to be sampled too, else null.  Synchronises with st.
+hipError_t piece_plan_build(const int32_t *pos, int64_t nseg, const int32_t *crd, int64_t nnz, const int32_t *parent, PiecePlan &plan, hipStream_t st);
 
 }  // namespace comet

@@ -98,15 +98,20 @@ struct FiberPlan {
     LightCopy light;      // all other fibers (row = fiber)
 };
 
+// The different coordinates in a part of a list are counted in four samples of it, each about what one XCD works on at a time, with
+// kSampleLook nonzeros of each looked up in the sample in front of it, and in sixteen samples of kSampleLook.
+constexpr int kSampleNnz = 1 << 18, kSamples = 4, kSampleLook = 1 << 15, kLooks = 16;
+
 // Plan of the rank-R kernel (pieces.hpp).
 struct PiecePlan {
     int64_t nseg = 0, ntiles = 0, npieces = 0, njoins = 0;
     int     units = 0;                 // units per tile
     int     max_parts = 0;             // most partial sums in a tile
     int64_t ncut = 0, ncut_long = 0;   // segments cut by tile boundaries: over few tiles, over many
-    // of samples of the list, about: different coordinates among kSampleNnz consecutive nonzeros, and which share of a sample's nonzeros have
-    // a coordinate that the sample in front of it has (0 while unknown)
-    int64_t distinct = 0;
+    // of samples of the list, about: different coordinates among kSampleNnz consecutive nonzeros and among kSampleLook, and which share of a
+    // sample's nonzeros have a coordinate that the sample in front of it has (0 while unknown); MTTKRP: different coordinates of the parent level among
+    // kSampleLook consecutive segments (both `few`: all of them while unknown)
+    int64_t distinct = 0, few = kSampleLook, parent_few = kSampleLook;
     double  common = 0.0;
     DevRef  tiles_mem, pieces_mem;
     // int4 [ntiles + 1]: first nonzero, segment, piece and join of a tile

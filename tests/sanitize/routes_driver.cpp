@@ -1,5 +1,6 @@
 // Host check of the rules that choose a kernel by what a list's plan has counted: prints the route of each list given on stdin.
-//   segreduce RANK nnz segments pieces distinct common joins    -> walk | pieces
+//   segreduce RANK nnz segments pieces distinct common joins            -> walk | pieces
+//   mttkrp RANK nnz fibers few-of-C few-of-B longest-slice              -> wave | walk
 #include <cstdio>
 #include <cstring>
 
@@ -20,6 +21,15 @@ int main() {
             sc.pieces.common = common;
             sc.pieces.njoins = joins;
             printf("%s\n", comet::segreduce_takes_walk(sc, rank) ? "walk" : "pieces");
+        } else if (!strcmp(op, "mttkrp")) {
+            long few, parent_few, slice;
+            if (scanf("%ld %ld %ld %ld %ld %ld", &rank, &nnz, &nseg, &few, &parent_few, &slice) != 6) return 1;
+            sc.nnz = nnz;
+            sc.nseg = nseg;
+            sc.pieces.few = few;
+            sc.pieces.parent_few = parent_few;
+            sc.max_parent_len = slice;
+            printf("%s\n", comet::mttkrp_takes_wave(sc, rank) ? "wave" : "walk");
         } else {
             return 1;
         }

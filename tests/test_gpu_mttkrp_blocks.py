@@ -1,6 +1,7 @@
 """MTTKRP on lists long enough for wavefronts that take blocks of nonzeros: fibers and slices that end at every place of a block, a
-lane group and a run of 1024 nonzeros, blocks with as many fibers or slices as nonzeros, every layout of the rows, both sides of
-the size rules, operands whose row offsets need 64 bits, and lists that keep the walk because a fiber or a slice is empty."""
+lane group and a run of 1024 nonzeros, blocks with as many fibers or slices as nonzeros, every layout of the rows, operands whose row
+offsets need 64 bits; and lists that keep the walk over nonzeros: below the sizes, with rows of C spread over more than the caches hold, with an empty
+fiber or slice.  Which of the two ran shows in the last bits: they add in different orders, and the walk is what variant 3 takes."""
 import numpy as np
 import pytest
 import torch
@@ -62,13 +63,14 @@ def _lists(nnz):
     return torch.tensor(np.array(fibers)), torch.tensor(slices)
 
 
-def _tensor(nnz):
+def _tensor(nnz, spread):
+    """Fibers begin at one of `spread` different rows of C."""
     lens, nfib = _lists(nnz)
     fiber = torch.repeat_interleave(torch.arange(lens.numel()), lens)
     slice_of = torch.repeat_interleave(torch.arange(nfib.numel()), nfib)
     j = torch.arange(lens.numel()) - (torch.cumsum(nfib, 0) - nfib)[slice_of]
-    k = torch.arange(fiber.numel()) - (torch.cumsum(lens, 0) - lens)[fiber]
-    dims = (nfib.numel() * 4 // 3 + 5, int(nfib.max()) + 2, int(lens.max()) + 1)
+    k = torch.arange(fiber.numel()) - (torch.cumsum(lens, 0) - lens)[fiber] + fiber * 7 % spread
+    dims = (nfib.numel() * 4 // 3 + 5, int(nfib.max()) + 2, int(lens.max()) + spread)
     i = slice_of + slice_of // 3                                        # three of four rows are stored
     return dims, i[fiber].int(), j[fiber].int(), k.int(), gen.dense_operand(9, 0, (nnz, 1)).reshape(-1)
 
@@ -76,31 +78,39 @@ def _tensor(nnz):
 _kept = {}
 
 
-def _case(nnz):
-    if nnz not in _kept:
+def _case(nnz, spread=6000):
+    if (nnz, spread) not in _kept:
         _kept.clear()
-        _kept[nnz] = _tensor(nnz)
-    return _kept[nnz]
+        _kept[nnz, spread] = _tensor(nnz, spread)
+    return _kept[nnz, spread]
 
 
 SMALL = 1 << 20                                                         # from here on at even ranks above 32
-CASES = [(SMALL, 34), (SMALL + 1, 40), (SMALL + 63, 50), (SMALL + 700, 62), (SMALL - 1, 40), (5 << 19, 20), ((5 << 19) + 31, 30), ((5 << 19) - 1, 20),
-         ((5 << 20) + 1, 9), ((5 << 20) + 1, 10), ((5 << 20) + 1, 15), ((10 << 20) + 5, 32)]
+NEAR, FAR = 6000, 40000
+CASES = [(SMALL, NEAR, 34, True), (SMALL, NEAR, 44, True), (SMALL + 1, NEAR, 40, True), (SMALL + 63, NEAR, 50, True), (SMALL + 700, NEAR, 62, True),
+         (SMALL - 1, NEAR, 40, False), (SMALL, FAR, 40, False), (SMALL, FAR, 62, False),
+         (5 << 19, NEAR, 20, True), ((5 << 19) + 31, NEAR, 30, True), ((5 << 19) - 1, NEAR, 20, False),
+         ((5 << 20) + 1, NEAR, 9, True), ((5 << 20) + 1, NEAR, 10, True), ((5 << 20) + 1, NEAR, 15, True), ((5 << 20) + 1, FAR, 10, False),
+         ((10 << 20) + 5, 9000, 32, True), ((10 << 20) + 5, 9000, 64, True), ((10 << 20) + 5, 9000, 96, True), ((10 << 20) + 5, 9000, 128, True),
+         ((10 << 20) + 5, FAR, 32, False), ((40 << 20) + 1, NEAR, 16, True), ((40 << 20) - 1, NEAR, 16, False)]
 
 
-@pytest.mark.parametrize("nnz,R", CASES)
-def test_blocks(comet, nnz, R):
-    dims, i, j, k, vals = _case(nnz)
-    print("mttkrp blocks R=%d nnz=%d" % (R, nnz), flush=True)
-    X = comet.from_levels(fmt.pack_csf3(dims, i, j, k, vals).to("cuda")).set_variant(2)
+@pytest.mark.parametrize("nnz,spread,R,blocks", CASES)
+def test_blocks(comet, nnz, spread, R, blocks):
+    dims, i, j, k, vals = _case(nnz, spread)
+    print("mttkrp blocks R=%d nnz=%d spread=%d" % (R, nnz, spread), flush=True)
+    T = fmt.pack_csf3(dims, i, j, k, vals).to("cuda")
+    X, plain = comet.from_levels(T).set_variant(2), comet.from_levels(T).set_variant(3)
     B, C, old = (gen.dense_operand(5, n, (d, R)) for n, d in ((0, dims[1]), (1, dims[2]), (2, dims[0])))
+    factors = [None, B.to("cuda"), C.to("cuda")]
     ref, absum = oracle.mttkrp(np_(i), np_(j), np_(k), np_(vals), dims, np_(B), np_(C))
     M = torch.full((dims[0], R), float("nan"), dtype=torch.float64, device="cuda")
-    comet.comet_mttkrp(X, 0, [None, B.to("cuda"), C.to("cuda")], M)
+    comet.comet_mttkrp(X, 0, factors, M)
     assert_values_close(np_(M), ref, absum, "mttkrp R=%d" % R)
-    assert torch.equal(M, comet.comet_mttkrp(X, 0, [None, B.to("cuda"), C.to("cuda")])), "two runs differ"
+    assert torch.equal(M, comet.comet_mttkrp(X, 0, factors)), "two runs differ"
+    assert torch.equal(M, comet.comet_mttkrp(plain, 0, factors)) != blocks
     D = old.to("cuda")
-    comet.comet_mttkrp_axpby(X, 0, 0.75, [None, B.to("cuda"), C.to("cuda")], -0.5, D)
+    comet.comet_mttkrp_axpby(X, 0, 0.75, factors, -0.5, D)
     assert_values_close(np_(D), 0.75 * ref - 0.5 * np_(old), 0.75 * absum + 0.5 * np.abs(np_(old)), "axpby R=%d" % R)
 
 
@@ -124,6 +134,7 @@ def test_row_offsets_beyond_4_gib(comet, nnz, R, level):
     BC[level - 1] = F
     print("mttkrp blocks wide R=%d level=%d rows=%d" % (R, level, wide), flush=True)
     M = comet.comet_mttkrp(X, 0, [None] + BC)
+    assert not torch.equal(M, comet.comet_mttkrp(X.set_variant(3), 0, [None] + BC))
     ref, absum = oracle.mttkrp(np_(i), np_(j), np_(k), np_(vals), dims, np_(small[0]), np_(small[1]))
     assert_values_close(np_(M), ref, absum, "wide R=%d level=%d" % (R, level))
 
@@ -149,3 +160,4 @@ def test_lists_with_something_empty(comet, empty):
     M = torch.full((dims[0], R), float("nan"), dtype=torch.float64, device="cuda")
     comet.comet_mttkrp(X, 0, [None, B.to("cuda"), C.to("cuda")], M)
     assert_values_close(np_(M), ref, absum, "empty %s" % empty)
+    assert torch.equal(M, comet.comet_mttkrp(X.set_variant(3), 0, [None, B.to("cuda"), C.to("cuda")]))

@@ -55,3 +55,48 @@ def test_segments_take_the_faster_kernel(routes, rank, nnz, per, distinct, commo
 def test_segments_without_a_plan(routes, rank, nnz, route):
     """"pieces" means that the caller finds no plan and takes the kernels that need none."""
     assert routes("segreduce", rank, nnz, nnz // 30, 0, 0, 0.0, 0) == route
+
+
+POWER = (4_000, 13_500, 4 * M)                             # rows of C in 32768 nonzeros, rows of B in 32768 fibers, nonzeros of the longest slice
+UNIFORM = {3_000: (3_000, 16_100, 790), 8_000: (7_900, 32_100, 1600), 15_000: (13_300, 16_100, 950), 30_000: (19_900, 28_000, 950),
+           60_000: (25_300, 32_100, 1600), 300_000: (31_000, 16_100, 1750)}
+
+
+@pytest.mark.parametrize("rank,power,r3,r8,r15,r30,r60,r300", [
+    # faster on the wavefronts (w) or the walk (-), 44 M nonzeros; "?": within 2 %
+    (9, "w", "w", "w", "w", "w", "?", "-"),
+    (10, "w", "w", "w", "w", "w", "-", "-"),
+    (15, "w", "?", "w", "w", "-", "-", "-"),
+    (16, "w", "?", "?", "?", "-", "-", "?"),
+    (20, "w", "w", "w", "w", "w", "?", "-"),
+    (32, "w", "?", "?", "-", "-", "-", "-"),
+    (34, "w", "-", "-", "-", "-", "-", "-"),
+    (40, "w", "w", "w", "w", "-", "-", "-"),
+    (62, "w", "w", "w", "-", "-", "-", "-"),
+    (64, "w", "-", "w", "w", "w", "w", "?"),
+    (96, "w", "?", "w", "w", "?", "-", "-"),
+    (128, "w", "w", "w", "w", "w", "w", "-"),
+])
+def test_mttkrp_takes_the_faster_kernel(routes, rank, power, r3, r8, r15, r30, r60, r300):
+    n = 44 * M
+    facts = [(3.6, POWER), (2.25, UNIFORM[3_000]), (5, UNIFORM[8_000]), (3, UNIFORM[15_000]), (3, UNIFORM[30_000]), (5, UNIFORM[60_000]),
+             (6, UNIFORM[300_000])]
+    for want, (per, fact) in zip((power, r3, r8, r15, r30, r60, r300), facts):
+        if want != "?":
+            assert routes("mttkrp", rank, n, int(n / per), *fact) == ("wave" if want == "w" else "walk"), (rank, per, fact)
+
+
+@pytest.mark.parametrize("rank,nnz,per,route", [
+    (16, 150 * M, 4, "wave"), (64, 20 * M, 3.46, "wave"), (16, 41 * M, 3.6, "walk"), (10, 5 * M, 3, "walk"), (10, 6 * M, 3, "wave"), (20, 2_700_000, 3, "wave"),
+    (20, 2_600_000, 3, "walk"), (32, 10 * M, 3, "walk"), (40, 1_100_000, 3, "wave"), (40, 1 * M, 3, "walk"), (8, 60 * M, 3, "walk"), (48, 60 * M, 3, "walk"),
+    (33, 60 * M, 3, "walk"), (66, 60 * M, 3, "walk"), (10, 60 * M, 1.9, "walk"), (40, 60 * M, 8.1, "walk"), (10, 60 * M, 30, "wave")])
+def test_mttkrp_by_size(routes, rank, nnz, per, route):
+    assert routes("mttkrp", rank, nnz, int(nnz / per), *POWER) == route
+
+
+def test_mttkrp_without_samples(routes):
+    """A list whose plan there was no memory for counts as one whose rows come from memory."""
+    for rank in range(1, 129):
+        want = "wave" if 18 <= rank <= 30 and rank % 2 == 0 else "walk"
+        assert routes("mttkrp", rank, 3 * M, M, 32768, 32768, 100_000) == want
+        assert routes("mttkrp", rank, 44 * M, 11 * M, 32768, 32768, 100_000) == "walk"
