@@ -541,9 +541,13 @@ size_t mttkrp_call_bytes(const Schedule &sc, int64_t R, MttkrpRoute route) {
 }
 
 size_t mttkrp_scratch_bytes(const Schedule &sc, int64_t R) {
-    // ranks below R may take another route than R does
-    const size_t a = stream_scratch_bytes(sc.nchunks, R), b = (size_t)sc.mttkrp.ntiles * (size_t)R * 2 * sizeof(double);
-    return a > b ? a : b;
+    // the walk, which serves variant 3 and the largest factors at every rank, and what each rank up to R takes otherwise
+    size_t need = stream_scratch_bytes(walk_tiles(sc), R);
+    for (int64_t r = 1; r <= R; ++r) {
+        const size_t b = mttkrp_call_bytes(sc, r, mttkrp_route(sc, 0, r, false));
+        if (b > need) need = b;
+    }
+    return need;
 }
 
 hipError_t stream_mttkrp(const Schedule &sc, const int32_t *pos2, const int32_t *crd1, int64_t nslice, const int32_t *pos3, const int32_t *crd2,

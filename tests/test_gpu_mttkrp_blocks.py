@@ -161,3 +161,50 @@ def test_lists_with_something_empty(comet, empty):
     comet.comet_mttkrp(X, 0, [None, B.to("cuda"), C.to("cuda")], M)
     assert_values_close(np_(M), ref, absum, "empty %s" % empty)
     assert torch.equal(M, comet.comet_mttkrp(X.set_variant(3), 0, [None, B.to("cuda"), C.to("cuda")]))
+
+
+def test_reserved_scratch_serves_every_rank(comet):
+    """After reserve the calls of every rank up to it allocate nothing (a capture would refuse that), whichever kernel each takes."""
+    dims, i, j, k, vals = _case((5 << 20) + 1)
+    T = fmt.pack_csf3(dims, i, j, k, vals).to("cuda")
+    X, fresh = comet.from_levels(T).set_variant(2), comet.from_levels(T).set_variant(2)
+    X.reserve(62)
+    ranks = (2, 9, 10, 16, 20, 34, 40, 62)
+    factors = {R: [None] + [gen.dense_operand(5, n, (d, R)).cuda() for n, d in ((0, dims[1]), (1, dims[2]))] for R in ranks}
+    out = {R: torch.full((dims[0], R), float("nan"), dtype=torch.float64, device="cuda") for R in ranks}
+    g = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(g, stream=side):
+        for R in ranks:
+            comet.comet_mttkrp(X, 0, factors[R], out[R])
+    want = {R: comet.comet_mttkrp(fresh, 0, factors[R]) for R in ranks}
+    for rep in range(3):
+        for R in ranks:
+            out[R].fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for R in ranks:
+            assert torch.equal(out[R], want[R]), "replay %d rank %d" % (rep, R)
+
+
+def test_reserve_takes_what_the_routes_need(comet):
+    """32 M nonzeros, 30 per fiber, and a fiber without any, so that no rank is taken by blocks: the pieces of TTM need most, 46 MB at
+    rank 128.  A summary per 1024 nonzeros would be 64."""
+    n, per = 32_000_000, 30
+    fibers = n // per
+    i32 = dict(dtype=torch.int32, device="cuda")
+    fiber_ends = torch.cat([torch.arange(fibers + 1, **i32) * per, torch.tensor([fibers * per], **i32)])
+    slices = 1000
+    slice_ends = torch.arange(slices + 1, **i32) * (fibers // slices)
+    slice_ends[-1] = fibers + 1
+    k = torch.arange(fibers * per, **i32) % per
+    j = torch.arange(fibers + 1, **i32)
+    X = comet.comet_tensor_create((slices, fibers + 1, per), [comet.COMET_CU] * 3, [torch.tensor([0, slices], **i32), slice_ends, fiber_ends],
+                                  [torch.arange(slices, **i32), j, k], torch.ones(fibers * per, dtype=torch.float64, device="cuda"), comet.COMET_VALIDATE | comet.COMET_LEAN)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    X.reserve(128)
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info()[0] < 55 << 20
