@@ -264,7 +264,11 @@ comet_status comet_ttm(const comet_tensor *X, int mode, const double *U, int64_t
  *   factors  host array of 3 device pointers indexed by MODE: factors[m] is the [size of mode m x R]
  *            row-major factor of mode m; factors[mode] is ignored.
  *   M        device, [size of mode `mode` x R] row-major, overwritten (rows without a stored
- *            slice = 0). */
+ *            slice = 0).
+ * By the size and structure of X and by R, a row of the middle level's factor is multiplied with what a whole fiber
+ * adds up to, with parts of that, or with every product x_ijk c_kr alone.  These differ by rounding only while all of
+ * them are finite.  Where a factor is infinite or NaN, or a product overflows, m_ir is not finite if the slice names it, and
+ * whether it is an infinity or a NaN may differ from kernel to kernel; slices that name no such row are not touched by it. */
 comet_status comet_mttkrp(const comet_tensor *X, int mode, const double *const *factors,
                           int64_t R, double *M, void *stream);
 

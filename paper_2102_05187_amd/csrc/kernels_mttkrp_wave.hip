@@ -11,7 +11,8 @@
 // of a block issued and used inside it, took 1591.  Runs of 4096 nonzeros per wavefront are level for 150 M and leave the chip unevenly filled for 20 M (820 us
 // at rank 64, and 740).
 //
-// Sums.  No nonzero asks whether its fiber ends: (value * C) * B is added to the lane group's part of the open slice.  Where no slice
+// Sums.  No nonzero asks whether its fiber ends: (value * C) * B is added to the lane group's part of the open slice (the other kernels add up
+// value * C over a fiber, or a part of it, first; for factors that are not finite this makes an infinity there a NaN here or the reverse, see comet.h).  Where no slice
 // ends in a block (85 % of the blocks of that tensor) the parts of the lane groups just go on; where some do, those that lie in one lane group's
 // nonzeros are stored by it, and the others are put together in LDS in the order of the nonzeros.  What is open at either end of the run goes through the carry
 // fix-up of the other walks.  The order of every sum is the program's.

@@ -75,7 +75,8 @@ hipError_t fiber_ttm(const FiberPlan &plan, const int32_t *crd, const double *va
 // Number of compute units of the current device (cached per device).
 int current_device_cu_count();
 
-// M[crd1[s], :] = sum_{f in slice s} B[crd2[f], :] * (sum_{p in fiber f} vals[p] * C[crd3[p], :]) over the schedule sc.
+// M[crd1[s], :] = sum_{f in slice s} B[crd2[f], :] * (sum_{p in fiber f} vals[p] * C[crd3[p], :]) over the schedule sc; the fiber's sum in parts, each
+// multiplied with the row of B: where a tile or a lane group's nonzeros end (walk), at most 16 nonzeros (pieces), every nonzero (wavefronts).
 // dense_rows = the larger number of rows of B and C.
 // route: from mttkrp_route.  Every stored slice's row is written.  gaps: the rows that are not stored are cleared too (scaled by beta), which only the
 // pieces do; otherwise the caller has done that.

@@ -208,3 +208,34 @@ def test_reserve_takes_what_the_routes_need(comet):
     X.reserve(128)
     torch.cuda.synchronize()
     assert before - torch.cuda.mem_get_info()[0] < 55 << 20
+
+
+@pytest.mark.parametrize("variant", [2, 3])
+@pytest.mark.parametrize("nnz,R", [(300_001, 20), (SMALL + 63, 50), ((5 << 19) + 31, 20), ((5 << 20) + 1, 11)])
+def test_factors_that_are_not_finite(comet, nnz, R, variant):
+    """Blocks, pieces (the shortest list) and the walk.  Slices that name no such row have the result that they have without it, bit for
+    bit, though kernels load row 0 of C and the last fiber's row of B behind the list's end; the others infinity where all products are positive, and
+    else something that is not finite (which depends on what is added up before it is multiplied)."""
+    dims, i, j, k, vals = _case(nnz)
+    print("mttkrp not finite R=%d nnz=%d variant=%d" % (R, nnz, variant), flush=True)
+    B, C = (gen.dense_operand(5, n, (d, R)) for n, d in ((0, dims[1]), (1, dims[2])))
+    last = int(j[-1])
+    for positive in (True, False):
+        v, b, c = (x.abs() + 0.1 if positive else x for x in (vals, B, C))
+        X = comet.from_levels(fmt.pack_csf3(dims, i, j, k, v).to("cuda")).set_variant(variant)
+        want = comet.comet_mttkrp(X, 0, [None, b.cuda(), c.cuda()])
+        for what in ("B", "C"):
+            bad_b, bad_c = b.clone(), c.clone()
+            if what == "B":
+                bad_b[[last, 2500]] = float("inf")
+                names = (j == last) | (j == 2500)
+            else:
+                bad_c[[0, 1234]] = float("inf")
+                names = (k == 0) | (k == 1234)
+            rows = torch.zeros(dims[0], dtype=torch.bool)
+            rows[i[names].long().unique()] = True
+            assert rows.any() and not rows.all()
+            M = comet.comet_mttkrp(X, 0, [None, bad_b.cuda(), bad_c.cuda()])
+            assert torch.equal(M[~rows.cuda()], want[~rows.cuda()]), what
+            hit = M[rows.cuda()]
+            assert bool((hit == float("inf")).all() if positive else (~torch.isfinite(hit)).all()), what
