@@ -38,11 +38,12 @@ def test_rows_around_walkers_and_tiles(comet, layout, rest):
     print("rank-16 walk %s rest=%d nnz=%d" % (layout, rest, nnz), flush=True)
     A = comet.from_levels((fmt.pack_csr if layout == "csr" else fmt.pack_dcsr)(I, J, rows, cols, vals),
                           comet.COMET_VALIDATE | comet.COMET_LEAN).set_variant(2)
-    B = gen.dense_operand(3, 0, (J, R))
+    B, old = gen.dense_operand(3, 0, (J, R)), gen.dense_operand(4, 0, (I, R))
     C = torch.full((I, R), float("nan"), dtype=torch.float64, device="cuda")
     comet.comet_spmm(A, B.to("cuda"), C)
     ref, absum = oracle.spmm(np_(rows), np_(cols), np_(vals), (I, J), np_(B))
     assert_values_close(np_(C), ref, absum, "rank-16 walk %s" % layout)
-    D = torch.ones_like(C)
+    assert torch.equal(C, comet.comet_spmm(A, B.to("cuda"))), "two runs differ"
+    D = old.to("cuda")
     comet.comet_spmm_axpby(A, 0.75, B.to("cuda"), -0.5, D)
-    assert_values_close(np_(D), 0.75 * ref - 0.5, 0.75 * absum + 0.5, "axpby %s" % layout)
+    assert_values_close(np_(D), 0.75 * ref - 0.5 * np_(old), 0.75 * absum + 0.5 * np.abs(np_(old)), "axpby %s" % layout)
