@@ -741,12 +741,13 @@ hipError_t heavy_spmm(const HeavyPlan &plan, const int32_t *rowmap, const double
 // the windows of a fiber in a fixed order.  The remaining fibers stay with the nonzero-tiled kernel, which skips
 // the heavy ones.
 //
-// What bounds it is the issue of vector instructions, with the reads of LDS close behind.  Groups of 16 because the
+// What bounds it is the issue of instructions of all kinds (one is under way in 75 % of the SIMDs' cycles, vector arithmetic in 47 %), with LDS
+// close behind (at work 50 % of the time, a third of that bank conflicts).  Groups of 16 because the
 // hardware broadcasts a lane over a row of 16 inside an addition or a multiplication: a step is three instructions
 // per row of four items, and was eleven per eight with groups of 8, whose broadcasts are moves.  A block always takes
 // 16 items, those behind a piece's end with a row of zeros, so that no step asks whether the piece goes on (with that
 // question 243 us where this takes 196).  65 M nonzeros in 55 K fibers, rank 16: 270 us before, 196 now
-// (780 MB of nonzeros at 4 TB/s); whole calls of TTM on 100 M nonzeros, rank 16, 733 and 667; 60 M, 5000 rows of
+// (780 MB of nonzeros at 4 TB/s); whole calls of TTM on 100 M nonzeros, rank 16, 735 and 669; 60 M, 5000 rows of
 // rank 32, 719 and 673; 4 M in half a million fibers, rank 16, 97 and 59.
 namespace {
 

@@ -1,15 +1,15 @@
 // MTTKRP, long lists: a wavefront works alone on kChunk consecutive nonzeros (k_mttkrp_wave).
 //
 // What bounds it.  A load of 64 lanes keeps the texture-address unit for 16 to 18 clocks, whatever it hits, and every kernel of this file's
-// kind spends most of its time on that (88 % busy here), so what counts is how many such loads a nonzero costs.  The walk over two levels
+// kind spends most of its time on that (84 % busy here on average, the busiest 97 %), so what counts is how many such loads a nonzero costs.  The walk over two levels
 // (kernels_mttkrp.hip) loads a row of C and a row of B for each, because it cannot know which of the lane groups of a wavefront end a fiber.
 // Here the nonzeros are taken in blocks of 8 per lane group.  The fibers of a block are consecutive, so their rows of B are loaded for all lane
 // groups together, one per fiber, into LDS, from where each nonzero reads the one of its fiber.  Per block: 8 loads of C for 64 nonzeros (rank 16) and
-// one of B for 8 fibers, 2.6 on average for the power-law tensor of 150 M nonzeros; 31.7 M loads in all where the walk has 42.1 M,
-// 1601 us before and 1393 now.  The rows of C of the next block are loaded as those of the current one are used, one for one, and its rows of
+// one of B for 8 fibers, 2.6 on average for the power-law tensor of 150 M nonzeros; 30.7 M loads in all where the walk has 40.7 M,
+// 1602 us before and 1393 now.  The rows of C of the next block are loaded as those of the current one are used, one for one, and its rows of
 // B in front of them, so that loads are in flight all the time without a wait of their own; blocks of 16 per lane group, with the loads
 // of a block issued and used inside it, took 1591.  Runs of 4096 nonzeros per wavefront are level for 150 M and leave the chip unevenly filled for 20 M (820 us
-// at rank 64, and 740).
+// at rank 64, and 753).
 //
 // Sums.  No nonzero asks whether its fiber ends: (value * C) * B is added to the lane group's part of the open slice (the other kernels add up
 // value * C over a fiber, or a part of it, first; for factors that are not finite this makes an infinity there a NaN here or the reverse, see comet.h).  Where no slice

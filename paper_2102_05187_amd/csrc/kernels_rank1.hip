@@ -238,8 +238,8 @@ __global__ void __launch_bounds__(256) k_stream_rank1(const int32_t *__restrict_
 // L1 / texture-address path, which handles only about one scattered 8-byte gather every two clocks per CU,
 // is then left to the streaming loads.
 // Otherwise the vector is gathered through L1, a chunk per wavefront; coordinate lists only, whose runs are found here with all loads
-// of eight rows of 64 items under way at once, and none behind a comparison: 5 M nonzeros, 60 013 values in the vector, 47.4 us a call with a
-// load of both coordinates and both predecessors per item behind branches, and 44.3 with five wavefronts per SIMD (a third of the time are the gathers,
+// of eight rows of 64 items under way at once, and none behind a comparison: 5 M nonzeros, 60 013 values in the vector, 47.6 us a call with a
+// load of both coordinates and both predecessors per item behind branches, and 44.5 with five wavefronts per SIMD (a third of the time are the gathers,
 // the rest a chunk's chain of loads); 46.1 with all 16 rows unrolled (three per SIMD), 58.7 with six. Compressed levels keep
 // k_stream_rank1 there: 4.7 M nonzeros in short rows, 59 us, and 62 here.
 // COO = true: the input is a sorted coordinate list [CN,S,S]; segment ends come from neighbour

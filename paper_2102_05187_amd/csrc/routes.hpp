@@ -13,7 +13,7 @@ inline bool segreduce_takes_walk(const Schedule &sc, int64_t R) {
     if ((R != 8 && R != 16) || n < kWalkNnz) return false;
     if (p.ntiles == 0) return true;                        // there was no memory for the plan of the pieces
     // Very many nonzeros in short segments, of which the walk keeps more in flight.  Whole calls on the walk and on the pieces, rank 16, us:
-    // TTM on 100 M (35 M of them, 5 per fiber, off the sweep) 667 and 700; 30 M at random, 7.5 per fiber, 347 and 356, 4 per fiber 420 and
+    // TTM on 100 M (35 M of them, 5 per fiber, off the sweep) 669 and 700; 30 M at random, 7.5 per fiber, 347 and 356, 4 per fiber 420 and
     // 420.  15 M, 5 and 2.5 per fiber, 212 and 205, 281 and 266.
     if (n <= 8 * sc.nseg) return R == 16 && n >= int64_t(24) << 20;
     // Longer segments: the pieces gain where every part of the list has operand rows of its own (banded matrices: 12 M, 12 per row, rank 16, 229
@@ -53,8 +53,8 @@ inline bool segreduce_takes_walk(const Schedule &sc, int64_t R) {
 //    64    1694  1669   1827  1984   1976  1832   3016  2299   3689  3373   3534  3425   3728  3784
 //    96    2553  2504   2944  2990   3492  2747   5113  3872   5850  5849   5440  5645   5623  6071
 //   128    4206  3318   4675  3977   5268  3709   7165  4595   7902  6746   7337  6973   7390  7644
-// Rank 16: 150 M, power, 1601 and 1393; 2 per fiber, c 13 000, b 32 000, 633 and 647.  Rank 32: 2 per fiber, c 7900, 1131 and 1166.  Rank 40: 2 per fiber, c 7900, b 28 000,
-// 1862 and 2115.  Rank 64: 20 M, power, 771 and 740.  3 M, 5 per fiber, c 25 300: rank 20 1.12 times as fast, 30 1.02.
+// Rank 16: 150 M, power, 1602 and 1393; 2 per fiber, c 13 000, b 32 000, 633 and 647.  Rank 32: 2 per fiber, c 7900, 1131 and 1166.  Rank 40: 2 per fiber, c 7900, b 28 000,
+// 1862 and 2115.  Rank 64: 20 M, power, 772 and 753.  3 M, 5 per fiber, c 25 300: rank 20 1.12 times as fast, 30 1.02.
 // The lines below left few of 13 200 calls on random lists (uniform and power-law modes, 2 to 30 nonzeros per fiber, 2 to 10^5 fibers per slice, 1.2 M to
 // 45 M nonzeros) with the slower kernel: 270 are more than 2 % slower than on the walk, and 3770 were with lines on sizes and ranks alone.
 inline bool mttkrp_takes_wave(const Schedule &sc, int64_t R) {
