@@ -741,8 +741,8 @@ hipError_t heavy_spmm(const HeavyPlan &plan, const int32_t *rowmap, const double
 // the windows of a fiber in a fixed order.  The remaining fibers stay with the nonzero-tiled kernel, which skips
 // the heavy ones.
 //
-// What bounds it is the issue of instructions of all kinds (one is under way in 75 % of the SIMDs' cycles, vector arithmetic in 47 %), with LDS
-// close behind (at work 50 % of the time, a third of that bank conflicts).  Groups of 16 because the
+// What bounds it is the issue of instructions (those of all kinds are active for 75 % of the SIMDs' cycles, vector arithmetic alone for 47 %), with
+// LDS close behind (at work 44 % of the time, a third of that bank conflicts).  Groups of 16 because the
 // hardware broadcasts a lane over a row of 16 inside an addition or a multiplication: a step is three instructions
 // per row of four items, and was eleven per eight with groups of 8, whose broadcasts are moves.  A block always takes
 // 16 items, those behind a piece's end with a row of zeros, so that no step asks whether the piece goes on (with that
