@@ -267,8 +267,8 @@ comet_status comet_ttm(const comet_tensor *X, int mode, const double *U, int64_t
  *            slice = 0).
  * By the size and structure of X and by R, a row of the middle level's factor is multiplied with what a whole fiber
  * adds up to, with parts of that, or with every product x_ijk c_kr alone.  These differ by rounding only while all of
- * them are finite.  Where a factor is infinite or NaN, or a product overflows, m_ir is not finite if the slice names it, and
- * whether it is an infinity or a NaN may differ from kernel to kernel; slices that name no such row are not touched by it. */
+ * them are finite.  A factor that is infinite or NaN makes m_ir an infinity or a NaN in every slice that names it, and in no
+ * other; which of the two may differ from kernel to kernel, and so may whether an intermediate result overflows. */
 comet_status comet_mttkrp(const comet_tensor *X, int mode, const double *const *factors,
                           int64_t R, double *M, void *stream);
 

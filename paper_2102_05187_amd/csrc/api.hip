@@ -125,7 +125,7 @@ comet_status build_schedule(comet_tensor &t, hipStream_t st, bool part = false) 
         if (rs != COMET_OK) return rs;
         sc.empty_segments = facts[0];
         if (t.fmt == Format::CSF3) sc.empty_slices = facts[2];
-        // optional, like the plans of the sweeps below: without the memory for it, what would run on it takes the simple kernels
+        // optional, like the plans of the sweeps below: without the memory for it, what would run on it takes the simple kernels (long lists at ranks 8 and 16 the walk)
         hipError_t ppe = comet::piece_plan_build(t.pos_i(leaf), sc.nseg, t.crd_i(leaf), sc.nnz, t.fmt == Format::CSF3 ? t.crd_i(1) : nullptr, sc.pieces, st);
         if (ppe == hipErrorOutOfMemory) { (void)hipGetLastError(); ppe = hipSuccess; }
         HIP_TRY(ppe);

@@ -1,6 +1,7 @@
-// MTTKRP kernels and the choice among them (the third one is in kernels_mttkrp_wave.hip).  Short lists: lane groups of 4, 8 or 16 walk the pieces of the fibers of a tile (k_mttkrp_pieces, mttkrp_plan.hpp);
+// MTTKRP kernels.  Short lists: lane groups of 4, 8 or 16 walk the pieces of the fibers of a tile (k_mttkrp_pieces, mttkrp_plan.hpp);
 // a tile is a chain of dependent loads -- its descriptor, its nonzeros, rows of B and C, the sums -- and what bounds the kernel is how
-// many of them are in flight.  All others: lane groups walk runs of nonzeros over two nested segment levels (k_stream_mttkrp).
+// many of them are in flight.  Long lists: wavefronts over blocks of nonzeros (kernels_mttkrp_wave.hip), or lane groups that walk runs of nonzeros over two
+// nested segment levels (k_stream_mttkrp); mttkrp_route chooses.
 // A piece loads rows of C in groups of four, none behind its batch's last group; with up to seven more rows per piece, fibers of 12 / 30 /
 // 200 nonzeros, rank 10, 2.3 M, took 39 / 40 / 37 us instead of 36 / 35 / 32, rank 33 107 / 117 / 108 instead of 90 / 87 / 79.
 #include "mttkrp_plan.hpp"

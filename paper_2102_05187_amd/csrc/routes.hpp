@@ -17,16 +17,23 @@ inline bool segreduce_takes_walk(const Schedule &sc, int64_t R) {
     // 420.  15 M, 5 and 2.5 per fiber, 212 and 205, 281 and 266.
     if (n <= 8 * sc.nseg) return R == 16 && n >= int64_t(24) << 20;
     // Longer segments: the pieces gain where every part of the list has operand rows of its own (banded matrices: 12 M, 12 per row, rank 16, 229
-    // and 137) or where the rows come from behind the L2 (11 M, 16 per row in 300 000 columns, 216 and 209), and lose where the list goes on
-    // using the same rows, which the L2 then holds, and segments differ in length, so that some are cut up:
+    // and 137), where the rows come from behind the L2 (11 M, 16 per row in 300 000 columns, 216 and 209) and where there is little but short segments or little but
+    // long ones (TTM over power-law fibers, 20 M, rank 8, 170 and 155).  They lose where the whole list uses the same rows, which the L2 then holds, and
+    // segments of middle lengths differ: the pieces of a tile fill the lane groups' last turn badly.
     //   rank 16   20 per row, 30 000 columns: 11 M 100 and 112, 40 M 328 and 385; 60 000 (7.6 MB of rows) 434 and 451, 120 000 610 and 603 at 16 per row;
-    //             150 per row 277 and 303; columns that follow a power law (58 000 in a sample), 34 M, 290 and 357, 22 M in rows of 9, 203 and 213;
+    //             150 per row 277 and 303; columns that follow a power law (58 000 in a sample), 34 M, 290 and 357; 9 per row, 22 M, 203 and 213;
     //             every row 9 long: 24 M 253 and 231, 16 long: 200 and 201
-    //   rank 8    20 per row, 30 000 columns: 11 M 90 and 91, 24 M 181 and 190, 40 M 295 and 309; 9 per row, power-law rows and columns, 19 M, 149 and 169; 120 000, 16 per row, 458 and 444; power-law
-    //             columns, 31 M, 258 and 287; 32 per row 281 and 269; 150 per row 262 and 242; every row 20 long 292 and 248
-    if (p.common < 0.75) return false;
-    if (R == 16) return p.distinct <= 78000 && 512 * p.njoins >= sc.nseg;
-    return n <= 28 * sc.nseg && p.distinct <= 67000 && 200 * p.njoins >= sc.nseg;
+    //   rank 8    20 per row, 30 000 columns: 11 M 90 and 91, 24 M 181 and 190, 40 M 295 and 309; 120 000, 16 per row, 458 and 444; power-law rows and
+    //             columns, 31 M, 258 and 287, 19 M, 9 per row, 149 and 169; 32 per row 281 and 269; 150 per row 262 and 242; every row 20 long 292 and 248
+    // The lines are those that left fewest of 3200 calls on random lists (three kinds of lengths, uniform and power-law columns, TTM of power-law tensors) with the
+    // slower kernel: 6 are more than 3 % slower than on the pieces, the worst 1.04 times; 59 than on the walk, most of them by 3 to 6 %.
+    const int64_t whole = sc.nseg - p.njoins, in_parts = 30 * (p.npieces - whole);      // segments in one piece; nonzeros of the others, about
+    // a power-law mode: samples share their frequent coordinates and not the rest
+    const bool power = p.common <= 0.985 && p.distinct <= 72000;
+    if (p.common < 0.72 || p.distinct > (p.common <= 0.8 || R == 8 ? 92000 : 85000)) return false;
+    if (R == 8) return 100 * in_parts <= (power ? 48 : 42) * n && (30 * p.njoins >= sc.nseg || (power && n >= 8 * p.npieces && 90 * p.njoins >= sc.nseg));
+    if (power && 100 * in_parts >= n && (n >= 8 * p.npieces || (n >= int64_t(19) << 20 && 2 * n >= 5 * p.npieces))) return true;
+    return 1000 * in_parts >= n && 10 * (n - in_parts) >= 33 * whole && (2 * n >= 19 * p.npieces || (n >= int64_t(24) << 20 && 2 * n >= 17 * p.npieces));
 }
 
 // MTTKRP, lists and ranks that do not take the pieces: the wavefronts over blocks of nonzeros (k_mttkrp_wave), or the walk over nonzeros (k_stream_mttkrp).

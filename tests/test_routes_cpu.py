@@ -24,37 +24,42 @@ def routes(tmp_path_factory):
     return ask
 
 
-# rank, nonzeros, nonzeros per segment, different coordinates and common share of a sample, share of the segments that are cut up
-@pytest.mark.parametrize("rank,nnz,per,distinct,common,cut,route", [
-    (16, 11 * M, 20, 30_000, 1.0, 0.08, "walk"),           # uneven rows over rows that an L2 holds: 100 us, and 112 on the pieces
-    (16, 40 * M, 20, 59_000, 0.99, 0.08, "walk"),          # 434 and 451
-    (16, 34 * M, 13.5, 58_000, 0.85, 0.03, "walk"),        # power-law columns: 290 and 357
-    (16, 40 * M, 150, 30_000, 1.0, 0.9, "walk"),           # 277 and 303
-    (16, 40 * M, 16, 106_000, 0.9, 0.05, "pieces"),        # 608 and 603
-    (16, 11 * M, 12, 24_000, 0.02, 0.02, "pieces"),        # near the diagonal: 229 and 137
-    (16, 24 * M, 9, 30_000, 1.0, 0.0, "pieces"),           # rows of one length: 253 and 231
-    (16, 40 * M, 3, 30_000, 1.0, 0.0, "walk"),             # very many in short segments
-    (16, 15 * M, 3, 30_000, 1.0, 0.0, "pieces"),
-    (16, 10 * M, 20, 30_000, 1.0, 0.08, "pieces"),         # short lists
-    (8, 40 * M, 20, 30_000, 1.0, 0.08, "walk"),            # 295 and 309
-    (8, 31 * M, 15, 62_000, 0.85, 0.05, "walk"),           # power-law columns: 258 and 287
-    (8, 11 * M, 20, 30_000, 1.0, 0.08, "walk"),            # 90 and 91
-    (8, 10 * M, 20, 30_000, 1.0, 0.08, "pieces"),
-    (8, 40 * M, 32, 30_000, 1.0, 0.2, "pieces"),           # 281 and 269
-    (8, 40 * M, 20, 30_000, 1.0, 0.0, "pieces"),           # 292 and 248
-    (8, 40 * M, 16, 106_000, 0.9, 0.05, "pieces"),         # 458 and 444
-    (8, 40 * M, 3, 30_000, 1.0, 0.0, "pieces"),
-    (32, 40 * M, 20, 30_000, 1.0, 0.08, "pieces"),
+# rank, nonzeros, nonzeros per segment, different coordinates and common share of a sample, share of the segments that are cut up,
+# and share of the nonzeros in them
+@pytest.mark.parametrize("rank,nnz,per,distinct,common,cut,long,route", [
+    (16, 11 * M, 20, 30_000, 1.0, 0.09, 0.33, "walk"),     # uneven rows over rows that an L2 holds: 100 us, and 112 on the pieces
+    (16, 40 * M, 20, 59_000, 0.99, 0.09, 0.33, "walk"),    # 434 and 451
+    (16, 34 * M, 13.5, 58_000, 0.85, 0.03, 0.14, "walk"),  # power-law columns: 290 and 357
+    (16, 40 * M, 150, 30_000, 1.0, 0.73, 0.96, "walk"),    # 277 and 303
+    (16, 22 * M, 9.4, 13_500, 0.97, 0.01, 0.03, "walk"),   # 203 and 213
+    (16, 27 * M, 15, 85_700, 0.75, 0.03, 0.14, "walk"),    # power-law columns of a large operand: 0.90
+    (16, 40 * M, 16, 106_000, 0.9, 0.05, 0.2, "pieces"),   # 608 and 603
+    (16, 11 * M, 12, 24_000, 0.02, 0.02, 0.1, "pieces"),   # near the diagonal: 229 and 137
+    (16, 24 * M, 9, 30_000, 1.0, 0.0, 0.0, "pieces"),      # rows of one length: 253 and 231
+    (16, 40 * M, 3, 30_000, 1.0, 0.0, 0.0, "walk"),        # very many in short segments
+    (16, 15 * M, 3, 30_000, 1.0, 0.0, 0.0, "pieces"),
+    (16, 10 * M, 20, 30_000, 1.0, 0.09, 0.33, "pieces"),   # short lists
+    (8, 40 * M, 20, 30_000, 1.0, 0.09, 0.33, "walk"),      # 295 and 309
+    (8, 31 * M, 15, 62_000, 0.85, 0.05, 0.39, "walk"),     # power-law columns: 258 and 287
+    (8, 11 * M, 20, 30_000, 1.0, 0.09, 0.33, "walk"),      # 90 and 91
+    (8, 20 * M, 11.6, 3_429, 1.0, 0.03, 0.65, "pieces"),   # TTM over power-law fibers: 170 and 155
+    (8, 10 * M, 20, 30_000, 1.0, 0.09, 0.33, "pieces"),
+    (8, 40 * M, 32, 30_000, 1.0, 0.22, 0.56, "pieces"),    # 281 and 269
+    (8, 40 * M, 20, 30_000, 1.0, 0.0, 0.0, "pieces"),      # 292 and 248
+    (8, 40 * M, 16, 106_000, 0.9, 0.05, 0.2, "pieces"),    # 458 and 444
+    (8, 40 * M, 3, 30_000, 1.0, 0.0, 0.0, "pieces"),
+    (32, 40 * M, 20, 30_000, 1.0, 0.09, 0.33, "pieces"),
 ])
-def test_segments_take_the_faster_kernel(routes, rank, nnz, per, distinct, common, cut, route):
+def test_segments_take_the_faster_kernel(routes, rank, nnz, per, distinct, common, cut, long, route):
     nseg = int(nnz / per)
-    assert routes("segreduce", rank, nnz, nseg, nnz // 1400, distinct, common, int(cut * nseg)) == route
+    joins = int(cut * nseg)
+    assert routes("segreduce", rank, nnz, nseg, nnz // 1400, distinct, common, joins, nseg - joins + int(long * nnz / 30)) == route
 
 
 @pytest.mark.parametrize("rank,nnz,route", [(8, 11 * M, "walk"), (16, 11 * M, "walk"), (16, 10 * M, "pieces"), (32, 40 * M, "pieces")])
 def test_segments_without_a_plan(routes, rank, nnz, route):
     """"pieces" means that the caller finds no plan and takes the kernels that need none."""
-    assert routes("segreduce", rank, nnz, nnz // 30, 0, 0, 0.0, 0) == route
+    assert routes("segreduce", rank, nnz, nnz // 30, 0, 0, 0.0, 0, 0) == route
 
 
 POWER = (4_000, 13_500, 4 * M)                             # rows of C in 32768 nonzeros, rows of B in 32768 fibers, nonzeros of the longest slice
